@@ -75,10 +75,9 @@ struct Selection {
 
 template <int SELECT_NCH>
 __device__ __forceinline__ Selection obtain_selection(const uint16_t* __restrict__ x, int K, int k,
-                                                      int32_t* idx_g, uint16_t* xsel_g, int bid) {
+                                                      int32_t* idx_g, uint16_t* xsel_g, SelectShared& sh, int bid) {
     if constexpr (SELECT_NCH > 0) {
         extern __shared__ uint4 s_sel_raw[];  // int32 idx[k], then fp16 xsel[k]
-        __shared__ SelectShared sh;
         int32_t* idx_l = reinterpret_cast<int32_t*>(s_sel_raw);
         uint16_t* xs_l = reinterpret_cast<uint16_t*>(idx_l + k);
         block_select_topk<kBlockThreads, SELECT_NCH>(x, K, k, sh, idx_l, xs_l);
@@ -160,12 +159,18 @@ __device__ __forceinline__ void fetch_block(const FetchJobs& jobs, const Finaliz
     constexpr int SUB = 64 / LPR;                       // rows a wavefront loads with one instruction
     constexpr int UNROLL = (4096 / 64) / (int)sizeof(piece_t);  // loads in flight per lane: 4 KiB per wavefront
     static_assert(kBlockThreads == kFetchSegmentCols, "one thread per column of the segment");
-    __shared__ float red[kWavesPerBlock * SUB][kFetchSegmentCols];
+    // the selection and the sum over the wavefronts follow one another and share their LDS
+    __shared__ union Lds {
+        float red[kWavesPerBlock * SUB][kFetchSegmentCols];
+        SelectShared sh;
+        __device__ Lds() {}
+    } lds;
+    auto& red = lds.red;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Selection sel = obtain_selection<SELECT_NCH>(x, K, k, idx_g, xsel_g, bid);
+    const Selection sel = obtain_selection<SELECT_NCH>(x, K, k, idx_g, xsel_g, lds.sh, bid);
     const int32_t* idx = sel.idx;
     const uint16_t* xsel = sel.xsel;
     const BlockTask t = block_task(jobs, segments, bid);

@@ -3,7 +3,7 @@
 // own.  The paper's kernel uses an approximate, chunked bucket Top-K (Section
 // 4.3); this is the exact Top-K it uses as its quality reference (Section 5.2).
 // The algorithm is in select_block.h; one workgroup does the whole selection
-// (256 threads up to 8192 channels, 1024 threads above).
+// (one chunk of 8 channels per thread up to 8192 channels, 1024 threads above).
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
@@ -27,8 +27,10 @@ hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, voi
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* xs = static_cast<uint16_t*>(xsel_out);
     const dim3 one(1);
-    if (K <= 4096) return launch_kernel(tm, select_topk_kernel<256, 2>, one, dim3(256), 0, stream, xp, K, k, idx_out, xs);
-    if (K <= 8192) return launch_kernel(tm, select_topk_kernel<256, 4>, one, dim3(256), 0, stream, xp, K, k, idx_out, xs);
+    // one chunk of 8 channels per thread as long as that gives enough threads: no list of chunks is needed then
+    if (K <= 2048) return launch_kernel(tm, select_topk_kernel<256, 1>, one, dim3(256), 0, stream, xp, K, k, idx_out, xs);
+    if (K <= 4096) return launch_kernel(tm, select_topk_kernel<512, 1>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
+    if (K <= 8192) return launch_kernel(tm, select_topk_kernel<1024, 1>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 16384)
         return launch_kernel(tm, select_topk_kernel<1024, 2>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 32768)

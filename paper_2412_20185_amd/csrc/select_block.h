@@ -2,25 +2,37 @@
 // Top-K of Section 5.2; a tie at the cut goes to the lower index).  Used by the
 // stand-alone selection kernel and by kernels that select for themselves.
 //
-// Radix select, nothing is sorted, x is read once and stays in registers:
-//   * wavefront w owns the 64*NCH consecutive 8-key chunks starting at
-//     w*64*NCH; lane l holds chunk w*64*NCH + j*64 + l for j = 0..NCH-1 (one
-//     coalesced 128-bit load per j), so inside a wavefront the channel order
-//     is (j, lane, position in the chunk) and wavefronts follow one another;
-//   * the order of |x| is the order of the 15-bit key (fp16 bits, sign
-//     cleared); an LDS histogram over the high 8 key bits finds the bin
-//     holding the k-th largest key (kHistCopies copies picked by lane would
-//     spread atomics that collide on few bins; measured, one copy is fastest); a
-//     second histogram over the low 7 bits of the keys in that bin finds the
-//     key T itself and how many keys equal to T are still needed.  Every
-//     wavefront scans the histograms for itself (DPP prefix sum + readlane),
-//     which saves the barriers a single scanning wavefront would need;
-//   * per round j every thread counts its keys > T and == T; a wave prefix
-//     sum per round, the round totals (readlane) and per-wave totals in LDS
-//     give each thread the number of such keys at lower indices, hence each
-//     selected element its output position: keys > T all go out, keys == T
-//     only the first `need` in index order.  Only marked keys are visited when
-//     writing.  Output is in ascending index order.
+// x is read once and stays in registers: wavefront w owns the 64*NCH consecutive
+// 8-key chunks starting at w*64*NCH; lane l holds chunk w*64*NCH + j*64 + l for
+// j = 0..NCH-1 (one coalesced 128-bit load per j), so inside a wavefront the
+// channel order is (j, lane, position in the chunk) and wavefronts follow one
+// another.  The order of |x| is the order of the 15-bit key (fp16 bits, sign
+// cleared).  Output is in ascending index order.
+//
+// What bounds the selection is the instruction issue of the one compute unit it
+// runs on, so few instructions may touch every key.  Two forms:
+//
+//   chunks (select_by_chunks), when k is at most a third of the number of chunks
+//   and at most 576 (beyond, the bound is too low to exclude much, and the list
+//   may not hold the chunks): k chunks hold a key at least as large as the k-th
+//   largest chunk maximum, so that is a lower bound of the k-th largest key.
+//     1. chunk maxima by packed 16-bit maxima; a 256-bin LDS histogram of their
+//        high 8 bits gives the bin that holds the k-th largest; its lower edge L
+//        is the bound;
+//     2. chunks with a maximum >= L, little more than k, go to an LDS list in
+//        order, one or a few per thread (left out when every thread has one chunk);
+//     3. a 256-bin LDS histogram of key - L over their keys gives T, the k-th
+//        largest key itself, and how many keys equal to T are needed; only when
+//        T >= L + 255 (large |x| crowded into few chunks) it is formed twice more,
+//        over 128-key bins and inside the bin that holds T;
+//     4. masks of the keys > T and == T and one prefix sum place every selected
+//        element.
+//   radix (select_by_radix), for larger k, or when more than kMaxListed chunks
+//   reach L (many equal keys): LDS histograms of all keys over their high 8 and
+//   low 7 bits, then masks and prefix sums over every key.
+// Stand-alone kernel in graph replays, radix for every key -> chunks, us: K = 1024, k = 32: 3.4 -> 2.6; 4096, 60:
+// 3.7 -> 3.1; 8192, 81: 5.4 -> 4.1; 14336, 286: 6.3 -> 4.6; 28672, 286: 9.8 -> 5.3.  With k = 400 of 4096 the bound
+// is so low that the chunks took 5.4 against 3.5 for radix; with k = 1433 of 28672 the list overflowed.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -29,12 +41,17 @@
 namespace decdec {
 
 constexpr int kSelectMaxChunks = 8;  // 8-key chunks per thread at most
-constexpr int kHistCopies = 1;
 
+constexpr int kMaxListed = 1024;     // chunks with a key that may be selected
+constexpr int kMaxByChunks = 576;    // the bin of L alone can make the list 1.77 times as long as k (|x| normal, k 1 % of K)
+
+// LDS of the selection; nothing in it is needed afterwards, so it may share its place with other data.
 struct SelectShared {
-    unsigned hist1[kHistCopies][256];
-    unsigned hist2[128];
-    unsigned wtot[16];  // per wave: (keys > T) | (keys == T) << 16
+    uint4 list[kMaxListed];
+    uint16_t list_chunk[kMaxListed];
+    __attribute__((aligned(16))) unsigned hist1[256];
+    __attribute__((aligned(16))) unsigned hist2[256];
+    __attribute__((aligned(16))) unsigned wtot[2][16];  // per wave: listed chunks; (keys > T) | (keys == T) << 16
 };
 
 template <int CTRL, int ROW_MASK, bool BOUND_CTRL>
@@ -53,82 +70,244 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
     return v;
 }
 
-// Run by all 64 lanes of a wavefront.  hist holds COPIES histograms of
-// NB = 64*PER bins in ascending key order whose sum has at least kk >= 1 keys.
-// Finds the bin b with fewer than kk keys in the bins above it and at least kk
-// in the bins >= b; returns b and kk - (#keys above b) in every lane.
-template <int PER, int COPIES>
-__device__ __forceinline__ void wave_find_bin(const unsigned* hist, unsigned kk, unsigned& bin, unsigned& rem,
-                                              int lane) {
-    constexpr int NB = 64 * PER;
+// Run by all 64 lanes of a wavefront.  hist (16-byte aligned) holds NB = 64 * PER bins in ascending key order whose
+// sum has at least kk >= 1 entries.  Finds the bin with fewer than kk entries in the bins above it and at least kk
+// in the bins from it up; returns it and kk - (entries above it) in every lane.
+template <int PER>
+__device__ __forceinline__ void wave_find_bin(const unsigned* hist, unsigned kk, unsigned& bin, unsigned& rem, int lane) {
     unsigned c[PER], tot = 0;
+    if constexpr (PER == 4) {
+        const uint4 v = reinterpret_cast<const uint4*>(hist)[lane];
+        c[0] = v.x;
+        c[1] = v.y;
+        c[2] = v.z;
+        c[3] = v.w;
+    } else {
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int b = NB - 1 - (lane * PER + j);  // descending key order
-        c[j] = 0;
-#pragma unroll
-        for (int r = 0; r < COPIES; ++r) c[j] += hist[r * NB + b];
-        tot += c[j];
+        for (int j = 0; j < PER; ++j) c[j] = hist[lane * PER + j];
     }
-    unsigned above = wave_incl_scan(tot) - tot;  // keys in bins above this lane's bins
-    unsigned b_l = 0, r_l = 1;
-    bool found = false;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
+    for (int j = 0; j < PER; ++j) tot += c[j];
+    const unsigned incl = wave_incl_scan(tot);
+    unsigned above = (unsigned)__builtin_amdgcn_readlane((int)incl, 63) - incl;  // entries above this lane's bins
+    const bool found = above < kk && kk <= above + tot;
+    unsigned b_l = 0, r_l = 1;
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) {
         if (above < kk && kk <= above + c[j]) {
-            b_l = (unsigned)(NB - 1 - (lane * PER + j));
+            b_l = (unsigned)(lane * PER + j);
             r_l = kk - above;
-            found = true;
         }
         above += c[j];
     }
-    const unsigned long long mask = __ballot(found);  // exactly one lane unless the histogram is short of kk keys
+    const unsigned long long mask = __ballot(found);  // exactly one lane unless the histogram is short of kk entries
     const int src = mask ? __builtin_ctzll(mask) : 0;
     bin = (unsigned)__builtin_amdgcn_readlane((int)b_l, src);
     rem = (unsigned)__builtin_amdgcn_readlane((int)r_l, src);
 }
 
+// Key e of four words of a chunk.  The words come by value: chosen by reference they would be kept in scratch memory.
+__device__ __forceinline__ uint32_t word_of(uint32_t x, uint32_t y, uint32_t z, uint32_t w, int e) {
+    const uint32_t lo = e & 2 ? y : x, hi = e & 2 ? w : z;
+    return e & 4 ? hi : lo;
+}
 __device__ __forceinline__ unsigned key_of(const uint4& c, int e) {
-    const uint32_t w = e < 2 ? c.x : e < 4 ? c.y : e < 6 ? c.z : c.w;
+    const uint32_t w = word_of(c.x, c.y, c.z, c.w, e);
     return ((e & 1) ? (w >> 16) : w) & 0x7FFFu;
 }
 __device__ __forceinline__ uint16_t raw_of(const uint4& c, int e) {
-    const uint32_t w = e < 2 ? c.x : e < 4 ? c.y : e < 6 ? c.z : c.w;
+    const uint32_t w = word_of(c.x, c.y, c.z, c.w, e);
     return (uint16_t)((e & 1) ? (w >> 16) : (w & 0xFFFFu));
 }
 
-// All THREADS threads of the workgroup call this.  Requires K a multiple of 8,
-// K <= 8*THREADS*NCH, x 16-byte aligned, 1 <= k <= K.  idx_out / xsel_out may
-// point to global memory or LDS; xsel_out may be null.  Ends with the outputs
-// written but not yet synchronised (the caller adds the barrier it needs).
-template <int THREADS, int NCH>
-__device__ __forceinline__ void block_select_topk(const uint16_t* __restrict__ x, int K, int k, SelectShared& sh,
-                                                  int32_t* idx_out, uint16_t* xsel_out) {
-    static_assert(THREADS % 64 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nchunks = K / 8;
-    const int c0 = wave * 64 * NCH + lane;  // this thread's chunk of round j is c0 + 64*j
-    const uint4* x128 = reinterpret_cast<const uint4*>(x);
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
-    uint4 ch[NCH];
+__device__ __forceinline__ unsigned pk_max_u16(unsigned a, unsigned b) {
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a),
+                                                                  __builtin_bit_cast(ushort2_t, b)));
+}
+
+__device__ __forceinline__ unsigned chunk_max(const uint4& c) {
+    const unsigned m = pk_max_u16(pk_max_u16(c.x & 0x7FFF7FFFu, c.y & 0x7FFF7FFFu),
+                                  pk_max_u16(c.z & 0x7FFF7FFFu, c.w & 0x7FFF7FFFu));
+    return max(m >> 16, m & 0xFFFFu);
+}
+
+// Number of set bits of a lane mask in front of this lane.
+__device__ __forceinline__ unsigned lanes_before(unsigned long long mask) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+// Sum of the waves' totals in front of `wave`, and of all of them.
+template <int WAVES>
+__device__ __forceinline__ void totals_before(const unsigned* wtot, int wave, unsigned& before, unsigned& all) {
+    before = all = 0;
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) ch[j] = c0 + 64 * j < nchunks ? x128[c0 + 64 * j] : make_uint4(0, 0, 0, 0);
-    for (int i = tid; i < kHistCopies * 256; i += THREADS) (&sh.hist1[0][0])[i] = 0;
-    for (int i = tid; i < 128; i += THREADS) sh.hist2[i] = 0;
+    for (int w = 0; w < WAVES; w += 4) {
+        const uint4 t = *reinterpret_cast<const uint4*>(wtot + w);
+        before += (w < wave ? t.x : 0u) + (w + 1 < wave ? t.y : 0u) + (w + 2 < wave ? t.z : 0u) + (w + 3 < wave ? t.w : 0u);
+        all += t.x + t.y + t.z + t.w;
+    }
+}
+
+// Writes the marked keys of one chunk: all of `gt`, of `eq` those with fewer than `need` equal keys in front.
+__device__ __forceinline__ void write_marked(const uint4& c, int channel0, unsigned gt, unsigned eq, unsigned pos_gt,
+                                             unsigned seen_eq, unsigned need, unsigned k, int32_t* idx_out,
+                                             uint16_t* xsel_out) {
+    unsigned m = gt | eq;
+    while (m) {
+        const int e = __builtin_ctz(m);
+        m &= m - 1;
+        const bool is_gt = (gt >> e) & 1u;
+        const unsigned pos = pos_gt + min(seen_eq, need);
+        // pos < k always holds for a taken key; the bound keeps a logic error from writing outside
+        if ((is_gt || seen_eq < need) && pos < k) {
+            idx_out[pos] = channel0 + e;
+            if (xsel_out) xsel_out[pos] = raw_of(c, e);
+        }
+        pos_gt += is_gt;
+        seen_eq += !is_gt;
+    }
+}
+
+// Bit e: key e of the chunk is > below, by packed saturating subtractions (the selection runs once per launch, so
+// its instructions come cold from memory: fewer of them count for more than their issue time).
+__device__ __forceinline__ unsigned mark_above(const uint4& c, unsigned below) {
+    const ushort2_t lim = __builtin_bit_cast(ushort2_t, below * 0x10001u), one = {1, 1};
+    const unsigned w[4] = {c.x & 0x7FFF7FFFu, c.y & 0x7FFF7FFFu, c.z & 0x7FFF7FFFu, c.w & 0x7FFF7FFFu};
+    unsigned m = 0;  // bits 2 i and 16 + 2 i: the two keys of word i
+#pragma unroll
+    for (int i = 3; i >= 0; --i) {
+        const ushort2_t over = __builtin_elementwise_sub_sat(__builtin_bit_cast(ushort2_t, w[i]), lim);
+        m = (m << 2) | __builtin_bit_cast(unsigned, __builtin_elementwise_min(over, one));
+    }
+    return (m | (m >> 15)) & 0xFFu;
+}
+
+// Bit e of gt / eq: key e of the chunk is > T / == T (T >= 1).
+__device__ __forceinline__ void mark_chunk(const uint4& c, unsigned T, unsigned& gt, unsigned& eq) {
+    gt = mark_above(c, T);
+    eq = mark_above(c, T - 1) & ~gt;
+}
+
+// Requires 1 <= k <= nchunks and sh.hist1, sh.hist2 cleared (with a barrier behind).  False, in all threads, when the
+// chunks do not give the selection: nothing has been written to the outputs then.
+template <int THREADS, int NCH>
+__device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared& sh,
+                                                 int32_t* idx_out, uint16_t* xsel_out) {
+    constexpr int WAVES = THREADS / 64;
+    constexpr int PER = NCH == 1 ? 1 : (kMaxListed + THREADS - 1) / THREADS;  // listed chunks per thread at most
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c0 = wave * 64 * NCH + lane;
+
+    unsigned cm[NCH];  // absent chunks: 0
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+        cm[j] = chunk_max(ch[j]);
+        if (c0 + 64 * j < nchunks) atomicAdd(&sh.hist1[cm[j] >> 7], 1u);
+    }
     __syncthreads();
+    unsigned bin, need;
+    wave_find_bin<4>(sh.hist1, (unsigned)k, bin, need, lane);
+    const unsigned L = bin << 7;
+    if (L == 0) return false;
+
+    uint4 mine[PER];
+    int chunk[PER];
+    if constexpr (NCH == 1) {
+        mine[0] = ch[0];
+        chunk[0] = c0;
+    } else {
+        unsigned at[NCH], total = 0;
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) {
+            const unsigned long long b = __ballot(cm[j] >= L);
+            at[j] = total + lanes_before(b);
+            total += (unsigned)__builtin_popcountll(b);
+        }
+        if (lane == 0) sh.wtot[0][wave] = total;
+        __syncthreads();
+        unsigned before, listed;
+        totals_before<WAVES>(sh.wtot[0], wave, before, listed);
+        listed = (unsigned)__builtin_amdgcn_readfirstlane((int)listed);
+        if (listed > (unsigned)kMaxListed) return false;
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) {
+            if (cm[j] >= L) {
+                sh.list[before + at[j]] = ch[j];
+                sh.list_chunk[before + at[j]] = (uint16_t)(c0 + 64 * j);
+            }
+        }
+        __syncthreads();
+        const int per = (int)(listed + THREADS - 1) / THREADS;
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const int i = tid * per + p;
+            const bool have = p < per && i < (int)listed;
+            mine[p] = have ? sh.list[i] : make_uint4(0, 0, 0, 0);  // keys below L: never taken
+            chunk[p] = have ? sh.list_chunk[i] : 0;
+        }
+    }
+    unsigned T = L;
+    int shift = 0;  // bins of 2^shift keys from T on; the last one takes everything above
+    while (true) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            unsigned m = mark_above(mine[p], T - 1);
+            while (m) {
+                atomicAdd(&sh.hist2[min((key_of(mine[p], __builtin_ctz(m)) - T) >> shift, 255u)], 1u);
+                m &= m - 1;
+            }
+        }
+        __syncthreads();
+        wave_find_bin<4>(sh.hist2, (unsigned)k, bin, need, lane);  // need: keys equal to T to take (>= 1) in the end
+        T += bin << shift;
+        if (shift == 0 && bin < 255) break;
+        shift = shift == 0 ? 7 : 0;  // 256 bins of 128 cover every key; then 128 keys at the most
+        __syncthreads();
+        for (int i = tid; i < 256; i += THREADS) sh.hist2[i] = 0;
+        __syncthreads();
+    }
+
+    unsigned gt[PER], eq[PER], cnt = 0;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        mark_chunk(mine[p], T, gt[p], eq[p]);
+        cnt += (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
+    }
+    const unsigned incl = wave_incl_scan(cnt);
+    if (lane == 63) sh.wtot[1][wave] = incl;
+    __syncthreads();
+    unsigned before, all;
+    totals_before<WAVES>(sh.wtot[1], wave, before, all);  // no carry between the halves: at most 8192 marked keys
+    before += incl - cnt;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        write_marked(mine[p], chunk[p] * 8, gt[p], eq[p], before & 0xFFFFu, before >> 16, need, (unsigned)k, idx_out, xsel_out);
+        before += (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
+    }
+    return true;
+}
+
+// Any 1 <= k <= K.  Requires sh.hist1, sh.hist2 cleared (with a barrier behind).
+template <int THREADS, int NCH>
+__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared& sh,
+                                                int32_t* idx_out, uint16_t* xsel_out) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c0 = wave * 64 * NCH + lane;  // this thread's chunk of round j is c0 + 64*j
 
     // pass 1: high 8 bits of the key
-    unsigned* h1 = sh.hist1[lane & (kHistCopies - 1)];
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
         if (c0 + 64 * j < nchunks) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) atomicAdd(&h1[key_of(ch[j], e) >> 7], 1u);
+            for (int e = 0; e < 8; ++e) atomicAdd(&sh.hist1[key_of(ch[j], e) >> 7], 1u);
         }
     }
     __syncthreads();
     unsigned b1, rem1;
-    wave_find_bin<4, kHistCopies>(&sh.hist1[0][0], (unsigned)k, b1, rem1, lane);
+    wave_find_bin<4>(sh.hist1, (unsigned)k, b1, rem1, lane);
 
     // pass 2: low 7 bits of the keys inside bin b1
 #pragma unroll
@@ -142,60 +321,72 @@ __device__ __forceinline__ void block_select_topk(const uint16_t* __restrict__ x
         }
     }
     __syncthreads();
-    unsigned b2, need;  // need: keys equal to T still to take (>= 1)
-    wave_find_bin<2, 1>(sh.hist2, rem1, b2, need, lane);
+    unsigned b2, need;  // need: keys equal to T to take (>= 1)
+    wave_find_bin<2>(sh.hist2, rem1, b2, need, lane);
     const unsigned T = (b1 << 7) | b2;
 
-    // compaction in index order.  Per round: bit e of gtm[j] / eqm[j] = key e of the chunk is > T / == T;
-    // counts are packed as (> T) | (== T) << 16 (at most 4096 each per wavefront: no carry between the halves).
+    // compaction in index order; counts are packed as (> T) | (== T) << 16 (at most 4096 each per wavefront: no
+    // carry between the halves)
     unsigned gtm[NCH], eqm[NCH], excl[NCH];  // excl: this wave's marked keys at lower indices (earlier rounds, lower lanes)
     unsigned wave_cnt = 0;                    // uniform: marked keys of the rounds so far
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-        unsigned g = 0, q = 0;
+        gtm[j] = eqm[j] = 0;
         if (c0 + 64 * j < nchunks) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const unsigned key = key_of(ch[j], e);
-                g |= (unsigned)(key > T) << e;
-                q |= (unsigned)(key == T) << e;
+                gtm[j] |= (unsigned)(key > T) << e;
+                eqm[j] |= (unsigned)(key == T) << e;
             }
         }
-        gtm[j] = g;
-        eqm[j] = q;
-        const unsigned cnt = (unsigned)__builtin_popcount(g) | ((unsigned)__builtin_popcount(q) << 16);
+        const unsigned cnt = (unsigned)__builtin_popcount(gtm[j]) | ((unsigned)__builtin_popcount(eqm[j]) << 16);
         const unsigned incl = wave_incl_scan(cnt);
         excl[j] = wave_cnt + incl - cnt;
         wave_cnt += (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    if (lane == 0) sh.wtot[wave] = wave_cnt;
+    if (lane == 0) sh.wtot[0][wave] = wave_cnt;
     __syncthreads();
     unsigned base_gt = 0, base_eq = 0;  // marked keys of the wavefronts before this one
 #pragma unroll
     for (int w = 0; w < THREADS / 64; ++w) {
-        const unsigned t = sh.wtot[w];
+        const unsigned t = sh.wtot[0][w];
         base_gt += w < wave ? (t & 0xFFFFu) : 0u;
         base_eq += w < wave ? (t >> 16) : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-        unsigned m = gtm[j] | eqm[j];
-        if (m == 0) continue;  // most threads: a chunk holds 8 keys, of which k/K are selected
-        unsigned pos_gt = base_gt + (excl[j] & 0xFFFFu), seen_eq = base_eq + (excl[j] >> 16);
-        while (m) {
-            const int e = __builtin_ctz(m);
-            m &= m - 1;
-            const bool is_gt = (gtm[j] >> e) & 1u;
-            const unsigned pos = pos_gt + min(seen_eq, need);
-            // pos < k always holds for a taken key; the bound keeps a logic error from writing outside
-            if ((is_gt || seen_eq < need) && pos < (unsigned)k) {
-                idx_out[pos] = (c0 + 64 * j) * 8 + e;
-                if (xsel_out) xsel_out[pos] = raw_of(ch[j], e);
-            }
-            pos_gt += is_gt;
-            seen_eq += !is_gt;
-        }
+    for (int j = 0; j < NCH; ++j)
+        write_marked(ch[j], (c0 + 64 * j) * 8, gtm[j], eqm[j], base_gt + (excl[j] & 0xFFFFu), base_eq + (excl[j] >> 16), need,
+                     (unsigned)k, idx_out, xsel_out);
+}
+
+// All THREADS threads of the workgroup call this.  Requires K a multiple of 8,
+// K <= 8*THREADS*NCH, x 16-byte aligned, 1 <= k <= K.  idx_out / xsel_out may
+// point to global memory or LDS; xsel_out may be null.  Ends with the outputs
+// written but not yet synchronised (the caller adds the barrier it needs).
+template <int THREADS, int NCH>
+__device__ __forceinline__ void block_select_topk(const uint16_t* __restrict__ x, int K, int k, SelectShared& sh,
+                                                  int32_t* idx_out, uint16_t* xsel_out) {
+    static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nchunks = K / 8;
+    const int c0 = wave * 64 * NCH + lane;
+    const uint4* x128 = reinterpret_cast<const uint4*>(x);
+
+    uint4 ch[NCH];
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) ch[j] = c0 + 64 * j < nchunks ? x128[c0 + 64 * j] : make_uint4(0, 0, 0, 0);
+    const auto clear = [&] {
+        for (int i = tid; i < 256; i += THREADS) sh.hist1[i] = sh.hist2[i] = 0;
+        __syncthreads();
+    };
+    clear();
+    if (3 * k <= nchunks && k <= kMaxByChunks) {
+        if (select_by_chunks<THREADS, NCH>(ch, nchunks, k, sh, idx_out, xsel_out)) return;
+        __syncthreads();
+        clear();
     }
+    select_by_radix<THREADS, NCH>(ch, nchunks, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace decdec
