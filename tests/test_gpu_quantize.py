@@ -76,6 +76,27 @@ def test_residual_quantiser_matches_oracle_bit_for_bit(rbits, K, N):
     assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
 
 
+@pytest.mark.parametrize("rbits,K,N", [(8, 1, 16), (8, 127, 48), (4, 128, 1024), (4, 129, 1056), (2, 257, 4096), (8, 300, 1008), (8, 131, 4112)])
+def test_residual_scale_search_at_its_edges(rbits, K, N):
+    """Rows around a multiple of the 128 that are staged at a time, columns on both sides of the 1024 and 4096 where the
+    column blocks widen, and columns whose quotients by a candidate scale are exact half-integers: equal to the oracle's bits."""
+    g = np.random.default_rng([78, rbits, K, N])
+    R32 = (g.standard_normal((K, N)) * np.exp2(g.uniform(-30, 8, N))).astype(np.float32)
+    qmax = 2 ** (rbits - 1) - 1
+    for n in range(0, N, 5):  # column maximum a power of two times qmax: S = that power at alpha = 1, ties at every half
+        p = np.float32(2.0 ** g.integers(-18, 6))
+        R32[:, n] = (g.integers(-2 * qmax, 2 * qmax + 1, K) * np.float32(0.5)) * p
+        R32[0, n] = qmax * p
+    R32[:, 7] = 0.0
+    q_ref, S_ref = oracle.quantize_residual_sym(R32.astype(np.float64), rbits)
+    codes = torch.zeros((K, N * rbits // 8), dtype=torch.uint8, pin_memory=True)
+    S = torch.zeros(N, dtype=torch.float16, device="cuda")
+    dd.decdec_quantize_residual(K, N, rbits, torch.from_numpy(R32).cuda(), codes, S)
+    torch.cuda.synchronize()
+    assert np.array_equal(S.cpu().numpy().view(np.uint16), S_ref.view(np.uint16))
+    assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
+
+
 @pytest.mark.parametrize("rbits", [4, 2, 8])
 def test_uniform_linear_with_integer_residuals_end_to_end(rbits):
     """Device-prepared layer (quantiser, fp32 residual, residual quantiser) through the hot path,
