@@ -143,8 +143,7 @@ int decdec_ws_set_fetch_split(decdec_ws* ws, int32_t row_split);
  * K over workgroups of another size, so its part sums may round differently.
  *   FUSED (default): one kernel whose first workgroups do steps 1-3 (selection,
  *     zero-copy fetch, residual GEMV) and whose other workgroups do the base
- *     GEMV, on the caller's stream (fp16 and 4-bit residuals; the 2- and 8-bit
- *     formats run as SERIAL).
+ *     GEMV, on the caller's stream.
  *   SERIAL: residual kernel and base GEMV kernel one after the other on the
  *     caller's stream.
  *   TWO_STREAMS: the arrangement of Section 4.1: steps 1-3 on the workspace's

@@ -643,9 +643,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     // producers a column has in all.
     long tiles = 0;
     for (int m = 0; m < count; ++m) tiles += sh.N[m] / kTileCols;
-    // The one-grid kernel is built for fp16 and 4-bit residuals; the other formats take the separate kernels.
-    const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED &&
-                       (d0->rfmt == DECDEC_R_FP16 || d0->rfmt == DECDEC_R_INT4_SYM_COL);
+    const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED;
     const GemvPlan gp = gemv_plan(tiles, sh.K / kGroup, c.gemv_gpw, fused ? kWavesPerBlock : c.gemv_wpb);
     const int gpw = gp.gpw, wpb = gp.wpb, gslices = gp.slices;
     FetchPlan plan{0, 0, 0};

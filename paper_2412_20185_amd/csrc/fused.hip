@@ -12,8 +12,7 @@
 // finish while the fetch workgroups are still waiting for the host link, and
 // every workgroup adds its part sums into the per-column accumulators, the
 // last arrival writing y (finalize.h), so nothing has to be joined and nothing
-// else has to be launched.  (fp16 and 4-bit residuals; the 2- and 8-bit variants
-// of the bit-width study use the separate kernels.)  How many workgroups fetch (the paper's n_tb,
+// else has to be launched.  How many workgroups fetch (the paper's n_tb,
 // Section 4.4) follows from the number of wavefronts that share the rows of a
 // column segment (decdec_ws_set_fetch_split).
 #include <hip/hip_runtime.h>
@@ -67,7 +66,13 @@ hipError_t launch_nch(int nch, const KernelTimer* tm, dim3 grid, unsigned lds, h
 
 template <int KIND, typename... A>
 hipError_t launch_rfmt(int rfmt, A... a) {
-    return rfmt == 0 ? launch_nch<KIND, 16>(a...) : launch_nch<KIND, 4>(a...);
+    switch (rfmt) {
+        case 0: return launch_nch<KIND, 16>(a...);
+        case 1: return launch_nch<KIND, 4>(a...);
+        case 2: return launch_nch<KIND, 2>(a...);
+        case 3: return launch_nch<KIND, 8>(a...);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -76,7 +81,6 @@ hipError_t launch_compensated_gemv(int kind, int rfmt, const MultiShape& sh, con
                                    const FetchOperands& fop, const void* x, int select_chunks, int32_t* idx, void* xsel,
                                    int k, float* gpart, int gslices, int gpw, float* cpart, const FetchPlan& plan,
                                    const FinalizeArgs& fa, hipStream_t stream, const KernelTimer* tm) {
-    if (rfmt != 0 && rfmt != 1) return hipErrorInvalidValue;  // built for fp16 and 4-bit residuals only
     const int G = sh.K / kGroup;
     GemvJobs gj{};
     const FetchJobs fj = make_fetch_jobs(sh, fop);
