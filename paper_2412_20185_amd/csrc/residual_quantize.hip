@@ -118,7 +118,7 @@ constexpr int kMaxSlots = 80;     // threads that share a column's candidates x 
 //   * d has at most 24 significant bits and S q at most 18, so r - S q and d d are exact, fused or not.
 // An infinity or a NaN among the values makes err a NaN in both forms, and a NaN is never the least error.  Rows
 // beyond K count as zeros: they leave err as it is.
-// A 4096 x 4096 layer prepared with 4-bit residual codes: 18.8 -> 0.52 ms, of which the search is now 0.29 (0.15 at
+// A 4096 x 4096 layer prepared with 4-bit residual codes: 18.8 -> 0.49 ms, of which the search is now 0.26 (0.15 at
 // the issue rate) and the way of the codes to pinned host memory 0.15.
 template <int COLS, int WAVES, int APT>
 __global__ __launch_bounds__(64 * WAVES) void residual_scale_kernel(const float* __restrict__ R, int K, int N,
@@ -133,7 +133,10 @@ __global__ __launch_bounds__(64 * WAVES) void residual_scale_kernel(const float*
 
     const int tid = threadIdx.x;
     const int col = tid % COLS, slot = tid / COLS;
-    const float* src = R + (size_t)blockIdx.x * COLS + col;
+    // Workgroups go to the eight XCDs in turn: give each XCD's L2 adjacent columns, so that it reads a line once.
+    const int blocks = (int)gridDim.x, xcd = (int)blockIdx.x % 8;
+    const int block = xcd * (blocks / 8) + min(xcd, blocks % 8) + (int)blockIdx.x / 8;
+    const float* src = R + (size_t)block * COLS + col;
 
     float mx = 0.f;
     int k = slot;
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(64 * WAVES) void residual_scale_kernel(const float*
                 best = s_bits[a][tid];
             }
         }
-        scales_out[(size_t)blockIdx.x * COLS + tid] = __builtin_bit_cast(_Float16, best);
+        scales_out[(size_t)block * COLS + tid] = __builtin_bit_cast(_Float16, best);
     }
 }
 
@@ -256,12 +259,13 @@ hipError_t launch_quantize_residual(int bits, const float* R, void* codes_out, v
     _Float16* S = static_cast<_Float16*>(scales_out);
     // N is a multiple of 16.  Few columns: narrow blocks with one candidate per thread, so that every compute unit has
     // work; many: wide blocks, which read whole 64-byte pieces of a row and convert and load it for more candidates at
-    // once.  With 4096 rows, search and encoding into GPU memory, blocks of 4 / 8 / 16 columns, us: N = 256
-    // 115 / 144 / 348; 1024 139 / 162 / 358; 2048 219 / 180 / 361; 4096 379 / 300 / 374; 8192 629 / 650 / 544; 14336
-    // 1009 / 1033 / 960.
+    // once.  The line at 6144 columns: three workgroups of nine wavefronts fit a compute unit, so that up to there all
+    // run at once.  With 4096 rows, search and encoding into GPU memory, blocks of 4 / 8 / 16 columns, us: N = 256
+    // 110 / 146 / 340; 1024 119 / 152 / 346; 2048 186 / 165 / 353; 4096 304 / 267 / 358; 6144 434 / 383 / 510; 8192
+    // 549 / 616 / 520; 14336 961 / 984 / 921.
     if (N <= 1024) {
         residual_scale_kernel<4, 5, 1><<<dim3((unsigned)(N / 4)), dim3(320), 0, stream>>>(R, K, N, qmax, S);
-    } else if (N <= 4096) {
+    } else if (N <= 6144) {
         residual_scale_kernel<8, 9, 1><<<dim3((unsigned)(N / 8)), dim3(576), 0, stream>>>(R, K, N, qmax, S);
     } else {
         residual_scale_kernel<16, 4, 5><<<dim3((unsigned)(N / 16)), dim3(256), 0, stream>>>(R, K, N, qmax, S);

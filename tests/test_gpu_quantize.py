@@ -76,9 +76,9 @@ def test_residual_quantiser_matches_oracle_bit_for_bit(rbits, K, N):
     assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
 
 
-@pytest.mark.parametrize("rbits,K,N", [(8, 1, 16), (8, 127, 48), (4, 128, 1024), (4, 129, 1056), (2, 257, 4096), (8, 300, 1008), (8, 131, 4112)])
+@pytest.mark.parametrize("rbits,K,N", [(8, 1, 16), (8, 127, 48), (4, 128, 1024), (4, 129, 1056), (2, 257, 6144), (8, 300, 1008), (8, 131, 6160)])
 def test_residual_scale_search_at_its_edges(rbits, K, N):
-    """Rows around a multiple of the 128 that are staged at a time, columns on both sides of the 1024 and 4096 where the
+    """Rows around a multiple of the 128 that are staged at a time, columns on both sides of the 1024 and 6144 where the
     column blocks widen, and columns whose quotients by a candidate scale are exact half-integers: equal to the oracle's bits."""
     g = np.random.default_rng([78, rbits, K, N])
     R32 = (g.standard_normal((K, N)) * np.exp2(g.uniform(-30, 8, N))).astype(np.float32)
