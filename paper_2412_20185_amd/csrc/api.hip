@@ -575,8 +575,6 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     if (lin == nullptr || count < 1 || count > kMaxMulti || core == nullptr || x == nullptr) return DECDEC_EINVAL;
     Core& c = *core;
     MultiShape sh{};
-    GemvOperands gop{};
-    FetchOperands fop{};
     void* ys[kMaxMulti] = {};
     sh.n = count;
     const decdec_desc* d0 = lin[0].desc;
@@ -594,11 +592,6 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
         if (!aligned(L.zeros_or_lut_f16_dev, L.desc->wfmt == DECDEC_W_LUT_COL8 ? 16 : 2)) return DECDEC_EINVAL;
         sh.N[m] = L.desc->N;
         sh.col0[m + 1] = sh.col0[m] + L.desc->N;
-        gop.Wq[m] = L.Wq_dev;
-        gop.scales[m] = L.scales_f16_dev;
-        gop.zeros_or_lut[m] = L.zeros_or_lut_f16_dev;
-        fop.R[m] = L.R_pinned;
-        fop.R_scales[m] = L.R_scales_f16_dev;
         ys[m] = L.y_f16_dev;
     }
     sh.K = d0->K;
@@ -645,24 +638,46 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     for (int m = 0; m < count; ++m) tiles += sh.N[m] / kTileCols;
     const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED;
     const GemvPlan gp = gemv_plan(tiles, sh.K / kGroup, c.gemv_gpw, fused ? kWavesPerBlock : c.gemv_wpb);
-    const int gpw = gp.gpw, wpb = gp.wpb, gslices = gp.slices;
+    const int gslices = gp.slices;
     FetchPlan plan{0, 0, 0};
     if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm);
     const int cslices = plan.slices;
 
-    FinalizeArgs fa{};
+    CallArgs a{};
+    int tiles_to = 0, segs_to = 0;
     for (int m = 0; m < count; ++m) {
-        fa.y[m] = static_cast<_Float16*>(ys[m]);
-        fa.col0[m] = sh.col0[m];
+        MatArgs& mat = a.mat[m];
+        mat.Wq = static_cast<const uint4*>(lin[m].Wq_dev);
+        mat.scales = static_cast<const uint16_t*>(lin[m].scales_f16_dev);
+        mat.zeros_or_lut = static_cast<const uint16_t*>(lin[m].zeros_or_lut_f16_dev);
+        mat.R = static_cast<const uint4*>(lin[m].R_pinned);
+        mat.Rs = static_cast<const uint16_t*>(lin[m].R_scales_f16_dev);
+        mat.y = static_cast<_Float16*>(ys[m]);
+        mat.N = sh.N[m];
+        mat.col0 = sh.col0[m];
+        mat.tile_end = tiles_to += sh.N[m] / kTileCols;
+        mat.seg_end = segs_to += (sh.N[m] + kFetchSegmentCols - 1) / kFetchSegmentCols;
     }
-    fa.acc = c.inkernel_accumulate ? c.acc : nullptr;
-    fa.gpart = c.gpart;
-    fa.cpart = c.cpart;
-    fa.gslices = gslices;
-    fa.cslices = cslices;
-    fa.Ntot = sh.col0[count];
+    a.x = static_cast<const uint16_t*>(x);
+    a.acc = c.inkernel_accumulate ? c.acc : nullptr;
+    a.n = count;
+    a.G = sh.K / kGroup;
+    a.gslices = gslices;
+    a.gpw = gp.gpw;
+    a.gdiv = reciprocal_of(gslices);
+    a.producers = gslices + cslices;
     // One slice and no residual term: the base GEMV rounds and writes y itself, nothing is left to add.
-    fa.direct = k == 0 && gslices == 1 ? 1 : 0;
+    a.direct = k == 0 && gslices == 1 ? 1 : 0;
+    a.Ntot = sh.col0[count];
+    a.gpart = c.gpart;
+    a.k = k;
+    a.cslices = cslices;
+    a.row_waves = plan.row_waves;
+    a.cdiv = reciprocal_of(cslices);
+    a.nfetch = plan.segments * plan.slices;
+    a.cpart = c.cpart;
+    a.tiles = (int)tiles;
+    a.segments = plan.segments;
 
     if (c.acc_dirty) {
         DD_HIP(launch_clear_u32(reinterpret_cast<unsigned*>(c.acc), 2 * c.maxN, stream));
@@ -671,12 +686,12 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     bool forked = false;  // TWO_STREAMS: the side stream has been made to wait for `stream` and not yet joined back
     const int rc_enq = [&]() -> int {
         if (k == 0) {
-            DD_HIP(launch_gemv(kind, sh, gop, x, c.gpart, gslices, gpw, wpb, fa, stream, tm[0]));
+            DD_HIP(launch_gemv(kind, a, gp.wpb, stream, tm[0]));
             if (pmask) *pmask |= 1;
         } else {
-            // The kernels that follow read idx / xsel only; the const is dropped for the shared signatures.
-            int32_t* idx = const_cast<int32_t*>(idx_in);
-            void* xsel = const_cast<void*>(xsel_in);
+            // The kernels that follow only read a selection that is given; the const is dropped for the shared struct.
+            a.idx = const_cast<int32_t*>(idx_in);
+            a.xsel = static_cast<uint16_t*>(const_cast<void*>(xsel_in));
             int select_chunks = 0;
             const bool two_streams = c.mode == DECDEC_MODE_TWO_STREAMS;
             hipStream_t comp = two_streams ? c.side : stream;  // where steps 1-3 run
@@ -687,8 +702,8 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
                 forked = true;
             }
             if (!have_idx) {
-                idx = c.idx;
-                xsel = c.xsel;
+                a.idx = c.idx;
+                a.xsel = static_cast<uint16_t*>(c.xsel);
                 select_chunks = c.separate_select ? 0 : fetch_select_chunks(sh.K, k);
                 if (select_chunks == 0) {
                     DD_HIP(launch_select_topk(x, sh.K, k, c.idx, c.xsel, comp, tm[1]));
@@ -696,15 +711,13 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
                 }
             }
             if (fused) {
-                DD_HIP(launch_compensated_gemv(kind, d0->rfmt, sh, gop, fop, x, select_chunks, idx, xsel, k, c.gpart,
-                                               gslices, gpw, c.cpart, plan, fa, stream, tm[2]));
+                DD_HIP(launch_compensated_gemv(kind, d0->rfmt, a, select_chunks, stream, tm[2]));
                 if (pmask) *pmask |= 4;
             } else {
-                DD_HIP(launch_fetch(d0->rfmt, sh, fop, x, select_chunks, idx, xsel, k, c.cpart, plan, fa, comp,
-                                    tm[2]));
+                DD_HIP(launch_fetch(d0->rfmt, a, select_chunks, comp, tm[2]));
                 if (pmask) *pmask |= 4;
                 if (two_streams) DD_HIP(hipEventRecord(c.ev_join, c.side));
-                DD_HIP(launch_gemv(kind, sh, gop, x, c.gpart, gslices, gpw, wpb, fa, stream, tm[0]));
+                DD_HIP(launch_gemv(kind, a, gp.wpb, stream, tm[0]));
                 if (pmask) *pmask |= 1;
                 if (two_streams) {
                     DD_HIP(hipStreamWaitEvent(stream, c.ev_join, 0));
@@ -712,7 +725,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
                 }
             }
         }
-        if (!c.inkernel_accumulate && !fa.direct) {
+        if (!c.inkernel_accumulate && !a.direct) {
             DD_HIP(launch_accumulate(sh, ys, c.gpart, gslices, c.cpart, cslices, stream, tm[3]));
             if (pmask) *pmask |= 8;
         }

@@ -8,13 +8,9 @@ namespace decdec {
 namespace {
 
 template <int BITS, int SELECT_NCH>
-__global__ __launch_bounds__(kBlockThreads) void fetch_kernel(const FetchJobs jobs, const FinalizeArgs fa,
-                                                             const uint16_t* __restrict__ x, int32_t* idx_g,
-                                                             uint16_t* xsel_g, int k, int K, int Ntot,
-                                                             float* __restrict__ cpart, int segments, int slices,
-                                                             int row_waves) {
-    fetch_block<BITS, SELECT_NCH>(jobs, fa, x, idx_g, xsel_g, k, K, Ntot, cpart, segments, slices, row_waves,
-                                  (int)blockIdx.x);
+__global__ __launch_bounds__(kBlockThreads) void fetch_kernel(const CallArgs a) {
+    touch_args(a);
+    fetch_block<BITS, SELECT_NCH>(a, (int)blockIdx.x);
 }
 
 }  // namespace
@@ -49,42 +45,24 @@ int fetch_select_chunks(int K, int k) {
 }
 
 template <int NCH>
-static hipError_t launch_fetch_nch(int rfmt, const FetchJobs& jobs, const FinalizeArgs& fa, const uint16_t* x,
-                                   int32_t* idx, uint16_t* xs, int k, int K, int Ntot, float* cpart,
-                                   const FetchPlan& p, hipStream_t stream, const KernelTimer* tm) {
-    const unsigned lds = NCH > 0 ? (unsigned)(((size_t)k * 6 + 15) / 16 * 16) : 0u;
-    const dim3 grid((unsigned)(p.segments * p.slices)), block(kBlockThreads);
+static hipError_t launch_fetch_nch(int rfmt, const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
+    const unsigned lds = selection_lds_bytes(NCH, a.k);
+    const dim3 grid((unsigned)(a.segments * a.cslices)), block(kBlockThreads);
     switch (rfmt) {
-        case 0:
-            return launch_kernel(tm, fetch_kernel<16, NCH>, grid, block, lds, stream, jobs, fa, x, idx, xs, k, K, Ntot,
-                                 cpart, p.segments, p.slices, p.row_waves);
-        case 1:
-            return launch_kernel(tm, fetch_kernel<4, NCH>, grid, block, lds, stream, jobs, fa, x, idx, xs, k, K, Ntot,
-                                 cpart, p.segments, p.slices, p.row_waves);
-        case 2:
-            return launch_kernel(tm, fetch_kernel<2, NCH>, grid, block, lds, stream, jobs, fa, x, idx, xs, k, K, Ntot,
-                                 cpart, p.segments, p.slices, p.row_waves);
-        default:
-            return launch_kernel(tm, fetch_kernel<8, NCH>, grid, block, lds, stream, jobs, fa, x, idx, xs, k, K, Ntot,
-                                 cpart, p.segments, p.slices, p.row_waves);
+        case 0: return launch_kernel(tm, fetch_kernel<16, NCH>, grid, block, lds, stream, a);
+        case 1: return launch_kernel(tm, fetch_kernel<4, NCH>, grid, block, lds, stream, a);
+        case 2: return launch_kernel(tm, fetch_kernel<2, NCH>, grid, block, lds, stream, a);
+        default: return launch_kernel(tm, fetch_kernel<8, NCH>, grid, block, lds, stream, a);
     }
 }
 
-// select_chunks > 0: the kernel selects for itself from x (and writes the selection to idx / xsel);
-// 0: idx / xsel hold the selection already.
-hipError_t launch_fetch(int rfmt, const MultiShape& sh, const FetchOperands& op, const void* x, int select_chunks,
-                        int32_t* idx, void* xsel, int k, float* cpart, const FetchPlan& plan, const FinalizeArgs& fa,
-                        hipStream_t stream, const KernelTimer* tm) {
-    const FetchJobs jobs = make_fetch_jobs(sh, op);
-    const uint16_t* xp = static_cast<const uint16_t*>(x);
-    uint16_t* xs = static_cast<uint16_t*>(xsel);
-    const int Ntot = sh.col0[sh.n];
+hipError_t launch_fetch(int rfmt, const CallArgs& a, int select_chunks, hipStream_t stream, const KernelTimer* tm) {
     switch (select_chunks) {
-        case 0: return launch_fetch_nch<0>(rfmt, jobs, fa, xp, idx, xs, k, sh.K, Ntot, cpart, plan, stream, tm);
-        case 1: return launch_fetch_nch<1>(rfmt, jobs, fa, xp, idx, xs, k, sh.K, Ntot, cpart, plan, stream, tm);
-        case 2: return launch_fetch_nch<2>(rfmt, jobs, fa, xp, idx, xs, k, sh.K, Ntot, cpart, plan, stream, tm);
-        case 4: return launch_fetch_nch<4>(rfmt, jobs, fa, xp, idx, xs, k, sh.K, Ntot, cpart, plan, stream, tm);
-        case 8: return launch_fetch_nch<8>(rfmt, jobs, fa, xp, idx, xs, k, sh.K, Ntot, cpart, plan, stream, tm);
+        case 0: return launch_fetch_nch<0>(rfmt, a, stream, tm);
+        case 1: return launch_fetch_nch<1>(rfmt, a, stream, tm);
+        case 2: return launch_fetch_nch<2>(rfmt, a, stream, tm);
+        case 4: return launch_fetch_nch<4>(rfmt, a, stream, tm);
+        case 8: return launch_fetch_nch<8>(rfmt, a, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }

@@ -29,41 +29,13 @@
 
 #include "finalize.h"
 #include "kernels.h"
+#include "layout.h"
 #include "select_block.h"
 
 namespace decdec {
 
-constexpr int kFetchSegmentCols = 512;  // output columns of one column segment = threads of a workgroup
-
 __device__ __forceinline__ float h2f(uint32_t bits16) {
     return (float)__builtin_bit_cast(_Float16, (uint16_t)bits16);
-}
-
-struct FetchJobs {
-    const uint4* R[kMaxMulti];
-    const uint16_t* Rs[kMaxMulti];
-    int N[kMaxMulti];
-    int col0[kMaxMulti];
-    int wc_end[kMaxMulti];  // cumulative count of column segments up to and including matrix m
-    int n;
-};
-
-// Workgroup `bid` of the residual grid: row slice rs = bid / segments, column
-// segment bid % segments of the concatenated matrices.
-struct BlockTask {
-    int m, wc, rs;
-};
-
-__device__ __forceinline__ BlockTask block_task(const FetchJobs& jobs, int segments, int bid) {
-    BlockTask t;
-    t.rs = bid / segments;
-    const int c = bid - t.rs * segments;
-    int m = 0;
-#pragma unroll
-    for (int i = 0; i < kMaxMulti - 1; ++i) m += (i + 1 < jobs.n && c >= jobs.wc_end[i]) ? 1 : 0;
-    t.m = m;
-    t.wc = c - (m > 0 ? jobs.wc_end[m - 1] : 0);
-    return t;
 }
 
 // sc_indices / x[sc_indices] as the fetch loops see them: global memory, or LDS
@@ -148,11 +120,10 @@ __device__ __forceinline__ void accumulate_piece(const typename RowPiece<BITS>::
 // After the row loop the sums of the wavefronts (and half-wavefronts) are added through LDS in a fixed
 // order: thread t of the workgroup ends up with the segment's sum for column t and adds it into the
 // column's accumulator (finalize.h), or, when a separate kernel does the adding, writes it to row rs of cpart.
+//
+// Workgroup `bid` is slice rs = bid % a.cslices of segment bid / a.cslices, counted over all matrices.
 template <int BITS, int SELECT_NCH>
-__device__ __forceinline__ void fetch_block(const FetchJobs& jobs, const FinalizeArgs& fa,
-                                            const uint16_t* __restrict__ x, int32_t* idx_g, uint16_t* xsel_g, int k,
-                                            int K, int Ntot, float* __restrict__ cpart, int segments, int slices,
-                                            int row_waves, int bid) {
+__device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     typedef typename RowPiece<BITS>::type piece_t;
     constexpr int CPL = BITS == 2 ? 16 : 8;             // columns per lane
     constexpr int LPR = kFetchSegmentCols / CPL;        // lanes that cover the segment's part of one row
@@ -170,28 +141,47 @@ __device__ __forceinline__ void fetch_block(const FetchJobs& jobs, const Finaliz
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Selection sel = obtain_selection<SELECT_NCH>(x, K, k, idx_g, xsel_g, lds.sh, bid);
+    const int k = a.k, K = a.G * kGroup;
+    const int row_waves = a.row_waves, slices = a.cslices;
+    const int seg = divide_by(bid, a.cdiv);
+    const int rs = bid - seg * slices;
+    int m = 0, seg0 = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxMulti - 1; ++i) {
+        if (i + 1 < a.n && seg >= a.mat[i].seg_end) {
+            m = i + 1;
+            seg0 = a.mat[i].seg_end;
+        }
+    }
+    const int wc = seg - seg0;
+    const MatArgs& mat = a.mat[m];
+    int N = mat.N, col0 = mat.col0, producers = a.producers;
+    const uint4* rows_base = mat.R;
+    const uint16_t* Rs = mat.Rs;
+    _Float16* y = mat.y;
+    unsigned long long* acc_words = a.acc;
+    asm volatile("" : "+s"(N), "+s"(col0), "+s"(producers), "+s"(rows_base), "+s"(Rs), "+s"(y), "+s"(acc_words));
+
+    const Selection sel = obtain_selection<SELECT_NCH>(a.x, K, k, a.idx, a.xsel, lds.sh, bid);
     const int32_t* idx = sel.idx;
     const uint16_t* xsel = sel.xsel;
-    const BlockTask t = block_task(jobs, segments, bid);
-    const int N = jobs.N[t.m];
-    const piece_t* __restrict__ R = reinterpret_cast<const piece_t*>(jobs.R[t.m]);
+    const piece_t* __restrict__ R = reinterpret_cast<const piece_t*>(rows_base);
     const int sub = lane / LPR;                       // which of the SUB rows of a load instruction
-    const int piece = t.wc * LPR + (lane % LPR);      // this lane's CPL columns of a row
+    const int piece = wc * LPR + (lane % LPR);      // this lane's CPL columns of a row
     const bool active = piece * CPL < N;
     const size_t row_pieces = (size_t)(N / CPL);
     // rows of this wavefront: slice (rs, wave) out of slices * row_waves equal shares of the k selected rows
     const int rows_per = (k + slices * row_waves - 1) / (slices * row_waves);
-    const int j0 = min((t.rs * row_waves + wave) * rows_per, k);
+    const int j0 = min((rs * row_waves + wave) * rows_per, k);
     const int j1 = wave < row_waves ? min(j0 + rows_per, k) : j0;
 
-    const int ocol = t.wc * kFetchSegmentCols + tid;  // the column this thread owns after the LDS round
+    const int ocol = wc * kFetchSegmentCols + tid;  // the column this thread owns after the LDS round
     const bool owns = ocol < N;
     // The column scale is requested before the rows, so that it arrives behind the first row loads instead
     // of costing a round trip of its own after the last one.
     uint16_t sraw = 0;
     if constexpr (BITS != 16) {
-        if (owns) sraw = jobs.Rs[t.m][ocol];
+        if (owns) sraw = Rs[ocol];
     }
 
     float acc[CPL];
@@ -236,29 +226,17 @@ __device__ __forceinline__ void fetch_block(const FetchJobs& jobs, const Finaliz
     if constexpr (BITS != 16) val *= h2f(sraw);
 
     if (owns) {
-        if (fa.acc != nullptr) {
-            arrive(fa, t.m, ocol, val);
+        if (acc_words != nullptr) {
+            arrive(acc_words + col0 + ocol, y + ocol, producers, val);
         } else {
-            cpart[(size_t)t.rs * Ntot + jobs.col0[t.m] + ocol] = val;
+            a.cpart[(size_t)rs * a.Ntot + col0 + ocol] = val;
         }
     }
 }
 
-// Host: kernel-side description of the matrices of one call.
-inline FetchJobs make_fetch_jobs(const MultiShape& sh, const FetchOperands& op) {
-    FetchJobs jobs{};
-    jobs.n = sh.n;
-    const int cpw = kFetchSegmentCols;
-    int wc = 0;
-    for (int m = 0; m < sh.n; ++m) {
-        jobs.R[m] = static_cast<const uint4*>(op.R[m]);
-        jobs.Rs[m] = static_cast<const uint16_t*>(op.R_scales[m]);
-        jobs.N[m] = sh.N[m];
-        jobs.col0[m] = sh.col0[m];
-        wc += (sh.N[m] + cpw - 1) / cpw;
-        jobs.wc_end[m] = wc;
-    }
-    return jobs;
+// Host: dynamic LDS of a kernel that selects for itself.
+inline unsigned selection_lds_bytes(int select_chunks, int k) {
+    return select_chunks > 0 ? (unsigned)(((size_t)k * 6 + 15) / 16 * 16) : 0u;
 }
 
 }  // namespace decdec

@@ -32,17 +32,6 @@
 
 namespace decdec {
 
-struct FinalizeArgs {
-    _Float16* y[kMaxMulti];
-    int col0[kMaxMulti];           // first concatenated column of matrix m
-    unsigned long long* acc;       // one word per concatenated column, zero between calls; null: the
-                                   // producers leave fp32 partial rows and a separate kernel adds them
-    float* gpart;                  // [gslices][Ntot]   (acc == null only)
-    float* cpart;                  // [cslices][Ntot]   (acc == null only)
-    int gslices, cslices, Ntot;
-    int direct;                    // 1: the base GEMV is the only producer and has one slice: it writes y itself
-};
-
 constexpr float kFixedScale = 1073741824.f;       // 2^30
 constexpr float kFixedInvScale = 1.f / 1073741824.f;
 constexpr float kFixedLimit = 2097152.f;          // 2^21
@@ -59,14 +48,13 @@ __device__ __forceinline__ long long to_fixed(float v) {
 // Fixed-point sum -> the fp16 result (one rounding to fp32, exact scaling, one rounding to fp16).
 __device__ __forceinline__ _Float16 from_fixed(long long s) { return (_Float16)((float)s * kFixedInvScale); }
 
-// One thread per column: add part sum v of column n of matrix m.  Called once by every one of the
-// gslices + cslices producers of that column; the last one writes y[n].
-__device__ __forceinline__ void arrive(const FinalizeArgs& fa, int m, int n, float v) {
-    unsigned long long* word = fa.acc + fa.col0[m] + n;
+// One thread per column: add part sum v into the column's accumulator.  Called once by every one of the `producers`
+// of that column; the last one writes *y.
+__device__ __forceinline__ void arrive(unsigned long long* word, _Float16* y, int producers, float v) {
     const unsigned long long term = ((unsigned long long)to_fixed(v) << kArrivalBits) + 1ull;
     const unsigned long long old = __hip_atomic_fetch_add(word, term, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((int)(old & ((1ull << kArrivalBits) - 1)) + 1 == fa.gslices + fa.cslices) {
-        fa.y[m][n] = from_fixed((long long)(old + term) >> kArrivalBits);
+    if ((int)(old & ((1ull << kArrivalBits) - 1)) + 1 == producers) {
+        *y = from_fixed((long long)(old + term) >> kArrivalBits);
         __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next call
     }
 }

@@ -24,96 +24,50 @@ namespace decdec {
 namespace {
 
 template <int KIND, int RBITS, int SELECT_NCH>
-__global__ __launch_bounds__(kBlockThreads) void compensated_gemv_kernel(
-    const GemvJobs gjobs, const FetchJobs fjobs, const FinalizeArgs fa, const uint16_t* __restrict__ x,
-    int32_t* idx_g, uint16_t* xsel_g, int k, int K, int Ntot, float* __restrict__ gpart, float* __restrict__ cpart,
-    int G, int gslices, int gpw, int segments, int cslices, int row_waves, int nfetch) {
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(SELECT_NCH == 8 || RBITS == 2 ? 6 : 8))) void compensated_gemv_kernel(const CallArgs a) {
+    touch_args(a);
     const int bid = (int)blockIdx.x;
-    if (bid < nfetch) {
-        fetch_block<RBITS, SELECT_NCH>(fjobs, fa, x, idx_g, xsel_g, k, K, Ntot, cpart, segments, cslices, row_waves, bid);
+    if (bid < a.nfetch) {
+        fetch_block<RBITS, SELECT_NCH>(a, bid);
     } else {
-        gemv_block<KIND, kWavesPerBlock, 2>(gjobs, fa, reinterpret_cast<const uint32_t*>(x), gpart, Ntot, G, gslices,
-                                            gpw, bid - nfetch);
+        gemv_block<KIND, kWavesPerBlock, 2>(a, bid - a.nfetch);
     }
 }
 
 template <int KIND, int RBITS>
-hipError_t launch_nch(int nch, const KernelTimer* tm, dim3 grid, unsigned lds, hipStream_t stream,
-                      const GemvJobs& gj, const FetchJobs& fj, const FinalizeArgs& fa, const uint16_t* x, int32_t* idx,
-                      uint16_t* xs, int k, int K, int Ntot, float* gpart, float* cpart, int G, int gslices, int gpw,
-                      int segments, int cslices, int row_waves, int nfetch) {
-    const dim3 block(kBlockThreads);
+hipError_t launch_nch(const CallArgs& a, int nch, hipStream_t stream, const KernelTimer* tm) {
+    const dim3 grid((unsigned)(a.nfetch + a.tiles * a.gslices)), block(kBlockThreads);
+    const unsigned lds = selection_lds_bytes(nch, a.k);
     switch (nch) {
-        case 0:
-            return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0>, grid, block, lds, stream, gj, fj, fa, x, idx,
-                                 xs, k, K, Ntot, gpart, cpart, G, gslices, gpw, segments, cslices, row_waves, nfetch);
-        case 1:
-            return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1>, grid, block, lds, stream, gj, fj, fa, x, idx,
-                                 xs, k, K, Ntot, gpart, cpart, G, gslices, gpw, segments, cslices, row_waves, nfetch);
-        case 2:
-            return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 2>, grid, block, lds, stream, gj, fj, fa, x, idx,
-                                 xs, k, K, Ntot, gpart, cpart, G, gslices, gpw, segments, cslices, row_waves, nfetch);
-        case 4:
-            return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 4>, grid, block, lds, stream, gj, fj, fa, x, idx,
-                                 xs, k, K, Ntot, gpart, cpart, G, gslices, gpw, segments, cslices, row_waves, nfetch);
-        case 8:
-            return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 8>, grid, block, lds, stream, gj, fj, fa, x, idx,
-                                 xs, k, K, Ntot, gpart, cpart, G, gslices, gpw, segments, cslices, row_waves, nfetch);
-        default:
-            return hipErrorInvalidValue;
+        case 0: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0>, grid, block, lds, stream, a);
+        case 1: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1>, grid, block, lds, stream, a);
+        case 2: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 2>, grid, block, lds, stream, a);
+        case 4: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 4>, grid, block, lds, stream, a);
+        case 8: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 8>, grid, block, lds, stream, a);
+        default: return hipErrorInvalidValue;
     }
 }
 
-template <int KIND, typename... A>
-hipError_t launch_rfmt(int rfmt, A... a) {
+template <int KIND>
+hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, hipStream_t stream, const KernelTimer* tm) {
     switch (rfmt) {
-        case 0: return launch_nch<KIND, 16>(a...);
-        case 1: return launch_nch<KIND, 4>(a...);
-        case 2: return launch_nch<KIND, 2>(a...);
-        case 3: return launch_nch<KIND, 8>(a...);
+        case 0: return launch_nch<KIND, 16>(a, nch, stream, tm);
+        case 1: return launch_nch<KIND, 4>(a, nch, stream, tm);
+        case 2: return launch_nch<KIND, 2>(a, nch, stream, tm);
+        case 3: return launch_nch<KIND, 8>(a, nch, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }
 
 }  // namespace
 
-hipError_t launch_compensated_gemv(int kind, int rfmt, const MultiShape& sh, const GemvOperands& gop,
-                                   const FetchOperands& fop, const void* x, int select_chunks, int32_t* idx, void* xsel,
-                                   int k, float* gpart, int gslices, int gpw, float* cpart, const FetchPlan& plan,
-                                   const FinalizeArgs& fa, hipStream_t stream, const KernelTimer* tm) {
-    const int G = sh.K / kGroup;
-    GemvJobs gj{};
-    const FetchJobs fj = make_fetch_jobs(sh, fop);
-    gj.n = sh.n;
-    int tiles = 0;
-    for (int m = 0; m < sh.n; ++m) {
-        gj.Wq[m] = static_cast<const uint4*>(gop.Wq[m]);
-        gj.scales[m] = static_cast<const uint16_t*>(gop.scales[m]);
-        gj.zeros_or_lut[m] = static_cast<const uint16_t*>(gop.zeros_or_lut[m]);
-        gj.N[m] = sh.N[m];
-        gj.col0[m] = sh.col0[m];
-        tiles += sh.N[m] / kTileCols;
-        gj.tile_end[m] = tiles;
-    }
-    const int nfetch = plan.segments * plan.slices;
-    const dim3 grid((unsigned)(nfetch + tiles * gslices));
-    const unsigned lds = select_chunks > 0 ? (unsigned)(((size_t)k * 6 + 15) / 16 * 16) : 0u;
-    const uint16_t* xp = static_cast<const uint16_t*>(x);
-    uint16_t* xs = static_cast<uint16_t*>(xsel);
-    const int Ntot = sh.col0[sh.n];
+hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, hipStream_t stream,
+                                   const KernelTimer* tm) {
     switch (kind) {
-        case PACK_U4:
-            return launch_rfmt<PACK_U4>(rfmt, select_chunks, tm, grid, lds, stream, gj, fj, fa, xp, idx, xs, k, sh.K, Ntot,
-                                        gpart, cpart, G, gslices, gpw, plan.segments, plan.slices, plan.row_waves, nfetch);
-        case PACK_U3:
-            return launch_rfmt<PACK_U3>(rfmt, select_chunks, tm, grid, lds, stream, gj, fj, fa, xp, idx, xs, k, sh.K, Ntot,
-                                        gpart, cpart, G, gslices, gpw, plan.segments, plan.slices, plan.row_waves, nfetch);
-        case PACK_LUT3:
-            return launch_rfmt<PACK_LUT3>(rfmt, select_chunks, tm, grid, lds, stream, gj, fj, fa, xp, idx, xs, k, sh.K,
-                                          Ntot, gpart, cpart, G, gslices, gpw, plan.segments, plan.slices,
-                                          plan.row_waves, nfetch);
-        default:
-            return hipErrorInvalidValue;
+        case PACK_U4: return launch_rfmt<PACK_U4>(rfmt, a, select_chunks, stream, tm);
+        case PACK_U3: return launch_rfmt<PACK_U3>(rfmt, a, select_chunks, stream, tm);
+        case PACK_LUT3: return launch_rfmt<PACK_LUT3>(rfmt, a, select_chunks, stream, tm);
+        default: return hipErrorInvalidValue;
     }
 }
 

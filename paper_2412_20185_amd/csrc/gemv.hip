@@ -8,29 +8,24 @@ namespace decdec {
 namespace {
 
 template <int KIND, int WPB, int NBUF>
-__global__ __launch_bounds__(WPB * 64) void gemv_kernel(const GemvJobs jobs, const FinalizeArgs fa,
-                                                        const uint32_t* __restrict__ x32, float* __restrict__ part,
-                                                        int Ntot, int G, int slices, int gpw) {
-    gemv_block<KIND, WPB, NBUF>(jobs, fa, x32, part, Ntot, G, slices, gpw, (int)blockIdx.x);
+__global__ __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(NBUF == 2 ? 8 : 4))) void gemv_kernel(const CallArgs a) {
+    touch_args(a);
+    gemv_block<KIND, WPB, NBUF>(a, (int)blockIdx.x);
 }
 
 template <int KIND, int WPB>
-hipError_t launch_depth(int nbuf, const KernelTimer* tm, dim3 grid, hipStream_t stream, const GemvJobs& jobs,
-                        const FinalizeArgs& fa, const uint32_t* x32, float* part, int Ntot, int G, int slices, int gpw) {
-    const dim3 block(WPB * 64);
-    if (nbuf >= 4)
-        return launch_kernel(tm, gemv_kernel<KIND, WPB, 4>, grid, block, 0, stream, jobs, fa, x32, part, Ntot, G, slices,
-                             gpw);
-    return launch_kernel(tm, gemv_kernel<KIND, WPB, 2>, grid, block, 0, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
+hipError_t launch_depth(const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
+    const dim3 grid((unsigned)(a.tiles * a.gslices)), block(WPB * 64);
+    if (a.gpw > 2) return launch_kernel(tm, gemv_kernel<KIND, WPB, 4>, grid, block, 0, stream, a);  // tiles a wave keeps in flight
+    return launch_kernel(tm, gemv_kernel<KIND, WPB, 2>, grid, block, 0, stream, a);
 }
 
 template <int KIND>
-hipError_t launch_waves(int wpb, int nbuf, const KernelTimer* tm, dim3 grid, hipStream_t stream, const GemvJobs& jobs,
-                        const FinalizeArgs& fa, const uint32_t* x32, float* part, int Ntot, int G, int slices, int gpw) {
+hipError_t launch_waves(const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm) {
     switch (wpb) {
-        case 4: return launch_depth<KIND, 4>(nbuf, tm, grid, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
-        case 8: return launch_depth<KIND, 8>(nbuf, tm, grid, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
-        case 16: return launch_depth<KIND, 16>(nbuf, tm, grid, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
+        case 4: return launch_depth<KIND, 4>(a, stream, tm);
+        case 8: return launch_depth<KIND, 8>(a, stream, tm);
+        case 16: return launch_depth<KIND, 16>(a, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }
@@ -58,34 +53,12 @@ GemvPlan gemv_plan(long tiles, int G, int gpw_request, int wpb_request) {
     return p;
 }
 
-hipError_t launch_gemv(int kind, const MultiShape& sh, const GemvOperands& op, const void* x, float* part,
-                       int slices, int gpw, int wpb, const FinalizeArgs& fa, hipStream_t stream, const KernelTimer* tm) {
-    const int G = sh.K / kGroup;
-    GemvJobs jobs{};
-    jobs.n = sh.n;
-    int tiles = 0;
-    for (int m = 0; m < sh.n; ++m) {
-        jobs.Wq[m] = static_cast<const uint4*>(op.Wq[m]);
-        jobs.scales[m] = static_cast<const uint16_t*>(op.scales[m]);
-        jobs.zeros_or_lut[m] = static_cast<const uint16_t*>(op.zeros_or_lut[m]);
-        jobs.N[m] = sh.N[m];
-        jobs.col0[m] = sh.col0[m];
-        tiles += sh.N[m] / kTileCols;
-        jobs.tile_end[m] = tiles;
-    }
-    const dim3 grid((unsigned)(tiles * slices));
-    const uint32_t* x32 = static_cast<const uint32_t*>(x);
-    const int Ntot = sh.col0[sh.n];
-    const int nbuf = gpw > 2 ? 4 : 2;  // tiles a wave keeps in flight
+hipError_t launch_gemv(int kind, const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm) {
     switch (kind) {
-        case PACK_U4:
-            return launch_waves<PACK_U4>(wpb, nbuf, tm, grid, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
-        case PACK_U3:
-            return launch_waves<PACK_U3>(wpb, nbuf, tm, grid, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
-        case PACK_LUT3:
-            return launch_waves<PACK_LUT3>(wpb, nbuf, tm, grid, stream, jobs, fa, x32, part, Ntot, G, slices, gpw);
-        default:
-            return hipErrorInvalidValue;
+        case PACK_U4: return launch_waves<PACK_U4>(a, wpb, stream, tm);
+        case PACK_U3: return launch_waves<PACK_U3>(a, wpb, stream, tm);
+        case PACK_LUT3: return launch_waves<PACK_LUT3>(a, wpb, stream, tm);
+        default: return hipErrorInvalidValue;
     }
 }
 

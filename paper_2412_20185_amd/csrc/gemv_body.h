@@ -16,7 +16,8 @@
 //     are used at two bit positions p (4 and 7), each with its own
 //     accumulators, combined once per group;
 //   * all lanes of a wave need the same activations, so x is read through the
-//     scalar cache into SGPRs and used as the scalar operand of the dot;
+//     scalar cache into SGPRs and used as the scalar operand of the dot; (see
+//     tile_dot for when);
 //   * the zero point is factored out of the inner loop:
 //     sum_k s (q_k - z) x_k = s (sum_k q_k x_k - z sum_k x_k), with the
 //     group's sum of x formed once per wave by a DPP reduction;
@@ -64,49 +65,66 @@ __device__ __forceinline__ float wave_sum(float v) {
 // and by 2^24 once per group.
 constexpr float kTwoPow24 = 16777216.f;
 
-// sum_k q_k x_k over one group for one lane, 4-bit layout.  xs: the group's 64
-// activation pairs (wave-uniform address).
-__device__ __forceinline__ float group_dot_u4(const uint4 (&q)[4], const uint32_t* __restrict__ xs) {
-    float a = 0.f, b = 0.f, c = 0.f, d = 0.f;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t wd[4] = {q[p].x, q[p].y, q[p].z, q[p].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int w = 4 * p + i;
-            const uint32_t t = wd[i];
-            a = dot2((t << 4) & 0x00F000F0u, xs[4 * w + 0], a);
-            b = dot2(t & 0x00F000F0u, xs[4 * w + 1], b);
-            c = dot2((t >> 4) & 0x00F000F0u, xs[4 * w + 2], c);
-            d = dot2((t >> 8) & 0x00F000F0u, xs[4 * w + 3], d);
-        }
-    }
-    return ((a + b) + (c + d)) * (kTwoPow24 / 16.f);
+// A tile is worked off in four quarters: KIND's words 4c..4c+3 (4-bit) or 3c..3c+2 with the activation pairs from
+// kQuarterPairs * c on, which sit in 16 SGPRs.
+typedef uint32_t u32x16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+template <int KIND>
+constexpr int kQuarterPairs = KIND == PACK_U3 ? 15 : 16;  // 3-bit: 12 words of five pairs; pairs 60..63 in spare bits
+
+// Wave-uniform loads from x through the scalar cache (4-byte aligned).
+template <typename V>
+__device__ __forceinline__ V load_scalar(const uint32_t* x) {
+    typedef V __attribute__((aligned(4))) loose_t;
+    typedef const __attribute__((address_space(4))) loose_t* scalar_ptr;
+    return *(scalar_ptr)(uintptr_t)x;
 }
 
-// Same for the 3-bit layout: fields at bits 0-2, 4-6, 7-9, 10-12, 13-15 of
-// each half and a spare bit 3 that carries one bit of pairs 60..63.
-__device__ __forceinline__ float group_dot_u3(const uint4 (&q)[3], const uint32_t* __restrict__ xs) {
-    float a4 = 0.f, b4 = 0.f, c4 = 0.f, a7 = 0.f, b7 = 0.f;
-    float e[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        const uint32_t wd[4] = {q[p].x, q[p].y, q[p].z, q[p].w};
+// Partial sums of one group for one lane.
+template <int KIND>
+struct GroupAcc;
+
+// 4-bit layout: word w, nibble i of each half -> pair 4w + i.
+template <>
+struct GroupAcc<PACK_U4> {
+    float a = 0.f, b = 0.f, c = 0.f, d = 0.f;
+    __device__ __forceinline__ void quarter(const uint32_t* wd, const u32x16_t& xs, uint32_t) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int w = 4 * p + i;
-            const uint32_t t = wd[i], lo = t << 4, hi = t >> 6;
-            a4 = dot2(lo & 0x00700070u, xs[5 * w + 0], a4);   // bits 0-2
-            b4 = dot2(t & 0x00700070u, xs[5 * w + 1], b4);    // bits 4-6
-            a7 = dot2(t & 0x03800380u, xs[5 * w + 2], a7);    // bits 7-9
-            c4 = dot2(hi & 0x00700070u, xs[5 * w + 3], c4);   // bits 10-12
-            b7 = dot2(hi & 0x03800380u, xs[5 * w + 4], b7);   // bits 13-15
-            e[w % 3] = dot2(lo & 0x00800080u, xs[60 + w / 3], e[w % 3]);  // spare bit 3
+            const uint32_t t = wd[i];
+            a = dot2((t << 4) & 0x00F000F0u, xs[4 * i + 0], a);
+            b = dot2(t & 0x00F000F0u, xs[4 * i + 1], b);
+            c = dot2((t >> 4) & 0x00F000F0u, xs[4 * i + 2], c);
+            d = dot2((t >> 8) & 0x00F000F0u, xs[4 * i + 3], d);
         }
     }
-    const float at7 = (a7 + b7) + ((e[0] + 2.f * e[1]) + 4.f * e[2]);
-    return (((a4 + b4) + c4) * 0.0625f + at7 * 0.0078125f) * kTwoPow24;
-}
+    __device__ __forceinline__ float sum() const { return ((a + b) + (c + d)) * (kTwoPow24 / 16.f); }
+};
+
+// 3-bit layout: fields at bits 0-2, 4-6, 7-9, 10-12, 13-15 of each half and a spare bit 3 that carries one bit of
+// pair 60 + quarter.
+template <>
+struct GroupAcc<PACK_U3> {
+    float a4 = 0.f, b4 = 0.f, c4 = 0.f, a7 = 0.f, b7 = 0.f;
+    float e[3] = {0.f, 0.f, 0.f};
+    __device__ __forceinline__ void quarter(const uint32_t* wd, const u32x16_t& xs, uint32_t x_spare) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t t = wd[i], lo = t << 4, hi = t >> 6;
+            a4 = dot2(lo & 0x00700070u, xs[5 * i + 0], a4);   // bits 0-2
+            b4 = dot2(t & 0x00700070u, xs[5 * i + 1], b4);    // bits 4-6
+            a7 = dot2(t & 0x03800380u, xs[5 * i + 2], a7);    // bits 7-9
+            c4 = dot2(hi & 0x00700070u, xs[5 * i + 3], c4);   // bits 10-12
+            b7 = dot2(hi & 0x03800380u, xs[5 * i + 4], b7);   // bits 13-15
+            e[i] = dot2(lo & 0x00800080u, x_spare, e[i]);     // spare bit 3
+        }
+    }
+    __device__ __forceinline__ float sum() const {
+        const float at7 = (a7 + b7) + ((e[0] + 2.f * e[1]) + 4.f * e[2]);
+        return (((a4 + b4) + c4) * 0.0625f + at7 * 0.0078125f) * kTwoPow24;
+    }
+};
 
 // Per-lane codebook as byte tables for v_perm_b32 lookups.
 struct LutTables {
@@ -123,15 +141,13 @@ __device__ __forceinline__ LutTables make_lut_tables(uint4 l) {
     return t;
 }
 
-// sum_k lut[c_k] x_k over one group for one lane, LUT layout.
-__device__ __forceinline__ float group_dot_lut3(const uint4 (&q)[3], const LutTables& T,
-                                                const uint32_t* __restrict__ xs) {
-    const uint32_t wd[12] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y,
-                             q[1].z, q[1].w, q[2].x, q[2].y, q[2].z, q[2].w};
+// LUT layout: the byte selectors of three words, looked up in the column's codebook.
+template <>
+struct GroupAcc<PACK_LUT3> {
+    LutTables T;
     float acc0 = 0.f, acc1 = 0.f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const uint32_t w0 = wd[3 * b], w1 = wd[3 * b + 1], w2 = wd[3 * b + 2];
+    __device__ __forceinline__ void quarter(const uint32_t* wd, const u32x16_t& xs, uint32_t) {
+        const uint32_t w0 = wd[0], w1 = wd[1], w2 = wd[2];
         uint32_t sel[8];
         sel[0] = w0 & 0x07070707u;
         sel[1] = (w0 >> 3) & 0x07070707u;
@@ -147,15 +163,12 @@ __device__ __forceinline__ float group_dot_lut3(const uint4 (&q)[3], const LutTa
             const uint32_t hi = __builtin_amdgcn_perm(T.hi47, T.hi03, sel[s]);
             const uint32_t p01 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
             const uint32_t p23 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
-            acc0 = dot2(p01, xs[16 * b + 2 * s], acc0);
-            acc1 = dot2(p23, xs[16 * b + 2 * s + 1], acc1);
+            acc0 = dot2(p01, xs[2 * s], acc0);
+            acc1 = dot2(p23, xs[2 * s + 1], acc1);
         }
     }
-    return acc0 + acc1;
-}
-
-
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+    __device__ __forceinline__ float sum() const { return acc0 + acc1; }
+};
 
 // 128-bit load of data that is read exactly once (the weight stream).
 __device__ __forceinline__ uint4 load_streaming(const uint4* p) {
@@ -186,62 +199,89 @@ __device__ __forceinline__ void load_tile(TileRegs<KIND>& r, const uint4* __rest
     }
 }
 
+// x: the group's 64 activation pairs.  A scalar load that misses costs a trip to the L2 or to memory, and scalar loads
+// cannot be waited for one by one; so two quarters of x, and one word of each line of the others, are asked for
+// together while the weights are still under way, and each later quarter while the one before it is worked off.
 template <int KIND>
-__device__ __forceinline__ float tile_dot(const TileRegs<KIND>& r, const LutTables& T,
-                                          const uint32_t* __restrict__ xs) {
+__device__ __forceinline__ float tile_dot(const TileRegs<KIND>& r, const LutTables& T, const uint32_t* x) {
+    constexpr int kWords = words_per_lane(KIND) / 4, QP = kQuarterPairs<KIND>;
+    u32x16_t xa = load_scalar<u32x16_t>(x), xb = load_scalar<u32x16_t>(x + QP);
+    u32x4_t tail{};
+    if constexpr (KIND == PACK_U3) {
+        tail = load_scalar<u32x4_t>(x + 60);
+        uint32_t line = load_scalar<uint32_t>(x + 32);
+        asm volatile("" : "+s"(xa), "+s"(xb), "+s"(tail) : "s"(line));
+    } else {
+        uint32_t line2 = load_scalar<uint32_t>(x + 32), line3 = load_scalar<uint32_t>(x + 48);
+        asm volatile("" : "+s"(xa), "+s"(xb) : "s"(line2), "s"(line3));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    uint32_t wd[4 * kWords];
+#pragma unroll
+    for (int p = 0; p < kWords; ++p) {
+        wd[4 * p] = r.q[p].x;
+        wd[4 * p + 1] = r.q[p].y;
+        wd[4 * p + 2] = r.q[p].z;
+        wd[4 * p + 3] = r.q[p].w;
+    }
+    GroupAcc<KIND> acc;
+    if constexpr (KIND == PACK_LUT3) acc.T = T;
+    acc.quarter(wd, xa, tail[0]);
+    xa = load_scalar<u32x16_t>(x + 2 * QP);
+    __builtin_amdgcn_sched_barrier(0);
+    acc.quarter(wd + kWords, xb, tail[1]);
+    xb = load_scalar<u32x16_t>(x + 3 * QP);
+    __builtin_amdgcn_sched_barrier(0);
+    acc.quarter(wd + 2 * kWords, xa, tail[2]);
+    acc.quarter(wd + 3 * kWords, xb, tail[3]);
     if constexpr (KIND == PACK_LUT3) {
-        return group_dot_lut3(r.q, T, xs);
+        return acc.sum();
     } else {
         const float gs = wave_sum(dot2(r.xp, 0x3C003C00u, 0.f));  // sum of the group's 128 activations
-        float d;
-        if constexpr (KIND == PACK_U4) {
-            d = group_dot_u4(r.q, xs);
-        } else {
-            d = group_dot_u3(r.q, xs);
-        }
         const float s = (float)__builtin_bit_cast(_Float16, r.s);
         const float z = (float)__builtin_bit_cast(_Float16, r.z);
-        return s * (d - z * gs);
+        return s * (acc.sum() - z * gs);
     }
 }
 
-struct GemvJobs {
-    const uint4* Wq[kMaxMulti];
-    const uint16_t* scales[kMaxMulti];
-    const uint16_t* zeros_or_lut[kMaxMulti];
-    int N[kMaxMulti];
-    int col0[kMaxMulti];
-    int tile_end[kMaxMulti];  // cumulative count of 64-column tiles up to and including matrix m
-    int n;
-};
-
-// Work of workgroup `bid` out of (total tiles) * slices workgroups of WPB wavefronts; workgroup (nt, ks)
+// Work of workgroup `bid` out of a.tiles * a.gslices workgroups of WPB wavefronts; workgroup (nt, ks)
 // covers column tile nt (of whichever matrix it falls in) and groups
 // [ks*WPB*gpw, (ks+1)*WPB*gpw), wave w of it the gpw groups starting at
-// (ks*WPB + w)*gpw.  part is fp32 [slices][Ntot].  A wave keeps the loads of
+// (ks*WPB + w)*gpw.  A wave keeps the loads of
 // NBUF tiles in flight: the tile NBUF groups ahead is requested as soon as the
-// registers of the current one are free.  With fa.direct (one slice, nothing
+// registers of the current one are free.  With a.direct (one slice, nothing
 // else to add) the workgroup rounds its sums to fp16 and writes y itself.
 template <int KIND, int WPB, int NBUF>
-__device__ __forceinline__ void gemv_block(const GemvJobs& jobs, const FinalizeArgs& fa,
-                                           const uint32_t* __restrict__ x32, float* __restrict__ part, int Ntot,
-                                           int G, int slices, int gpw, int bid) {
+__device__ __forceinline__ void gemv_block(const CallArgs& a, int bid) {
     constexpr int P = words_per_lane(KIND) / 4;  // 16-byte pieces per lane per tile
     constexpr int kTileStride = P * kTileCols;   // uint4 per tile
     __shared__ float red[WPB][kTileCols];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gt = bid / slices;  // tile index over all matrices
-    const int ks = bid - gt * slices;
-    int m = 0;
+    const int gt = divide_by(bid, a.gdiv);  // tile index over all matrices
+    const int ks = bid - gt * a.gslices;
+    int m = 0, tile0 = 0;
 #pragma unroll
-    for (int i = 0; i < kMaxMulti - 1; ++i) m += (i + 1 < jobs.n && gt >= jobs.tile_end[i]) ? 1 : 0;
-    const int nt = gt - (m > 0 ? jobs.tile_end[m - 1] : 0);
-    const int N = jobs.N[m];
+    for (int i = 0; i < kMaxMulti - 1; ++i) {
+        if (i + 1 < a.n && gt >= a.mat[i].tile_end) {
+            m = i + 1;
+            tile0 = a.mat[i].tile_end;
+        }
+    }
+    const MatArgs& mat = a.mat[m];
+    const int nt = gt - tile0;
+    const int N = mat.N, G = a.G, gpw = a.gpw;
     const int n = nt * kTileCols + lane;
-    const uint16_t* __restrict__ scales = jobs.scales[m];
-    const uint16_t* __restrict__ zeros_or_lut = jobs.zeros_or_lut[m];
+    const uint16_t* scales = mat.scales;
+    const uint16_t* zeros_or_lut = mat.zeros_or_lut;
+    const uint32_t* x32 = reinterpret_cast<const uint32_t*>(a.x);
+    // for the end: read now, so that the last step does not begin with a trip to memory
+    _Float16* y = mat.y;
+    int col0 = mat.col0, producers = a.producers, direct = a.direct;
+    unsigned long long* acc = a.acc;
+    asm volatile("" : "+s"(y), "+s"(col0), "+s"(producers), "+s"(direct), "+s"(acc));
 
     int g = (ks * WPB + wave) * gpw;
     const int g_end = min(g + gpw, G);
@@ -252,7 +292,7 @@ __device__ __forceinline__ void gemv_block(const GemvJobs& jobs, const FinalizeA
     }
 
     float total = 0.f;
-    const uint4* tile = jobs.Wq[m] + ((size_t)nt * G + g) * kTileStride + lane;
+    const uint4* tile = mat.Wq + ((size_t)nt * G + g) * kTileStride + lane;
     if constexpr (NBUF == 2) {
         TileRegs<KIND> ra, rb;
         if (g < g_end) load_tile<KIND>(ra, tile, scales, zeros_or_lut, x32, g, N, n, lane);
@@ -296,12 +336,12 @@ __device__ __forceinline__ void gemv_block(const GemvJobs& jobs, const FinalizeA
         for (int span = 1; span < WPB; span *= 2)
 #pragma unroll
             for (int w = 0; w + span < WPB; w += 2 * span) v[w] += v[w + span];
-        if (fa.direct) {
-            fa.y[m][n] = (_Float16)v[0];
-        } else if (fa.acc != nullptr) {
-            arrive(fa, m, n, v[0]);
+        if (direct) {
+            y[n] = (_Float16)v[0];
+        } else if (acc != nullptr) {
+            arrive(acc + col0 + n, y + n, producers, v[0]);
         } else {
-            part[(size_t)ks * Ntot + jobs.col0[m] + n] = v[0];
+            a.gpart[(size_t)ks * a.Ntot + col0 + n] = v[0];
         }
     }
 }

@@ -13,6 +13,7 @@ namespace decdec {
 constexpr int kBlockThreads = 512;
 constexpr int kWavesPerBlock = kBlockThreads / 64;
 
+constexpr int kFetchSegmentCols = 512;  // output columns of one column segment = threads of a fetch workgroup
 constexpr int kMaxGemvSlices = 16;   // part sums per column the base GEMV may contribute (K-slices)
 constexpr int kMaxFetchSlices = 16;  // part sums per column the residual kernel may contribute (row slices)
 constexpr int kSelectThreads = 1024;
@@ -48,24 +49,63 @@ struct MultiShape {
     int col0[kMaxMulti + 1];  // first concatenated column of matrix m; col0[n] = Ntot
 };
 
-struct GemvOperands {
-    const void* Wq[kMaxMulti];
-    const void* scales[kMaxMulti];
-    const void* zeros_or_lut[kMaxMulti];
+// Kernel arguments of the base-GEMV, residual and one-grid kernels.  They arrive cold: every 64-byte line of them is
+// a trip to memory for the first wavefront of a compute unit that reads it, and a kernel here runs for only a few such
+// trips.  So one matrix is one line, everything else is two, and touch_args asks for all of them at once, before
+// anything waits for a value: what is read by index afterwards, the matrix a workgroup falls into, is then at hand.
+struct alignas(64) MatArgs {
+    const uint4* Wq;
+    const uint16_t* scales;
+    const uint16_t* zeros_or_lut;
+    const uint4* R;       // residual rows
+    const uint16_t* Rs;   // fp16 [N] column scales (integer residuals) or null
+    _Float16* y;
+    int N;
+    int col0;      // first concatenated column
+    int tile_end;  // 64-column tiles of the matrices up to and including this one
+    int seg_end;   // 512-column segments likewise
+};
+static_assert(sizeof(MatArgs) == 64, "one line");
+
+struct CallArgs {
+    MatArgs mat[kMaxMulti];
+    const uint16_t* x;
+    unsigned long long* acc;  // one word per concatenated column, zero between calls; null: the producers leave fp32
+                              // partial rows and a separate kernel adds them
+    int n;                    // matrices
+    int G;                    // groups of 128 input channels
+    int gslices, gpw;         // K-slices of the base GEMV, groups per wavefront
+    unsigned gdiv;            // reciprocal_of(gslices)
+    int producers;            // part sums per column: gslices + cslices
+    int direct;               // 1: the base GEMV is the only producer and has one slice: it writes y itself
+    int Ntot;
+    float* gpart;             // fp32 [gslices][Ntot]   (acc == null only)
+    int k;
+    int cslices, row_waves;   // workgroups per column segment, wavefronts of each that share its rows
+    unsigned cdiv;            // reciprocal_of(cslices)
+    int nfetch;               // workgroups of the residual part of the one-grid kernel
+    int32_t* idx;             // the selection: written by the kernel that selects, read by the others
+    uint16_t* xsel;
+    float* cpart;             // fp32 [cslices][Ntot]   (acc == null only)
+    int tiles, segments;      // over all matrices
 };
 
-struct FetchOperands {
-    const void* R[kMaxMulti];         // pinned residual rows
-    const void* R_scales[kMaxMulti];  // fp16 [N_m] (int4 residuals) or null
-};
+// i / d as the high word of i * reciprocal_of(d), for d <= 16 and i < 2^28 (a grid of more would need more weights
+// than the card holds): one scalar multiplication where a division takes forty instructions ahead of the first load.
+inline unsigned reciprocal_of(int d) { return d > 1 ? (unsigned)((0x100000000ull + d - 1) / d) : 0u; }
+__device__ __forceinline__ int divide_by(int i, unsigned reciprocal) {
+    return reciprocal ? (int)__umulhi((unsigned)i, reciprocal) : i;
+}
+
+__device__ __forceinline__ void touch_args(const CallArgs& a) {
+    asm volatile("" ::"s"(a.mat[0].N), "s"(a.mat[1].N), "s"(a.mat[2].N), "s"(a.mat[3].N), "s"(a.x), "s"(a.xsel), "s"(a.n),
+                 "s"(a.mat[0].tile_end), "s"(a.mat[1].tile_end), "s"(a.mat[2].tile_end), "s"(a.gslices), "s"(a.gdiv),
+                 "s"(a.gpw), "s"(a.G), "s"(a.nfetch));
+}
 
 // gemv.hip ---------------------------------------------------------------
-// part: fp32 [slices][Ntot], written only when fa.acc is null (a separate kernel adds the rows); may be null otherwise.
-struct FinalizeArgs;
 // wpb: wavefronts per workgroup (4, 8 or 16).
-hipError_t launch_gemv(int kind, const MultiShape& sh, const GemvOperands& op, const void* x, float* part,
-                       int slices, int gpw, int wpb, const FinalizeArgs& fa, hipStream_t stream,
-                       const KernelTimer* tm = nullptr);
+hipError_t launch_gemv(int kind, const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm = nullptr);
 // How K is cut: workgroups of `wpb` wavefronts, each wavefront walking `gpw` groups of 128 input channels,
 // `slices` workgroups (and part sums per column) per 64-column tile.  Requests of 0 leave the choice to the
 // library; inside the one-grid kernel wpb is kWavesPerBlock.
@@ -86,7 +126,7 @@ hipError_t launch_select_bucket(const void* x, int K, int k_chunk, float b0, flo
 // fetch.hip --------------------------------------------------------------
 // How the residual kernel is laid out: `segments` column segments (one 16-byte piece per lane and row; all
 // matrices of the call together) x `slices` workgroups per segment; `row_waves` wavefronts of each workgroup
-// share its rows.  cpart is fp32 [slices][Ntot] (used only when fa.acc is null).
+// share its rows.
 struct FetchPlan {
     int segments, slices, row_waves;
 };
@@ -94,18 +134,15 @@ struct FetchPlan {
 // memory, not behind the host link.
 FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool in_hbm);
 // select_chunks (from fetch_select_chunks) > 0: the kernel runs the exact top-k on x itself and writes
-// the selection to idx / xsel; 0: idx / xsel hold the selection already (x is not read).
+// the selection to a.idx / a.xsel; 0: they hold the selection already (x is not read).
 int fetch_select_chunks(int K, int k);
-hipError_t launch_fetch(int rfmt, const MultiShape& sh, const FetchOperands& op, const void* x, int select_chunks,
-                        int32_t* idx, void* xsel, int k, float* cpart, const FetchPlan& plan, const FinalizeArgs& fa,
-                        hipStream_t stream, const KernelTimer* tm = nullptr);
+hipError_t launch_fetch(int rfmt, const CallArgs& a, int select_chunks, hipStream_t stream,
+                        const KernelTimer* tm = nullptr);
 
 // fused.hip -------------------------------------------------------------
 // Base GEMV and residual kernel in one grid (the fetch workgroups come first).
-hipError_t launch_compensated_gemv(int kind, int rfmt, const MultiShape& sh, const GemvOperands& gop,
-                                   const FetchOperands& fop, const void* x, int select_chunks, int32_t* idx, void* xsel,
-                                   int k, float* gpart, int gslices, int gpw, float* cpart, const FetchPlan& plan,
-                                   const FinalizeArgs& fa, hipStream_t stream, const KernelTimer* tm = nullptr);
+hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, hipStream_t stream,
+                                   const KernelTimer* tm = nullptr);
 
 // accumulate.hip ---------------------------------------------------------
 // y_m[n] = fp16( sum_s gpart[s][col0[m]+n] + sum_r cpart[r][col0[m]+n] ), the terms added in the fixed point of finalize.h
