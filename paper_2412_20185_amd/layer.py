@@ -35,8 +35,8 @@ class UniformLinear:
         self.zeros = torch.empty((K // 128, N), dtype=torch.float16, device="cuda")
         want16 = keep_residual and rbits == 16
         R_dev = torch.empty((K, N), dtype=torch.float16, device="cuda") if want16 else None
+        # No wait between the kernels: the stream orders them, and the host allocates pinned memory meanwhile.
         B.decdec_quantize_uniform(self.desc, Wd, self.Wq, self.scales, self.zeros, R_dev)
-        torch.cuda.synchronize()
         self.R = self.R_scales = None
         if want16:
             self.R = torch.empty((K, N), dtype=torch.float16, pin_memory=True)
@@ -47,10 +47,7 @@ class UniformLinear:
             self.R = torch.empty((K, N * rbits // 8), dtype=torch.uint8, pin_memory=True)
             self.R_scales = torch.empty(N, dtype=torch.float16, device="cuda")
             B.decdec_quantize_residual(K, N, rbits, R32, self.R, self.R_scales)
-            torch.cuda.synchronize()
-            del R32
         torch.cuda.synchronize()
-        del Wd, R_dev
 
     def residual_to_device(self):
         """Moves the residual from pinned host memory into GPU memory (for a GPU with room for it:
