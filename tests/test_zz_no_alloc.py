@@ -1,6 +1,9 @@
 """The entry point that allocates nothing (decdec_gemv_static, for callers that cannot call hipMalloc):
 called through the C ABI, its output must equal decdec_gemv's bit for bit, on two calls in a row of which
 the second is smaller (the static scratch keeps the first call's contents)."""
+import contextlib
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -11,6 +14,20 @@ import paper_2412_20185_amd as dd
 from helpers import Problem, assert_parity
 
 pytestmark = pytest.mark.gpu
+
+
+@contextlib.contextmanager
+def _no_collection():
+    """Reference cycles that hold device tensors (a failed call's traceback does, inside pytest.raises) are freed by the
+    cycle collector whenever it happens to run: collect them now, and keep it from running until the readings are taken."""
+    gc.collect()
+    was_on = gc.isenabled()
+    gc.disable()
+    try:
+        yield
+    finally:
+        if was_on:
+            gc.enable()
 
 
 def _both(p, x, k, ws):
@@ -25,11 +42,12 @@ def _both(p, x, k, ws):
         torch.cuda.synchronize()
         y_st.fill_(float("nan"))
         _both.warm = True
-    free_before, torch_before = torch.cuda.mem_get_info()[0], torch.cuda.memory_allocated()
-    dd.decdec_gemv_static(p.desc, xd, d["Wq"], d["scales"], d["zl"], d["R"], d["Rs"], k, y_st)
-    torch.cuda.synchronize()
-    # nothing was allocated, by the library (free device memory as the driver reports it) or through torch
-    assert torch.cuda.mem_get_info()[0] >= free_before and torch.cuda.memory_allocated() == torch_before
+    with _no_collection():
+        free_before, torch_before = torch.cuda.mem_get_info()[0], torch.cuda.memory_allocated()
+        dd.decdec_gemv_static(p.desc, xd, d["Wq"], d["scales"], d["zl"], d["R"], d["Rs"], k, y_st)
+        torch.cuda.synchronize()
+        # nothing was allocated, by the library (free device memory as the driver reports it) or through torch
+        assert torch.cuda.mem_get_info()[0] >= free_before and torch.cuda.memory_allocated() == torch_before
     return y_ws.cpu().numpy(), y_st.cpu().numpy()
 
 
@@ -48,6 +66,28 @@ def test_static_entry_point_equals_workspace_entry_point(rfmt):
             assert np.array_equal(y_ws.view(np.uint16), y_st.view(np.uint16)), (rfmt, step)
             y_ref, sc = p.reference(x, k)
             assert_parity(y_st, y_ref, sc, sc, what=f"static {rfmt} step {step}")
+    finally:
+        ws.close()
+
+
+def test_check_is_not_disturbed_by_garbage_of_earlier_tests(monkeypatch):
+    p = Problem(workloads.weights(96, 0, 2, 512, 192), 4)
+    x = workloads.x_gauss_outliers(96, 0, 1, 0, p.K)
+    ws = dd.Workspace(512, 192, 9)
+    call = dd.decdec_gemv_static
+
+    def call_with_collector(*args):  # as if it ran during the call, if it may
+        if gc.isenabled():
+            gc.collect()
+        return call(*args)
+
+    try:
+        _both(p, x, 9, ws)
+        monkeypatch.setattr(dd, "decdec_gemv_static", call_with_collector)
+        cycle = [torch.empty(1 << 20, dtype=torch.uint8, device="cuda")]
+        cycle.append(cycle)
+        del cycle
+        _both(p, x, 9, ws)
     finally:
         ws.close()
 
