@@ -160,7 +160,13 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     const uint16_t* Rs = mat.Rs;
     _Float16* y = mat.y;
     unsigned long long* acc_words = a.acc;
-    asm volatile("" : "+s"(N), "+s"(col0), "+s"(producers), "+s"(rows_base), "+s"(Rs), "+s"(y), "+s"(acc_words));
+    hold_scalar(N);
+    hold_scalar(col0);
+    hold_scalar(producers);
+    hold_scalar(rows_base);
+    hold_scalar(Rs);
+    hold_scalar(y);
+    hold_scalar(acc_words);
 
     const Selection sel = obtain_selection<SELECT_NCH>(a.x, K, k, a.idx, a.xsel, lds.sh, bid);
     const int32_t* idx = sel.idx;

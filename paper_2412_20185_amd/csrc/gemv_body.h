@@ -281,7 +281,11 @@ __device__ __forceinline__ void gemv_block(const CallArgs& a, int bid) {
     _Float16* y = mat.y;
     int col0 = mat.col0, producers = a.producers, direct = a.direct;
     unsigned long long* acc = a.acc;
-    asm volatile("" : "+s"(y), "+s"(col0), "+s"(producers), "+s"(direct), "+s"(acc));
+    hold_scalar(y);
+    hold_scalar(col0);
+    hold_scalar(producers);
+    hold_scalar(direct);
+    hold_scalar(acc);
 
     int g = (ks * WPB + wave) * gpw;
     const int g_end = min(g + gpw, G);

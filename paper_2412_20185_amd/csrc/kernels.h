@@ -103,6 +103,17 @@ __device__ __forceinline__ void touch_args(const CallArgs& a) {
                  "s"(a.gpw), "s"(a.G), "s"(a.nfetch));
 }
 
+// Has a value loaded into a scalar register by here.  What an asm statement returns is a pointer of unknown address space,
+// and accesses through it are flat ones, which count as LDS accesses too and are waited for together with all of them:
+// pointers are held as pointers to global memory.
+__device__ __forceinline__ void hold_scalar(int& v) { asm volatile("" : "+s"(v)); }
+template <typename T>
+__device__ __forceinline__ void hold_scalar(T*& p) {
+    auto global = (__attribute__((address_space(1))) T*)p;
+    asm volatile("" : "+s"(global));
+    p = (T*)global;
+}
+
 // gemv.hip ---------------------------------------------------------------
 // wpb: wavefronts per workgroup (4, 8 or 16).
 hipError_t launch_gemv(int kind, const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm = nullptr);

@@ -1,0 +1,63 @@
+"""What the compiler made of the kernels, read from the built library: properties that its resource report or a reader of
+the source does not show, and that have cost time without changing a result."""
+import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+from paper_2412_20185_amd import build
+
+LLVM = "/opt/rocm/llvm/bin"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _tool(name):
+    path = shutil.which(name) or os.path.join(LLVM, name)
+    if not os.path.exists(path):
+        pytest.skip(f"{name} is not installed")
+    return path
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """The gfx950 code object of every source file, as files."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    with open(build.LIB, "rb") as f:
+        data = f.read()
+    out = tmp_path_factory.mktemp("code")
+    paths = []
+    at = data.find(MAGIC)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", data, at + 24)
+        p = at + 32
+        for _ in range(n):
+            offset, size, idlen = struct.unpack_from("<QQQ", data, p)
+            target = data[p + 24:p + 24 + idlen].decode()
+            p += 24 + idlen
+            if "gfx950" in target and size:
+                paths.append(out / f"{len(paths)}.co")
+                paths[-1].write_bytes(data[at + offset:at + offset + size])
+        at = data.find(MAGIC, at + 24)
+    assert len(paths) >= len(build.SOURCES) - 1, "code objects not found in the library"
+    return paths
+
+
+def test_no_flat_memory_access(code_objects):
+    """A pointer whose address space the compiler does not know is accessed by flat instructions, which count as LDS
+    accesses too and are waited for together with all of them.  Every pointer here is to global memory or LDS."""
+    flat = {}
+    for path in code_objects:
+        text = subprocess.run([_tool("llvm-objdump"), "-d", "--no-show-raw-insn", path], capture_output=True, text=True,
+                              check=True).stdout
+        name = None
+        for line in text.splitlines():
+            m = re.match(r"[0-9a-f]+ <(.*)>:", line)
+            if m:
+                name = m.group(1)
+            elif re.search(r"\bflat_(load|store|atomic)", line):
+                flat[name] = flat.get(name, 0) + 1
+    assert not flat
