@@ -160,9 +160,7 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     const uint16_t* Rs = mat.Rs;
     _Float16* y = mat.y;
     unsigned long long* acc_words = a.acc;
-    hold_scalar(N);
-    hold_scalar(col0);
-    hold_scalar(producers);
+    hold_scalar(N, col0, producers);
     hold_scalar(rows_base);
     hold_scalar(Rs);
     hold_scalar(y);
@@ -206,13 +204,16 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
+            const bool valid = j + u * SUB + sub < j1 && (unsigned)row[u] < (unsigned)K;
             v[u] = piece_t{};
-            if (j + u * SUB + sub < j1 && active && (unsigned)row[u] < (unsigned)K)
-                v[u] = R[(size_t)row[u] * row_pieces + piece];
+            if (valid && active) v[u] = R[(size_t)row[u] * row_pieces + piece];
+            xraw[u] = valid ? xraw[u] : 0;
+            // The lanes of `valid` are done with here.  Otherwise they are kept for the loop below, and sixteen such masks
+            // do not fit beside the rest into the 80 scalar registers that leave room for eight wavefronts a SIMD.
+            if constexpr (SUB == 1) hold_vector(xraw[u]);
         }
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-            xs[u] = (j + u * SUB + sub < j1 && (unsigned)row[u] < (unsigned)K) ? h2f(xraw[u]) : 0.f;
+        for (int u = 0; u < UNROLL; ++u) xs[u] = h2f(xraw[u]);
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
             if (j + u * SUB < j1) accumulate_piece<BITS, CPL>(v[u], xs[u], acc);  // wave-uniform: rows it does not have cost nothing

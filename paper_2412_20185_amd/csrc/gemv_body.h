@@ -278,13 +278,11 @@ __device__ __forceinline__ void gemv_block(const CallArgs& a, int bid) {
     const uint16_t* zeros_or_lut = mat.zeros_or_lut;
     const uint32_t* x32 = reinterpret_cast<const uint32_t*>(a.x);
     // for the end: read now, so that the last step does not begin with a trip to memory
-    _Float16* y = mat.y;
     int col0 = mat.col0, producers = a.producers, direct = a.direct;
-    unsigned long long* acc = a.acc;
+    hold_scalar(col0, producers, direct);
+    _Float16* y = mat.y;
     hold_scalar(y);
-    hold_scalar(col0);
-    hold_scalar(producers);
-    hold_scalar(direct);
+    unsigned long long* acc = a.acc;
     hold_scalar(acc);
 
     int g = (ks * WPB + wave) * gpw;

@@ -13,6 +13,10 @@ namespace decdec {
 constexpr int kBlockThreads = 512;
 constexpr int kWavesPerBlock = kBlockThreads / 64;
 
+// Eight wavefronts a SIMD take at most 64 vector and 80 scalar registers each.  The compiler's occupancy remark promises
+// eight up to 100 scalar registers, but the chip takes some for itself: of 512 workgroups of 1024 threads all start at once
+// at 80 registers, and 256 have to wait at 82.
+
 constexpr int kFetchSegmentCols = 512;  // output columns of one column segment = threads of a fetch workgroup
 constexpr int kMaxGemvSlices = 16;   // part sums per column the base GEMV may contribute (K-slices)
 constexpr int kMaxFetchSlices = 16;  // part sums per column the residual kernel may contribute (row slices)
@@ -103,10 +107,11 @@ __device__ __forceinline__ void touch_args(const CallArgs& a) {
                  "s"(a.gpw), "s"(a.G), "s"(a.nfetch));
 }
 
-// Has a value loaded into a scalar register by here.  What an asm statement returns is a pointer of unknown address space,
+// Has a value in a register by here.  What an asm statement returns is a pointer of unknown address space,
 // and accesses through it are flat ones, which count as LDS accesses too and are waited for together with all of them:
 // pointers are held as pointers to global memory.
-__device__ __forceinline__ void hold_scalar(int& v) { asm volatile("" : "+s"(v)); }
+__device__ __forceinline__ void hold_scalar(int& a, int& b, int& c) { asm volatile("" : "+s"(a), "+s"(b), "+s"(c)); }
+__device__ __forceinline__ void hold_vector(uint32_t& v) { asm volatile("" : "+v"(v)); }
 template <typename T>
 __device__ __forceinline__ void hold_scalar(T*& p) {
     auto global = (__attribute__((address_space(1))) T*)p;

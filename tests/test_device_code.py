@@ -61,3 +61,22 @@ def test_no_flat_memory_access(code_objects):
             elif re.search(r"\bflat_(load|store|atomic)", line):
                 flat[name] = flat.get(name, 0) + 1
     assert not flat
+
+
+def test_registers_of_every_kernel(code_objects):
+    """No scratch memory, and of the scalar registers no more set aside in vector lanes than the pointers and counts that
+    are kept for a workgroup's last step come to (at most 20): the sixteen lane masks of a row loop would be 32 more.  The
+    kernels that are meant to run with eight wavefronts a SIMD (64 vector registers) stay within the 80 scalar registers
+    that allow it."""
+    seen = 0
+    for path in code_objects:
+        notes = subprocess.run([_tool("llvm-readelf"), "--notes", path], capture_output=True, text=True, check=True).stdout
+        for entry in notes.split("  - .agpr_count")[1:]:
+            value = lambda key: int(re.search(rf"\.{key}: +(\d+)", entry).group(1))  # noqa: E731
+            name = re.search(r"\.name: +(\S+)", entry).group(1)
+            seen += 1
+            assert value("private_segment_fixed_size") == 0 and value("vgpr_spill_count") == 0, name
+            assert value("sgpr_spill_count") <= 20, (name, value("sgpr_spill_count"))
+            if "gemv_kernel" in name and value("vgpr_count") <= 64:
+                assert value("sgpr_count") <= 80, (name, value("sgpr_count"))
+    assert seen > 100
