@@ -12,12 +12,12 @@
 namespace decdec {
 namespace {
 
-template <int THREADS, int NCH>
+template <int THREADS, int NCH, bool RADIX = false>
 __global__ __launch_bounds__(THREADS) void select_topk_kernel(const uint16_t* __restrict__ x, int K, int k,
                                                              int32_t* __restrict__ idx_out,
                                                              uint16_t* __restrict__ xsel_out) {
     __shared__ SelectShared sh;
-    block_select_topk<THREADS, NCH>(x, K, k, sh, idx_out, xsel_out);
+    block_select_topk<THREADS, NCH, RADIX>(x, K, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace
@@ -31,11 +31,18 @@ hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, voi
     if (K <= 2048) return launch_kernel(tm, select_topk_kernel<256, 1>, one, dim3(256), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 4096) return launch_kernel(tm, select_topk_kernel<512, 1>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 8192) return launch_kernel(tm, select_topk_kernel<1024, 1>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
+    // Above, a k too large for the chunk form has a kernel without it, with its marked keys' words chosen by comparisons
+    // (select_block.h).  us, the kernel with both forms -> without: K = 14336, k = 1433: 7.24 -> 7.14; 28672, 2867:
+    // 11.53 -> 11.40; 32768, 3276: 12.14 -> 11.98.  Up to 8192 the two take the same, or this one 0.02 more.
+    const bool radix = !select_tries_chunks(K / 8, k);
     if (K <= 16384)
-        return launch_kernel(tm, select_topk_kernel<1024, 2>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
+        return launch_kernel(tm, radix ? select_topk_kernel<1024, 2, true> : select_topk_kernel<1024, 2>, one, dim3(1024), 0, stream,
+                             xp, K, k, idx_out, xs);
     if (K <= 32768)
-        return launch_kernel(tm, select_topk_kernel<1024, 4>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
-    return launch_kernel(tm, select_topk_kernel<1024, 8>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
+        return launch_kernel(tm, radix ? select_topk_kernel<1024, 4, true> : select_topk_kernel<1024, 4>, one, dim3(1024), 0, stream,
+                             xp, K, k, idx_out, xs);
+    return launch_kernel(tm, radix ? select_topk_kernel<1024, 8, true> : select_topk_kernel<1024, 8>, one, dim3(1024), 0, stream,
+                         xp, K, k, idx_out, xs);
 }
 
 }  // namespace decdec

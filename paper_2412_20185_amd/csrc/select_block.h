@@ -45,6 +45,8 @@ constexpr int kSelectMaxChunks = 8;  // 8-key chunks per thread at most
 constexpr int kMaxListed = 1024;     // chunks with a key that may be selected
 constexpr int kMaxByChunks = 576;    // the bin of L alone can make the list 1.77 times as long as k (|x| normal, k 1 % of K)
 
+__host__ __device__ inline bool select_tries_chunks(int nchunks, int k) { return 3 * k <= nchunks && k <= kMaxByChunks; }
+
 // LDS of the selection; nothing in it is needed afterwards, so it may share its place with other data.
 struct SelectShared {
     uint4 list[kMaxListed];
@@ -106,17 +108,27 @@ __device__ __forceinline__ void wave_find_bin(const unsigned* hist, unsigned kk,
     rem = (unsigned)__builtin_amdgcn_readlane((int)r_l, src);
 }
 
-// Key e of four words of a chunk.  The words come by value: chosen by reference they would be kept in scratch memory.
+// Word e / 2 of a chunk, by its bits or (MANY) by comparisons: the former is the quicker one where few keys of a chunk are
+// marked, the latter where many are (select.hip).  The words come by value: chosen by reference they would be kept in
+// scratch memory.
+template <bool MANY>
 __device__ __forceinline__ uint32_t word_of(uint32_t x, uint32_t y, uint32_t z, uint32_t w, int e) {
-    const uint32_t lo = e & 2 ? y : x, hi = e & 2 ? w : z;
-    return e & 4 ? hi : lo;
+    if constexpr (MANY) {
+        uint32_t r = e >= 2 ? y : x;
+        r = e >= 4 ? z : r;
+        return e >= 6 ? w : r;
+    } else {
+        const uint32_t lo = e & 2 ? y : x, hi = e & 2 ? w : z;
+        return e & 4 ? hi : lo;
+    }
 }
 __device__ __forceinline__ unsigned key_of(const uint4& c, int e) {
-    const uint32_t w = word_of(c.x, c.y, c.z, c.w, e);
+    const uint32_t w = word_of<false>(c.x, c.y, c.z, c.w, e);
     return ((e & 1) ? (w >> 16) : w) & 0x7FFFu;
 }
+template <bool MANY = false>
 __device__ __forceinline__ uint16_t raw_of(const uint4& c, int e) {
-    const uint32_t w = word_of(c.x, c.y, c.z, c.w, e);
+    const uint32_t w = word_of<MANY>(c.x, c.y, c.z, c.w, e);
     return (uint16_t)((e & 1) ? (w >> 16) : (w & 0xFFFFu));
 }
 
@@ -151,6 +163,7 @@ __device__ __forceinline__ void totals_before(const unsigned* wtot, int wave, un
 }
 
 // Writes the marked keys of one chunk: all of `gt`, of `eq` those with fewer than `need` equal keys in front.
+template <bool MANY = false>
 __device__ __forceinline__ void write_marked(const uint4& c, int channel0, unsigned gt, unsigned eq, unsigned pos_gt,
                                              unsigned seen_eq, unsigned need, unsigned k, int32_t* idx_out,
                                              uint16_t* xsel_out) {
@@ -163,7 +176,7 @@ __device__ __forceinline__ void write_marked(const uint4& c, int channel0, unsig
         // pos < k always holds for a taken key; the bound keeps a logic error from writing outside
         if ((is_gt || seen_eq < need) && pos < k) {
             idx_out[pos] = channel0 + e;
-            if (xsel_out) xsel_out[pos] = raw_of(c, e);
+            if (xsel_out) xsel_out[pos] = raw_of<MANY>(c, e);
         }
         pos_gt += is_gt;
         seen_eq += !is_gt;
@@ -290,8 +303,8 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
     return true;
 }
 
-// Any 1 <= k <= K.  Requires sh.hist1, sh.hist2 cleared (with a barrier behind).
-template <int THREADS, int NCH>
+// Any 1 <= k <= K.  Requires sh.hist1, sh.hist2 cleared (with a barrier behind).  MANY: many keys per chunk are marked.
+template <int THREADS, int NCH, bool MANY = false>
 __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared& sh,
                                                 int32_t* idx_out, uint16_t* xsel_out) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -356,15 +369,16 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
     }
 #pragma unroll
     for (int j = 0; j < NCH; ++j)
-        write_marked(ch[j], (c0 + 64 * j) * 8, gtm[j], eqm[j], base_gt + (excl[j] & 0xFFFFu), base_eq + (excl[j] >> 16), need,
+        write_marked<MANY>(ch[j], (c0 + 64 * j) * 8, gtm[j], eqm[j], base_gt + (excl[j] & 0xFFFFu), base_eq + (excl[j] >> 16), need,
                      (unsigned)k, idx_out, xsel_out);
 }
 
 // All THREADS threads of the workgroup call this.  Requires K a multiple of 8,
 // K <= 8*THREADS*NCH, x 16-byte aligned, 1 <= k <= K.  idx_out / xsel_out may
 // point to global memory or LDS; xsel_out may be null.  Ends with the outputs
-// written but not yet synchronised (the caller adds the barrier it needs).
-template <int THREADS, int NCH>
+// written but not yet synchronised (the caller adds the barrier it needs).  RADIX: the caller knows that
+// select_tries_chunks(K / 8, k) is false.
+template <int THREADS, int NCH, bool RADIX = false>
 __device__ __forceinline__ void block_select_topk(const uint16_t* __restrict__ x, int K, int k, SelectShared& sh,
                                                   int32_t* idx_out, uint16_t* xsel_out) {
     static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
@@ -381,12 +395,12 @@ __device__ __forceinline__ void block_select_topk(const uint16_t* __restrict__ x
         __syncthreads();
     };
     clear();
-    if (3 * k <= nchunks && k <= kMaxByChunks) {
+    if (!RADIX && select_tries_chunks(nchunks, k)) {
         if (select_by_chunks<THREADS, NCH>(ch, nchunks, k, sh, idx_out, xsel_out)) return;
         __syncthreads();
         clear();
     }
-    select_by_radix<THREADS, NCH>(ch, nchunks, k, sh, idx_out, xsel_out);
+    select_by_radix<THREADS, NCH, RADIX>(ch, nchunks, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace decdec

@@ -57,6 +57,23 @@ def test_stand_alone(K):
             assert np.array_equal(xs.cpu().numpy().view(np.uint16), x[sc].view(np.uint16)), (K, name, k)
 
 
+@pytest.mark.parametrize("K", [8192, 8200, 16384, 16392, 32768, 32776, 65536])
+def test_on_both_sides_of_the_line_between_the_forms(K):
+    """k at most a third of the chunks and at most 576 goes by chunks; one more by radix, above 8192 channels in a kernel
+    of its own, from which every key of a chunk may be written."""
+    x = np.random.default_rng(K + 1).standard_normal(K).astype(np.float16)
+    line = min(K // 8 // 3, 576)
+    xd = torch.from_numpy(x).cuda()
+    for k in (line, line + 1, K - 1, K):
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        xs = torch.zeros(k, dtype=torch.float16, device="cuda")
+        dd.decdec_select_topk(xd, K, k, idx, xs)
+        torch.cuda.synchronize()
+        sc = oracle.topk_abs(x, k)
+        assert np.array_equal(idx.cpu().numpy(), sc), (K, k)
+        assert np.array_equal(xs.cpu().numpy().view(np.uint16), x[sc].view(np.uint16)), (K, k)
+
+
 @pytest.mark.parametrize("K", [128, 4096, 4224, 8192, 8320, 16384, 16512, 32768])
 def test_inside_the_one_grid_kernel(K):
     lin = StoredLinear.random(K, 64, 3, dd.W_UNIFORM_G128, 16, seed=1)
