@@ -12,11 +12,11 @@
 //                           0.31, ..., 1.00 (a tie keeps the larger alpha).
 //   residual_encode_kernel  the codes, packed row by row for the fetch kernel.
 //
-// The search is written so that a CPU can reproduce it bit for bit: every
-// step is one IEEE fp64 operation (no contraction into fused multiply-adds),
-// the error of a column is summed over its rows in ascending order, and the
-// conversion of a scale to fp16 is one round-to-nearest-even done with integer
-// arithmetic.
+// Scales and codes have the bits that one IEEE fp64 operation per step gives,
+// the error of a column summed over its rows in ascending order, so that a CPU
+// can reproduce them; the search takes fewer, fused steps with the same results
+// (residual_scale_kernel says why they are the same).  The conversion of a scale
+// to fp16 is one round-to-nearest-even done with integer arithmetic.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
@@ -110,15 +110,15 @@ constexpr int kMaxSlots = 80;     // threads that share a column's candidates x 
 //     q = clip(rint(r / S), -qmax, qmax),   d = r - S q,   err = err + d d        (one rounding each)
 // because
 //   * |r| gives the same d d as r (every step is odd in r), and needs one clip instead of two;
-//   * |r| fl(1/S) is off from r / S by less than 2^-44 (|r| / S < 1000: S is at least half of 0.3 max|r| / qmax, and
+//   * |r| fl(1/S) is off from r / S by less than 2^-43 (|r| / S < 1000: S is at least half of 0.3 max|r| / qmax, and
 //     where it is replaced by 1, |r| < 2^-15), while a quotient that is not a half-integer is at least 2^-25 away from
 //     one (S is a multiple of 2^(e-10) and |r| >= S / 2 one of 2^(e-24), S < 2^(e+1)): the same integer; and where it is
 //     one, both neighbours give |d| = S / 2;
 //   * adding 1.5 * 2^52 in the same fused step rounds to that integer (the products lie far below 2^51);
 //   * d has at most 24 significant bits and S q at most 18, so r - S q and d d are exact, fused or not.
-// An infinity or a NaN among the values makes err a NaN in both forms, and a NaN is never the least error.  Rows
-// beyond K count as zeros: they leave err as it is.
-// A 4096 x 4096 layer prepared with 4-bit residual codes: 18.8 -> 0.49 ms, of which the search is now 0.26 (0.15 at
+// That is for finite values.  An infinity or a NaN in the column makes err a NaN for every candidate, and a NaN is never
+// the least error: the column gets S = 1.  Rows beyond K count as zeros: they leave err as it is.
+// A 4096 x 4096 layer prepared with 4-bit residual codes: 18.8 -> 0.47 ms, of which the search is now 0.26 (0.15 at
 // the issue rate) and the way of the codes to pinned host memory 0.15.
 template <int COLS, int WAVES, int APT>
 __global__ __launch_bounds__(64 * WAVES) void residual_scale_kernel(const float* __restrict__ R, int K, int N,

@@ -97,6 +97,34 @@ def test_residual_scale_search_at_its_edges(rbits, K, N):
     assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
 
 
+@pytest.mark.parametrize("rbits", [2, 4, 8])
+def test_residual_columns_that_are_not_finite_get_scale_one(rbits):
+    """An infinity or a NaN makes a column's error a NaN for every candidate scale; columns of large finite values, whose
+    greater candidates round to an infinite scale, keep the finite ones: as in the oracle."""
+    K, N = 130, 64
+    R32 = np.random.default_rng([79, rbits]).standard_normal((K, N)).astype(np.float32)
+    R32[:, 0] = np.inf
+    R32[:, 1] = -np.inf
+    R32[::2, 2] = np.inf
+    R32[1::2, 2] = -np.inf
+    R32[K - 1, 3] = np.inf
+    R32[0, 4] = np.nan
+    R32[:, 5] = np.nan
+    R32[:, 6] *= 6e4 * (2 ** (rbits - 1) - 1)
+    with np.errstate(invalid="ignore", over="ignore"):
+        q_ref, S_ref = oracle.quantize_residual_sym(R32.astype(np.float64), rbits)
+    assert np.all(S_ref[:6] == 1) and np.isfinite(S_ref[6])
+    q_ref[np.isnan(R32)] = 0
+    codes = torch.zeros((K, N * rbits // 8), dtype=torch.uint8, pin_memory=True)
+    S = torch.zeros(N, dtype=torch.float16, device="cuda")
+    dd.decdec_quantize_residual(K, N, rbits, torch.from_numpy(R32).cuda(), codes, S)
+    torch.cuda.synchronize()
+    assert np.array_equal(S.cpu().numpy().view(np.uint16), S_ref.view(np.uint16))
+    per = 8 // rbits
+    whole = ~np.isnan(R32).reshape(K, -1, per).any(axis=2)  # a NaN has no code: bytes without one
+    assert np.array_equal(codes.numpy()[whole], dd.decdec_pack_residual_int(q_ref, rbits)[whole])
+
+
 @pytest.mark.parametrize("rbits", [4, 2, 8])
 def test_uniform_linear_with_integer_residuals_end_to_end(rbits):
     """Device-prepared layer (quantiser, fp32 residual, residual quantiser) through the hot path,
