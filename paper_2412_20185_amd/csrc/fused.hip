@@ -26,9 +26,9 @@ namespace {
 // Eight wavefronts a SIMD (kernels.h), so that the base-GEMV workgroups keep the memory busy: with the cap taken off the
 // Llama-3-8B layers with rows in GPU memory take 145.7 us a step instead of 141.5, four layers without compensation 111.2
 // instead of 103.6.  Six where the vector registers allow no more: eight chunks of keys per thread, or 2-bit rows (16 column
-// sums and 16 row pieces a lane), need up to 80.  Up to 17 scalar values that no loop uses wait in the lanes of a vector
-// register meanwhile; that costs nothing that could be measured, whereas 32-43 of them with 4-bit rows, many out of the row
-// loop, cost 2-5 % of a small step.
+// sums and 16 row pieces a lane), need up to 80.  Up to 24 scalar values wait in the lanes of a vector register where they
+// are not used; that costs nothing that could be measured, whereas 32-43 of them with 4-bit rows, many out of the row loop,
+// cost 2-5 % of a small step.
 template <int KIND, int RBITS, int SELECT_NCH>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(SELECT_NCH == 8 || RBITS == 2 ? 6 : 8)))
 void compensated_gemv_kernel(const CallArgs a) {

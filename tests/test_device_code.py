@@ -46,28 +46,39 @@ def code_objects(tmp_path_factory):
     return paths
 
 
+def _disassembly(path):
+    """(kernel name, its instructions) of a code object."""
+    text = subprocess.run([_tool("llvm-objdump"), "-d", "--no-show-raw-insn", path], capture_output=True, text=True,
+                          check=True).stdout
+    name, lines = None, []
+    for line in text.splitlines():
+        m = re.match(r"[0-9a-f]+ <(.*)>:", line)
+        if m:
+            if name:
+                yield name, lines
+            name, lines = m.group(1), []
+        else:
+            lines.append(line.split("//")[0].strip())
+    if name:
+        yield name, lines
+
+
 def test_no_flat_memory_access(code_objects):
     """A pointer whose address space the compiler does not know is accessed by flat instructions, which count as LDS
     accesses too and are waited for together with all of them.  Every pointer here is to global memory or LDS."""
     flat = {}
     for path in code_objects:
-        text = subprocess.run([_tool("llvm-objdump"), "-d", "--no-show-raw-insn", path], capture_output=True, text=True,
-                              check=True).stdout
-        name = None
-        for line in text.splitlines():
-            m = re.match(r"[0-9a-f]+ <(.*)>:", line)
-            if m:
-                name = m.group(1)
-            elif re.search(r"\bflat_(load|store|atomic)", line):
-                flat[name] = flat.get(name, 0) + 1
+        for name, lines in _disassembly(path):
+            n = sum(line.startswith(("flat_load", "flat_store", "flat_atomic")) for line in lines)
+            if n:
+                flat[name] = n
     assert not flat
 
 
 def test_registers_of_every_kernel(code_objects):
-    """No scratch memory, and of the scalar registers no more set aside in vector lanes than the pointers and counts that
-    are kept for a workgroup's last step come to (at most 20): the sixteen lane masks of a row loop would be 32 more.  The
-    kernels that are meant to run with eight wavefronts a SIMD (64 vector registers) stay within the 80 scalar registers
-    that allow it."""
+    """No scratch memory, and of the scalar registers at most 24 set aside in vector lanes: pointers and counts that are
+    kept for a workgroup's last step.  The sixteen lane masks of a row loop would be 32 more.  The kernels that are meant to
+    run with eight wavefronts a SIMD (64 vector registers) stay within the 80 scalar registers that allow it."""
     seen = 0
     for path in code_objects:
         notes = subprocess.run([_tool("llvm-readelf"), "--notes", path], capture_output=True, text=True, check=True).stdout
@@ -76,7 +87,35 @@ def test_registers_of_every_kernel(code_objects):
             name = re.search(r"\.name: +(\S+)", entry).group(1)
             seen += 1
             assert value("private_segment_fixed_size") == 0 and value("vgpr_spill_count") == 0, name
-            assert value("sgpr_spill_count") <= 20, (name, value("sgpr_spill_count"))
+            assert value("sgpr_spill_count") <= 24, (name, value("sgpr_spill_count"))
             if "gemv_kernel" in name and value("vgpr_count") <= 64:
                 assert value("sgpr_count") <= 80, (name, value("sgpr_count"))
     assert seen > 100
+
+
+def test_row_requests_of_a_batch_do_not_wait_for_one_another(code_objects):
+    """The residual kernels request a batch of rows (4 KiB a wavefront) before they use the first one.  A wait among the
+    requests that is not over until one of them has returned would make the batch several trips over the host link.  (2-bit
+    rows with the selection supplied take two rows a request and read the row numbers by vector loads, waited for in two
+    groups; all of them first was measured slower.)"""
+    batch = {16: ("global_load_dwordx4", 4), 8: ("global_load_dwordx2", 8), 4: ("global_load_dword", 16), 2: ("global_load_dword", 16)}
+    seen = set()
+    for path in code_objects:
+        for name, lines in _disassembly(path):
+            m = re.search(r"(?:fetch_kernelI|compensated_gemv_kernelILi\d+E)Li(\d+)ELi(\d+)E", name)
+            if not m or m.groups() == ("2", "0"):
+                continue
+            op, rows = batch[int(m.group(1))]
+            run, free, found = 0, True, False  # requests in a row, none of them waited for so far
+            for line in lines:
+                word = line.split(" ")[0]
+                if word == op and not line.endswith(" nt"):  # the weight stream is non-temporal
+                    run += 1
+                    found |= free and run >= rows
+                elif word.startswith(("global_load", "global_store", "global_atomic")):
+                    run, free = 0, True
+                elif (w := re.search(r"^s_waitcnt.*vmcnt\((\d+)\)", line)) and run and run < rows and int(w.group(1)) < run:
+                    free = False
+            assert found, name
+            seen.add((name.split("kernel")[0][-12:],) + m.groups())
+    assert len(seen) >= 4 * 5 - 1
