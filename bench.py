@@ -394,7 +394,7 @@ def main() -> int:
         "dtype": "f16",
         "data": "synthetic",
         "config": {
-            "workload": "configs[1]: Llama-3-8B-shaped decode layer, batch 1, 7 GEMVs, 3-bit uniform group-128 "
+            "workload": "Llama-3-8B-shaped decode layer, batch 1, 7 GEMVs, 3-bit uniform group-128 "
                         "weights, fp16 activations with 0.5% outlier channels, fp16 host residuals, k = 2% of K "
                         "(81 / 286)",
             "layers_rotated": args.layers,
@@ -585,7 +585,7 @@ def main() -> int:
         del r4, int4_layers
         log("4-bit-residual rows done")
 
-        # ---- configs[2]: the same layer shapes at 4 bits, k_chunk sweep, the paper's latency model beside it
+        # ---- the same layer shapes at 4 bits, k_chunk sweep, the paper's latency model beside it
         if layers4:
             step4 = make_step(make_groups(layers4))
             r3 = StepRunner(torch, step4, gs, math.lcm(len(layers4), args.xpool), bool(args.graph))
@@ -618,7 +618,7 @@ def main() -> int:
                              "model_nominal_us_per_step": round(nominal, 2),
                              "model_measured_us_per_step": round(measured, 2)})
             out["configs"]["llama3_8b_layer_4bit_vs_kchunk"] = {
-                "workload": "configs[2]: the Llama-3-8B layer shapes at 4 bits, fp16 host residuals, k_chunk channels per 1024 "
+                "workload": "the Llama-3-8B layer shapes at 4 bits, fp16 host residuals, k_chunk channels per 1024 "
                             f"input channels, outlier positions redrawn every step; {len(layers4)} layers rotated",
                 "weight_bytes_per_step": sum(w4_call),
                 "model": "sum over the 4 calls of max(base, transfer): nominal = weight bytes / 8 TB/s against residual bytes / "
@@ -638,10 +638,10 @@ def main() -> int:
     if extra:
         from paper_2412_20185_amd.layer import random_layer
         cases = [
-            ("llama3_70b_layer", "configs[3]: Llama-3-70B-shaped layer, 3-bit codebook weights (8 fp16 entries per output "
+            ("llama3_70b_layer", "Llama-3-70B-shaped layer, 3-bit codebook weights (8 fp16 entries per output "
              "column), Student-t activations, fp16 host residuals, k = 1 % of K (81 / 286)",
              workloads.LLAMA3_70B_LAYER, dd.W_LUT_COL8, 16, 2, lambda K: workloads.k_for_fraction(K, 0.01), 4, {}),
-            ("llama3_8b_32_layer_step", "configs[4]: 32-layer Llama-3-8B-shaped decode step (224 GEMVs), 3-bit group-128 "
+            ("llama3_8b_32_layer_step", "32-layer Llama-3-8B-shaped decode step (224 GEMVs), 3-bit group-128 "
              "weights, Student-t activations with 0.5 % outlier channels x30 redrawn each step, 4-bit host residuals, "
              "k_chunk = 15 (k = 60 / 210: residual bytes 1.9 % of the weight bytes)",
              workloads.LLAMA3_8B_LAYER, dd.W_UNIFORM_G128, 4, 32, lambda K: workloads.k_for_kchunk(K, 15), 5,
