@@ -7,7 +7,7 @@
     python -m paper_2412_20185_amd.microbench fetch    residual fetch kernel per shape and number of wavefronts per column segment: us, GB/s
     python -m paper_2412_20185_amd.microbench ksweep   latency of a Llama-3-8B layer versus k (4-bit weights),
                                                        next to the knee model of the paper (Section 5.1)
-    python -m paper_2412_20185_amd.microbench select   exact radix select versus the paper's approximate bucket
+    python -m paper_2412_20185_amd.microbench select   exact select versus the paper's approximate bucket
                                                        Top-K (Section 4.3): time per launch and recall
     python -m paper_2412_20185_amd.microbench rformats residual formats of the bit-width study (Table 2) at equal link
                                                        bytes: fetch kernel time and link rate for 2/4/8-bit and fp16 rows
