@@ -179,8 +179,9 @@ int decdec_ws_set_separate_select(decdec_ws* ws, int32_t on);
  * are assumed finite; a NaN part sum counts as -2^21. */
 int decdec_ws_set_inkernel_accumulate(decdec_ws* ws, int32_t on);
 
-/* Number of 128-channel groups each wavefront of the base GEMV walks through
- * (how finely K is split over the chip); 0 restores the built-in choice. */
+/* Number of 128-channel groups each wavefront of the base GEMV walks through,
+ * 64 output columns wide (how finely K is split over the chip); 0 restores the
+ * built-in choice. */
 int decdec_ws_set_gemv_split(decdec_ws* ws, int32_t groups_per_wave);
 /* Wavefronts per workgroup (4, 8 or 16; 0 restores the built-in choice) of the
  * base GEMV when it runs as a kernel of its own.  A workgroup adds the sums of
@@ -192,11 +193,12 @@ int decdec_ws_set_gemv_waves(decdec_ws* ws, int32_t waves_per_workgroup);
  * uncompensated call (k == 0) over K input channels and N_total output columns
  * (all matrices of a decdec_gemv_multi call together) would be launched with
  * under this workspace's current settings: number of workgroups, threads per
- * workgroup, K-slices per 64-column tile.  Any output pointer may be NULL.
+ * workgroup, workgroups per 64-column tile (K-slices times blocks of columns).
+ * Any output pointer may be NULL.
  * Benchmarks use it to tell whether a stored profile still describes the
  * kernels that run. */
 int decdec_ws_gemv_launch_shape(const decdec_ws* ws, int32_t K, int32_t N_total, int32_t* workgroups,
-                                int32_t* threads, int32_t* k_slices);
+                                int32_t* threads, int32_t* per_tile);
 
 /* Kernel timing for benchmarks.  capacity > 0 allocates that many sets of HIP
  * events (set-up call: allocates, synchronises) and makes every later

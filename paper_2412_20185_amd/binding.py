@@ -187,7 +187,7 @@ class Workspace:
         _check(lib().decdec_ws_set_gemv_waves(self.handle, waves_per_workgroup), "decdec_ws_set_gemv_waves")
 
     def gemv_launch_shape(self, K: int, N_total: int):
-        """(workgroups, threads per workgroup, K-slices) of the base GEMV kernel of a k = 0 call."""
+        """(workgroups, threads per workgroup, workgroups per 64-column tile) of the base GEMV kernel of a k = 0 call."""
         wg, th, sl = C.c_int32(), C.c_int32(), C.c_int32()
         _check(lib().decdec_ws_gemv_launch_shape(self.handle, K, N_total, C.byref(wg), C.byref(th), C.byref(sl)),
                "decdec_ws_gemv_launch_shape")

@@ -382,13 +382,14 @@ int decdec_ws_set_gemv_waves(decdec_ws* ws, int32_t waves_per_workgroup) {
 }
 
 int decdec_ws_gemv_launch_shape(const decdec_ws* ws, int32_t K, int32_t N_total, int32_t* workgroups,
-                                int32_t* threads, int32_t* k_slices) {
+                                int32_t* threads, int32_t* per_tile) {
     if (ws == nullptr || K <= 0 || K % kGroup != 0 || N_total <= 0 || N_total % kTileCols != 0) return DECDEC_EINVAL;
     const long tiles = N_total / kTileCols;
-    const GemvPlan gp = gemv_plan(tiles, K / kGroup, ws->core.gemv_gpw, ws->core.gemv_wpb);
-    if (workgroups) *workgroups = (int32_t)(tiles * gp.slices);
-    if (threads) *threads = gp.wpb * 64;
-    if (k_slices) *k_slices = gp.slices;
+    const GemvPlan gp = gemv_plan(tiles, K / kGroup, ws->core.gemv_gpw, ws->core.gemv_wpb, false);
+    const int32_t each = kTileCols / gp.cols * gp.slices;
+    if (workgroups) *workgroups = (int32_t)tiles * each;
+    if (threads) *threads = workgroup_waves(gp.waves) * 64;
+    if (per_tile) *per_tile = each;
     return DECDEC_OK;
 }
 
@@ -637,7 +638,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     long tiles = 0;
     for (int m = 0; m < count; ++m) tiles += sh.N[m] / kTileCols;
     const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED;
-    const GemvPlan gp = gemv_plan(tiles, sh.K / kGroup, c.gemv_gpw, fused ? kWavesPerBlock : c.gemv_wpb);
+    const GemvPlan gp = gemv_plan(tiles, sh.K / kGroup, c.gemv_gpw, c.gemv_wpb, fused);
     const int gslices = gp.slices;
     FetchPlan plan{0, 0, 0};
     if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm);
@@ -664,6 +665,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     a.G = sh.K / kGroup;
     a.gslices = gslices;
     a.gpw = gp.gpw;
+    a.waves = gp.waves;
     a.gdiv = reciprocal_of(gslices);
     a.producers = gslices + cslices;
     // One slice and no residual term: the base GEMV rounds and writes y itself, nothing is left to add.
@@ -686,7 +688,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     bool forked = false;  // TWO_STREAMS: the side stream has been made to wait for `stream` and not yet joined back
     const int rc_enq = [&]() -> int {
         if (k == 0) {
-            DD_HIP(launch_gemv(kind, a, gp.wpb, stream, tm[0]));
+            DD_HIP(launch_gemv(kind, a, gp.cols, stream, tm[0]));
             if (pmask) *pmask |= 1;
         } else {
             // The kernels that follow only read a selection that is given; the const is dropped for the shared struct.
@@ -711,13 +713,13 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
                 }
             }
             if (fused) {
-                DD_HIP(launch_compensated_gemv(kind, d0->rfmt, a, select_chunks, stream, tm[2]));
+                DD_HIP(launch_compensated_gemv(kind, d0->rfmt, a, select_chunks, !residuals_in_hbm, stream, tm[2]));
                 if (pmask) *pmask |= 4;
             } else {
                 DD_HIP(launch_fetch(d0->rfmt, a, select_chunks, comp, tm[2]));
                 if (pmask) *pmask |= 4;
                 if (two_streams) DD_HIP(hipEventRecord(c.ev_join, c.side));
-                DD_HIP(launch_gemv(kind, a, gp.wpb, stream, tm[0]));
+                DD_HIP(launch_gemv(kind, a, gp.cols, stream, tm[0]));
                 if (pmask) *pmask |= 1;
                 if (two_streams) {
                     DD_HIP(hipStreamWaitEvent(stream, c.ev_join, 0));

@@ -46,13 +46,16 @@ struct Selection {
 };
 
 template <int SELECT_NCH>
-__device__ __forceinline__ Selection obtain_selection(const uint16_t* __restrict__ x, int K, int k,
-                                                      int32_t* idx_g, uint16_t* xsel_g, SelectShared& sh, int bid) {
+__device__ __forceinline__ Selection obtain_selection(const uint4* keys, int K, int k, int32_t* idx_g, uint16_t* xsel_g,
+                                                      SelectShared& sh, int bid) {
     if constexpr (SELECT_NCH > 0) {
         extern __shared__ uint4 s_sel_raw[];  // int32 idx[k], then fp16 xsel[k]
         int32_t* idx_l = reinterpret_cast<int32_t*>(s_sel_raw);
         uint16_t* xs_l = reinterpret_cast<uint16_t*>(idx_l + k);
-        block_select_topk<kBlockThreads, SELECT_NCH>(x, K, k, sh, idx_l, xs_l);
+        uint4 ch[SELECT_NCH];
+#pragma unroll
+        for (int j = 0; j < SELECT_NCH; ++j) ch[j] = keys[j];
+        block_select_topk<kBlockThreads, SELECT_NCH>(ch, K, k, sh, idx_l, xs_l);
         __syncthreads();
         if (bid == 0) {
             for (int i = threadIdx.x; i < k; i += kBlockThreads) {
@@ -149,6 +152,9 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k = a.k, K = a.G * kGroup;
+    // the keys are asked for before anything else: the selection is the first link of this workgroup's chain of waits
+    uint4 keys[SELECT_NCH > 0 ? SELECT_NCH : 1];
+    if constexpr (SELECT_NCH > 0) load_keys(a.x, K, keys);
     const int row_waves = a.row_waves, slices = a.cslices;
     const int seg = divide_by(bid, a.cdiv);
     const int rs = bid - seg * slices;
@@ -173,7 +179,7 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     hold_scalar(y);
     hold_scalar(acc_words);
 
-    const Selection sel = obtain_selection<SELECT_NCH>(a.x, K, k, a.idx, a.xsel, lds.sh, bid);
+    const Selection sel = obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid);
     const int32_t* idx = sel.idx;
     const uint16_t* xsel = sel.xsel;
     const piece_t* __restrict__ R = reinterpret_cast<const piece_t*>(rows_base);

@@ -17,18 +17,18 @@
 // column segment (decdec_ws_set_fetch_split).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fetch_body.h"
 #include "gemv_body.h"
 
 namespace decdec {
 namespace {
 
-// Eight wavefronts a SIMD (kernels.h), so that the base-GEMV workgroups keep the memory busy: with the cap taken off the
-// Llama-3-8B layers with rows in GPU memory take 145.7 us a step instead of 141.5, four layers without compensation 111.2
-// instead of 103.6.  Six where the vector registers allow no more: eight chunks of keys per thread, or 2-bit rows (16 column
-// sums and 16 row pieces a lane), need up to 80.  Up to 24 scalar values wait in the lanes of a vector register where they
-// are not used; that costs nothing that could be measured, whereas 32-43 of them with 4-bit rows, many out of the row loop,
-// cost 2-5 % of a small step.
+// Eight wavefronts a SIMD (kernels.h), so that the base-GEMV workgroups keep the memory busy.  They take 64 columns a
+// wavefront: with blocks of 16 columns Llama-3-8B layers with rows in GPU memory take 141 us a step instead of 134.  Six
+// where the vector registers allow no more: eight chunks of keys per thread, or 2-bit rows (16 column sums and 16 row pieces
+// a lane), need up to 80.
 template <int KIND, int RBITS, int SELECT_NCH>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(SELECT_NCH == 8 || RBITS == 2 ? 6 : 8)))
 void compensated_gemv_kernel(const CallArgs a) {
@@ -37,14 +37,22 @@ void compensated_gemv_kernel(const CallArgs a) {
     if (bid < a.nfetch) {
         fetch_block<RBITS, SELECT_NCH>(a, bid);
     } else {
-        gemv_block<KIND, kWavesPerBlock, 2>(a, bid - a.nfetch);
+        gemv_block<KIND, kOneGridCols, kWavesPerBlock>(a, bid - a.nfetch, kWavesPerBlock);
     }
 }
 
+// With rows behind the link the call lasts as long as selection and rows, and the base GEMV of the same compute unit slows
+// the selection down: three workgroups a compute unit instead of four, by the LDS they ask for (its 160 KB less than four
+// times as much; the kernels have 22 KB without asking).  us: 8192 x 8192 (codebook), 20 fp16 rows 13.0 -> 12.35;
+// 14336 x 4096, 56 8-bit rows 11.42 -> 11.31.  No difference up to 4096 channels, where the selection is short; with rows in
+// GPU memory, where the base GEMV is what lasts, 7.3 -> 7.8 (14336 x 4096, 286 fp16 rows).
+constexpr unsigned kLdsOfThree = 42 * 1024, kStaticLds = 22 * 1024;
+
 template <int KIND, int RBITS>
-hipError_t launch_nch(const CallArgs& a, int nch, hipStream_t stream, const KernelTimer* tm) {
-    const dim3 grid((unsigned)(a.nfetch + a.tiles * a.gslices)), block(kBlockThreads);
-    const unsigned lds = selection_lds_bytes(nch, a.k);
+hipError_t launch_nch(const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
+    const dim3 grid((unsigned)(a.nfetch + a.tiles * (kTileCols / kOneGridCols) * a.gslices)), block(kBlockThreads);
+    unsigned lds = selection_lds_bytes(nch, a.k);
+    if (over_link && nch > 1) lds = std::max(lds, kLdsOfThree - kStaticLds);
     switch (nch) {
         case 0: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0>, grid, block, lds, stream, a);
         case 1: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1>, grid, block, lds, stream, a);
@@ -56,24 +64,24 @@ hipError_t launch_nch(const CallArgs& a, int nch, hipStream_t stream, const Kern
 }
 
 template <int KIND>
-hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, hipStream_t stream, const KernelTimer* tm) {
+hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
     switch (rfmt) {
-        case 0: return launch_nch<KIND, 16>(a, nch, stream, tm);
-        case 1: return launch_nch<KIND, 4>(a, nch, stream, tm);
-        case 2: return launch_nch<KIND, 2>(a, nch, stream, tm);
-        case 3: return launch_nch<KIND, 8>(a, nch, stream, tm);
+        case 0: return launch_nch<KIND, 16>(a, nch, over_link, stream, tm);
+        case 1: return launch_nch<KIND, 4>(a, nch, over_link, stream, tm);
+        case 2: return launch_nch<KIND, 2>(a, nch, over_link, stream, tm);
+        case 3: return launch_nch<KIND, 8>(a, nch, over_link, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }
 
 }  // namespace
 
-hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, hipStream_t stream,
+hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, bool over_link, hipStream_t stream,
                                    const KernelTimer* tm) {
     switch (kind) {
-        case PACK_U4: return launch_rfmt<PACK_U4>(rfmt, a, select_chunks, stream, tm);
-        case PACK_U3: return launch_rfmt<PACK_U3>(rfmt, a, select_chunks, stream, tm);
-        case PACK_LUT3: return launch_rfmt<PACK_LUT3>(rfmt, a, select_chunks, stream, tm);
+        case PACK_U4: return launch_rfmt<PACK_U4>(rfmt, a, select_chunks, over_link, stream, tm);
+        case PACK_U3: return launch_rfmt<PACK_U3>(rfmt, a, select_chunks, over_link, stream, tm);
+        case PACK_LUT3: return launch_rfmt<PACK_LUT3>(rfmt, a, select_chunks, over_link, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }

@@ -2,65 +2,101 @@
 // separate kernels).  The device code is in gemv_body.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "gemv_body.h"
 
 namespace decdec {
 namespace {
 
-// Eight wavefronts a SIMD (kernels.h), so that two workgroups of 16 fit a compute unit: with the cap taken off, one does, and
-// gate + up of the Llama-3-8B shape runs in two rounds (32 layers 921 us instead of 846).  Four where four tiles in flight
-// need up to 104 vector registers.
-template <int KIND, int WPB, int NBUF>
-__global__ __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(NBUF == 2 ? 8 : 4))) void gemv_kernel(const CallArgs a) {
+// Eight wavefronts a SIMD (kernels.h): a wavefront holds one tile, and the others of its compute unit cover its trip to memory.
+template <int KIND, int COLS, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8))) void gemv_kernel(const CallArgs a) {
     touch_args(a);
-    gemv_block<KIND, WPB, NBUF>(a, (int)blockIdx.x);
+    asm volatile("" ::"s"(a.tiles), "s"(a.waves));
+    gemv_block<KIND, COLS, WAVES>(a, (int)blockIdx.x, a.waves);
 }
 
-template <int KIND, int WPB>
-hipError_t launch_depth(const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
-    const dim3 grid((unsigned)(a.tiles * a.gslices)), block(WPB * 64);
-    if (a.gpw > 2) return launch_kernel(tm, gemv_kernel<KIND, WPB, 4>, grid, block, 0, stream, a);  // tiles a wave keeps in flight
-    return launch_kernel(tm, gemv_kernel<KIND, WPB, 2>, grid, block, 0, stream, a);
+template <int KIND, int COLS>
+hipError_t launch_waves(const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
+    const dim3 grid((unsigned)(a.tiles * (kTileCols / COLS) * a.gslices)), block(workgroup_waves(a.waves) * 64);
+    switch (workgroup_waves(a.waves)) {
+        case 4: return launch_kernel(tm, gemv_kernel<KIND, COLS, 4>, grid, block, 0, stream, a);
+        case 8: return launch_kernel(tm, gemv_kernel<KIND, COLS, 8>, grid, block, 0, stream, a);
+        default: return launch_kernel(tm, gemv_kernel<KIND, COLS, 16>, grid, block, 0, stream, a);
+    }
 }
 
 template <int KIND>
-hipError_t launch_waves(const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm) {
-    switch (wpb) {
-        case 4: return launch_depth<KIND, 4>(a, stream, tm);
-        case 8: return launch_depth<KIND, 8>(a, stream, tm);
-        case 16: return launch_depth<KIND, 16>(a, stream, tm);
+hipError_t launch_cols(const CallArgs& a, int cols, hipStream_t stream, const KernelTimer* tm) {
+    switch (cols) {
+        case 16: return launch_waves<KIND, 16>(a, stream, tm);
+        case 32: return launch_waves<KIND, 32>(a, stream, tm);
+        case 64: return launch_waves<KIND, 64>(a, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }
 
 }  // namespace
 
-GemvPlan gemv_plan(long tiles, int G, int gpw_request, int wpb_request) {
-    // One group per wavefront, so that a wavefront requests all its weights at once, as long as the chip
-    // holds the wavefronts that makes at one time; two groups beyond that.  A K-slice more costs one atomic
-    // per column (finalize.h), so the slices are not kept few: small matrices take small workgroups, which
-    // start sooner and spread over more compute units; in between, the largest workgroups (a workgroup that
-    // walks all of K alone writes y itself); the largest matrices run in several rounds of workgroups,
-    // which medium workgroups fill more evenly.  Read from a sweep over the shapes of Llama-3 8B and 70B.
-    GemvPlan p;
-    const long units = tiles * G;  // (tile, group) pairs = wavefront iterations
-    p.wpb = wpb_request > 0 ? wpb_request : units <= 4096 ? 4 : units <= 16384 ? 16 : 8;
-    p.gpw = gpw_request > 0 ? gpw_request : units <= 12288 ? 1 : 2;
-    int per_block = p.gpw * p.wpb;
-    p.slices = (G + per_block - 1) / per_block;
-    while (p.slices > kMaxGemvSlices) {
-        ++p.gpw;
-        per_block = p.gpw * p.wpb;
-        p.slices = (G + per_block - 1) / per_block;
-    }
-    return p;
+namespace {
+
+constexpr int kCus = 256;
+int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
+
+// `waves` wavefronts of `cols` columns, `gpw` turns each; as many slices as that takes, at most kMaxGemvSlices.
+GemvPlan sliced(int G, int cols, int waves, int gpw) {
+    const int turns = ceil_div(G, kTileCols / cols);  // of one wavefront over all of K
+    gpw = std::max(gpw, ceil_div(turns, (long)waves * kMaxGemvSlices));
+    return GemvPlan{cols, waves, gpw, ceil_div(turns, (long)waves * gpw)};
 }
 
-hipError_t launch_gemv(int kind, const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm) {
+}  // namespace
+
+GemvPlan gemv_plan(long tiles, int G, int gpw_request, int waves_request, bool one_grid) {
+    if (one_grid) return sliced(G, kOneGridCols, kWavesPerBlock, std::max(gpw_request, 1));
+    if (gpw_request > 0 || waves_request > 0) return sliced(G, 64, waves_request > 0 ? waves_request : 8, std::max(gpw_request, 1));
+
+    // One tile per wavefront.  us per call in graph replays on rotating weights, the plan before this one (64 columns only,
+    // two groups per wavefront from 12288 tiles on) -> now; 3-bit / 4-bit / codebook.
+    //
+    // One workgroup over all of K, which writes y itself, where that still gives the chip enough to do.
+    //   4096 x 4096: 4.10 / 4.44 / 4.38 -> 3.59 / 3.82 / 3.68;  4096 x 28672: 11.0 / 12.3 / 12.4 -> 10.0 / 12.1 / 11.0;
+    //   1024 x 1024: 3.2 / 3.3 / 3.3 -> 2.7 / 2.6 / 2.7;  8192 x 4096: 5.17 / 5.70 / 5.49 -> 4.66 / 5.38 / 4.84
+    const int turns16 = ceil_div(G, 4), turns32 = ceil_div(G, 2);
+    const long blocks16 = 4 * tiles, blocks32 = 2 * tiles;
+    const int rounds16 = ceil_div(blocks16, kCus), rounds32 = ceil_div(blocks32, kCus);
+    if (turns16 <= 8) {
+        // Blocks of 32 columns where those of 16 would leave compute units idle in their last round and twice as wide ones
+        // do not take longer for it: N = 5120, 6144 and 14336 with K = 4096 4.42 -> 4.29, 4.52 -> 4.37, 6.83 -> 6.43.
+        if (turns32 <= 16 && blocks16 % kCus != 0 && rounds16 == 2 * rounds32) return GemvPlan{32, turns32, 1, 1};
+        return GemvPlan{16, turns16, 1, 1};
+    }
+    // Up to K = 8192 the same with up to 16 wavefronts and one workgroup per compute unit, or half as many as there are; up to
+    // 6144 also with two.  us for that and for slices: 8192 x 4096 4.6 and 5.1, 5120 x 8192 5.5 and 5.9; but 8192 x 1024 3.9
+    // and 3.5, 8192 x 5120 6.3 and 5.7, 8192 x 8192 in 4 bits 8.9 and 8.6.
+    if (turns16 <= 16 && blocks16 >= kCus / 2 && (blocks16 <= kCus || (blocks16 == 2 * kCus && turns16 <= 12)))
+        return GemvPlan{16, turns16, 1, 1};
+    // K-slices, one atomic per column each (finalize.h): workgroups of four wavefronts while the chip holds all of them at one
+    // time, which start sooner; else of eight at most, in the widest blocks whose slices are few enough.
+    //   8192 x 10240: 9.6 / 11.1 / 10.1 -> 8.5 / 10.0 / 9.9;  28672 x 8192: 18.5 / 22.6 / 21.5 -> 17.2 / 21.1 / 20.9;
+    //   13824 x 5120: 8.7 / 10.0 / 9.7 -> 7.7 / 8.9 / 8.9;  8192 x 5120 by four and by eight: 5.7 and 5.9
+    if (G <= 4 * kMaxGemvSlices && tiles * G <= 8192) return sliced(G, 64, 4, 1);
+    if (G <= 8 * kMaxGemvSlices) {
+        // More slices of fewer wavefronts, if all workgroups still start at one time (four per compute unit): 14336 x 4096 in
+        // 14 and 16 slices 7.24 / 8.27 / 7.67 and 7.10 / 7.91 / 7.41 (8704 x 4096 in 9 and 14: 5.96 -> 5.74); in 16 slices of
+        // 13824 x 4608, which do not, 7.6 instead of 7.3.
+        const int slices = std::max(ceil_div(G, 8), (int)std::min<long>(4 * kCus / tiles, kMaxGemvSlices));
+        return sliced(G, 64, ceil_div(G, slices), 1);
+    }
+    return sliced(G, G <= 16 * kMaxGemvSlices ? 32 : 16, 8, 1);
+}
+
+hipError_t launch_gemv(int kind, const CallArgs& a, int cols, hipStream_t stream, const KernelTimer* tm) {
     switch (kind) {
-        case PACK_U4: return launch_waves<PACK_U4>(a, wpb, stream, tm);
-        case PACK_U3: return launch_waves<PACK_U3>(a, wpb, stream, tm);
-        case PACK_LUT3: return launch_waves<PACK_LUT3>(a, wpb, stream, tm);
+        case PACK_U4: return launch_cols<PACK_U4>(a, cols, stream, tm);
+        case PACK_U3: return launch_cols<PACK_U3>(a, cols, stream, tm);
+        case PACK_LUT3: return launch_cols<PACK_LUT3>(a, cols, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }

@@ -78,7 +78,7 @@ struct CallArgs {
                               // partial rows and a separate kernel adds them
     int n;                    // matrices
     int G;                    // groups of 128 input channels
-    int gslices, gpw;         // K-slices of the base GEMV, groups per wavefront
+    int gslices, gpw, waves;  // base GEMV: K-slices, turns per wavefront, wavefronts per workgroup
     unsigned gdiv;            // reciprocal_of(gslices)
     int producers;            // part sums per column: gslices + cslices
     int direct;               // 1: the base GEMV is the only producer and has one slice: it writes y itself
@@ -120,15 +120,17 @@ __device__ __forceinline__ void hold_scalar(T*& p) {
 }
 
 // gemv.hip ---------------------------------------------------------------
-// wpb: wavefronts per workgroup (4, 8 or 16).
-hipError_t launch_gemv(int kind, const CallArgs& a, int wpb, hipStream_t stream, const KernelTimer* tm = nullptr);
-// How K is cut: workgroups of `wpb` wavefronts, each wavefront walking `gpw` groups of 128 input channels,
-// `slices` workgroups (and part sums per column) per 64-column tile.  Requests of 0 leave the choice to the
-// library; inside the one-grid kernel wpb is kWavesPerBlock.
+hipError_t launch_gemv(int kind, const CallArgs& a, int cols, hipStream_t stream, const KernelTimer* tm = nullptr);
+// How the work is cut: a wavefront takes `cols` columns (16, 32 or 64) of 64 / cols groups of 128 input channels at a time,
+// `gpw` times; workgroups with `waves` such wavefronts (at most 16; they have workgroup_waves of them), `slices` workgroups (and part sums per column) per block of
+// `cols` columns.  Requests of 0 leave the choice to the library; others are for 64 columns.  one_grid: inside the
+// one-grid kernel, where cols is kOneGridCols and waves kWavesPerBlock.
 struct GemvPlan {
-    int wpb, gpw, slices;
+    int cols, waves, gpw, slices;
 };
-GemvPlan gemv_plan(long tiles, int G, int gpw_request, int wpb_request);
+inline int workgroup_waves(int waves) { return waves <= 4 ? 4 : waves <= 8 ? 8 : 16; }
+constexpr int kOneGridCols = 64;
+GemvPlan gemv_plan(long tiles, int G, int gpw_request, int waves_request, bool one_grid);
 
 // select.hip -------------------------------------------------------------
 hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, void* xsel_out, hipStream_t stream,
@@ -156,8 +158,8 @@ hipError_t launch_fetch(int rfmt, const CallArgs& a, int select_chunks, hipStrea
                         const KernelTimer* tm = nullptr);
 
 // fused.hip -------------------------------------------------------------
-// Base GEMV and residual kernel in one grid (the fetch workgroups come first).
-hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, hipStream_t stream,
+// Base GEMV and residual kernel in one grid (the fetch workgroups come first).  over_link: residual rows in host memory.
+hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, bool over_link, hipStream_t stream,
                                    const KernelTimer* tm = nullptr);
 
 // accumulate.hip ---------------------------------------------------------

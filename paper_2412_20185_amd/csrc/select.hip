@@ -17,7 +17,9 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const uint16_t* __
                                                              int32_t* __restrict__ idx_out,
                                                              uint16_t* __restrict__ xsel_out) {
     __shared__ SelectShared sh;
-    block_select_topk<THREADS, NCH, RADIX>(x, K, k, sh, idx_out, xsel_out);
+    uint4 ch[NCH];
+    load_keys(x, K, ch);
+    block_select_topk<THREADS, NCH, RADIX>(ch, K, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace

@@ -373,23 +373,25 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
                      (unsigned)k, idx_out, xsel_out);
 }
 
-// All THREADS threads of the workgroup call this.  Requires K a multiple of 8,
-// K <= 8*THREADS*NCH, x 16-byte aligned, 1 <= k <= K.  idx_out / xsel_out may
+// The keys of a thread: chunk j * 64 + lane of its wavefront's run.  Requires K a multiple of 8, K <= 8 * THREADS * NCH and
+// x 16-byte aligned.
+template <int NCH>
+__device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, int K, uint4 (&ch)[NCH]) {
+    const int tid = threadIdx.x, c0 = (tid >> 6) * 64 * NCH + (tid & 63), nchunks = K / 8;
+    const uint4* x128 = reinterpret_cast<const uint4*>(x);
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) ch[j] = c0 + 64 * j < nchunks ? x128[c0 + 64 * j] : make_uint4(0, 0, 0, 0);
+}
+
+// All THREADS threads of the workgroup call this, with their keys (load_keys) and 1 <= k <= K.  idx_out / xsel_out may
 // point to global memory or LDS; xsel_out may be null.  Ends with the outputs
 // written but not yet synchronised (the caller adds the barrier it needs).  RADIX: the caller knows that
 // select_tries_chunks(K / 8, k) is false.
 template <int THREADS, int NCH, bool RADIX = false>
-__device__ __forceinline__ void block_select_topk(const uint16_t* __restrict__ x, int K, int k, SelectShared& sh,
+__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, int k, SelectShared& sh,
                                                   int32_t* idx_out, uint16_t* xsel_out) {
     static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nchunks = K / 8;
-    const int c0 = wave * 64 * NCH + lane;
-    const uint4* x128 = reinterpret_cast<const uint4*>(x);
-
-    uint4 ch[NCH];
-#pragma unroll
-    for (int j = 0; j < NCH; ++j) ch[j] = c0 + 64 * j < nchunks ? x128[c0 + 64 * j] : make_uint4(0, 0, 0, 0);
+    const int tid = threadIdx.x, nchunks = K / 8;
     const auto clear = [&] {
         for (int i = tid; i < 256; i += THREADS) sh.hist1[i] = sh.hist2[i] = 0;
         __syncthreads();

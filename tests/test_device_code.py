@@ -119,3 +119,38 @@ def test_row_requests_of_a_batch_do_not_wait_for_one_another(code_objects):
             assert found, name
             seen.add((name.split("kernel")[0][-12:],) + m.groups())
     assert len(seen) >= 4 * 5 - 1
+
+
+def test_dots_with_a_shared_activation_are_given_their_wait_states(code_objects):
+    """The compiler does not see what is inside an asm statement.  A register that a DPP operand names must not be written by
+    either of the two vector instructions in front of it, and the result of a dot is not read by another kind of instruction
+    for three wait states."""
+    seen = 0
+    for path in code_objects:
+        for name, lines in _disassembly(path):
+            if "row_newbcast" not in "".join(lines):
+                continue
+            seen += 1
+            recent = []                      # registers written by the last vector instructions, one entry per wait state
+            pending = {}                     # results of dots: wait states left
+            for line in lines:
+                op, _, rest = line.partition(" ")
+                regs = re.findall(r"\bv(?:\[(\d+):(\d+)\]|(\d+))", rest)
+                regs = [set(range(int(a), int(b) + 1)) if a else {int(c)} for a, b, c in regs]
+                if op == "s_nop":
+                    states = int(rest, 0) + 1
+                else:
+                    states = 1
+                    if op == "v_dot2c_f32_f16_dpp":
+                        for written in recent[-2:]:
+                            assert not regs[1] & written, (name, line)
+                        assert not (regs[1] | regs[2]) & pending.keys(), (name, line)
+                    elif op.startswith("v_"):
+                        for r in regs:
+                            assert not r & pending.keys(), (name, line)
+                pending = {r: n - states for r, n in pending.items() if n > states}
+                if op == "v_dot2c_f32_f16_dpp":
+                    pending.update({r: 3 for r in regs[0]})
+                recent += [regs[0] if op.startswith("v_") and regs else set()] + [set()] * (states - 1)
+                recent = recent[-2:]
+    assert seen >= 60
