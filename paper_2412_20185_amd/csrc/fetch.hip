@@ -2,6 +2,8 @@
 // in fetch_body.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fetch_body.h"
 
 namespace decdec {
@@ -28,6 +30,13 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     // fill the link, and every column has one part sum fewer to add); measured 0.6 % on the Llama-3-8B layer
     if (row_split <= 0 && !in_hbm && rfmt == 0 && p.segments >= 8 && per_segment > kWavesPerBlock)
         per_segment = kWavesPerBlock;
+    // Rows in device memory: every workgroup more makes the selection once more beside the base GEMV and adds one more part sum
+    // per column, so no more of them than have four rows per wavefront.  us, one grid: 4096 x 14336 (codebook), 60 4-bit rows
+    // 8.3 -> 7.7; 8192 x 8192, 80 fp16 rows 7.4 -> 7.0.  With eight rows or more 4096 x 6144, 60 4-bit rows takes 6.6, not 6.3.
+    if (row_split <= 0 && in_hbm) {
+        constexpr int rows = 4 * kWavesPerBlock;
+        per_segment = std::min(per_segment, (k + rows - 1) / rows * kWavesPerBlock);
+    }
     if (per_segment > kMaxFetchSlices * kWavesPerBlock) per_segment = kMaxFetchSlices * kWavesPerBlock;
     if (per_segment > k) per_segment = k;
     if (per_segment < 1) per_segment = 1;
