@@ -97,6 +97,28 @@ def test_residual_scale_search_at_its_edges(rbits, K, N):
     assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
 
 
+@pytest.mark.parametrize("rbits,K,N", [(4, 383, 64), (4, 384, 64), (4, 2049, 64), (4, 1000, 2048), (2, 3000, 2112), (8, 1500, 2112), (4, 262143, 32), (4, 262144, 32)])
+def test_residual_scale_search_by_bounds(rbits, K, N):
+    """Each width of the column blocks, both sides of the row counts between which most candidates are ruled out beforehand, and
+    columns whose values crowd a few bins of the histogram or leave many candidates equal or nearly so: the oracle's bits."""
+    g = np.random.default_rng([80, rbits, K, N])
+    R32 = (g.uniform(-1, 1, (K, N)) * np.exp2(g.uniform(-12, 0, N))).astype(np.float32)
+    R32[:, 0::8] = g.standard_normal((K, len(range(0, N, 8)))) * 3e-3
+    R32[:, 1::8] = g.laplace(size=(K, len(range(1, N, 8)))) * 1e-3
+    R32[:, 2::8] = np.float32(0.75) * g.integers(-1, 2, (K, len(range(2, N, 8))))   # one magnitude: one bin
+    R32[:, 3::16] = np.where(g.random((K, len(range(3, N, 16)))) < 4 / K, 1.0, 0.0)  # almost all zero
+    R32[:, 4::16] = g.integers(-7, 8, (K, len(range(4, N, 16)))) * np.float32(2.0 ** -9)  # zero error at alpha = 1 with 4 bits
+    R32[:, 5::16] = np.float32(3e-7) * g.standard_normal((K, len(range(5, N, 16))))  # subnormal scales, many of them the same
+    R32[:, 6::16] = np.where(g.random((K, len(range(6, N, 16)))) < 0.01, g.standard_normal((K, len(range(6, N, 16)))), 1e-4)
+    q_ref, S_ref = oracle.quantize_residual_sym(R32.astype(np.float64), rbits)
+    codes = torch.zeros((K, N * rbits // 8), dtype=torch.uint8, pin_memory=True)
+    S = torch.zeros(N, dtype=torch.float16, device="cuda")
+    dd.decdec_quantize_residual(K, N, rbits, torch.from_numpy(R32).cuda(), codes, S)
+    torch.cuda.synchronize()
+    assert np.array_equal(S.cpu().numpy().view(np.uint16), S_ref.view(np.uint16))
+    assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
+
+
 @pytest.mark.parametrize("rbits", [2, 4, 8])
 def test_residual_columns_that_are_not_finite_get_scale_one(rbits):
     """An infinity or a NaN makes a column's error a NaN for every candidate scale; columns of large finite values, whose
