@@ -200,3 +200,30 @@ def test_launch_shape_query_follows_the_workspace_settings():
             ws.gemv_launch_shape(4000, 4096)
     finally:
         ws.close()
+
+
+def test_current_stream_is_torchs_in_every_context():
+    """Without a stream argument a call goes to the stream that torch would use: the default one, that of a stream context, one
+    made elsewhere, and each thread's own."""
+    import threading
+
+    from paper_2412_20185_amd import binding
+
+    def want():
+        return torch.cuda.current_stream().cuda_stream or None
+
+    torch.cuda.init()
+    assert binding._stream(None) == want() and want() is None
+    side = torch.cuda.Stream()
+    seen = []
+    with torch.cuda.stream(side):
+        assert binding._stream(None) == want() == side.cuda_stream
+        with torch.cuda.stream(torch.cuda.ExternalStream(torch.cuda.Stream().cuda_stream)):
+            assert binding._stream(None) == want() != side.cuda_stream
+        t = threading.Thread(target=lambda: seen.append((binding._stream(None), want())))
+        t.start()
+        t.join()
+    assert seen[0][0] == seen[0][1] and binding._stream(None) is None
+    with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=side):
+        assert binding._stream(None) == want() == side.cuda_stream
+        torch.zeros(1, device="cuda")
