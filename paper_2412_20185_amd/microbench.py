@@ -84,17 +84,17 @@ def gemv(args):
 
 
 def gemvshape(args):
-    """Launch shapes of the base GEMV (k = 0): wavefronts per workgroup x groups of 128 input channels per
-    wavefront, with the K-slices added by the accumulate kernel (acc), inside the kernel with one atomic per
-    column and slice (ink) or not at all because one workgroup covers all of K (direct).  Kernel durations from the
-    dispatch timestamps; call = wall time per call over HIP-graph replays of 16 back-to-back calls on
+    """Launch shapes of the base GEMV (k = 0): the library's own plan (waves = gpw = 0), and wavefronts of 64 columns,
+    wavefronts per workgroup x groups of 128 input channels per wavefront, with the K-slices added by the accumulate
+    kernel (acc), inside the kernel with one atomic per column and slice (ink) or not at all because one workgroup covers
+    all of K (direct).  per tile: workgroups per 64 columns.  Kernel durations from the dispatch timestamps; call = wall time per call over HIP-graph replays of 16 back-to-back calls on
     rotating weight copies."""
     import time
     ws = B.Workspace(28672, 28672, 16)
     shapes = [("8B", n, K, N) for n, K, N in SHAPES_8B if n != "k/v"] + [("70B", n, K, N) for n, K, N in SHAPES_70B]
     fmts = {"u3": (3, B.W_UNIFORM_G128), "u4": (4, B.W_UNIFORM_G128), "lut3": (3, B.W_LUT_COL8)}
     stream = torch.cuda.Stream()
-    print(f"{'model':4s} {'shape':8s} {'fmt':5s} {'waves':>5s} {'gpw':>4s} {'slices':>6s} {'sum':>7s} {'gemv us':>8s} "
+    print(f"{'model':4s} {'shape':8s} {'fmt':5s} {'waves':>5s} {'gpw':>4s} {'per tile':>8s} {'sum':>7s} {'gemv us':>8s} "
           f"{'acc us':>7s} {'call us':>8s} {'GB/s(gemv)':>10s} {'GB/s(call)':>10s}")
     for model, name, K, N in shapes:
         G = K // 128
@@ -103,7 +103,7 @@ def gemvshape(args):
             d, Wq, sc, zl, nbytes = _operands(K, N, bits, wfmt)
             x = torch.randn(K, device="cuda").half()
             y = torch.empty(N, dtype=torch.float16, device="cuda")
-            combos = [(0, 0, 0)]
+            combos = [(0, 0, 1)]
             for wpb in (4, 8, 16):
                 for gpw in sorted({1, 2, 4, max(1, G // wpb), max(1, G // (2 * wpb)), max(1, G // (4 * wpb))}):
                     if gpw * wpb <= G or gpw == 1:
@@ -137,11 +137,9 @@ def gemvshape(args):
                 del g
                 us = prof["gemv"][0] * 1e3 / prof["gemv"][1]
                 acc = prof["accumulate"][0] * 1e3 / max(prof["accumulate"][1], 1)
-                eff_wpb = wpb or 4
-                eff_gpw = gpw or max(1, -(-(N // 64) * G // 8192))
-                slices = -(-G // (eff_gpw * eff_wpb))
-                how = "direct" if slices == 1 else ("ink" if ink else "acc")
-                print(f"{model:4s} {name:8s} {tag:5s} {wpb:5d} {gpw:4d} {slices:6d} {how:>7s} {us:8.2f} {acc:7.2f} "
+                per_tile = ws.gemv_launch_shape(K, N)[2]
+                how = "plan" if wpb == 0 else "direct" if per_tile == 1 else "ink" if ink else "acc"
+                print(f"{model:4s} {name:8s} {tag:5s} {wpb:5d} {gpw:4d} {per_tile:8d} {how:>7s} {us:8.2f} {acc:7.2f} "
                       f"{call_us:8.2f} {nbytes / us / 1e3:10.0f} {nbytes / call_us / 1e3:10.0f}", flush=True)
             del Wq
     ws.close()
