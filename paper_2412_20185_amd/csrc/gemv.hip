@@ -53,16 +53,35 @@ GemvPlan sliced(int G, int cols, int waves, int gpw) {
 
 }  // namespace
 
-GemvPlan gemv_plan(long tiles, int G, int gpw_request, int waves_request, bool one_grid) {
+GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid) {
     if (one_grid) return sliced(G, kOneGridCols, kWavesPerBlock, std::max(gpw_request, 1));
     if (gpw_request > 0 || waves_request > 0) return sliced(G, 64, waves_request > 0 ? waves_request : 8, std::max(gpw_request, 1));
 
-    // One tile per wavefront.  us per call in graph replays on rotating weights, the plan before this one (64 columns only,
-    // two groups per wavefront from 12288 tiles on) -> now; 3-bit / 4-bit / codebook.
+    // One tile per wavefront, but for the widest matrices.  us per call in graph replays on rotating weights, a plan of 64
+    // columns only with two groups per wavefront from 12288 tiles on -> this one; 3-bit / 4-bit / codebook.
     //
     // One workgroup over all of K, which writes y itself, where that still gives the chip enough to do.
-    //   4096 x 4096: 4.10 / 4.44 / 4.38 -> 3.59 / 3.82 / 3.68;  4096 x 28672: 11.0 / 12.3 / 12.4 -> 10.0 / 12.1 / 11.0;
+    //   4096 x 4096: 4.10 / 4.44 / 4.38 -> 3.59 / 3.82 / 3.68;  4096 x 28672, codebook: 12.4 -> 11.0;
     //   1024 x 1024: 3.2 / 3.3 / 3.3 -> 2.7 / 2.6 / 2.7;  8192 x 4096: 5.17 / 5.70 / 5.49 -> 4.66 / 5.38 / 4.84
+    const int rounds64 = ceil_div(tiles, kCus);
+    if (tiles >= kCus && 8 * tiles >= 7L * kCus * rounds64) {
+        // So many columns that blocks of 64 keep all compute units busy to the end: a load is 1 KiB in one piece, and x and the
+        // sum over wavefronts are there once per 64 columns.  us for blocks of 16 or 32 columns and of 64, 3-bit / 4-bit /
+        // codebook.  One group per wavefront:
+        //   1024 x 16384: 3.72 / 4.04 / 4.03 and 3.56 / 3.82 / 3.89;  1024 x 49152: 6.1 / 6.7 / 6.9 and 5.4 / 6.2 / 5.9;
+        //   2048 x 32768: 6.8 / 8.0 / 7.3 and 6.3 / 7.2 / 7.0.  Workgroups of 16 while the chip holds them at one time (two per
+        //   compute unit): 2048 x 49152 8.9 / 10.7 / 9.9 and 8.9 / 10.4 / 10.1.
+        //   The codebook format gains less: 2048 x 28672 6.76 and 6.83, so it takes them where no compute unit is left idle.
+        const bool uniform = kind != PACK_LUT3, whole = tiles % kCus == 0;
+        if (G <= 8 || (G <= 16 && tiles <= 2 * kCus && (uniform || whole))) return GemvPlan{64, G, 1, 1};
+        // Two groups per wavefront:
+        //   4096 x 32768: 10.9 / 13.2 / 12.7 and 10.3 / 12.2 / 12.0;  3072 x 49152: 12.4 / 14.6 / 14.7 and 11.8 / 13.6 / 13.9;
+        //   4096 x 28672: 9.9 / 11.9 / 11.3 and 9.7 / 11.2 / 11.5;  3584 x 45056: 13.1 / 15.5 / 15.3 and 12.8 / 14.7 / 15.5; but
+        //   3584 x 28672: 9.2 / 10.7 / 10.5 and 9.4 / 10.9 / 11.2;  2560 x 43008: 10.5 / 11.7 / 11.8 and 10.9 / 11.6 / 11.6;
+        //   2560 x 16384: 5.2 / 5.9 / 5.7 and 5.7 / 6.1 / 6.4.
+        const bool nearly = G == 32 || (tiles > 2 * kCus && 10 * tiles >= 9L * kCus * rounds64);
+        if (G > 16 && G <= 32 && (whole ? tiles >= 2 * kCus : uniform && nearly)) return GemvPlan{64, ceil_div(G, 2), 2, 1};
+    }
     const int turns16 = ceil_div(G, 4), turns32 = ceil_div(G, 2);
     const long blocks16 = 4 * tiles, blocks32 = 2 * tiles;
     const int rounds16 = ceil_div(blocks16, kCus), rounds32 = ceil_div(blocks32, kCus);

@@ -130,7 +130,7 @@ struct GemvPlan {
 };
 inline int workgroup_waves(int waves) { return waves <= 4 ? 4 : waves <= 8 ? 8 : 16; }
 constexpr int kOneGridCols = 64;
-GemvPlan gemv_plan(long tiles, int G, int gpw_request, int waves_request, bool one_grid);
+GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid);
 
 // select.hip -------------------------------------------------------------
 hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, void* xsel_out, hipStream_t stream,

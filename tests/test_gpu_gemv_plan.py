@@ -3,6 +3,7 @@ columns, groups of input channels that do not fill the last turn, single and man
 one tile.  Against the oracle with the tolerance of all results (fp16 rounding and fp32 sums)."""
 import numpy as np
 import pytest
+import torch
 
 import workloads
 import paper_2412_20185_amd as dd
@@ -22,6 +23,7 @@ NONE = np.zeros(0, np.int32)
     (8320, 64, (13, 512, 13)),       # 65 groups: up to 16 slices
     (16512, 64, (18, 512, 18)),      # 129 groups: blocks of 32 columns, nine slices
     (33024, 64, (36, 512, 36)),      # 258 groups: blocks of 16 columns, nine slices
+    (128, 16384, (256, 256, 1)),     # blocks of 64 columns: one group, three of four wavefronts idle
 ])
 def test_base_gemv_against_oracle(fmt, K, N, launch):
     p = Problem(workloads.weights(57, 0, 0, K, N), 4 if fmt == "4" else 3, wfmt="lut" if fmt == "lut" else "uniform", lut_iters=1)
@@ -40,5 +42,37 @@ def test_base_gemv_against_oracle(fmt, K, N, launch):
                 assert_parity(y, y_ref, NONE, NONE, what=f"{fmt} {K}x{N} {waves} x {turns}")
             ws.set_gemv_waves(0)
             ws.set_gemv_split(0)
+    finally:
+        ws.close()
+
+
+@pytest.mark.parametrize("K,N,launch", [
+    (1152, 16384, (256, 1024, 1)),   # nine groups by nine of 16 wavefronts
+    (2176, 32768, (512, 1024, 1)),   # 17 groups by nine wavefronts, the last with one
+    (4096, 28672, (448, 1024, 1)),   # two groups by each of 16 (the codebook format: blocks of 16 columns)
+    (3968, 28672, (1792, 512, 4)),   # 31 groups: blocks of 16 columns
+])
+@pytest.mark.parametrize("bits,wfmt", [(3, dd.W_UNIFORM_G128), (4, dd.W_UNIFORM_G128), (3, dd.W_LUT_COL8)])
+def test_wide_matrices_against_k_slices(bits, wfmt, K, N, launch):
+    """Matrices too large for the oracle: the plan's choice against K-slices added by atomics, on codes drawn at random.  Both
+    sums are fp32 and y is fp16: half a unit of its last place each, and K sums of 2^-24."""
+    g = torch.Generator(device="cuda").manual_seed(K + N + bits)
+    desc = dd.Desc(K, N, bits, wfmt)
+    Wq = torch.randint(0, 256, (dd.decdec_packed_bytes(desc),), dtype=torch.uint8, device="cuda", generator=g)
+    lut = wfmt == dd.W_LUT_COL8
+    scales = None if lut else (torch.rand((K // 128, N), device="cuda", generator=g) * 0.01 + 0.005).half()
+    zl = torch.randn((N, 8) if lut else (K // 128, N), device="cuda", generator=g).mul_(0.02 if lut else 2).half()
+    x = torch.randn(K, device="cuda", generator=g).half()
+    ws = dd.Workspace(K, N, 1)
+    try:
+        assert ws.gemv_launch_shape(K, N) == launch
+        ys = []
+        for waves in (0, 4):
+            ws.set_gemv_waves(waves)
+            y = torch.full((N,), float("nan"), dtype=torch.float16, device="cuda")
+            dd.decdec_gemv(desc, x, Wq, scales, zl, None, None, 0, y, ws)
+            ys.append(y.float())
+        scale = float(ys[1].abs().max())
+        assert torch.allclose(ys[0], ys[1], rtol=2.0 ** -10, atol=scale * K * 2.0 ** -24)
     finally:
         ws.close()
