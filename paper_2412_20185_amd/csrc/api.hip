@@ -688,7 +688,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     bool forked = false;  // TWO_STREAMS: the side stream has been made to wait for `stream` and not yet joined back
     const int rc_enq = [&]() -> int {
         if (k == 0) {
-            DD_HIP(launch_gemv(kind, a, gp.cols, stream, tm[0]));
+            DD_HIP(launch_gemv(kind, a, gp, stream, tm[0]));
             if (pmask) *pmask |= 1;
         } else {
             // The kernels that follow only read a selection that is given; the const is dropped for the shared struct.
@@ -719,7 +719,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
                 DD_HIP(launch_fetch(d0->rfmt, a, select_chunks, comp, tm[2]));
                 if (pmask) *pmask |= 4;
                 if (two_streams) DD_HIP(hipEventRecord(c.ev_join, c.side));
-                DD_HIP(launch_gemv(kind, a, gp.cols, stream, tm[0]));
+                DD_HIP(launch_gemv(kind, a, gp, stream, tm[0]));
                 if (pmask) *pmask |= 1;
                 if (two_streams) {
                     DD_HIP(hipStreamWaitEvent(stream, c.ev_join, 0));

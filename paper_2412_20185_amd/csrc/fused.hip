@@ -37,7 +37,7 @@ void compensated_gemv_kernel(const CallArgs a) {
     if (bid < a.nfetch) {
         fetch_block<RBITS, SELECT_NCH>(a, bid);
     } else {
-        gemv_block<KIND, kOneGridCols, kWavesPerBlock>(a, bid - a.nfetch, kWavesPerBlock);
+        gemv_block<KIND, kOneGridCols, kWavesPerBlock, 1>(a, bid - a.nfetch, kWavesPerBlock);
     }
 }
 

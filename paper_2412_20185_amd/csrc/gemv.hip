@@ -10,29 +10,30 @@ namespace decdec {
 namespace {
 
 // Eight wavefronts a SIMD (kernels.h): a wavefront holds one tile, and the others of its compute unit cover its trip to memory.
-template <int KIND, int COLS, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8))) void gemv_kernel(const CallArgs a) {
+// Four where it holds kDeepTiles.
+template <int KIND, int COLS, int WAVES, int DEPTH>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(DEPTH == 1 ? 8 : 4))) void gemv_kernel(const CallArgs a) {
     touch_args(a);
     asm volatile("" ::"s"(a.tiles), "s"(a.waves));
-    gemv_block<KIND, COLS, WAVES>(a, (int)blockIdx.x, a.waves);
+    gemv_block<KIND, COLS, WAVES, DEPTH>(a, (int)blockIdx.x, a.waves);
 }
 
-template <int KIND, int COLS>
+template <int KIND, int COLS, int DEPTH = 1>
 hipError_t launch_waves(const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
     const dim3 grid((unsigned)(a.tiles * (kTileCols / COLS) * a.gslices)), block(workgroup_waves(a.waves) * 64);
     switch (workgroup_waves(a.waves)) {
-        case 4: return launch_kernel(tm, gemv_kernel<KIND, COLS, 4>, grid, block, 0, stream, a);
-        case 8: return launch_kernel(tm, gemv_kernel<KIND, COLS, 8>, grid, block, 0, stream, a);
-        default: return launch_kernel(tm, gemv_kernel<KIND, COLS, 16>, grid, block, 0, stream, a);
+        case 4: return launch_kernel(tm, gemv_kernel<KIND, COLS, 4, DEPTH>, grid, block, 0, stream, a);
+        case 8: return launch_kernel(tm, gemv_kernel<KIND, COLS, 8, DEPTH>, grid, block, 0, stream, a);
+        default: return launch_kernel(tm, gemv_kernel<KIND, COLS, 16, DEPTH>, grid, block, 0, stream, a);
     }
 }
 
 template <int KIND>
-hipError_t launch_cols(const CallArgs& a, int cols, hipStream_t stream, const KernelTimer* tm) {
-    switch (cols) {
+hipError_t launch_cols(const CallArgs& a, const GemvPlan& plan, hipStream_t stream, const KernelTimer* tm) {
+    switch (plan.cols) {
         case 16: return launch_waves<KIND, 16>(a, stream, tm);
         case 32: return launch_waves<KIND, 32>(a, stream, tm);
-        case 64: return launch_waves<KIND, 64>(a, stream, tm);
+        case 64: return plan.depth > 1 ? launch_waves<KIND, 64, kDeepTiles>(a, stream, tm) : launch_waves<KIND, 64>(a, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }
@@ -41,7 +42,7 @@ hipError_t launch_cols(const CallArgs& a, int cols, hipStream_t stream, const Ke
 
 namespace {
 
-constexpr int kCus = 256;
+constexpr int kCus = 256, kSimds = 4 * kCus;
 int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 // `waves` wavefronts of `cols` columns, `gpw` turns each; as many slices as that takes, at most kMaxGemvSlices.
@@ -51,11 +52,36 @@ GemvPlan sliced(int G, int cols, int waves, int gpw) {
     return GemvPlan{cols, waves, gpw, ceil_div(turns, (long)waves * gpw)};
 }
 
+// What a caller asks for, in wavefronts of 64 columns; 0 is left to the library.
+GemvPlan requested(int kind, long tiles, int G, int gpw, int waves) {
+    // Two turns where they let one workgroup cover all of K, of matrices wide enough for that: 4096 x 28672 by 16 wavefronts
+    // 11.5 -> 9.9 us.
+    if (gpw == 0) gpw = tiles >= kCus && waves < G && G <= 2 * waves ? 2 : 1;
+    // Four wavefronts start sooner where the chip holds all of them at one time (2048 x 2048, one turn: eight take 3.8 us, four
+    // 3.5; 4096 x 4096, codebook, four turns: 7.6 and 5.8), 16 where those cover all of K of a wide matrix (4096 x 28672, two
+    // turns, 4 bit: eight 12.8, 16 11.5; 8192 x 28672, four turns, 3 bit: 18.5 and 17.6), eight otherwise (14336 x 4096, four
+    // turns: eight 7.8, 16 10.4).
+    if (waves == 0) waves = G > 8 && tiles * G <= 4096 ? 4 : tiles >= kCus && G > 8 * gpw && G <= 16 * gpw ? 16 : 8;
+    GemvPlan p = sliced(G, 64, waves, gpw);
+    // Several tiles on their way where the chain of turns is long for the number of wavefronts (those with work) that hide one
+    // another's trips: eight turns per wavefront of a SIMD, three in the codebook format, whose turns take longer.  us with one
+    // tile and with kDeepTiles, 3-bit / 4-bit / codebook:
+    //   28672 x 8192, 4 wavefronts x 56 turns: 48.8 / 48.8 / 55.4 and 31.1 / 31.8 / 37.6;  14336 x 4096, 4 x 28: 25.2 / 25.1 /
+    //   28.7 and 16.5 / 16.6 / 19.8;  4096 x 28672, 8 x 14: 16.9 / 17.2 / 20.6 and 14.6 / 15.5 / 17.3;  8192 x 8192, 8 x 8
+    //   (8 per SIMD): 11.0 / 11.0 / 13.2 and 10.1 / 10.9 / 11.5;  28672 x 8192, 8 x 14 (7 per SIMD): 19.1 / 20.7 / 22.3 and
+    //   18.5 / 22.1 / 20.1.
+    const long working = tiles * ceil_div(G, p.gpw);
+    if (p.gpw > 1 && tiles * p.slices * waves <= 4 * kSimds &&
+        (long)std::min(p.gpw, G) * kSimds >= (kind == PACK_LUT3 ? 3 : 8) * working)
+        p.depth = kDeepTiles;
+    return p;
+}
+
 }  // namespace
 
 GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid) {
     if (one_grid) return sliced(G, kOneGridCols, kWavesPerBlock, std::max(gpw_request, 1));
-    if (gpw_request > 0 || waves_request > 0) return sliced(G, 64, waves_request > 0 ? waves_request : 8, std::max(gpw_request, 1));
+    if (gpw_request > 0 || waves_request > 0) return requested(kind, tiles, G, gpw_request, waves_request);
 
     // One tile per wavefront, but for the widest matrices.  us per call in graph replays on rotating weights, a plan of 64
     // columns only with two groups per wavefront from 12288 tiles on -> this one; 3-bit / 4-bit / codebook.
@@ -111,11 +137,11 @@ GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_reque
     return sliced(G, G <= 16 * kMaxGemvSlices ? 32 : 16, 8, 1);
 }
 
-hipError_t launch_gemv(int kind, const CallArgs& a, int cols, hipStream_t stream, const KernelTimer* tm) {
+hipError_t launch_gemv(int kind, const CallArgs& a, const GemvPlan& plan, hipStream_t stream, const KernelTimer* tm) {
     switch (kind) {
-        case PACK_U4: return launch_cols<PACK_U4>(a, cols, stream, tm);
-        case PACK_U3: return launch_cols<PACK_U3>(a, cols, stream, tm);
-        case PACK_LUT3: return launch_cols<PACK_LUT3>(a, cols, stream, tm);
+        case PACK_U4: return launch_cols<PACK_U4>(a, plan, stream, tm);
+        case PACK_U3: return launch_cols<PACK_U3>(a, plan, stream, tm);
+        case PACK_LUT3: return launch_cols<PACK_LUT3>(a, plan, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }

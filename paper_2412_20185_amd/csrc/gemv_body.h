@@ -27,7 +27,8 @@
 //     group's sum of x formed once per row by a DPP reduction;
 //   * a wavefront asks for one tile and works it off; what hides the trip to
 //     memory is the other wavefronts of the compute unit (gemv_plan says how
-//     many workgroups of how many wavefronts);
+//     many workgroups of how many wavefronts).  Only where a caller asks for
+//     long chains of few wavefronts are several tiles on their way;
 //   * a workgroup adds the sums of its wavefronts through LDS and either writes
 //     y itself (it covers all of K and there is no residual term) or adds them
 //     into the per-column accumulators with one atomic per column (finalize.h).
@@ -270,11 +271,12 @@ __device__ __forceinline__ float tile_dot(TileRegs<KIND>& r, const LutTables& T)
 }
 
 // Work of workgroup `bid`: COLS columns of one tile of one of the matrices, K-slice ks of a.gslices.  The first
-// `waves` of its WAVES wavefronts take 64 / COLS groups at a time, one per COLS lanes, a.gpw times each.
+// `waves` of its WAVES wavefronts take 64 / COLS groups at a time, one per COLS lanes, a.gpw times each, with the tiles of
+// DEPTH turns on their way.
 //
 // Adjacent blocks of fewer than 64 columns share the 128-byte lines of the scales and zero points (and lie in one tile):
 // they go to one XCD, whose L2 then reads a line once (workgroups go to the eight XCDs in turn).
-template <int KIND, int COLS, int WAVES>
+template <int KIND, int COLS, int WAVES, int DEPTH>
 __device__ __forceinline__ void gemv_block(const CallArgs& a, int bid, int waves) {
     constexpr int P = words_per_lane(KIND) / 4;  // 16-byte pieces per lane per tile
     constexpr int kTileStride = P * kTileCols;   // uint4 per tile
@@ -318,19 +320,62 @@ __device__ __forceinline__ void gemv_block(const CallArgs& a, int bid, int waves
     const uint4* column = mat.Wq + (size_t)nt * G * kTileStride + tcol;
     const int g_first = (ks * waves + wave) * gpw * GPI;  // wave-uniform
     const int g_end = wave < waves ? min(g_first + gpw * GPI, G) : 0;
+    const auto load = [&](TileRegs<KIND>& r, int g) {
+        load_tile<KIND>(r, column + (size_t)g * kTileStride, scales, zeros_or_lut, x128, g, N, n, lane);
+    };
+    const auto load_codebook = [&] {
+        uint4 c{};
+        if constexpr (KIND == PACK_LUT3) c = reinterpret_cast<const uint4*>(zeros_or_lut)[n];
+        return c;
+    };
     // One turn, from the loads on.  Lanes beyond the last group read it once more and add nothing.
     const auto turn = [&](int g0) {
         const int mine = g0 + (GPI > 1 ? lane / COLS : 0), g = GPI > 1 ? min(mine, G - 1) : mine;
-        uint4 codebook{};
-        if constexpr (KIND == PACK_LUT3) codebook = reinterpret_cast<const uint4*>(zeros_or_lut)[n];
+        const uint4 codebook = load_codebook();
         TileRegs<KIND> r;
-        load_tile<KIND>(r, column + (size_t)g * kTileStride, scales, zeros_or_lut, x128, g, N, n, lane);
+        load(r, g);
         const float v = tile_dot<KIND>(r, make_lut_tables(codebook));
         total += GPI == 1 || mine < G ? v : 0.f;
     };
-    // The usual single turn as straight code: in a loop the compiler waits for all of a tile before it starts on the first
-    // word (4096 x 28672: 11.5 instead of 10.2 us).
-    if (gpw == 1) {
+    if constexpr (DEPTH > 1) {
+        // Long chains of few wavefronts (gemv.hip): DEPTH tiles on their way.  The loop asks for one wherever it has used
+        // one, without conditions: where it depends on the path how many requests are on their way, the compiler waits for all.
+        TileRegs<KIND> r[DEPTH];
+        int g = g_first;
+        if (g + DEPTH <= g_end) {
+            const uint4 codebook = load_codebook();
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) load(r[i], g + i);
+            const LutTables T = make_lut_tables(codebook);
+            for (; g + 2 * DEPTH <= g_end; g += DEPTH) {
+#pragma unroll
+                for (int i = 0; i < DEPTH; ++i) {
+                    total += tile_dot<KIND>(r[i], T);
+                    load(r[i], g + i + DEPTH);
+                }
+            }
+            const int left = g_end - g - DEPTH;  // fewer than DEPTH, besides those on their way
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                total += tile_dot<KIND>(r[i], T);
+                if (i < left) load(r[i], g + i + DEPTH);
+            }
+#pragma unroll
+            for (int i = 0; i < DEPTH - 1; ++i)
+                if (i < left) total += tile_dot<KIND>(r[i], T);
+        } else if (g < g_end) {
+            const uint4 codebook = load_codebook();
+#pragma unroll
+            for (int i = 0; i < DEPTH - 1; ++i)
+                if (g + i < g_end) load(r[i], g + i);
+            const LutTables T = make_lut_tables(codebook);
+#pragma unroll
+            for (int i = 0; i < DEPTH - 1; ++i)
+                if (g + i < g_end) total += tile_dot<KIND>(r[i], T);
+        }
+    } else if (gpw == 1) {
+        // The usual single turn as straight code: in a loop the compiler waits for all of a tile before it starts on the first
+        // word (4096 x 28672: 11.5 instead of 10.2 us).
         if (g_first < g_end) turn(g_first);
     } else {
         int g0 = g_first;

@@ -120,17 +120,19 @@ __device__ __forceinline__ void hold_scalar(T*& p) {
 }
 
 // gemv.hip ---------------------------------------------------------------
-hipError_t launch_gemv(int kind, const CallArgs& a, int cols, hipStream_t stream, const KernelTimer* tm = nullptr);
 // How the work is cut: a wavefront takes `cols` columns (16, 32 or 64) of 64 / cols groups of 128 input channels at a time,
-// `gpw` times; workgroups with `waves` such wavefronts (at most 16; they have workgroup_waves of them), `slices` workgroups (and part sums per column) per block of
-// `cols` columns.  Requests of 0 leave the choice to the library; others are for 64 columns.  one_grid: inside the
-// one-grid kernel, where cols is kOneGridCols and waves kWavesPerBlock.
+// `gpw` times, the tiles of `depth` turns on their way at one time (1 or kDeepTiles; more than 1 with 64 columns only);
+// workgroups with `waves` such wavefronts (at most 16; they have workgroup_waves of them), `slices` workgroups (and part sums
+// per column) per block of `cols` columns.  Requests of 0 leave the choice to the library; others are for 64 columns.
+// one_grid: inside the one-grid kernel, where cols is kOneGridCols, waves kWavesPerBlock and depth 1.
+constexpr int kDeepTiles = 4;
 struct GemvPlan {
-    int cols, waves, gpw, slices;
+    int cols, waves, gpw, slices, depth = 1;
 };
 inline int workgroup_waves(int waves) { return waves <= 4 ? 4 : waves <= 8 ? 8 : 16; }
 constexpr int kOneGridCols = 64;
 GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid);
+hipError_t launch_gemv(int kind, const CallArgs& a, const GemvPlan& plan, hipStream_t stream, const KernelTimer* tm = nullptr);
 
 // select.hip -------------------------------------------------------------
 hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, void* xsel_out, hipStream_t stream,

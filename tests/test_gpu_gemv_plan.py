@@ -46,6 +46,25 @@ def test_base_gemv_against_oracle(fmt, K, N, launch):
         ws.close()
 
 
+@pytest.mark.parametrize("fmt", ["3", "4", "lut"])
+def test_requested_chains_of_turns(fmt):
+    """Few wavefronts with many turns keep several tiles on their way: chains of fewer turns than that, one more, multiples
+    and remainders of it, and a last wavefront whose chain is shorter than the others' or empty (37 groups)."""
+    K, N = 37 * 128, 128
+    p = Problem(workloads.weights(58, 0, 0, K, N), 4 if fmt == "4" else 3, wfmt="lut" if fmt == "lut" else "uniform", lut_iters=1)
+    x = workloads.x_gauss_outliers(58, 0, 0, 0, K)
+    y_ref, _ = p.reference(x, 0)
+    ws = dd.Workspace(K, N, 1)
+    try:
+        for waves, turns in [(w, t) for w in (4, 8, 16) for t in (2, 3, 4, 5, 7, 8, 9, 12, 40)] + [(0, 3), (0, 10), (16, 0)]:
+            ws.set_gemv_waves(waves)
+            ws.set_gemv_split(turns)
+            y, _, _ = p.run(x, 0, ws)
+            assert_parity(y, y_ref, NONE, NONE, what=f"{fmt} {waves} x {turns}")
+    finally:
+        ws.close()
+
+
 @pytest.mark.parametrize("K,N,launch", [
     (1152, 16384, (256, 1024, 1)),   # nine groups by nine of 16 wavefronts
     (2176, 32768, (512, 1024, 1)),   # 17 groups by nine wavefronts, the last with one
