@@ -119,6 +119,19 @@ __device__ __forceinline__ void accumulate_piece(const typename RowPiece<BITS>::
     }
 }
 
+template <int BITS>
+constexpr int kLaneCols = BITS == 2 ? 16 : 8;                                  // columns per lane
+template <int BITS>
+constexpr int kLoadRows = 64 / (kFetchSegmentCols / kLaneCols<BITS>);  // rows a wavefront loads with one instruction
+
+// The selection and the sum over the wavefronts follow one another and share their LDS.
+template <int BITS>
+union FetchLds {
+    float red[kWavesPerBlock * kLoadRows<BITS>][kFetchSegmentCols];
+    SelectShared sh;
+    __device__ FetchLds() {}
+};
+
 // One workgroup = one column segment of 512 columns x the rows of row slice rs.  A lane reads 8 columns of a
 // row (16, 8 or 4 bytes for fp16, 8-bit and 4-bit rows: a wavefront 1 KiB down to 256 bytes of contiguous
 // row) or 16 columns of a 2-bit row (4 bytes; the two halves of a wavefront then take different rows).
@@ -135,17 +148,11 @@ __device__ __forceinline__ void accumulate_piece(const typename RowPiece<BITS>::
 template <int BITS, int SELECT_NCH>
 __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     typedef typename RowPiece<BITS>::type piece_t;
-    constexpr int CPL = BITS == 2 ? 16 : 8;             // columns per lane
+    constexpr int CPL = kLaneCols<BITS>, SUB = kLoadRows<BITS>;
     constexpr int LPR = kFetchSegmentCols / CPL;        // lanes that cover the segment's part of one row
-    constexpr int SUB = 64 / LPR;                       // rows a wavefront loads with one instruction
     constexpr int UNROLL = (4096 / 64) / (int)sizeof(piece_t);  // loads in flight per lane: 4 KiB per wavefront
     static_assert(kBlockThreads == kFetchSegmentCols, "one thread per column of the segment");
-    // the selection and the sum over the wavefronts follow one another and share their LDS
-    __shared__ union Lds {
-        float red[kWavesPerBlock * SUB][kFetchSegmentCols];
-        SelectShared sh;
-        __device__ Lds() {}
-    } lds;
+    __shared__ FetchLds<BITS> lds;
     auto& red = lds.red;
 
     const int tid = threadIdx.x;

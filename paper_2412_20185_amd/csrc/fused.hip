@@ -41,18 +41,10 @@ void compensated_gemv_kernel(const CallArgs a) {
     }
 }
 
-// With rows behind the link the call lasts as long as selection and rows, and the base GEMV of the same compute unit slows
-// the selection down: three workgroups a compute unit instead of four, by the LDS they ask for (its 160 KB less than four
-// times as much; the kernels have 22 KB without asking).  us: 8192 x 8192 (codebook), 20 fp16 rows 13.0 -> 12.35;
-// 14336 x 4096, 56 8-bit rows 11.42 -> 11.31.  No difference up to 4096 channels, where the selection is short; with rows in
-// GPU memory, where the base GEMV is what lasts, 7.3 -> 7.8 (14336 x 4096, 286 fp16 rows).
-constexpr unsigned kLdsOfThree = 42 * 1024, kStaticLds = 22 * 1024;
-
 template <int KIND, int RBITS>
 hipError_t launch_nch(const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
     const dim3 grid((unsigned)(a.nfetch + a.tiles * (kTileCols / kOneGridCols) * a.gslices)), block(kBlockThreads);
-    unsigned lds = selection_lds_bytes(nch, a.k);
-    if (over_link && nch > 1) lds = std::max(lds, kLdsOfThree - kStaticLds);
+    const unsigned lds = one_grid_lds(KIND, RBITS, nch, a.k, (long)a.tiles * a.gslices, over_link);
     switch (nch) {
         case 0: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0>, grid, block, lds, stream, a);
         case 1: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1>, grid, block, lds, stream, a);
@@ -75,6 +67,31 @@ hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, bool over_link, hip
 }
 
 }  // namespace
+
+// Dynamic LDS: the selection, and where three workgroups on a compute unit are better than four, what keeps a fourth out.
+//
+// With rows behind the link and more than 4096 channels a small call lasts as long as its selection and its rows, and the base
+// GEMV of the same compute unit slows the selection down.  That pays while the base GEMV is about one round of workgroups:
+// four per compute unit, two more in 3 bits, whose tiles are worked off faster, one more beside fp16 rows, which take longer
+// on the link (not in the codebook format).  Where it lasts longer, a fourth of the wavefronts that keep the memory busy is
+// missing.  us with four and with three, 3-bit / 4-bit / codebook:
+//   14336 x 4096 (896 workgroups), 28 4-bit rows 8.7 / 9.2 / 8.8 and 8.5 / 8.8 / 8.5;  8192 x 8192 (1024), 8 fp16 rows 8.9 / 9.1
+//   / 9.9 and 8.9 / 9.0 / 9.2;  8192 x 10240 (1280), 8 fp16 rows 9.9 / 10.5 / 10.9 and 9.5 / 10.1 / 11.2, 16 4-bit rows 9.3 /
+//   10.1 / 10.1 and 9.1 / 10.4 / 10.6;  14336 x 8192 (1792), 14 fp16 rows 12.3 / 12.4 / 13.3 and 11.6 / 12.6 / 13.6, 28 4-bit
+//   rows 11.1 / 12.0 / 12.9 and 11.2 / 12.6 / 13.4;  8192 x 57344, 8 fp16 rows 43.6 / 47.5 / 50.4 and 46.7 / 51.8 / 53.7.
+// Up to 4096 channels, where the selection is short, no difference; with rows in GPU memory, where the base GEMV is what lasts,
+// 7.3 and 7.8 (14336 x 4096, 286 fp16 rows).
+// Kernels with 2-bit rows or eight chunks of keys per thread have registers for three workgroups only.
+unsigned one_grid_lds(int kind, int rbits, int nch, int k, long base_workgroups, bool over_link) {
+    constexpr unsigned kCuLds = 160 * 1024, kLdsOfThree = 42 * 1024;
+    static_assert(3 * kLdsOfThree <= kCuLds && 4 * kLdsOfThree > kCuLds, "three workgroups");
+    constexpr unsigned kStatic = sizeof(FetchLds<16>) + sizeof(float) * kWavesPerBlock * kOneGridCols;
+    static_assert(sizeof(FetchLds<16>) == sizeof(FetchLds<8>) && sizeof(FetchLds<16>) == sizeof(FetchLds<4>), "one size");
+    const unsigned lds = selection_lds_bytes(nch, k);
+    const int rounds = 4 + (kind == PACK_U3 ? 2 : 0) + (rbits == 16 && kind != PACK_LUT3 ? 1 : 0);
+    const bool three = over_link && (nch == 2 || nch == 4) && rbits != 2 && base_workgroups <= rounds * kCus;
+    return three ? std::max(lds, kLdsOfThree - kStatic) : lds;
+}
 
 hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, bool over_link, hipStream_t stream,
                                    const KernelTimer* tm) {

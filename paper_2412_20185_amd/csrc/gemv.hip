@@ -42,7 +42,7 @@ hipError_t launch_cols(const CallArgs& a, const GemvPlan& plan, hipStream_t stre
 
 namespace {
 
-constexpr int kCus = 256, kSimds = 4 * kCus;
+constexpr int kSimds = 4 * kCus;
 int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 // `waves` wavefronts of `cols` columns, `gpw` turns each; as many slices as that takes, at most kMaxGemvSlices.

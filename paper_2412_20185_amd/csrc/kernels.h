@@ -17,6 +17,7 @@ constexpr int kWavesPerBlock = kBlockThreads / 64;
 // eight up to 100 scalar registers, but the chip takes some for itself: of 512 workgroups of 1024 threads all start at once
 // at 80 registers, and 256 have to wait at 82.
 
+constexpr int kCus = 256;               // compute units of the card
 constexpr int kFetchSegmentCols = 512;  // output columns of one column segment = threads of a fetch workgroup
 constexpr int kMaxGemvSlices = 16;   // part sums per column the base GEMV may contribute (K-slices)
 constexpr int kMaxFetchSlices = 16;  // part sums per column the residual kernel may contribute (row slices)
@@ -163,6 +164,9 @@ hipError_t launch_fetch(int rfmt, const CallArgs& a, int select_chunks, hipStrea
 // Base GEMV and residual kernel in one grid (the fetch workgroups come first).  over_link: residual rows in host memory.
 hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, bool over_link, hipStream_t stream,
                                    const KernelTimer* tm = nullptr);
+
+// Bytes of dynamic LDS per workgroup of it.
+unsigned one_grid_lds(int kind, int rbits, int nch, int k, long base_workgroups, bool over_link);
 
 // accumulate.hip ---------------------------------------------------------
 // y_m[n] = fp16( sum_s gpart[s][col0[m]+n] + sum_r cpart[r][col0[m]+n] ), the terms added in the fixed point of finalize.h

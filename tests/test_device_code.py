@@ -1,5 +1,6 @@
 """What the compiler made of the kernels, read from the built library: properties that its resource report or a reader of
 the source does not show, and that have cost time without changing a result."""
+import ctypes as C
 import os
 import re
 import shutil
@@ -8,6 +9,7 @@ import subprocess
 
 import pytest
 
+import paper_2412_20185_amd as dd
 from paper_2412_20185_amd import build
 
 LLVM = "/opt/rocm/llvm/bin"
@@ -154,3 +156,33 @@ def test_dots_with_a_shared_activation_are_given_their_wait_states(code_objects)
                 recent += [regs[0] if op.startswith("v_") and regs else set()] + [set()] * (states - 1)
                 recent = recent[-2:]
     assert seen >= 60
+
+
+def test_workgroups_of_the_one_grid_kernel_per_compute_unit(code_objects):
+    """Three workgroups or more fit a compute unit by their LDS, whatever the kernel's own part of it is; exactly three where a
+    small base GEMV runs beside a selection over more than 4096 channels and rows behind the link, and never fewer than the
+    registers allow with a wide one."""
+    lds_of = dd.lib()["_ZN6decdec12one_grid_ldsEiiiilb"]
+    lds_of.argtypes = [C.c_int] * 4 + [C.c_long, C.c_bool]
+    lds_of.restype = C.c_uint
+    cu, wavefronts = 160 * 1024, 8
+    seen = 0
+    for path in code_objects:
+        notes = subprocess.run([_tool("llvm-readelf"), "--notes", path], capture_output=True, text=True, check=True).stdout
+        for entry in notes.split("  - .agpr_count")[1:]:
+            m = re.search(r"compensated_gemv_kernelILi(\d+)ELi(\d+)ELi(\d+)E", re.search(r"\.name: +(\S+)", entry).group(1))
+            if not m:
+                continue
+            seen += 1
+            kind, bits, nch = map(int, m.groups())
+            own = int(re.search(r"\.group_segment_fixed_size: +(\d+)", entry).group(1))
+            vgprs = int(re.search(r"\.vgpr_count: +(\d+)", entry).group(1))
+            by_registers = 4 * min(8, 512 // (-(-vgprs // 8) * 8)) // wavefronts
+            fit = lambda *a: cu // (own + lds_of(kind, bits, nch, *a))  # noqa: E731
+            for k in (1, 64):
+                small, wide, near = fit(k, 900, True), fit(k, 1 << 14, True), fit(k, 900, False)
+                assert min(small, by_registers) == (3 if nch >= 2 or bits == 2 else 4), m.groups()
+                assert min(wide, near) >= by_registers, m.groups()
+            if nch:
+                assert fit(4096, 900, True) >= 2
+    assert seen == 3 * 4 * 5
