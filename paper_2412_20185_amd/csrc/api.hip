@@ -385,7 +385,7 @@ int decdec_ws_gemv_launch_shape(const decdec_ws* ws, int32_t K, int32_t N_total,
                                 int32_t* threads, int32_t* per_tile) {
     if (ws == nullptr || K <= 0 || K % kGroup != 0 || N_total <= 0 || N_total % kTileCols != 0) return DECDEC_EINVAL;
     const long tiles = N_total / kTileCols;
-    const GemvPlan gp = gemv_plan(PACK_U3, tiles, K / kGroup, ws->core.gemv_gpw, ws->core.gemv_wpb, false);
+    const GemvPlan gp = gemv_plan(PACK_U3, tiles, K / kGroup, ws->core.gemv_gpw, ws->core.gemv_wpb, false, false);
     const int32_t each = kTileCols / gp.cols * gp.slices;
     if (workgroups) *workgroups = (int32_t)tiles * each;
     if (threads) *threads = workgroup_waves(gp.waves) * 64;
@@ -638,7 +638,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     long tiles = 0;
     for (int m = 0; m < count; ++m) tiles += sh.N[m] / kTileCols;
     const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED;
-    const GemvPlan gp = gemv_plan(kind, tiles, sh.K / kGroup, c.gemv_gpw, c.gemv_wpb, fused);
+    const GemvPlan gp = gemv_plan(kind, tiles, sh.K / kGroup, c.gemv_gpw, c.gemv_wpb, fused, !residuals_in_hbm);
     const int gslices = gp.slices;
     FetchPlan plan{0, 0, 0};
     if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm);

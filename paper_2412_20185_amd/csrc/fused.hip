@@ -29,7 +29,10 @@ namespace {
 // wavefront: with blocks of 16 columns Llama-3-8B layers with rows in GPU memory take 141 us a step instead of 134.  Six
 // where the vector registers allow no more: eight chunks of keys per thread, or 2-bit rows (16 column sums and 16 row pieces
 // a lane), need up to 80.
-template <int KIND, int RBITS, int SELECT_NCH>
+//
+// DEPTH 2: the base GEMV takes more than one turn per wavefront, two at a time (28672 x 8192 in 4 bits, one at a time 23.4 us,
+// two 21.6).  A kernel of its own, because one that does either takes up to 4 % longer where there is one turn.
+template <int KIND, int RBITS, int SELECT_NCH, int DEPTH>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(SELECT_NCH == 8 || RBITS == 2 ? 6 : 8)))
 void compensated_gemv_kernel(const CallArgs a) {
     touch_args(a);
@@ -37,31 +40,38 @@ void compensated_gemv_kernel(const CallArgs a) {
     if (bid < a.nfetch) {
         fetch_block<RBITS, SELECT_NCH>(a, bid);
     } else {
-        gemv_block<KIND, kOneGridCols, kWavesPerBlock, 1>(a, bid - a.nfetch, kWavesPerBlock);
+        gemv_block<KIND, kOneGridCols, kWavesPerBlock, DEPTH>(a, bid - a.nfetch, kWavesPerBlock);
     }
 }
 
-template <int KIND, int RBITS>
+template <int KIND, int RBITS, int DEPTH>
 hipError_t launch_nch(const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
     const dim3 grid((unsigned)(a.nfetch + a.tiles * (kTileCols / kOneGridCols) * a.gslices)), block(kBlockThreads);
     const unsigned lds = one_grid_lds(KIND, RBITS, nch, a.k, (long)a.tiles * a.gslices, over_link);
     switch (nch) {
-        case 0: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0>, grid, block, lds, stream, a);
-        case 1: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1>, grid, block, lds, stream, a);
-        case 2: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 2>, grid, block, lds, stream, a);
-        case 4: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 4>, grid, block, lds, stream, a);
-        case 8: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 8>, grid, block, lds, stream, a);
-        default: return hipErrorInvalidValue;
+        case 0: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0, DEPTH>, grid, block, lds, stream, a);
+        case 1: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1, DEPTH>, grid, block, lds, stream, a);
+        case 2: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 2, DEPTH>, grid, block, lds, stream, a);
+        case 4: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 4, DEPTH>, grid, block, lds, stream, a);
+        default: break;
     }
+    // eight chunks: more than 128 groups, which 16 K-slices of eight wavefronts do not cover in one turn
+    if (nch != 8 || DEPTH != 2) return hipErrorInvalidValue;
+    return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 8, 2>, grid, block, lds, stream, a);
+}
+
+template <int KIND, int RBITS>
+hipError_t launch_turns(const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
+    return a.gpw > 1 ? launch_nch<KIND, RBITS, 2>(a, nch, over_link, stream, tm) : launch_nch<KIND, RBITS, 0>(a, nch, over_link, stream, tm);
 }
 
 template <int KIND>
 hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
     switch (rfmt) {
-        case 0: return launch_nch<KIND, 16>(a, nch, over_link, stream, tm);
-        case 1: return launch_nch<KIND, 4>(a, nch, over_link, stream, tm);
-        case 2: return launch_nch<KIND, 2>(a, nch, over_link, stream, tm);
-        case 3: return launch_nch<KIND, 8>(a, nch, over_link, stream, tm);
+        case 0: return launch_turns<KIND, 16>(a, nch, over_link, stream, tm);
+        case 1: return launch_turns<KIND, 4>(a, nch, over_link, stream, tm);
+        case 2: return launch_turns<KIND, 2>(a, nch, over_link, stream, tm);
+        case 3: return launch_turns<KIND, 8>(a, nch, over_link, stream, tm);
         default: return hipErrorInvalidValue;
     }
 }

@@ -79,8 +79,17 @@ GemvPlan requested(int kind, long tiles, int G, int gpw, int waves) {
 
 }  // namespace
 
-GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid) {
-    if (one_grid) return sliced(G, kOneGridCols, kWavesPerBlock, std::max(gpw_request, 1));
+GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid, bool over_link) {
+    if (one_grid) {
+        // A K-slice fewer is an atomic per column fewer, and in the codebook format the codebook once less; a turn more lets a
+        // workgroup last longer, which is what fills the chip less evenly.  Two turns from three rounds of wavefronts at eight a
+        // SIMD on; in 3 bits only with rows behind the link, in 4 bits not.  us with one turn and with two, 3-bit / 4-bit /
+        // codebook:  8192 x 57344, 8 fp16 rows 43.0 / 47.8 / 49.6 and 39.8 / 49.1 / 44.0;  14336 x 14336, 14 fp16 rows 17.3 /
+        // 19.8 / 20.1 and 16.7 / 20.1 / 19.5;  8192 x 20480, 16 4-bit rows 13.7 / 15.9 / 16.8 and 14.4 / 16.6 / 17.6;
+        // 4096 x 57344, 80 fp16 rows in GPU memory 19.2 / 23.4 / 21.9 and 20.1 / 24.0 / 21.2.
+        const bool two = tiles * G >= 3 * 8 * kSimds && (kind == PACK_LUT3 || (kind == PACK_U3 && over_link));
+        return sliced(G, kOneGridCols, kWavesPerBlock, gpw_request > 0 ? gpw_request : two ? 2 : 1);
+    }
     if (gpw_request > 0 || waves_request > 0) return requested(kind, tiles, G, gpw_request, waves_request);
 
     // One tile per wavefront, but for the widest matrices.  us per call in graph replays on rotating weights, a plan of 64

@@ -272,7 +272,7 @@ __device__ __forceinline__ float tile_dot(TileRegs<KIND>& r, const LutTables& T)
 
 // Work of workgroup `bid`: COLS columns of one tile of one of the matrices, K-slice ks of a.gslices.  The first
 // `waves` of its WAVES wavefronts take 64 / COLS groups at a time, one per COLS lanes, a.gpw times each, with the tiles of
-// DEPTH turns on their way.
+// DEPTH turns on their way (0: a.gpw is 1).
 //
 // Adjacent blocks of fewer than 64 columns share the 128-byte lines of the scales and zero points (and lie in one tile):
 // they go to one XCD, whose L2 then reads a line once (workgroups go to the eight XCDs in turn).
@@ -337,7 +337,7 @@ __device__ __forceinline__ void gemv_block(const CallArgs& a, int bid, int waves
         const float v = tile_dot<KIND>(r, make_lut_tables(codebook));
         total += GPI == 1 || mine < G ? v : 0.f;
     };
-    if constexpr (DEPTH > 1) {
+    if constexpr (DEPTH > 2) {
         // Long chains of few wavefronts (gemv.hip): DEPTH tiles on their way.  The loop asks for one wherever it has used
         // one, without conditions: where it depends on the path how many requests are on their way, the compiler waits for all.
         TileRegs<KIND> r[DEPTH];
@@ -373,7 +373,20 @@ __device__ __forceinline__ void gemv_block(const CallArgs& a, int bid, int waves
             for (int i = 0; i < DEPTH - 1; ++i)
                 if (g + i < g_end) total += tile_dot<KIND>(r[i], T);
         }
-    } else if (gpw == 1) {
+    } else if constexpr (DEPTH == 2) {
+        // Both tiles of two turns asked for before the first is worked off.
+        int g = g_first;
+        for (; g + 1 < g_end; g += 2) {
+            const uint4 codebook = load_codebook();
+            TileRegs<KIND> r0, r1;
+            load(r0, g);
+            load(r1, g + 1);
+            const LutTables T = make_lut_tables(codebook);
+            total += tile_dot<KIND>(r0, T);
+            total += tile_dot<KIND>(r1, T);
+        }
+        if (g < g_end) turn(g);
+    } else if (DEPTH == 0 || gpw == 1) {
         // The usual single turn as straight code: in a loop the compiler waits for all of a tile before it starts on the first
         // word (4096 x 28672: 11.5 instead of 10.2 us).
         if (g_first < g_end) turn(g_first);

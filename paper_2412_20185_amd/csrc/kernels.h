@@ -125,14 +125,15 @@ __device__ __forceinline__ void hold_scalar(T*& p) {
 // `gpw` times, the tiles of `depth` turns on their way at one time (1 or kDeepTiles; more than 1 with 64 columns only);
 // workgroups with `waves` such wavefronts (at most 16; they have workgroup_waves of them), `slices` workgroups (and part sums
 // per column) per block of `cols` columns.  Requests of 0 leave the choice to the library; others are for 64 columns.
-// one_grid: inside the one-grid kernel, where cols is kOneGridCols, waves kWavesPerBlock and depth 1.
+// one_grid: inside the one-grid kernel, where cols is kOneGridCols, waves kWavesPerBlock and depth 1 (several
+// turns are worked off two at a time); over_link: with residual rows in host memory.
 constexpr int kDeepTiles = 4;
 struct GemvPlan {
     int cols, waves, gpw, slices, depth = 1;
 };
 inline int workgroup_waves(int waves) { return waves <= 4 ? 4 : waves <= 8 ? 8 : 16; }
 constexpr int kOneGridCols = 64;
-GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid);
+GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid, bool over_link);
 hipError_t launch_gemv(int kind, const CallArgs& a, const GemvPlan& plan, hipStream_t stream, const KernelTimer* tm = nullptr);
 
 // select.hip -------------------------------------------------------------

@@ -65,6 +65,77 @@ def test_requested_chains_of_turns(fmt):
         ws.close()
 
 
+@pytest.mark.parametrize("fmt", ["3", "4", "lut"])
+def test_turns_of_the_one_grid_kernel(fmt):
+    """Two turns at a time: even and odd chains, and last wavefronts whose chain is cut off."""
+    K, N, k = 37 * 128, 128, 40
+    p = Problem(workloads.weights(59, 0, 0, K, N), 4 if fmt == "4" else 3, wfmt="lut" if fmt == "lut" else "uniform", lut_iters=1)
+    x = workloads.x_gauss_outliers(59, 0, 0, 0, K)
+    y_ref, sc = p.reference(x, k)
+    ws = dd.Workspace(K, N, k)
+    try:
+        for turns in (0, 2, 3, 4, 5, 40):
+            ws.set_gemv_split(turns)
+            y, idx, _ = p.run(x, k, ws)
+            assert_parity(y, y_ref, idx, sc, what=f"{fmt} {turns}")
+    finally:
+        ws.close()
+
+
+def random_layer(K, N, bits, wfmt):
+    """A matrix too large for the oracle, of codes drawn at random, and what it stands for: the fp32 residual of a zero matrix
+    is the negative of its weights, decoded by a kernel that shares nothing with the base GEMV."""
+    g = torch.Generator(device="cuda").manual_seed(K + N + bits)
+    desc = dd.Desc(K, N, bits, wfmt, dd.R_INT4_SYM_COL)
+    Wq = torch.randint(0, 256, (dd.decdec_packed_bytes(desc),), dtype=torch.uint8, device="cuda", generator=g)
+    lut = wfmt == dd.W_LUT_COL8
+    scales = None if lut else (torch.rand((K // 128, N), device="cuda", generator=g) * 0.01 + 0.005).half()
+    zl = torch.randn((N, 8) if lut else (K // 128, N), device="cuda", generator=g).mul_(0.02 if lut else 2).half()
+    x = torch.randn(K, device="cuda", generator=g).half()
+    W_hat = torch.empty((K, N), device="cuda")
+    dd.decdec_residual_f32(desc, torch.zeros((K, N), device="cuda"), Wq, scales, zl, W_hat)
+    return desc, Wq, scales, zl, x, W_hat.neg_()
+
+
+def assert_close_to_exact(y, exact, mass):
+    """Half a unit in the last place of fp16, and K sums in fp32 of terms that add up to `mass` in absolute value."""
+    bound = exact.abs() * 2.0 ** -11 + mass * 2.0 ** -20 + 2.0 ** -24
+    assert bool(((y.double() - exact).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("bits,wfmt", [(3, dd.W_UNIFORM_G128), (4, dd.W_UNIFORM_G128), (3, dd.W_LUT_COL8)])
+@pytest.mark.parametrize("K,N,place", [(8192, 24640, "device"), (8320, 24192, "pinned"), (4224, 57344, "pinned")])
+def test_one_grid_of_many_rounds(bits, wfmt, K, N, place):
+    """Base GEMVs of three rounds of wavefronts, some of whose workgroups take two turns by themselves, the last one cut off."""
+    desc, Wq, scales, zl, x, W_hat = random_layer(K, N, bits, wfmt)
+    k = 9
+    g = torch.Generator(device="cuda").manual_seed(7)
+    R = torch.randint(0, 256, (K, N // 2), dtype=torch.uint8, device="cuda", generator=g)
+    Rs = (torch.rand(N, device="cuda", generator=g) * 1e-3 + 1e-3).half()
+    idx = torch.empty(k, dtype=torch.int32, device="cuda")
+    xsel = torch.empty(k, dtype=torch.float16, device="cuda")
+    dd.decdec_select_topk(x, K, k, idx, xsel)
+    b = R[idx.long()].to(torch.int32)
+    q = torch.stack((b & 15, b >> 4), dim=2).view(k, N)
+    extra = (q - 16 * (q > 7)).double().mul_(Rs.double()) * xsel.double()[:, None]
+    exact = x.double() @ W_hat.double() + extra.sum(0)
+    mass = x.double().abs() @ W_hat.double().abs() + extra.abs().sum(0)
+    # the weights are differences of code and zero point, of which the kernel adds up the terms apart
+    if scales is not None:
+        mass += (scales.double() * (2 ** bits + zl.double().abs())).repeat_interleave(128, 0).mul_(x.double().abs()[:, None]).sum(0)
+    if place == "pinned":
+        host = torch.empty(R.shape, dtype=R.dtype, pin_memory=True)
+        R = host.copy_(R)
+    ws = dd.Workspace(K, N, k)
+    try:
+        for _ in range(2):
+            y = torch.full((N,), float("nan"), dtype=torch.float16, device="cuda")
+            dd.decdec_gemv(desc, x, Wq, scales, zl, R, Rs, k, y, ws)
+            assert_close_to_exact(y, exact, mass)
+    finally:
+        ws.close()
+
+
 @pytest.mark.parametrize("K,N,launch", [
     (1152, 16384, (256, 1024, 1)),   # nine groups by nine of 16 wavefronts
     (2176, 32768, (512, 1024, 1)),   # 17 groups by nine wavefronts, the last with one
