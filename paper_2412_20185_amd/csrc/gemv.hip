@@ -9,10 +9,10 @@
 namespace decdec {
 namespace {
 
-// Eight wavefronts a SIMD (kernels.h): a wavefront holds one tile, and the others of its compute unit cover its trip to memory.
-// Four where it holds kDeepTiles.
+// Eight wavefronts a SIMD (kernels.h): a wavefront holds one tile or two, and the others of its compute unit cover its trip to
+// memory.  Four where it holds kDeepTiles.
 template <int KIND, int COLS, int WAVES, int DEPTH>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(DEPTH == 1 ? 8 : 4))) void gemv_kernel(const CallArgs a) {
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(DEPTH <= 2 ? 8 : 4))) void gemv_kernel(const CallArgs a) {
     touch_args(a);
     asm volatile("" ::"s"(a.tiles), "s"(a.waves));
     gemv_block<KIND, COLS, WAVES, DEPTH>(a, (int)blockIdx.x, a.waves);
@@ -33,9 +33,13 @@ hipError_t launch_cols(const CallArgs& a, const GemvPlan& plan, hipStream_t stre
     switch (plan.cols) {
         case 16: return launch_waves<KIND, 16>(a, stream, tm);
         case 32: return launch_waves<KIND, 32>(a, stream, tm);
-        case 64: return plan.depth > 1 ? launch_waves<KIND, 64, kDeepTiles>(a, stream, tm) : launch_waves<KIND, 64>(a, stream, tm);
+        case 64: break;
         default: return hipErrorInvalidValue;
     }
+    if (plan.depth == kDeepTiles) return launch_waves<KIND, 64, kDeepTiles>(a, stream, tm);
+    if (plan.depth != 2) return launch_waves<KIND, 64>(a, stream, tm);
+    if (workgroup_waves(a.waves) != 16) return hipErrorInvalidValue;  // gemv_plan has two tiles there only
+    return launch_kernel(tm, gemv_kernel<KIND, 64, 16, 2>, dim3((unsigned)(a.tiles * a.gslices)), dim3(16 * 64), 0, stream, a);
 }
 
 }  // namespace
@@ -92,31 +96,38 @@ GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_reque
     }
     if (gpw_request > 0 || waves_request > 0) return requested(kind, tiles, G, gpw_request, waves_request);
 
-    // One tile per wavefront, but for the widest matrices.  us per call in graph replays on rotating weights, a plan of 64
-    // columns only with two groups per wavefront from 12288 tiles on -> this one; 3-bit / 4-bit / codebook.
+    // One tile per wavefront, but for the widest matrices.  us per call in graph replays on rotating weights, 3-bit / 4-bit /
+    // codebook; first a plan of 64 columns only, cut in K-slices, with two groups per wavefront from 12288 tiles on -> this one.
     //
     // One workgroup over all of K, which writes y itself, where that still gives the chip enough to do.
-    //   4096 x 4096: 4.10 / 4.44 / 4.38 -> 3.59 / 3.82 / 3.68;  4096 x 28672, codebook: 12.4 -> 11.0;
+    //   4096 x 4096: 4.10 / 4.44 / 4.38 -> 3.59 / 3.82 / 3.68;  4096 x 28672, codebook: 12.4 -> 10.9;
     //   1024 x 1024: 3.2 / 3.3 / 3.3 -> 2.7 / 2.6 / 2.7;  8192 x 4096: 5.17 / 5.70 / 5.49 -> 4.66 / 5.38 / 4.84
-    const int rounds64 = ceil_div(tiles, kCus);
-    if (tiles >= kCus && 8 * tiles >= 7L * kCus * rounds64) {
-        // So many columns that blocks of 64 keep all compute units busy to the end: a load is 1 KiB in one piece, and x and the
-        // sum over wavefronts are there once per 64 columns.  us for blocks of 16 or 32 columns and of 64, 3-bit / 4-bit /
-        // codebook.  One group per wavefront:
-        //   1024 x 16384: 3.72 / 4.04 / 4.03 and 3.56 / 3.82 / 3.89;  1024 x 49152: 6.1 / 6.7 / 6.9 and 5.4 / 6.2 / 5.9;
-        //   2048 x 32768: 6.8 / 8.0 / 7.3 and 6.3 / 7.2 / 7.0.  Workgroups of 16 while the chip holds them at one time (two per
-        //   compute unit): 2048 x 49152 8.9 / 10.7 / 9.9 and 8.9 / 10.4 / 10.1.
-        //   The codebook format gains less: 2048 x 28672 6.76 and 6.83, so it takes them where no compute unit is left idle.
-        const bool uniform = kind != PACK_LUT3, whole = tiles % kCus == 0;
-        if (G <= 8 || (G <= 16 && tiles <= 2 * kCus && (uniform || whole))) return GemvPlan{64, G, 1, 1};
-        // Two groups per wavefront:
-        //   4096 x 32768: 10.9 / 13.2 / 12.7 and 10.3 / 12.2 / 12.0;  3072 x 49152: 12.4 / 14.6 / 14.7 and 11.8 / 13.6 / 13.9;
-        //   4096 x 28672: 9.9 / 11.9 / 11.3 and 9.7 / 11.2 / 11.5;  3584 x 45056: 13.1 / 15.5 / 15.3 and 12.8 / 14.7 / 15.5; but
-        //   3584 x 28672: 9.2 / 10.7 / 10.5 and 9.4 / 10.9 / 11.2;  2560 x 43008: 10.5 / 11.7 / 11.8 and 10.9 / 11.6 / 11.6;
-        //   2560 x 16384: 5.2 / 5.9 / 5.7 and 5.7 / 6.1 / 6.4.
-        const bool nearly = G == 32 || (tiles > 2 * kCus && 10 * tiles >= 9L * kCus * rounds64);
-        if (G > 16 && G <= 32 && (whole ? tiles >= 2 * kCus : uniform && nearly)) return GemvPlan{64, ceil_div(G, 2), 2, 1};
+    //
+    // In blocks of 64 columns a load is 1 KiB in one piece, and x and the sum over wavefronts are there once per 64 columns: so
+    // where the columns are many enough to keep the compute units evenly busy with them, to `share` of the last round.  us for
+    // blocks of 16 or 32 columns and of 64:
+    const auto even = [&](double share) { return tiles >= share * kCus * ceil_div(tiles, kCus); };
+    bool wide;
+    if (G <= 8) {
+        // Few groups are few wavefronts a workgroup, so that small workgroups start all over the chip; but just above one round
+        // half as wide blocks are more even.  256 x 1024 2.40 / 2.23 / 2.55 and 2.30 / 2.14 / 2.48;  256 x 43008 4.6 / 4.6 / 5.0
+        // and 3.1 / 3.3 / 3.5;  1024 x 14336 3.35 / 3.51 / 3.73 and 3.29 / 3.45 / 3.61;  1024 x 24576 4.07 / 4.55 / 4.60 and
+        // 4.07 / 4.32 / 4.56;  1024 x 22528 3.85 / 4.20 / 4.29 and 4.03 / 4.38 / 4.50;  below 128 tiles 768 x 4096 8 % slower.
+        wide = G <= 2 ? tiles >= 16 : tiles >= kCus / 2 && (G <= 4 || tiles <= kCus || tiles > 2 * kCus || even(0.75));
+    } else if (G <= 16) {
+        // One group per wavefront, while the chip holds the workgroups of 16 at one time (two per compute unit):
+        // 2048 x 14336 4.28 / 4.74 / 4.87 and 4.17 / 4.56 / 4.70;  2048 x 28672 6.18 / 7.14 / 6.61 and 5.81 / 6.71 / 6.67;
+        // 2048 x 24576 (0.75) 5.64 / 6.47 / 6.06 and 5.59 / 6.34 / 6.63;  2048 x 36864 7.2 / 8.5 / 8.2 and 8.0 / 8.9 / 9.1.
+        wide = tiles <= 2 * kCus && even(0.875);
+    } else {
+        // Two groups per wavefront, both asked for at once: 4096 x 28672 (0.875) 9.8 / 11.7 / 11.1 and 9.4 / 11.2 / 10.9;
+        // 3584 x 28672 9.0 / 10.6 / 10.4 and 9.2 / 10.7 / 10.6;  2176 x 57152 (0.872) 12.6 / 14.0 / 14.4 and 11.1 / 12.4 / 12.2;
+        // 4096 x 49152 (1) 15.2 / 18.2 / 17.5 and 14.2 / 17.1 / 16.4;  3072 x 40960 (0.83) 10.5 / 12.3 / 12.3 and 10.7 / 12.4 /
+        // 11.8;  4096 x 36864 (0.75) 11.9 / 14.3 / 13.7 and 12.5 / 15.3 / 14.6.  One after the other 4096 x 28672 takes 9.7 /
+        // 11.3 / 11.1.
+        wide = G <= 32 && tiles > kCus && even(0.85);
     }
+    if (wide) return G <= 16 ? GemvPlan{64, G, 1, 1, 1} : GemvPlan{64, ceil_div(G, 2), 2, 1, 2};
     const int turns16 = ceil_div(G, 4), turns32 = ceil_div(G, 2);
     const long blocks16 = 4 * tiles, blocks32 = 2 * tiles;
     const int rounds16 = ceil_div(blocks16, kCus), rounds32 = ceil_div(blocks32, kCus);

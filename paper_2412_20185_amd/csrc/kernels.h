@@ -122,7 +122,7 @@ __device__ __forceinline__ void hold_scalar(T*& p) {
 
 // gemv.hip ---------------------------------------------------------------
 // How the work is cut: a wavefront takes `cols` columns (16, 32 or 64) of 64 / cols groups of 128 input channels at a time,
-// `gpw` times, the tiles of `depth` turns on their way at one time (1 or kDeepTiles; more than 1 with 64 columns only);
+// `gpw` times, the tiles of `depth` turns on their way at one time (1, 2 or kDeepTiles; more than 1 with 64 columns only);
 // workgroups with `waves` such wavefronts (at most 16; they have workgroup_waves of them), `slices` workgroups (and part sums
 // per column) per block of `cols` columns.  Requests of 0 leave the choice to the library; others are for 64 columns.
 // one_grid: inside the one-grid kernel, where cols is kOneGridCols, waves kWavesPerBlock and depth 1 (several
