@@ -78,7 +78,7 @@ hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, bool over_link, hip
 
 }  // namespace
 
-// Dynamic LDS: the selection, and where three workgroups on a compute unit are better than four, what keeps a fourth out.
+// Dynamic LDS: the selection, and where fewer workgroups on a compute unit are better, what keeps another one out.
 //
 // With rows behind the link and more than 4096 channels a small call lasts as long as its selection and its rows, and the base
 // GEMV of the same compute unit slows the selection down.  That pays while the base GEMV is about one round of workgroups:
@@ -91,16 +91,22 @@ hipError_t launch_rfmt(int rfmt, const CallArgs& a, int nch, bool over_link, hip
 //   rows 11.1 / 12.0 / 12.9 and 11.2 / 12.6 / 13.4;  8192 x 57344, 8 fp16 rows 43.6 / 47.5 / 50.4 and 46.7 / 51.8 / 53.7.
 // Up to 4096 channels, where the selection is short, no difference; with rows in GPU memory, where the base GEMV is what lasts,
 // 7.3 and 7.8 (14336 x 4096, 286 fp16 rows).
-// Kernels with 2-bit rows or eight chunks of keys per thread have registers for three workgroups only.
+// Kernels with eight chunks of keys per thread have registers for three workgroups only, and so have those with 2-bit rows:
+// two of these instead, up to 2.5 workgroups of the base GEMV per compute unit (a codebook loses 9 % at three).  us with three
+// and with two:  7680 x 4992 (624), 2 rows 7.3 / 7.5 / 7.2 and 7.1 / 7.1 / 7.1;  8192 x 6144 (768), 2 rows 7.4 / 7.9 / 7.5 and
+// 7.4 / 7.9 / 8.2;  8192 x 8192 (1024), 2 rows 7.8 / 8.6 / 8.9 and 8.8 / 9.5 / 9.7.
 unsigned one_grid_lds(int kind, int rbits, int nch, int k, long base_workgroups, bool over_link) {
-    constexpr unsigned kCuLds = 160 * 1024, kLdsOfThree = 42 * 1024;
+    constexpr unsigned kCuLds = 160 * 1024, kLdsOfThree = 42 * 1024, kLdsOfTwo = 55 * 1024;
     static_assert(3 * kLdsOfThree <= kCuLds && 4 * kLdsOfThree > kCuLds, "three workgroups");
-    constexpr unsigned kStatic = sizeof(FetchLds<16>) + sizeof(float) * kWavesPerBlock * kOneGridCols;
+    static_assert(2 * kLdsOfTwo <= kCuLds && 3 * kLdsOfTwo > kCuLds, "two workgroups");
+    constexpr unsigned kGemvLds = sizeof(float) * kWavesPerBlock * kOneGridCols;
+    constexpr unsigned kStatic = sizeof(FetchLds<16>) + kGemvLds, kStatic2 = sizeof(FetchLds<2>) + kGemvLds;
     static_assert(sizeof(FetchLds<16>) == sizeof(FetchLds<8>) && sizeof(FetchLds<16>) == sizeof(FetchLds<4>), "one size");
     const unsigned lds = selection_lds_bytes(nch, k);
+    if (!over_link || (nch != 2 && nch != 4)) return lds;
+    if (rbits == 2) return 2 * base_workgroups <= 5 * kCus ? std::max(lds, kLdsOfTwo - kStatic2) : lds;
     const int rounds = 4 + (kind == PACK_U3 ? 2 : 0) + (rbits == 16 && kind != PACK_LUT3 ? 1 : 0);
-    const bool three = over_link && (nch == 2 || nch == 4) && rbits != 2 && base_workgroups <= rounds * kCus;
-    return three ? std::max(lds, kLdsOfThree - kStatic) : lds;
+    return base_workgroups <= rounds * kCus ? std::max(lds, kLdsOfThree - kStatic) : lds;
 }
 
 hipError_t launch_compensated_gemv(int kind, int rfmt, const CallArgs& a, int select_chunks, bool over_link, hipStream_t stream,

@@ -160,8 +160,8 @@ def test_dots_with_a_shared_activation_are_given_their_wait_states(code_objects)
 
 def test_workgroups_of_the_one_grid_kernel_per_compute_unit(code_objects):
     """Three workgroups or more fit a compute unit by their LDS, whatever the kernel's own part of it is; exactly three where a
-    small base GEMV runs beside a selection over more than 4096 channels and rows behind the link, and never fewer than the
-    registers allow with a wide one."""
+    small base GEMV runs beside a selection over more than 4096 channels and rows behind the link (with 2-bit rows and the
+    smallest of them two), and never fewer than the registers allow with a wide one."""
     lds_of = dd.lib()["_ZN6decdec12one_grid_ldsEiiiilb"]
     lds_of.argtypes = [C.c_int] * 4 + [C.c_long, C.c_bool]
     lds_of.restype = C.c_uint
@@ -183,6 +183,8 @@ def test_workgroups_of_the_one_grid_kernel_per_compute_unit(code_objects):
                 small, wide, near = fit(k, 900, True), fit(k, 1 << 14, True), fit(k, 900, False)
                 assert min(small, by_registers) == (3 if nch >= 2 or bits == 2 else 4), m.groups()
                 assert min(wide, near) >= by_registers, m.groups()
+            if bits == 2 and nch in (2, 4):  # two beside the smallest
+                assert fit(1, 600, True) == 2
             if nch:
                 assert fit(4096, 900, True) >= 2
     assert seen == 3 * 4 * (2 * 4 + 1)
