@@ -81,9 +81,7 @@ GemvPlan requested(int kind, long tiles, int G, int gpw, int waves) {
     return p;
 }
 
-}  // namespace
-
-GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid, bool over_link) {
+GemvPlan plan_of(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid, bool over_link) {
     if (one_grid) {
         // A K-slice fewer is an atomic per column fewer, and in the codebook format the codebook once less; a turn more lets a
         // workgroup last longer, which is what fills the chip less evenly.  Two turns from three rounds of wavefronts at eight a
@@ -155,6 +153,16 @@ GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_reque
         return sliced(G, 64, ceil_div(G, slices), 1);
     }
     return sliced(G, G <= 16 * kMaxGemvSlices ? 32 : 16, 8, 1);
+}
+
+}  // namespace
+
+GemvPlan gemv_plan(int kind, long tiles, int G, int gpw_request, int waves_request, bool one_grid, bool over_link) {
+    const GemvPlan p = plan_of(kind, tiles, G, gpw_request, waves_request, one_grid, over_link);
+    // A grid has fewer than 2^32 threads (inside the one-grid kernel half of them at most): one workgroup of eight per tile where
+    // the plan would take more, from 2^20 tiles on.
+    const long threads = tiles * (kTileCols / p.cols) * p.slices * workgroup_waves(p.waves) * 64;
+    return threads < (one_grid ? 1L << 31 : 1L << 32) ? p : GemvPlan{64, 8, ceil_div(G, 8), 1, 1};
 }
 
 hipError_t launch_gemv(int kind, const CallArgs& a, const GemvPlan& plan, hipStream_t stream, const KernelTimer* tm) {

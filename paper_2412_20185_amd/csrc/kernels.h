@@ -182,6 +182,8 @@ hipError_t launch_quantize_uniform(int bits, const float* W, void* Wq, void* sca
                                    int N, hipStream_t stream);
 hipError_t launch_residual_f32(int kind, const float* W, const void* Wq, const void* scales, const void* zeros_or_lut,
                                float* R, int K, int N, hipStream_t stream);
+// Which of the two searches for the column scales a matrix gets; they give the same bits.
+bool residual_scale_by_bounds(int bits, int K, int N);
 hipError_t launch_quantize_residual(int bits, const float* R, void* codes_out, void* scales_out, int K, int N,
                                     hipStream_t stream);
 

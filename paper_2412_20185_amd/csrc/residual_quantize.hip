@@ -16,8 +16,9 @@
 // Scales and codes have the bits that one IEEE fp64 operation per step gives,
 // the error of a column summed over its rows in ascending order, so that a CPU
 // can reproduce them; the search takes fewer, fused steps with the same results
-// (add_error says why they are the same) and, for two and four bits, sums only
-// the candidates that may be the least.  The conversion of a scale to fp16 is one round-to-nearest-even done with integer arithmetic.
+// (add_error says why they are the same) and, where there are rows enough, sums
+// only the candidates that may be the least.  The conversion of a scale to fp16
+// is one round-to-nearest-even done with integer arithmetic.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
@@ -258,7 +259,8 @@ __global__ __launch_bounds__(64 * WAVES) void residual_scale_kernel(const float*
     }
 }
 
-// The same scales, for two and four bits.  One workgroup = COLS columns, kSlots threads each.  Nearly all candidates are ruled out by bounds first, so that what bounds the kernel is reading the columns three times:
+// The same scales.  One workgroup = COLS columns, kSlots threads each.  Nearly all candidates are ruled out by bounds first, so
+// that what bounds the kernel is reading the columns three times (in 8 bits the bounds themselves, 127 steps a candidate):
 //
 //   1. max|r| of every column.
 //   2. A histogram of |r|: per bin the number of values and the sum of their positions (26-bit whole numbers), one 64-bit
@@ -583,17 +585,24 @@ hipError_t launch_residual_f32(int kind, const float* W, const void* Wq, const v
     return hipGetLastError();
 }
 
+// Bounds first, where they pay: not for few rows, which for 8 bits, with 127 steps per candidate, are more; nor from
+// kMaxHistRows on, where the fields of a bin's word are too small, nor where a grid would have 2^32 threads.  us, search and
+// encoding into GPU memory, all candidates in fp64 / bounds first, 4 bits: 256 x 4096 25 / 29; 256 x 1024 16 / 16; 512 x 4096
+// 44 / 33; 1024 x 1024 35 / 17; 4096 x 256 106 / 23; 4096 x 4096 264 / 80; 14336 x 4096 901 / 220; 4096 x 14336 908 / 255.
+// 8 bits, residuals of the 3-bit quantiser: 1024 x 1024 36 / 74; 2048 x 4096 153 / 184; 3072 x 4096 212 / 199; 4096 x 1024
+// 113 / 87; 4096 x 4096 275 / 209; 14336 x 4096 915 / 451; 4096 x 14336 921 / 747.
+bool residual_scale_by_bounds(int bits, int K, int N) {
+    return K >= (bits == 8 ? 4096 : 384) && K < kMaxHistRows && (long)N * kSlots < 1L << 32;
+}
+
 hipError_t launch_quantize_residual(int bits, const float* R, void* codes_out, void* scales_out, int K, int N,
                                     hipStream_t stream) {
     if (bits != 2 && bits != 4 && bits != 8) return hipErrorInvalidValue;
     _Float16* S = static_cast<_Float16*>(scales_out);
-    // Bounds first, where they pay: not for few rows, nor from kMaxHistRows on, where the fields of a bin's word are too small,
-    // nor for 8 bits, whose 127 steps per candidate cost more than they save up to 4096 rows and leave many candidates above.
-    // us, search and encoding into GPU memory, all candidates in fp64 / bounds first, 4 bits: 256 x 4096 25 / 29; 256 x 1024
-    // 16 / 16; 512 x 4096 44 / 33; 1024 x 1024 35 / 17; 4096 x 256 106 / 23; 4096 x 4096 264 / 80; 14336 x 4096 901 / 220;
-    // 4096 x 14336 908 / 255.  8 bits: 1024 x 1024 35 / 73; 4096 x 4096 265 / 199.
-    if (bits == 8 || K < 384 || K >= kMaxHistRows) {
+    if (!residual_scale_by_bounds(bits, K, N)) {
         launch_scale_direct(R, K, N, (double)((1 << (bits - 1)) - 1), S, stream);
+    } else if (bits == 8) {
+        launch_scale_bounds<127>(R, K, N, S, stream);
     } else if (bits == 4) {
         launch_scale_bounds<7>(R, K, N, S, stream);
     } else {

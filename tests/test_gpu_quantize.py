@@ -97,7 +97,7 @@ def test_residual_scale_search_at_its_edges(rbits, K, N):
     assert np.array_equal(codes.numpy(), dd.decdec_pack_residual_int(q_ref, rbits))
 
 
-@pytest.mark.parametrize("rbits,K,N", [(4, 383, 64), (4, 384, 64), (4, 2049, 64), (4, 1000, 2048), (2, 3000, 2112), (8, 1500, 2112), (4, 262143, 32), (4, 262144, 32)])
+@pytest.mark.parametrize("rbits,K,N", [(4, 383, 64), (4, 384, 64), (4, 2049, 64), (4, 1000, 2048), (2, 3000, 2112), (8, 1500, 2112), (8, 4095, 64), (8, 4096, 64), (8, 4999, 2112), (4, 262143, 32), (4, 262144, 32)])
 def test_residual_scale_search_by_bounds(rbits, K, N):
     """Each width of the column blocks, both sides of the row counts between which most candidates are ruled out beforehand, and
     columns whose values crowd a few bins of the histogram or leave many candidates equal or nearly so: the oracle's bits."""

@@ -198,3 +198,54 @@ def test_header_is_plain_c_and_links_against_the_library(tmp_path):
                     str(src), "-o", str(exe), "-L", libdir, "-ldecdec", f"-Wl,-rpath,{libdir}"], check=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split(None, 2)
     assert out[0] == str(256 * 128 * 3 // 8) and out[1] == "8598" and "invalid" in out[2]
+
+
+class GemvPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("cols", "waves", "gpw", "slices", "depth")]
+
+
+def _gemv_plan(*args):
+    f = dd.lib()["_ZN6decdec9gemv_planEiliiibb"]
+    f.argtypes = [C.c_int, C.c_long] + [C.c_int] * 3 + [C.c_bool] * 2
+    f.restype = GemvPlan
+    return f(*args)
+
+
+def test_every_plan_of_the_base_gemv_is_one_its_kernels_can_run():
+    """All of K is covered, by no more slices than the accumulators count and none without work; the blocks and wavefronts are
+    those that kernels exist for; a grid has fewer than 2^32 threads at any number of columns; and what the library does by
+    itself does not follow from the format, which the query of the launch shape does not know."""
+    rng = np.random.default_rng(3)
+    tiles = sorted({*range(1, 70), *range(250, 260), *range(440, 520, 3), *np.exp(rng.uniform(0, np.log(1 << 23), 60)).astype(int).tolist(),
+                    1 << 21, (1 << 22) + 1, (1 << 23) - 1})
+    groups = sorted({*range(1, 40), *range(60, 70), *range(120, 140), 224, 255, 256, 257, 448, 512})
+    # (groups per wavefront, wavefronts, one grid, over the link); the format only decides between equal results
+    asked = [(0, 0, False, False), (1, 0, False, False), (2, 0, False, False), (5, 0, False, False), (1024, 0, False, False),
+             (0, 4, False, False), (0, 16, False, False), (3, 8, False, False), (0, 0, True, False), (0, 0, True, True), (2, 0, True, True)]
+    for t in tiles:
+        for G in groups:
+            for gpw, waves, one_grid, link in asked:
+                ps = [_gemv_plan(kind, int(t), G, gpw, waves, one_grid, link) for kind in range(3)]
+                for p in ps:
+                    what = (t, G, gpw, waves, one_grid, p.cols, p.waves, p.gpw, p.slices, p.depth)
+                    each = p.waves * p.gpw * (64 // p.cols)     # groups of a workgroup
+                    assert p.cols in (16, 32, 64) and 1 <= p.waves <= 16 and 1 <= p.slices <= 16, what
+                    assert each * p.slices >= G > each * (p.slices - 1), what
+                    threads = 256 if p.waves <= 4 else 512 if p.waves <= 8 else 1024
+                    assert t * (64 // p.cols) * p.slices * threads < 1 << (31 if one_grid and t < 1 << 22 else 32), what
+                    assert p.depth == 1 or (p.cols == 64 and not one_grid and p.gpw > 1), what
+                    assert p.depth in (1, 4) or (p.depth == 2 and threads == 1024 and p.gpw == 2), what
+                    if one_grid:
+                        assert p.cols == 64 and p.waves == 8, what
+                if not one_grid:
+                    assert len({(p.cols, p.waves, p.gpw, p.slices) for p in ps}) == 1, what
+
+
+def test_scale_search_whose_grid_fits():
+    by_bounds = dd.lib()["_ZN6decdec24residual_scale_by_boundsEiii"]
+    by_bounds.argtypes = [C.c_int] * 3
+    by_bounds.restype = C.c_bool
+    assert [by_bounds(b, k, 4096) for b, k in ((2, 383), (2, 384), (4, 262143), (4, 262144), (8, 4095), (8, 4096))] == [
+        False, True, True, False, False, True]
+    # 64 threads a column
+    assert by_bounds(4, 384, (1 << 26) - 64) and not by_bounds(4, 384, 1 << 26) and not by_bounds(4, 384, (1 << 31) - 64)
