@@ -160,6 +160,12 @@ __device__ __forceinline__ double wave_min(double v) {
     return v;
 }
 
+// What the lanes of a wavefront have written to LDS is there for its other lanes.
+__device__ __forceinline__ void wave_writes_seen() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 constexpr int kScaleRows = 128;   // rows of a column block staged in LDS at a time
 constexpr int kMaxSlots = 80;     // threads that share a column's candidates x candidates per thread, at most
 
@@ -406,7 +412,7 @@ __global__ __launch_bounds__(kSlots * COLS) void residual_scale_bounds_kernel(co
         }
         least = wave_min(least);
         if (lane == 0) s_bits[wave][kAlphas] = 0;
-        __builtin_amdgcn_wave_barrier();
+        wave_writes_seen();
         int count = 0;
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
@@ -417,6 +423,7 @@ __global__ __launch_bounds__(kSlots * COLS) void residual_scale_bounds_kernel(co
             if (left) s_left[wave][count + __builtin_popcountll(mask & ((1ull << lane) - 1))] = (unsigned char)c;
             count += __builtin_popcountll(mask);
         }
+        wave_writes_seen();
         if (lane == 0) {
             if (count <= 1) scales_out[n] = __builtin_bit_cast(_Float16, count == 1 ? s_bits[wave][s_left[wave][0]] : (uint16_t)0x3C00);
             s_count[wave] = count <= 1 ? 0 : count;
