@@ -123,39 +123,59 @@ def test_row_requests_of_a_batch_do_not_wait_for_one_another(code_objects):
     assert len(seen) >= 4 * 5 - 1
 
 
+def _wait_state_faults(lines):
+    """What the compiler does not see inside the asm dots: a register that a DPP operand names must not have been written by
+    either of the two vector instructions in front of it, and for three wait states no other kind of instruction may name the
+    result of a dot, nor may a dot read it as a factor.  Nothing is left open where the path goes on elsewhere."""
+    recent = []   # registers written by the last vector instructions, one entry per wait state
+    pending = {}  # results of dots: wait states left
+    for line in lines:
+        op, _, rest = line.partition(" ")
+        regs = re.findall(r"\bv(?:\[(\d+):(\d+)\]|(\d+))", rest)
+        regs = [set(range(int(a), int(b) + 1)) if a else {int(c)} for a, b, c in regs]
+        states = int(rest, 0) + 1 if op == "s_nop" else 1
+        dot = op == "v_dot2c_f32_f16_dpp"
+        if dot and any(written & regs[1] for written in recent[-2:]):
+            yield line
+        named = regs[1] | regs[2] if dot else set().union(*regs)
+        if named & pending.keys():
+            yield line
+        if pending and op.startswith(("s_branch", "s_cbranch", "s_setpc", "s_endpgm")):
+            yield line
+        pending = {r: n - states for r, n in pending.items() if n > states}
+        written = set()
+        if op.startswith("v_") and regs:
+            written = regs[0] | regs[1] if "swap" in op else regs[0]
+        if dot:
+            pending.update({r: 3 for r in regs[0]})
+        recent = (recent + [written] + [set()] * (states - 1))[-2:]
+
+
 def test_dots_with_a_shared_activation_are_given_their_wait_states(code_objects):
-    """The compiler does not see what is inside an asm statement.  A register that a DPP operand names must not be written by
-    either of the two vector instructions in front of it, and the result of a dot is not read by another kind of instruction
-    for three wait states."""
-    seen = 0
+    seen = {}
     for path in code_objects:
         for name, lines in _disassembly(path):
             if "row_newbcast" not in "".join(lines):
                 continue
-            seen += 1
-            recent = []                      # registers written by the last vector instructions, one entry per wait state
-            pending = {}                     # results of dots: wait states left
-            for line in lines:
-                op, _, rest = line.partition(" ")
-                regs = re.findall(r"\bv(?:\[(\d+):(\d+)\]|(\d+))", rest)
-                regs = [set(range(int(a), int(b) + 1)) if a else {int(c)} for a, b, c in regs]
-                if op == "s_nop":
-                    states = int(rest, 0) + 1
-                else:
-                    states = 1
-                    if op == "v_dot2c_f32_f16_dpp":
-                        for written in recent[-2:]:
-                            assert not regs[1] & written, (name, line)
-                        assert not (regs[1] | regs[2]) & pending.keys(), (name, line)
-                    elif op.startswith("v_"):
-                        for r in regs:
-                            assert not r & pending.keys(), (name, line)
-                pending = {r: n - states for r, n in pending.items() if n > states}
-                if op == "v_dot2c_f32_f16_dpp":
-                    pending.update({r: 3 for r in regs[0]})
-                recent += [regs[0] if op.startswith("v_") and regs else set()] + [set()] * (states - 1)
-                recent = recent[-2:]
-    assert seen >= 60
+            family = re.search(r"[a-z_]*gemv_kernel", name).group(0)
+            seen[family] = seen.get(family, 0) + 1
+            assert not list(_wait_state_faults(lines)), name
+    # formats x (columns x workgroup sizes, then those with several tiles on their way); x row formats x selections
+    assert seen == {"gemv_kernel": 3 * (3 * 3 + 3 + 1), "compensated_gemv_kernel": 3 * 4 * (2 * 4 + 1)}
+
+
+@pytest.mark.parametrize("lines,faults", [
+    (["v_mov_b32_e32 v5, v9", "v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0 row_mask:0xf bank_mask:0xf", "s_nop 2"], 1),
+    (["v_permlane16_swap_b32_e32 v9, v5", "s_nop 0", "v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "s_nop 2"], 1),
+    (["v_mov_b32_e32 v5, v9", "s_nop 1", "v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "s_nop 2", "v_add_f32_e32 v3, v1, v1"], 0),
+    (["v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "v_dot2c_f32_f16_dpp v1, v6, v2 row_newbcast:0", "s_nop 2"], 0),
+    (["v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "s_nop 1", "ds_write_b32 v7, v1"], 1),
+    (["v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "global_store_dword v[8:9], v1, off"], 1),
+    (["v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "s_nop 0", "v_dot2c_f32_f16_dpp v3, v5, v1 row_newbcast:1", "s_nop 2"], 1),
+    (["v_dot2c_f32_f16_dpp v1, v5, v2 row_newbcast:0", "s_cbranch_scc1 12"], 1),
+])
+def test_wait_states_that_are_missing_are_seen(lines, faults):
+    assert len(list(_wait_state_faults(lines))) == faults
 
 
 def test_workgroups_of_the_one_grid_kernel_per_compute_unit(code_objects):
