@@ -192,11 +192,9 @@ int decdec_ws_set_gemv_waves(decdec_ws* ws, int32_t waves_per_workgroup);
 /* Host-side query, nothing is enqueued: the grid the base GEMV kernel of an
  * uncompensated call (k == 0) over K input channels and N_total output columns
  * (all matrices of a decdec_gemv_multi call together) would be launched with
- * under this workspace's current settings in a uniform format (the codebook
- * format may take narrower blocks of columns): number of workgroups, threads
- * per workgroup, workgroups per 64-column tile (K-slices times blocks of
- * columns).
- * Any output pointer may be NULL.
+ * under this workspace's current settings, in any weight format: number of
+ * workgroups, threads per workgroup, workgroups per 64-column tile (K-slices
+ * times blocks of columns).  Any output pointer may be NULL.
  * Benchmarks use it to tell whether a stored profile still describes the
  * kernels that run. */
 int decdec_ws_gemv_launch_shape(const decdec_ws* ws, int32_t K, int32_t N_total, int32_t* workgroups,

@@ -4,12 +4,13 @@
 //
 // The K x N code matrix is cut into tiles of 128 input channels (one
 // quantisation group) x 64 output columns.  Tiles are stored column-tile
-// major: tile (nt, g) starts at ((nt * K/128) + g) * tile_bytes, so one
-// wavefront walking along K for its 64 columns reads one contiguous stream.
-// Inside a tile lane l (= column nt*64 + l) owns `bits` 16-byte pieces; piece
-// p of lane l sits at byte p*1024 + l*16, so every wave-wide 128-bit load is
-// one fully coalesced 1 KiB access.  A lane's pieces, read as 32-bit words
-// w = 4p + c, hold that column's 128 codes of the group.
+// major: tile (nt, g) starts at ((nt * K/128) + g) * tile_bytes, so the tiles
+// that workgroups of one column tile read are one contiguous stream.
+// Inside a tile column nt*64 + l owns `bits` 16-byte pieces; piece p of it
+// sits at byte p*1024 + l*16, so a 128-bit load of a wavefront that works on
+// 64 columns is one contiguous 1 KiB access, and of one that works on 32 or 16
+// columns of two or four groups pieces of 512 or 256 bytes.  A column's
+// pieces, read as 32-bit words w = 4p + c, hold its 128 codes of the group.
 //
 // Codes are placed so that a code can be turned into an fp16 operand of
 // v_dot2_f32_f16 with at most one shift and one AND: a 3- or 4-bit field that
