@@ -192,13 +192,18 @@ int decdec_ws_set_gemv_waves(decdec_ws* ws, int32_t waves_per_workgroup);
 /* Host-side query, nothing is enqueued: the grid the base GEMV kernel of an
  * uncompensated call (k == 0) over K input channels and N_total output columns
  * (all matrices of a decdec_gemv_multi call together) would be launched with
- * under this workspace's current settings, in any weight format: number of
- * workgroups, threads per workgroup, workgroups per 64-column tile (K-slices
+ * under this workspace's current settings with 3-bit uniform weights: number
+ * of workgroups, threads per workgroup, workgroups per 64-column tile (K-slices
  * times blocks of columns).  Any output pointer may be NULL.
  * Benchmarks use it to tell whether a stored profile still describes the
  * kernels that run. */
 int decdec_ws_gemv_launch_shape(const decdec_ws* ws, int32_t K, int32_t N_total, int32_t* workgroups,
                                 int32_t* threads, int32_t* per_tile);
+/* The same for the weight format and K of `d` (the grid of large matrices
+ * depends on the format); N_total output columns instead of d->N.  Returns the
+ * columns of a workgroup and the K-slices (part sums per column) apart. */
+int decdec_ws_gemv_launch_shape_of(const decdec_ws* ws, const decdec_desc* d, int32_t N_total, int32_t* workgroups,
+                                   int32_t* threads, int32_t* columns, int32_t* k_slices);
 
 /* Kernel timing for benchmarks.  capacity > 0 allocates that many sets of HIP
  * events (set-up call: allocates, synchronises) and makes every later

@@ -393,6 +393,20 @@ int decdec_ws_gemv_launch_shape(const decdec_ws* ws, int32_t K, int32_t N_total,
     return DECDEC_OK;
 }
 
+int decdec_ws_gemv_launch_shape_of(const decdec_ws* ws, const decdec_desc* d, int32_t N_total, int32_t* workgroups,
+                                   int32_t* threads, int32_t* columns, int32_t* k_slices) {
+    if (ws == nullptr || N_total <= 0 || N_total % kTileCols != 0) return DECDEC_EINVAL;
+    const int rc = check_desc(d);
+    if (rc != DECDEC_OK) return rc;
+    const long tiles = N_total / kTileCols;
+    const GemvPlan gp = gemv_plan(pack_kind(d), tiles, d->K / kGroup, ws->core.gemv_gpw, ws->core.gemv_wpb, false, false);
+    if (workgroups) *workgroups = (int32_t)tiles * (kTileCols / gp.cols) * gp.slices;
+    if (threads) *threads = workgroup_waves(gp.waves) * 64;
+    if (columns) *columns = gp.cols;
+    if (k_slices) *k_slices = gp.slices;
+    return DECDEC_OK;
+}
+
 int decdec_ws_read_selection(const decdec_ws* ws, int32_t k, int32_t* idx_host, void* xsel_f16_host) {
     if (ws == nullptr || k < 0 || k > ws->core.maxk) return DECDEC_EINVAL;
     // The selection may have been written by a kernel on any stream of the caller's: wait for the device.

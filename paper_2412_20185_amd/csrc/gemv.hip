@@ -38,8 +38,12 @@ hipError_t launch_cols(const CallArgs& a, const GemvPlan& plan, hipStream_t stre
     }
     if (plan.depth == kDeepTiles) return launch_waves<KIND, 64, kDeepTiles>(a, stream, tm);
     if (plan.depth != 2) return launch_waves<KIND, 64>(a, stream, tm);
-    if (workgroup_waves(a.waves) != 16) return hipErrorInvalidValue;  // gemv_plan has two tiles there only
-    return launch_kernel(tm, gemv_kernel<KIND, 64, 16, 2>, dim3((unsigned)(a.tiles * a.gslices)), dim3(16 * 64), 0, stream, a);
+    const dim3 grid((unsigned)(a.tiles * a.gslices)), block(workgroup_waves(a.waves) * 64);
+    switch (workgroup_waves(a.waves)) {  // gemv_plan has two tiles with these only
+        case 8: return launch_kernel(tm, gemv_kernel<KIND, 64, 8, 2>, grid, block, 0, stream, a);
+        case 16: return launch_kernel(tm, gemv_kernel<KIND, 64, 16, 2>, grid, block, 0, stream, a);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -105,27 +109,30 @@ GemvPlan plan_of(int kind, long tiles, int G, int gpw_request, int waves_request
     // where the columns are many enough to keep the compute units evenly busy with them, to `share` of the last round.  us for
     // blocks of 16 or 32 columns and of 64:
     const auto even = [&](double share) { return tiles >= share * kCus * ceil_div(tiles, kCus); };
-    bool wide;
+    int turns = 0;  // per wavefront, of 64 columns; 0: narrower blocks
     if (G <= 8) {
         // Few groups are few wavefronts a workgroup, so that small workgroups start all over the chip; but just above one round
         // half as wide blocks are more even.  256 x 1024 2.40 / 2.23 / 2.55 and 2.30 / 2.14 / 2.48;  256 x 43008 4.6 / 4.6 / 5.0
         // and 3.1 / 3.3 / 3.5;  1024 x 14336 3.35 / 3.51 / 3.73 and 3.29 / 3.45 / 3.61;  1024 x 24576 4.07 / 4.55 / 4.60 and
         // 4.07 / 4.32 / 4.56;  1024 x 22528 3.85 / 4.20 / 4.29 and 4.03 / 4.38 / 4.50;  below 128 tiles 768 x 4096 8 % slower.
-        wide = G <= 2 ? tiles >= 16 : tiles >= kCus / 2 && (G <= 4 || tiles <= kCus || tiles > 2 * kCus || even(0.75));
+        turns = G <= 2 ? tiles >= 16 : tiles >= kCus / 2 && (G <= 4 || tiles <= kCus || tiles > 2 * kCus || even(0.75));
     } else if (G <= 16) {
         // One group per wavefront, while the chip holds the workgroups of 16 at one time (two per compute unit):
         // 2048 x 14336 4.28 / 4.74 / 4.87 and 4.17 / 4.56 / 4.70;  2048 x 28672 6.18 / 7.14 / 6.61 and 5.81 / 6.71 / 6.67;
         // 2048 x 24576 (0.75) 5.64 / 6.47 / 6.06 and 5.59 / 6.34 / 6.63;  2048 x 36864 7.2 / 8.5 / 8.2 and 8.0 / 8.9 / 9.1.
-        wide = tiles <= 2 * kCus && even(0.875);
-    } else {
-        // Two groups per wavefront, both asked for at once: 4096 x 28672 (0.875) 9.8 / 11.7 / 11.1 and 9.4 / 11.2 / 10.9;
+        // Beyond that two by half as many wavefronts, both asked for at once:
+        // 1152 x 49152 (1) 6.9 / 7.1 / 7.9 and 5.8 / 6.6 / 6.5;  2048 x 45056 (0.92) 8.3 / 9.8 / 9.0 and 7.8 / 9.2 / 8.8;
+        // 2048 x 57152 (0.87) 9.4 / 11.0 / 11.6 and 9.4 / 11.3 / 11.1;  2048 x 40960 (0.83) 7.7 / 9.1 / 8.4 and 7.7 / 9.0 / 8.8.
+        turns = tiles <= 2 * kCus ? even(0.875) : even(0.9) ? 2 : 0;
+    } else if (G <= 32 && tiles > kCus && even(0.85)) {
+        // Two groups per wavefront likewise: 4096 x 28672 (0.875) 9.8 / 11.7 / 11.1 and 9.4 / 11.2 / 10.9;
         // 3584 x 28672 9.0 / 10.6 / 10.4 and 9.2 / 10.7 / 10.6;  2176 x 57152 (0.872) 12.6 / 14.0 / 14.4 and 11.1 / 12.4 / 12.2;
         // 4096 x 49152 (1) 15.2 / 18.2 / 17.5 and 14.2 / 17.1 / 16.4;  3072 x 40960 (0.83) 10.5 / 12.3 / 12.3 and 10.7 / 12.4 /
         // 11.8;  4096 x 36864 (0.75) 11.9 / 14.3 / 13.7 and 12.5 / 15.3 / 14.6.  One after the other 4096 x 28672 takes 9.7 /
         // 11.3 / 11.1.
-        wide = G <= 32 && tiles > kCus && even(0.85);
+        turns = 2;
     }
-    if (wide) return G <= 16 ? GemvPlan{64, G, 1, 1, 1} : GemvPlan{64, ceil_div(G, 2), 2, 1, 2};
+    if (turns > 0) return GemvPlan{64, ceil_div(G, turns), turns, 1, turns};
     const int turns16 = ceil_div(G, 4), turns32 = ceil_div(G, 2);
     const long blocks16 = 4 * tiles, blocks32 = 2 * tiles;
     const int rounds16 = ceil_div(blocks16, kCus), rounds32 = ceil_div(blocks32, kCus);
@@ -145,6 +152,18 @@ GemvPlan plan_of(int kind, long tiles, int G, int gpw_request, int waves_request
     //   8192 x 10240: 9.6 / 11.1 / 10.1 -> 8.5 / 10.0 / 9.9;  28672 x 8192: 18.5 / 22.6 / 21.5 -> 17.2 / 21.1 / 20.9;
     //   13824 x 5120: 8.7 / 10.0 / 9.7 -> 7.7 / 8.9 / 8.9;  8192 x 5120 by four and by eight: 5.7 and 5.9
     if (G <= 4 * kMaxGemvSlices && tiles * G <= 8192) return sliced(G, 64, 4, 1);
+    // With codebooks, and in 3 bits above 16384 channels, half as many slices of two tiles on their way once there are several
+    // rounds of workgroups.  us so and by the slices below, one tile a wavefront:
+    //   8192 x 30400 17.9 / 22.4 / 21.1 and 17.6 / 21.8 / 22.2;  14336 x 30400 28.7 / 37.5 / 33.4 and 27.9 / 35.9 / 36.5;
+    //   16512 x 8192 11.8 / 14.4 / 13.3 and 11.5 / 13.2 / 14.7;  20480 x 14336 20.9 / 25.3 / 23.9 and 20.3 / 24.4 / 26.0;
+    //   26752 x 30400 51.5 / 64.8 / 60.5 and 54.9 / 64.2 / 67.8;  16512 x 4096 8.0 / 9.3 / 9.1 and 7.5 / 8.3 / 8.9.
+    const long units = tiles * G;
+    const bool many_groups = G > 8 * kMaxGemvSlices;
+    if (kind == PACK_LUT3 ? units >= (many_groups ? 12 : 28) * kSimds : kind == PACK_U3 && many_groups && units >= 48 * kSimds) {
+        GemvPlan p = sliced(G, 64, 8, 2);
+        if (p.gpw == 2) p.depth = 2;
+        return p;
+    }
     if (G <= 8 * kMaxGemvSlices) {
         // More slices of fewer wavefronts, if all workgroups still start at one time (four per compute unit): 14336 x 4096 in
         // 14 and 16 slices 7.24 / 8.27 / 7.67 and 7.10 / 7.91 / 7.41 (8704 x 4096 in 9 and 14: 5.96 -> 5.74); in 16 slices of

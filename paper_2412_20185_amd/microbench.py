@@ -137,7 +137,8 @@ def gemvshape(args):
                 del g
                 us = prof["gemv"][0] * 1e3 / prof["gemv"][1]
                 acc = prof["accumulate"][0] * 1e3 / max(prof["accumulate"][1], 1)
-                per_tile = ws.gemv_launch_shape(K, N)[2]
+                _, _, columns, slices = ws.gemv_launch_shape_of(d)
+                per_tile = 64 // columns * slices
                 how = "plan" if wpb == 0 else "direct" if per_tile == 1 else "ink" if ink else "acc"
                 print(f"{model:4s} {name:8s} {tag:5s} {wpb:5d} {gpw:4d} {per_tile:8d} {how:>7s} {us:8.2f} {acc:7.2f} "
                       f"{call_us:8.2f} {nbytes / us / 1e3:10.0f} {nbytes / call_us / 1e3:10.0f}", flush=True)

@@ -143,17 +143,21 @@ def test_one_grid_of_many_rounds(bits, wfmt, K, N, place):
         ws.close()
 
 
-@pytest.mark.parametrize("K,N,launch", [
-    (1152, 16384, (256, 1024, 1)),   # nine groups by nine of 16 wavefronts
-    (2176, 32768, (512, 1024, 1)),   # 17 groups by nine wavefronts, the last with one
-    (4096, 28672, (448, 1024, 1)),   # two groups by each of 16
-    (3968, 28672, (448, 1024, 1)),   # 31 groups: the last wavefront with one
-    (2560, 40960, (2560, 512, 4)),   # 2.5 rounds of 64 columns: blocks of 16
-    (256, 43072, (673, 256, 1)),     # two groups: always blocks of 64, two of four wavefronts idle
-    (1024, 18176, (1136, 256, 4)),   # just above one round: blocks of 16
+@pytest.mark.parametrize("K,N,launches", [  # workgroups, threads, columns, K-slices; the same or in 3 bits, 4 bits, with codebooks
+    (1152, 16384, [(256, 1024, 64, 1)]),   # nine groups by nine of 16 wavefronts
+    (2176, 32768, [(512, 1024, 64, 1)]),   # 17 groups by nine wavefronts, the last with one
+    (4096, 28672, [(448, 1024, 64, 1)]),   # two groups by each of 16
+    (3968, 28672, [(448, 1024, 64, 1)]),   # 31 groups: the last wavefront with one
+    (2560, 40960, [(2560, 512, 16, 1)]),   # 2.5 rounds of 64 columns: blocks of 16
+    (1408, 47168, [(737, 512, 64, 1)]),    # 11 groups, two by each of six wavefronts
+    (256, 43072, [(673, 256, 64, 1)]),     # two groups: always blocks of 64, two of four wavefronts idle
+    (1024, 18176, [(1136, 256, 16, 1)]),   # just above one round: blocks of 16
+    (8320, 28288, [(3978, 512, 64, 9), (3978, 512, 64, 9), (2210, 512, 64, 5)]),        # codebooks: slices of two turns
+    (16640, 6208, [(1746, 512, 32, 9), (1746, 512, 32, 9), (873, 512, 64, 9)]),
+    (16640, 24256, [(3411, 512, 64, 9), (6822, 512, 32, 9), (3411, 512, 64, 9)]),       # in 3 bits too
 ])
 @pytest.mark.parametrize("bits,wfmt", [(3, dd.W_UNIFORM_G128), (4, dd.W_UNIFORM_G128), (3, dd.W_LUT_COL8)])
-def test_wide_matrices(bits, wfmt, K, N, launch):
+def test_wide_matrices(bits, wfmt, K, N, launches):
     """Matrices too large for the oracle: the plan's choice and K-slices added by atomics against sums in fp64."""
     desc, Wq, scales, zl, x, W_hat = random_layer(K, N, bits, wfmt)
     exact, mass = x.double() @ W_hat.double(), x.double().abs() @ W_hat.double().abs()
@@ -162,7 +166,9 @@ def test_wide_matrices(bits, wfmt, K, N, launch):
         mass += (scales.double() * (2 ** bits + zl.double().abs())).repeat_interleave(128, 0).mul_(x.double().abs()[:, None]).sum(0)
     ws = dd.Workspace(K, N, 1)
     try:
-        assert ws.gemv_launch_shape(K, N) == launch
+        launch = launches[-1 if wfmt == dd.W_LUT_COL8 else (bits - 3) % len(launches)]
+        assert ws.gemv_launch_shape_of(desc) == launch
+        assert (bits, wfmt) != (3, dd.W_UNIFORM_G128) or ws.gemv_launch_shape(K, N) == launch[:2] + (64 // launch[2] * launch[3],)
         for waves in (0, 4):
             ws.set_gemv_waves(waves)
             y = torch.full((N,), float("nan"), dtype=torch.float16, device="cuda")

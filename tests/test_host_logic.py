@@ -79,6 +79,7 @@ def test_validation_without_gpu():
     with pytest.raises(dd.DecdecError):
         dd.decdec_pack_residual_int4(np.full((4, 64), -8, np.int8))
     assert L.decdec_ws_gemv_launch_shape(None, 4096, 4096, None, None, None) == -1
+    assert L.decdec_ws_gemv_launch_shape_of(None, C.byref(good), 4096, None, None, None, None) == -1
     h = C.c_void_p()
     assert L.decdec_ws_create(0, 64, 0, C.byref(h)) == -1
     assert L.decdec_ws_create(128, 64, 129, C.byref(h)) == -1
@@ -213,20 +214,19 @@ def _gemv_plan(*args):
 
 def test_every_plan_of_the_base_gemv_is_one_its_kernels_can_run():
     """All of K is covered, by no more slices than the accumulators count and none without work; the blocks and wavefronts are
-    those that kernels exist for; a grid has fewer than 2^32 threads at any number of columns; and what the library does by
-    itself does not follow from the format, which the query of the launch shape does not know."""
+    those that kernels exist for; and a grid has fewer than 2^32 threads at any number of columns."""
     rng = np.random.default_rng(3)
     tiles = sorted({*range(1, 70), *range(250, 260), *range(440, 520, 3), *np.exp(rng.uniform(0, np.log(1 << 23), 60)).astype(int).tolist(),
                     1 << 21, (1 << 22) + 1, (1 << 23) - 1})
     groups = sorted({*range(1, 40), *range(60, 70), *range(120, 140), 224, 255, 256, 257, 448, 512})
-    # (groups per wavefront, wavefronts, one grid, over the link); the format only decides between equal results
+    # (groups per wavefront, wavefronts, one grid, over the link)
     asked = [(0, 0, False, False), (1, 0, False, False), (2, 0, False, False), (5, 0, False, False), (1024, 0, False, False),
              (0, 4, False, False), (0, 16, False, False), (3, 8, False, False), (0, 0, True, False), (0, 0, True, True), (2, 0, True, True)]
     for t in tiles:
         for G in groups:
             for gpw, waves, one_grid, link in asked:
-                ps = [_gemv_plan(kind, int(t), G, gpw, waves, one_grid, link) for kind in range(3)]
-                for p in ps:
+                for kind in range(3):
+                    p = _gemv_plan(kind, int(t), G, gpw, waves, one_grid, link)
                     what = (t, G, gpw, waves, one_grid, p.cols, p.waves, p.gpw, p.slices, p.depth)
                     each = p.waves * p.gpw * (64 // p.cols)     # groups of a workgroup
                     assert p.cols in (16, 32, 64) and 1 <= p.waves <= 16 and 1 <= p.slices <= 16, what
@@ -234,11 +234,9 @@ def test_every_plan_of_the_base_gemv_is_one_its_kernels_can_run():
                     threads = 256 if p.waves <= 4 else 512 if p.waves <= 8 else 1024
                     assert t * (64 // p.cols) * p.slices * threads < 1 << (31 if one_grid and t < 1 << 22 else 32), what
                     assert p.depth == 1 or (p.cols == 64 and not one_grid and p.gpw > 1), what
-                    assert p.depth in (1, 4) or (p.depth == 2 and threads == 1024 and p.gpw == 2), what
+                    assert p.depth in (1, 4) or (p.depth == 2 and threads >= 512 and p.gpw == 2), what
                     if one_grid:
                         assert p.cols == 64 and p.waves == 8, what
-                if not one_grid:
-                    assert len({(p.cols, p.waves, p.gpw, p.slices) for p in ps}) == 1, what
 
 
 def test_scale_search_whose_grid_fits():
