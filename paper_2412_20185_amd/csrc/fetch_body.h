@@ -47,7 +47,7 @@ struct Selection {
 
 template <int SELECT_NCH>
 __device__ __forceinline__ Selection obtain_selection(const uint4* keys, int K, int k, int32_t* idx_g, uint16_t* xsel_g,
-                                                      SelectShared& sh, int bid) {
+                                                      SelectShared<kBlockThreads, SELECT_NCH>& sh, int bid) {
     if constexpr (SELECT_NCH > 0) {
         extern __shared__ uint4 s_sel_raw[];  // int32 idx[k], then fp16 xsel[k]
         int32_t* idx_l = reinterpret_cast<int32_t*>(s_sel_raw);
@@ -125,10 +125,10 @@ template <int BITS>
 constexpr int kLoadRows = 64 / (kFetchSegmentCols / kLaneCols<BITS>);  // rows a wavefront loads with one instruction
 
 // The selection and the sum over the wavefronts follow one another and share their LDS.
-template <int BITS>
+template <int BITS, int SELECT_NCH>
 union FetchLds {
     float red[kWavesPerBlock * kLoadRows<BITS>][kFetchSegmentCols];
-    SelectShared sh;
+    SelectShared<kBlockThreads, SELECT_NCH> sh;
     __device__ FetchLds() {}
 };
 
@@ -152,7 +152,7 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     constexpr int LPR = kFetchSegmentCols / CPL;        // lanes that cover the segment's part of one row
     constexpr int UNROLL = (4096 / 64) / (int)sizeof(piece_t);  // loads in flight per lane: 4 KiB per wavefront
     static_assert(kBlockThreads == kFetchSegmentCols, "one thread per column of the segment");
-    __shared__ FetchLds<BITS> lds;
+    __shared__ FetchLds<BITS, SELECT_NCH> lds;
     auto& red = lds.red;
 
     const int tid = threadIdx.x;

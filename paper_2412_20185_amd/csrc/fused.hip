@@ -100,8 +100,9 @@ unsigned one_grid_lds(int kind, int rbits, int nch, int k, long base_workgroups,
     static_assert(3 * kLdsOfThree <= kCuLds && 4 * kLdsOfThree > kCuLds, "three workgroups");
     static_assert(2 * kLdsOfTwo <= kCuLds && 3 * kLdsOfTwo > kCuLds, "two workgroups");
     constexpr unsigned kGemvLds = sizeof(float) * kWavesPerBlock * kOneGridCols;
-    constexpr unsigned kStatic = sizeof(FetchLds<16>) + kGemvLds, kStatic2 = sizeof(FetchLds<2>) + kGemvLds;
-    static_assert(sizeof(FetchLds<16>) == sizeof(FetchLds<8>) && sizeof(FetchLds<16>) == sizeof(FetchLds<4>), "one size");
+    constexpr unsigned kStatic = sizeof(FetchLds<16, 2>) + kGemvLds, kStatic2 = sizeof(FetchLds<2, 2>) + kGemvLds;
+    static_assert(sizeof(FetchLds<16, 2>) == sizeof(FetchLds<8, 2>) && sizeof(FetchLds<16, 2>) == sizeof(FetchLds<4, 2>) &&
+                  sizeof(FetchLds<16, 2>) == sizeof(FetchLds<16, 4>) && sizeof(FetchLds<2, 2>) == sizeof(FetchLds<2, 4>), "one size");
     const unsigned lds = selection_lds_bytes(nch, k);
     if (!over_link || (nch != 2 && nch != 4)) return lds;
     if (rbits == 2) return 2 * base_workgroups <= 5 * kCus ? std::max(lds, kLdsOfTwo - kStatic2) : lds;

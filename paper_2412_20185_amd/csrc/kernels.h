@@ -120,6 +120,12 @@ __device__ __forceinline__ void hold_scalar(T*& p) {
     p = (T*)global;
 }
 
+// What the lanes of a wavefront have written to LDS is there for its other lanes.
+__device__ __forceinline__ void wave_writes_seen() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // gemv.hip ---------------------------------------------------------------
 // How the work is cut: a wavefront takes `cols` columns (16, 32 or 64) of 64 / cols groups of 128 input channels at a time,
 // `gpw` times, the tiles of `depth` turns on their way at one time (1, 2 or kDeepTiles; more than 1 with 64 columns only);

@@ -160,12 +160,6 @@ __device__ __forceinline__ double wave_min(double v) {
     return v;
 }
 
-// What the lanes of a wavefront have written to LDS is there for its other lanes.
-__device__ __forceinline__ void wave_writes_seen() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 constexpr int kScaleRows = 128;   // rows of a column block staged in LDS at a time
 constexpr int kMaxSlots = 80;     // threads that share a column's candidates x candidates per thread, at most
 

@@ -3,7 +3,7 @@
 // own.  The paper's kernel uses an approximate, chunked bucket Top-K (Section
 // 4.3); this is the exact Top-K it uses as its quality reference (Section 5.2).
 // The algorithm is in select_block.h; one workgroup does the whole selection
-// (one chunk of 8 channels per thread up to 8192 channels, 1024 threads above).
+// (one chunk of 8 channels per thread up to 4096 channels, two to eight above).
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
@@ -16,7 +16,7 @@ template <int THREADS, int NCH, bool RADIX = false>
 __global__ __launch_bounds__(THREADS) void select_topk_kernel(const uint16_t* __restrict__ x, int K, int k,
                                                              int32_t* __restrict__ idx_out,
                                                              uint16_t* __restrict__ xsel_out) {
-    __shared__ SelectShared sh;
+    __shared__ SelectShared<THREADS, NCH> sh;
     uint4 ch[NCH];
     load_keys(x, K, ch);
     block_select_topk<THREADS, NCH, RADIX>(ch, K, k, sh, idx_out, xsel_out);
@@ -32,17 +32,17 @@ hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, voi
     // one chunk of 8 channels per thread as long as that gives enough threads: no list of chunks is needed then
     if (K <= 2048) return launch_kernel(tm, select_topk_kernel<256, 1>, one, dim3(256), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 4096) return launch_kernel(tm, select_topk_kernel<512, 1>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
-    if (K <= 8192) return launch_kernel(tm, select_topk_kernel<1024, 1>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
-    // Above, a k too large for the chunk form has a kernel without it, with its marked keys' words chosen by comparisons
-    // (select_block.h).  us, the kernel with both forms -> without: K = 14336, k = 1433: 7.24 -> 7.14; 28672, 2867:
-    // 11.53 -> 11.40; 32768, 3276: 12.14 -> 11.98.  Up to 8192 the two take the same, or this one 0.02 more.
+    // Above, by chunks with eight wavefronts (select_block.h); a k too large for the chunk form has 1024 threads, and above 8192
+    // channels a kernel without that form, with its marked keys' words chosen by comparisons.  us, the kernel with both forms
+    // -> without: K = 14336, k = 1433: 7.24 -> 7.14; 28672, 2867: 11.53 -> 11.40; 32768, 3276: 12.14 -> 11.98.  Up to 8192 the
+    // two take the same, or this one 0.02 more.
     const bool radix = !select_tries_chunks(K / 8, k);
-    if (K <= 16384)
-        return launch_kernel(tm, radix ? select_topk_kernel<1024, 2, true> : select_topk_kernel<1024, 2>, one, dim3(1024), 0, stream,
-                             xp, K, k, idx_out, xs);
-    if (K <= 32768)
-        return launch_kernel(tm, radix ? select_topk_kernel<1024, 4, true> : select_topk_kernel<1024, 4>, one, dim3(1024), 0, stream,
-                             xp, K, k, idx_out, xs);
+    if (!radix && K <= 8192) return launch_kernel(tm, select_topk_kernel<512, 2>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
+    if (!radix && K <= 16384) return launch_kernel(tm, select_topk_kernel<512, 4>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
+    if (!radix && K <= 32768) return launch_kernel(tm, select_topk_kernel<512, 8>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
+    if (K <= 8192) return launch_kernel(tm, select_topk_kernel<1024, 1>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
+    if (K <= 16384) return launch_kernel(tm, select_topk_kernel<1024, 2, true>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
+    if (K <= 32768) return launch_kernel(tm, select_topk_kernel<1024, 4, true>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
     return launch_kernel(tm, radix ? select_topk_kernel<1024, 8, true> : select_topk_kernel<1024, 8>, one, dim3(1024), 0, stream,
                          xp, K, k, idx_out, xs);
 }

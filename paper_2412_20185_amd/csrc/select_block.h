@@ -13,47 +13,58 @@
 // runs on, so few instructions may touch every key.  Two forms:
 //
 //   chunks (select_by_chunks), when k is at most a third of the number of chunks
-//   and at most 576 (beyond, the bound is too low to exclude much, and the list
-//   may not hold the chunks): k chunks hold a key at least as large as the k-th
-//   largest chunk maximum, so that is a lower bound of the k-th largest key.
+//   and at most 576 (beyond, the bound is too low to exclude much): k chunks
+//   hold a key at least as large as the k-th largest chunk maximum, so that is a
+//   lower bound of the k-th largest key.
 //     1. chunk maxima by packed 16-bit maxima; a 256-bin LDS histogram of their
 //        high 8 bits gives the bin that holds the k-th largest; its lower edge L
 //        is the bound;
-//     2. chunks with a maximum >= L, little more than k, go to an LDS list in
-//        order, one or a few per thread (left out when every thread has one chunk);
+//     2. every wavefront lists its chunks with a maximum >= L, in order, in its
+//        own part of an LDS list and takes them back one or two per lane (left out
+//        when every thread has one chunk), so that no barrier and no sum over
+//        wavefronts stands in front of the next step;
 //     3. a 256-bin LDS histogram of key - L over their keys gives T, the k-th
 //        largest key itself, and how many keys equal to T are needed; only when
 //        T >= L + 255 (large |x| crowded into few chunks) it is formed twice more,
 //        over 128-key bins and inside the bin that holds T;
 //     4. masks of the keys > T and == T and one prefix sum place every selected
 //        element.
-//   radix (select_by_radix), for larger k, or when more than kMaxListed chunks
-//   reach L (many equal keys): LDS histograms of all keys over their high 8 and
-//   low 7 bits, then masks and prefix sums over every key.
-// Stand-alone kernel in graph replays, radix for every key -> chunks, us: K = 1024, k = 32: 3.4 -> 2.6; 4096, 60:
-// 3.7 -> 3.1; 8192, 81: 5.4 -> 4.1; 14336, 286: 6.3 -> 4.6; 28672, 286: 9.8 -> 5.3.  With k = 400 of 4096 the bound
-// is so low that the chunks took 5.4 against 3.5 for radix; with k = 1433 of 28672 the list overflowed.
+//   radix (select_by_radix), for larger k, or when more than kListedPerWave chunks
+//   of a wavefront reach L (many equal keys): LDS histograms of all keys over their
+//   high 8 and low 7 bits, then masks and prefix sums over every key.
+// Stand-alone kernel in graph replays, radix for every key -> chunks, us: K = 1024, k = 32: 3.4 -> 2.7; 4096, 60:
+// 3.7 -> 3.2; 8192, 81: 5.4 -> 3.6; 14336, 286: 6.3 -> 4.2; 28672, 286: 9.8 -> 4.8.  One list for all wavefronts, which
+// takes two barriers and a sum over them, took 4.2, 4.6 and 5.4 (K = 8192 up), of 1024 threads; the lists of sixteen
+// wavefronts 4.3, 4.8 and 5.4, because each of them issues the steps 3 and 4 for a quarter of its lanes only.  With k = 400 of 4096 the bound
+// is so low that the chunks took 5.4 against 3.5 for radix.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "kernels.h"
+
 namespace decdec {
 
 constexpr int kSelectMaxChunks = 8;  // 8-key chunks per thread at most
 
-constexpr int kMaxListed = 1024;     // chunks with a key that may be selected
 constexpr int kMaxByChunks = 576;    // the bin of L alone can make the list 1.77 times as long as k (|x| normal, k 1 % of K)
+// Chunks of a wavefront with a key that may be selected.  Of 1020 such chunks in all, each of eight wavefronts has 128 +- 10.
+template <int THREADS, int NCH>
+constexpr int kListedPerWave = THREADS <= 512 && NCH == 8 ? 192 : 128;
 
 __host__ __device__ inline bool select_tries_chunks(int nchunks, int k) { return 3 * k <= nchunks && k <= kMaxByChunks; }
 
 // LDS of the selection; nothing in it is needed afterwards, so it may share its place with other data.
+template <int THREADS, int NCH>
 struct SelectShared {
-    uint4 list[kMaxListed];
-    uint16_t list_chunk[kMaxListed];
+    static constexpr int kListed = NCH <= 1 ? 1 : THREADS / 64 * kListedPerWave<THREADS, NCH>;
+    uint4 list[kListed];
+    uint16_t list_chunk[kListed];
     __attribute__((aligned(16))) unsigned hist1[256];
     __attribute__((aligned(16))) unsigned hist2[256];
-    __attribute__((aligned(16))) unsigned wtot[2][16];  // per wave: listed chunks; (keys > T) | (keys == T) << 16
+    __attribute__((aligned(16))) unsigned wtot[16];  // per wave: (keys > T) | (keys == T) << 16
+    int overflow;                                     // 1: a wavefront's list is too short
 };
 
 template <int CTRL, int ROW_MASK, bool BOUND_CTRL>
@@ -150,16 +161,16 @@ __device__ __forceinline__ unsigned lanes_before(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
 }
 
-// Sum of the waves' totals in front of `wave`, and of all of them.
+// Sum of the waves' totals in front of `wave`.
 template <int WAVES>
-__device__ __forceinline__ void totals_before(const unsigned* wtot, int wave, unsigned& before, unsigned& all) {
-    before = all = 0;
+__device__ __forceinline__ unsigned totals_before(const unsigned* wtot, int wave) {
+    unsigned before = 0;
 #pragma unroll
     for (int w = 0; w < WAVES; w += 4) {
         const uint4 t = *reinterpret_cast<const uint4*>(wtot + w);
         before += (w < wave ? t.x : 0u) + (w + 1 < wave ? t.y : 0u) + (w + 2 < wave ? t.z : 0u) + (w + 3 < wave ? t.w : 0u);
-        all += t.x + t.y + t.z + t.w;
     }
+    return before;
 }
 
 // Writes the marked keys of one chunk: all of `gt`, of `eq` those with fewer than `need` equal keys in front.
@@ -203,13 +214,14 @@ __device__ __forceinline__ void mark_chunk(const uint4& c, unsigned T, unsigned&
     eq = mark_above(c, T - 1) & ~gt;
 }
 
-// Requires 1 <= k <= nchunks and sh.hist1, sh.hist2 cleared (with a barrier behind).  False, in all threads, when the
-// chunks do not give the selection: nothing has been written to the outputs then.
+// Requires 1 <= k <= nchunks and sh.hist1, sh.hist2, sh.overflow cleared (with a barrier behind).  False, in all threads, when
+// the chunks do not give the selection: nothing has been written to the outputs then.
 template <int THREADS, int NCH>
-__device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared& sh,
+__device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared<THREADS, NCH>& sh,
                                                  int32_t* idx_out, uint16_t* xsel_out) {
     constexpr int WAVES = THREADS / 64;
-    constexpr int PER = NCH == 1 ? 1 : (kMaxListed + THREADS - 1) / THREADS;  // listed chunks per thread at most
+    constexpr int LIST = kListedPerWave<THREADS, NCH>;
+    constexpr int PER = NCH == 1 ? 1 : LIST / 64;  // listed chunks per lane at most
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c0 = wave * 64 * NCH + lane;
@@ -228,45 +240,47 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
 
     uint4 mine[PER];
     int chunk[PER];
+    unsigned listed = 64;  // chunks of this wavefront
     if constexpr (NCH == 1) {
         mine[0] = ch[0];
         chunk[0] = c0;
     } else {
-        unsigned at[NCH], total = 0;
+        uint4* list = sh.list + wave * LIST;
+        uint16_t* list_chunk = sh.list_chunk + wave * LIST;
+        listed = 0;
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             const unsigned long long b = __ballot(cm[j] >= L);
-            at[j] = total + lanes_before(b);
-            total += (unsigned)__builtin_popcountll(b);
-        }
-        if (lane == 0) sh.wtot[0][wave] = total;
-        __syncthreads();
-        unsigned before, listed;
-        totals_before<WAVES>(sh.wtot[0], wave, before, listed);
-        listed = (unsigned)__builtin_amdgcn_readfirstlane((int)listed);
-        if (listed > (unsigned)kMaxListed) return false;
-#pragma unroll
-        for (int j = 0; j < NCH; ++j) {
-            if (cm[j] >= L) {
-                sh.list[before + at[j]] = ch[j];
-                sh.list_chunk[before + at[j]] = (uint16_t)(c0 + 64 * j);
+            const unsigned at = listed + lanes_before(b);
+            if (cm[j] >= L && at < (unsigned)LIST) {
+                list[at] = ch[j];
+                list_chunk[at] = (uint16_t)(c0 + 64 * j);
             }
+            listed += (unsigned)__builtin_popcountll(b);
         }
-        __syncthreads();
-        const int per = (int)(listed + THREADS - 1) / THREADS;
+        if (NCH * 64 > LIST && listed > (unsigned)LIST) {
+            if (lane == 0) sh.overflow = 1;
+            listed = LIST;
+        }
+        wave_writes_seen();
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
-            const int i = tid * per + p;
-            const bool have = p < per && i < (int)listed;
-            mine[p] = have ? sh.list[i] : make_uint4(0, 0, 0, 0);  // keys below L: never taken
-            chunk[p] = have ? sh.list_chunk[i] : 0;
+            const unsigned i = 64 * p + lane;
+            mine[p] = make_uint4(0, 0, 0, 0);  // keys below L: never taken
+            chunk[p] = 0;
+            if (i < listed) {
+                mine[p] = list[i];
+                chunk[p] = list_chunk[i];
+            }
         }
     }
+
     unsigned T = L;
     int shift = 0;  // bins of 2^shift keys from T on; the last one takes everything above
     while (true) {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
+            if (64u * p >= listed) break;  // wave-uniform
             unsigned m = mark_above(mine[p], T - 1);
             while (m) {
                 atomicAdd(&sh.hist2[min((key_of(mine[p], __builtin_ctz(m)) - T) >> shift, 255u)], 1u);
@@ -274,6 +288,7 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
             }
         }
         __syncthreads();
+        if (NCH * 64 > LIST && __builtin_amdgcn_readfirstlane(sh.overflow)) return false;
         wave_find_bin<4>(sh.hist2, (unsigned)k, bin, need, lane);  // need: keys equal to T to take (>= 1) in the end
         T += bin << shift;
         if (shift == 0 && bin < 255) break;
@@ -283,29 +298,32 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
         __syncthreads();
     }
 
-    unsigned gt[PER], eq[PER], cnt = 0;
+    unsigned gt[PER], eq[PER], at[PER], total = 0;  // at: marked keys of this wavefront in front of the chunk's
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
+        gt[p] = eq[p] = at[p] = 0;
+        if (64u * p >= listed) break;
         mark_chunk(mine[p], T, gt[p], eq[p]);
-        cnt += (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
+        const unsigned cnt = (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
+        const unsigned incl = wave_incl_scan(cnt) + total;
+        at[p] = incl - cnt;
+        total = PER == 1 ? incl : (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    const unsigned incl = wave_incl_scan(cnt);
-    if (lane == 63) sh.wtot[1][wave] = incl;
+    if (lane == 63) sh.wtot[wave] = total;
     __syncthreads();
-    unsigned before, all;
-    totals_before<WAVES>(sh.wtot[1], wave, before, all);  // no carry between the halves: at most 8192 marked keys
-    before += incl - cnt;
+    const unsigned before = totals_before<WAVES>(sh.wtot, wave);  // no carry between the halves: at most 16384 marked keys
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-        write_marked(mine[p], chunk[p] * 8, gt[p], eq[p], before & 0xFFFFu, before >> 16, need, (unsigned)k, idx_out, xsel_out);
-        before += (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
+        if (64u * p >= listed) break;
+        write_marked(mine[p], chunk[p] * 8, gt[p], eq[p], (before + at[p]) & 0xFFFFu, (before + at[p]) >> 16, need, (unsigned)k,
+                     idx_out, xsel_out);
     }
     return true;
 }
 
 // Any 1 <= k <= K.  Requires sh.hist1, sh.hist2 cleared (with a barrier behind).  MANY: many keys per chunk are marked.
 template <int THREADS, int NCH, bool MANY = false>
-__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared& sh,
+__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared<THREADS, NCH>& sh,
                                                 int32_t* idx_out, uint16_t* xsel_out) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c0 = wave * 64 * NCH + lane;  // this thread's chunk of round j is c0 + 64*j
@@ -358,12 +376,12 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
         excl[j] = wave_cnt + incl - cnt;
         wave_cnt += (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    if (lane == 0) sh.wtot[0][wave] = wave_cnt;
+    if (lane == 0) sh.wtot[wave] = wave_cnt;
     __syncthreads();
     unsigned base_gt = 0, base_eq = 0;  // marked keys of the wavefronts before this one
 #pragma unroll
     for (int w = 0; w < THREADS / 64; ++w) {
-        const unsigned t = sh.wtot[0][w];
+        const unsigned t = sh.wtot[w];
         base_gt += w < wave ? (t & 0xFFFFu) : 0u;
         base_eq += w < wave ? (t >> 16) : 0u;
     }
@@ -388,12 +406,13 @@ __device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, int K,
 // written but not yet synchronised (the caller adds the barrier it needs).  RADIX: the caller knows that
 // select_tries_chunks(K / 8, k) is false.
 template <int THREADS, int NCH, bool RADIX = false>
-__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, int k, SelectShared& sh,
+__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, int k, SelectShared<THREADS, NCH>& sh,
                                                   int32_t* idx_out, uint16_t* xsel_out) {
     static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
     const int tid = threadIdx.x, nchunks = K / 8;
     const auto clear = [&] {
         for (int i = tid; i < 256; i += THREADS) sh.hist1[i] = sh.hist2[i] = 0;
+        if (NCH * 64 > kListedPerWave<THREADS, NCH> && tid == 0) sh.overflow = 0;
         __syncthreads();
     };
     clear();
