@@ -689,6 +689,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     a.k = k;
     a.cslices = cslices;
     a.row_waves = plan.row_waves;
+    a.rows_per = k > 0 ? (k + cslices * plan.row_waves - 1) / (cslices * plan.row_waves) : 0;
     a.cdiv = reciprocal_of(cslices);
     a.nfetch = plan.segments * plan.slices;
     a.cpart = c.cpart;

@@ -186,7 +186,18 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     hold_scalar(y);
     hold_scalar(acc_words);
 
+    const int ocol = wc * kFetchSegmentCols + tid;  // the column this thread owns after the LDS round
+    const bool owns = ocol < N;
+    // The column scale is requested in front of the selection and first touched (hold_vector) behind the rows.  Converted where
+    // it is loaded, as the compiler has it, it is waited for in front of the first row request: us, before -> now: 4096 x 28672,
+    // 60 4-bit rows 22.8 -> 21.8; 14336 x 4096, 56 8-bit rows 11.4 -> 11.0; 210 8-bit rows in GPU memory 8.4 -> 7.9.  (With eight
+    // chunks of keys per thread there is no register for it during the selection.)
+    constexpr bool kScaleFirst = SELECT_NCH < 8;
+    uint32_t sraw = 0;
+    if constexpr (BITS != 16 && kScaleFirst) sraw = Rs[min(ocol, N - 1)];
+
     const Selection sel = obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid);
+    if constexpr (BITS != 16 && !kScaleFirst) sraw = Rs[min(ocol, N - 1)];
     const int32_t* idx = sel.idx;
     const uint16_t* xsel = sel.xsel;
     const piece_t* __restrict__ R = reinterpret_cast<const piece_t*>(rows_base);
@@ -195,18 +206,10 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     const bool active = piece * CPL < N;
     const size_t row_pieces = (size_t)(N / CPL);
     // rows of this wavefront: slice (rs, wave) out of slices * row_waves equal shares of the k selected rows
-    const int rows_per = (k + slices * row_waves - 1) / (slices * row_waves);
+    const int rows_per = a.rows_per;
     const int j0 = min((rs * row_waves + wave) * rows_per, k);
     const int j1 = wave < row_waves ? min(j0 + rows_per, k) : j0;
 
-    const int ocol = wc * kFetchSegmentCols + tid;  // the column this thread owns after the LDS round
-    const bool owns = ocol < N;
-    // The column scale is requested before the rows, so that it arrives behind the first row loads instead
-    // of costing a round trip of its own after the last one.
-    uint16_t sraw = 0;
-    if constexpr (BITS != 16) {
-        if (owns) sraw = Rs[ocol];
-    }
 
     float acc[CPL];
 #pragma unroll
@@ -271,7 +274,10 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
 #pragma unroll
     for (int w = 1; w < kWavesPerBlock * SUB; ++w)
         if (w < row_waves * SUB) val += red[w][tid];  // wave-uniform
-    if constexpr (BITS != 16) val *= h2f(sraw);
+    if constexpr (BITS != 16) {
+        hold_vector(sraw);
+        val *= h2f(sraw);
+    }
 
     if (owns) {
         if (acc_words != nullptr) {

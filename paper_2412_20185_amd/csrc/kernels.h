@@ -87,6 +87,7 @@ struct CallArgs {
     float* gpart;             // fp32 [gslices][Ntot]   (acc == null only)
     int k;
     int cslices, row_waves;   // workgroups per column segment, wavefronts of each that share its rows
+    int rows_per;             // rows of each of these wavefronts, rounded up
     unsigned cdiv;            // reciprocal_of(cslices)
     int nfetch;               // workgroups of the residual part of the one-grid kernel
     int32_t* idx;             // the selection: written by the kernel that selects, read by the others
