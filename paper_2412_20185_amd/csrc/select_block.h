@@ -32,11 +32,13 @@
 //   radix (select_by_radix), for larger k, or when more than kListedPerWave chunks
 //   of a wavefront reach L (many equal keys): LDS histograms of all keys over their
 //   high 8 and low 7 bits, then masks and prefix sums over every key.
+// Every phase is a chain of dependent instructions of a few wavefronts, about 2 ns each, and of LDS trips (with all of its
+// instructions in the cache it takes the same time): finding a bin and marking keys take as few as they can.
 // Stand-alone kernel in graph replays, radix for every key -> chunks, us: K = 1024, k = 32: 3.4 -> 2.7; 4096, 60:
-// 3.7 -> 3.2; 8192, 81: 5.4 -> 3.6; 14336, 286: 6.3 -> 4.2; 28672, 286: 9.8 -> 4.8.  One list for all wavefronts, which
-// takes two barriers and a sum over them, took 4.2, 4.6 and 5.4 (K = 8192 up), of 1024 threads; the lists of sixteen
-// wavefronts 4.3, 4.8 and 5.4, because each of them issues the steps 3 and 4 for a quarter of its lanes only.  With k = 400 of 4096 the bound
-// is so low that the chunks took 5.4 against 3.5 for radix.
+// 3.7 -> 3.0; 8192, 81: 5.4 -> 3.4; 14336, 286: 6.3 -> 3.9; 28672, 286: 9.8 -> 4.6.  One list for all wavefronts, which
+// takes two barriers and a sum over them, took 0.5 more (K = 8192 up) of 1024 threads; the lists of sixteen wavefronts 0.6 more
+// than those of eight, because each of them issues the steps 3 and 4 for a quarter of its lanes only.  With k = 400 of 4096
+// the bound is so low that the chunks took 5.4 against 3.5 for radix.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -88,7 +90,8 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
 // in the bins from it up; returns it and kk - (entries above it) in every lane.
 template <int PER>
 __device__ __forceinline__ void wave_find_bin(const unsigned* hist, unsigned kk, unsigned& bin, unsigned& rem, int lane) {
-    unsigned c[PER], tot = 0;
+    static_assert(PER == 4 || PER == 2, "bins per lane");
+    unsigned c[PER];
     if constexpr (PER == 4) {
         const uint4 v = reinterpret_cast<const uint4*>(hist)[lane];
         c[0] = v.x;
@@ -96,27 +99,28 @@ __device__ __forceinline__ void wave_find_bin(const unsigned* hist, unsigned kk,
         c[2] = v.z;
         c[3] = v.w;
     } else {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) c[j] = hist[lane * PER + j];
+        const uint2 v = reinterpret_cast<const uint2*>(hist)[lane];
+        c[0] = v.x;
+        c[1] = v.y;
     }
+    unsigned from[PER];  // entries in the lane's bins from this one up
+    from[PER - 1] = c[PER - 1];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) tot += c[j];
-    const unsigned incl = wave_incl_scan(tot);
-    unsigned above = (unsigned)__builtin_amdgcn_readlane((int)incl, 63) - incl;  // entries above this lane's bins
-    const bool found = above < kk && kk <= above + tot;
-    unsigned b_l = 0, r_l = 1;
+    for (int j = PER - 2; j >= 0; --j) from[j] = from[j + 1] + c[j];
+    const unsigned incl = wave_incl_scan(from[0]);
+    const unsigned above = (unsigned)__builtin_amdgcn_readlane((int)incl, 63) - incl;  // entries above this lane's bins
+    const unsigned want = kk - above;  // of the lane's own entries; 0 or "negative" where the bins above have enough
+    const unsigned long long mask = __ballot(want - 1u < from[0]);  // one lane unless the histogram is short of kk entries
+    unsigned b_l = (unsigned)(lane * PER + PER - 1), over = 0;  // over: entries of the lane above its bin
 #pragma unroll
-    for (int j = PER - 1; j >= 0; --j) {
-        if (above < kk && kk <= above + c[j]) {
-            b_l = (unsigned)(lane * PER + j);
-            r_l = kk - above;
-        }
-        above += c[j];
+    for (int j = PER - 1; j >= 1; --j) {
+        const bool below = from[j] < want;
+        b_l -= below;
+        over = below ? from[j] : over;
     }
-    const unsigned long long mask = __ballot(found);  // exactly one lane unless the histogram is short of kk entries
     const int src = mask ? __builtin_ctzll(mask) : 0;
     bin = (unsigned)__builtin_amdgcn_readlane((int)b_l, src);
-    rem = (unsigned)__builtin_amdgcn_readlane((int)r_l, src);
+    rem = (unsigned)__builtin_amdgcn_readlane((int)(want - over), src);
 }
 
 // Word e / 2 of a chunk, by its bits or (MANY) by comparisons: the former is the quicker one where few keys of a chunk are
@@ -194,18 +198,17 @@ __device__ __forceinline__ void write_marked(const uint4& c, int channel0, unsig
     }
 }
 
-// Bit e: key e of the chunk is > below, by packed saturating subtractions (the selection runs once per launch, so
-// its instructions come cold from memory: fewer of them count for more than their issue time).
+// Bit e: key e of the chunk is > below (below <= 0x7FFF), two keys at a time: with the sign bits set, no half borrows from the
+// other, and a half's sign bit stays where its key is large enough.  (Packed saturating subtractions and minima become
+// comparisons, selects and byte permutes in the compiler's hands, half as many instructions again.)
 __device__ __forceinline__ unsigned mark_above(const uint4& c, unsigned below) {
-    const ushort2_t lim = __builtin_bit_cast(ushort2_t, below * 0x10001u), one = {1, 1};
-    const unsigned w[4] = {c.x & 0x7FFF7FFFu, c.y & 0x7FFF7FFFu, c.z & 0x7FFF7FFFu, c.w & 0x7FFF7FFFu};
-    unsigned m = 0;  // bits 2 i and 16 + 2 i: the two keys of word i
+    constexpr unsigned kSigns = 0x80008000u;
+    const unsigned lim = (below + 1) * 0x10001u;
+    const unsigned w[4] = {c.x, c.y, c.z, c.w};
+    unsigned m = 0;
 #pragma unroll
-    for (int i = 3; i >= 0; --i) {
-        const ushort2_t over = __builtin_elementwise_sub_sat(__builtin_bit_cast(ushort2_t, w[i]), lim);
-        m = (m << 2) | __builtin_bit_cast(unsigned, __builtin_elementwise_min(over, one));
-    }
-    return (m | (m >> 15)) & 0xFFu;
+    for (int i = 0; i < 4; ++i) m = (m >> 2) | (((w[i] | kSigns) - lim) & kSigns);
+    return ((m >> 9) | (m >> 24)) & 0xFFu;  // bits 9 + 2 i and 25 + 2 i: the two keys of word i
 }
 
 // Bit e of gt / eq: key e of the chunk is > T / == T (T >= 1).
