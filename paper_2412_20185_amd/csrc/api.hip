@@ -654,7 +654,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED;
     const GemvPlan gp = gemv_plan(kind, tiles, sh.K / kGroup, c.gemv_gpw, c.gemv_wpb, fused, !residuals_in_hbm);
     const int gslices = gp.slices;
-    FetchPlan plan{0, 0, 0};
+    FetchPlan plan{0, 0, 0, 0};
     if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm);
     const int cslices = plan.slices;
 
@@ -722,6 +722,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
                 a.idx = c.idx;
                 a.xsel = static_cast<uint16_t*>(c.xsel);
                 select_chunks = c.separate_select ? 0 : fetch_select_chunks(sh.K, k);
+                a.early = select_chunks > 0 ? plan.early : 0;
                 if (select_chunks == 0) {
                     DD_HIP(launch_select_topk(x, sh.K, k, c.idx, c.xsel, comp, tm[1]));
                     if (pmask) *pmask |= 2;

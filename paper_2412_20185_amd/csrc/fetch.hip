@@ -40,6 +40,26 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     if (per_segment > kMaxFetchSlices * kWavesPerBlock) per_segment = kMaxFetchSlices * kWavesPerBlock;
     if (per_segment > k) per_segment = k;
     if (per_segment < 1) per_segment = 1;
+
+    // Rows asked for while the selection goes on (fetch_body.h).  They take about 0.35 us of the selection and use the link for
+    // up to 1.2 (4096 channels) to 2 (14336) before it is over: not with few bytes to fetch, nor where so many workgroups share
+    // a segment's rows that a good part is asked for by the wrong one, nor with so many segments that one row per wavefront
+    // is more than the link takes in that time.  us without and with, fp16 / 8-bit / 4-bit rows: 4096 x 4096, k = 60 14.9 -> 13.9 /
+    // 10.5 -> 9.2 / 8.1 -> 7.1; 14336 x 4096, k = 210 38.2 -> 36.9 / 22.4 -> 21.4 / 15.4 -> 14.7; but 4096 x 1024, k = 20 6.2 -> 6.2
+    // / 6.1 -> 6.6 / 5.9 -> 6.3; 4096 x 28672, k = 81 87.2 -> 88.7 (fp16).  A requested split is kept as it is, without.
+    constexpr int row_bits[] = {16, 4, 2, 8};
+    const int segment_bytes = kFetchSegmentCols / 8 * row_bits[rfmt];
+    const size_t bytes = (size_t)p.segments * segment_bytes * k;
+    const int one_each = p.segments * kWavesPerBlock * segment_bytes;  // a row per wavefront
+    constexpr int kLinkBytes = 256 * 1024;
+    p.early = 0;
+    if (row_split <= 0 && !in_hbm && rfmt != 2 && bytes > 64 * 1024 && per_segment <= 4 * kWavesPerBlock && one_each <= kLinkBytes &&
+        select_tries_chunks(sh.K / 8, k)) {
+        p.early = std::min((kLinkBytes + one_each - 1) / one_each, 2048 / segment_bytes);
+        // All wavefronts take rows then, while they are not too many for the link: 4096 x 28672, 60 4-bit rows 21.5 us with three
+        // of each workgroup, 20.8 with eight; 5120 x 13824 13.9 and 12.7; 8192 x 57344, two and eight 47.9 and 54.
+        if (p.segments * kWavesPerBlock <= 448) per_segment = std::min(std::max(per_segment, kWavesPerBlock), k);
+    }
     p.slices = (per_segment + kWavesPerBlock - 1) / kWavesPerBlock;
     p.row_waves = (per_segment + p.slices - 1) / p.slices;
     return p;
@@ -55,7 +75,7 @@ int fetch_select_chunks(int K, int k) {
 
 template <int NCH>
 static hipError_t launch_fetch_nch(int rfmt, const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
-    const unsigned lds = selection_lds_bytes(NCH, a.k);
+    const unsigned lds = fetch_lds_bytes(a, NCH);
     const dim3 grid((unsigned)(a.segments * a.cslices)), block(kBlockThreads);
     switch (rfmt) {
         case 0: return launch_kernel(tm, fetch_kernel<16, NCH>, grid, block, lds, stream, a);

@@ -24,6 +24,18 @@
 // selection is spread over the thread blocks; an exact select that is cheap
 // enough to repeat per workgroup needs none).  Workgroup 0 also writes the
 // selection to global memory for the caller.
+//
+// The link stands idle until the first row is requested: 2.0 us of a call with
+// 4096 channels, 3.4 with 14336 (stamps of the first workgroup).  But once the
+// bound of the selection is known, after 0.8 / 1.2 us, most of the selected
+// channels are: the maxima of the chunks in a bin above.  EARLY (below) requests
+// their rows then; the selection marks those that it has (a tag beside the
+// index), and they are worked off in their place among the others, so that the
+// sum has the same bits.  A row that is not selected after all is dropped.
+// 4096 x 4096, 60 4-bit rows 8.4 -> 7.1 us; 14336 x 4096, 56 8-bit rows 10.9 ->
+// 9.8; 5120 x 13824, 60 4-bit rows 15.0 -> 12.7.  What it costs is the issue of
+// the requests (a wavefront's request of 1 KiB occupies its compute unit for
+// about 50 ns, and the wavefronts that wait for it also make the selection).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -45,21 +57,22 @@ struct Selection {
     const uint16_t* xsel;
 };
 
-template <int SELECT_NCH>
+// `ask`: select_block.h.  What it adds to an index is above bit 15 (K <= 32768 here).
+template <int SELECT_NCH, typename Ask>
 __device__ __forceinline__ Selection obtain_selection(const uint4* keys, int K, int k, int32_t* idx_g, uint16_t* xsel_g,
-                                                      SelectShared<kBlockThreads, SELECT_NCH>& sh, int bid) {
+                                                      SelectShared<kBlockThreads, SELECT_NCH>& sh, int bid, const Ask& ask) {
     if constexpr (SELECT_NCH > 0) {
-        extern __shared__ uint4 s_sel_raw[];  // int32 idx[k], then fp16 xsel[k]
+        extern __shared__ uint4 s_sel_raw[];
         int32_t* idx_l = reinterpret_cast<int32_t*>(s_sel_raw);
         uint16_t* xs_l = reinterpret_cast<uint16_t*>(idx_l + k);
         uint4 ch[SELECT_NCH];
 #pragma unroll
         for (int j = 0; j < SELECT_NCH; ++j) ch[j] = keys[j];
-        block_select_topk<kBlockThreads, SELECT_NCH>(ch, K, k, sh, idx_l, xs_l);
+        block_select_topk<kBlockThreads, SELECT_NCH>(ch, K, k, sh, idx_l, xs_l, ask);
         __syncthreads();
         if (bid == 0) {
             for (int i = threadIdx.x; i < k; i += kBlockThreads) {
-                idx_g[i] = idx_l[i];
+                idx_g[i] = idx_l[i] & 0xFFFF;
                 xsel_g[i] = xs_l[i];
             }
         }
@@ -124,6 +137,16 @@ constexpr int kLaneCols = BITS == 2 ? 16 : 8;                                  /
 template <int BITS>
 constexpr int kLoadRows = 64 / (kFetchSegmentCols / kLaneCols<BITS>);  // rows a wavefront loads with one instruction
 
+// Rows asked for while the selection goes on: 32 bytes a lane, in registers until the selection is complete.  Not with
+// 2-bit rows, nor with eight chunks of keys per thread, where there are no registers for them.
+template <int BITS, int SELECT_NCH>
+constexpr bool kAsksEarly = SELECT_NCH > 0 && SELECT_NCH < 8 && BITS != 2;
+template <int BITS>
+constexpr int kLanesPerEarlyRow = kFetchSegmentCols * BITS / 128;  // 16 bytes each
+template <int BITS>
+constexpr int kEarlyRows = 2 * 64 / kLanesPerEarlyRow<BITS>;  // per wavefront
+static_assert(kEarlyRows<4> <= 8, "SelectShared::asked");
+
 // The selection and the sum over the wavefronts follow one another and share their LDS.
 template <int BITS, int SELECT_NCH>
 union FetchLds {
@@ -131,6 +154,16 @@ union FetchLds {
     SelectShared<kBlockThreads, SELECT_NCH> sh;
     __device__ FetchLds() {}
 };
+
+// Dynamic LDS: int32 idx[k] and fp16 xsel[k] of a selection made here, then the rows asked for early.
+__host__ __device__ inline unsigned selection_lds_bytes(int select_chunks, int k) {
+    return select_chunks > 0 ? (unsigned)(((size_t)k * 6 + 15) / 16 * 16) : 0u;
+}
+constexpr unsigned kEarlyLdsBytes = kWavesPerBlock * 2 * 64 * 16;
+// Host: of a kernel that selects for itself.
+inline unsigned fetch_lds_bytes(const CallArgs& a, int select_chunks) {
+    return selection_lds_bytes(select_chunks, a.k) + (a.early > 0 ? kEarlyLdsBytes : 0u);
+}
 
 // One workgroup = one column segment of 512 columns x the rows of row slice rs.  A lane reads 8 columns of a
 // row (16, 8 or 4 bytes for fp16, 8-bit and 4-bit rows: a wavefront 1 KiB down to 256 bytes of contiguous
@@ -145,14 +178,17 @@ union FetchLds {
 // column's accumulator (finalize.h), or, when a separate kernel does the adding, writes it to row rs of cpart.
 //
 // Workgroup `bid` is slice rs = bid % a.cslices of segment bid / a.cslices, counted over all matrices.
-template <int BITS, int SELECT_NCH>
-__device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
+//
+// EARLY: rows are asked for while the selection goes on (a.early of them per wavefront at most); code of its own, because the
+// few instructions that this takes on the way would cost calls without it up to 0.5 us.  fetch_plan says which calls.
+template <int BITS, int SELECT_NCH, bool EARLY>
+__device__ __forceinline__ void fetch_block(const CallArgs& a, int bid, FetchLds<BITS, SELECT_NCH>& lds) {
     typedef typename RowPiece<BITS>::type piece_t;
     constexpr int CPL = kLaneCols<BITS>, SUB = kLoadRows<BITS>;
     constexpr int LPR = kFetchSegmentCols / CPL;        // lanes that cover the segment's part of one row
     constexpr int UNROLL = (4096 / 64) / (int)sizeof(piece_t);  // loads in flight per lane: 4 KiB per wavefront
     static_assert(kBlockThreads == kFetchSegmentCols, "one thread per column of the segment");
-    __shared__ FetchLds<BITS, SELECT_NCH> lds;
+    static_assert(!EARLY || kAsksEarly<BITS, SELECT_NCH>, "early rows");
     auto& red = lds.red;
 
     const int tid = threadIdx.x;
@@ -196,8 +232,49 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     uint32_t sraw = 0;
     if constexpr (BITS != 16 && kScaleFirst) sraw = Rs[min(ocol, N - 1)];
 
-    const Selection sel = obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid);
-    if constexpr (BITS != 16 && !kScaleFirst) sraw = Rs[min(ocol, N - 1)];
+    // This wavefront's part of the rows that are nearly certain is asked for before the selection is complete.  Where several
+    // workgroups share a segment's rows, each takes those of the channels that are likely to be in its share.  The requests
+    // are made on every path, if need be for the first bytes of x: loads that only some paths make are waited for where the
+    // paths meet.
+    uint4 early0, early1;
+    const auto ask = [&](const uint4& chunk_keys, int chunk, unsigned top, unsigned edge) -> unsigned {
+        unsigned tag = 0;
+        if constexpr (EARLY) {
+            constexpr int LPE = kLanesPerEarlyRow<BITS>;
+            const int most = wave * slices / kWavesPerBlock == rs ? a.early : 0;
+            const bool wanted = top >= edge;
+            const unsigned long long b = __ballot(wanted);
+            const int rank = (int)lanes_before(b), n = min((int)__builtin_popcountll(b), most);
+            uint16_t* asked = lds.sh.asked[wave];
+            if (wanted && rank < n) {
+                const int e = __builtin_ctz(mark_above(chunk_keys, top - 1));
+                asked[rank] = (uint16_t)(chunk * 8 + e);
+                tag = (unsigned)e | (unsigned)(wave * kEarlyRows<BITS> + rank + 1) << 3;
+            }
+            wave_writes_seen();
+            const unsigned pieces = (unsigned)N * BITS / 128;
+            const unsigned at = wc * LPE + lane % LPE;
+            const int i0 = lane / LPE, i1 = 64 / LPE + lane / LPE;
+            const uint4* none = reinterpret_cast<const uint4*>(a.x);
+            const uint4 *p0 = rows_base + (size_t)asked[i0] * pieces + at, *p1 = rows_base + (size_t)asked[i1] * pieces + at;
+            p0 = i0 < n && at < pieces ? p0 : none;
+            p1 = i1 < n && at < pieces ? p1 : none;
+            early0 = *p0;
+            early1 = *p1;
+        }
+        return tag;
+    };
+    const Selection sel = [&] {
+        if constexpr (EARLY) {
+            return obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid, ask);
+        } else {
+            return obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid, AskNothing());
+        }
+    }();
+    if constexpr (BITS != 16 && !kScaleFirst) {
+        sraw = Rs[min(ocol, N - 1)];
+        __builtin_amdgcn_sched_barrier(0);  // not among the row requests
+    }
     const int32_t* idx = sel.idx;
     const uint16_t* xsel = sel.xsel;
     const piece_t* __restrict__ R = reinterpret_cast<const piece_t*>(rows_base);
@@ -214,7 +291,73 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     float acc[CPL];
 #pragma unroll
     for (int i = 0; i < CPL; ++i) acc[i] = 0.f;
-    for (int j = j0; j < j1; j += UNROLL * SUB) {
+    // A batch of up to UNROLL rows in sets of up to 8.  In a set every request is made, those without a row of their own for the
+    // first bytes of x.  So what was asked for early can be waited for alone; and sixteen conditions cost more than the requests
+    // that they save (4-bit rows, 4096 x 4096, 60 of them in GPU memory 6.06 us with conditions and 5.46 without, over the link
+    // 8.37 and 8.06), eight or four less (210 8-bit rows of 14336 x 4096 in GPU memory 7.8 and 8.1, 81 fp16 rows 5.33 and 5.53).
+    constexpr bool kAllRequests = EARLY || (BITS == 4 && SELECT_NCH > 0);
+    if constexpr (kAllRequests) {
+        constexpr int SET = UNROLL < 8 ? UNROLL : 8;
+        const char* lane_row = reinterpret_cast<const char*>(rows_base) + min(piece, (int)row_pieces - 1) * (int)sizeof(piece_t);
+        const char* none = reinterpret_cast<const char*>(a.x);
+        const unsigned row_bytes = (unsigned)row_pieces * (unsigned)sizeof(piece_t);
+        extern __shared__ uint4 s_sel_raw[];
+        uint4* early_lds = s_sel_raw + selection_lds_bytes(SELECT_NCH, k) / 16;
+        bool asked = EARLY;
+        int j = j0;
+        do {
+            piece_t v[UNROLL];
+#pragma unroll
+            for (int u0 = 0; u0 < UNROLL; u0 += SET) {
+                if (u0 > 0 && j + u0 >= j1) break;
+                unsigned entry[SET];
+#pragma unroll
+                for (int u = 0; u < SET; ++u) entry[u] = (unsigned)idx[min(j + u0 + u, k - 1)];
+#pragma unroll
+                for (int u = 0; u < SET; ++u) {
+                    const unsigned limit = j + u0 + u < j1 ? (unsigned)K : 0u;
+                    const char* row = lane_row + (unsigned long long)entry[u] * row_bytes;
+                    row = entry[u] < limit ? row : none;  // a tag: it has been asked for
+                    v[u0 + u] = *reinterpret_cast<const piece_t*>(row);
+                }
+            }
+            if constexpr (EARLY) {
+                if (asked) {
+                    asked = false;
+                    uint4* to = early_lds + wave * 128 + lane;
+                    to[0] = early0;
+                    to[64] = early1;
+                    __syncthreads();
+                }
+            }
+#pragma unroll
+            for (int u0 = 0; u0 < UNROLL; u0 += SET) {
+                if (j + u0 >= j1) break;
+                uint32_t xraw[SET];
+#pragma unroll
+                for (int u = 0; u < SET; ++u) xraw[u] = xsel[min(j + u0 + u, j1 - 1)];
+                if constexpr (EARLY) {
+                    const char* early_piece = reinterpret_cast<const char*>(early_lds) + lane * sizeof(piece_t);
+                    piece_t w[SET];
+                    unsigned slot[SET];  // 0: not asked for early
+#pragma unroll
+                    for (int u = 0; u < SET; ++u) slot[u] = (unsigned)__builtin_amdgcn_readfirstlane(idx[min(j + u0 + u, j1 - 1)]) >> 16;
+#pragma unroll
+                    for (int u = 0; u < SET; ++u)
+                        w[u] = *reinterpret_cast<const piece_t*>(early_piece + (max(slot[u], 1u) - 1) * (kFetchSegmentCols * BITS / 8));
+#pragma unroll
+                    for (int u = 0; u < SET; ++u)
+                        if (j + u0 + u < j1) accumulate_piece<BITS, CPL>(slot[u] ? w[u] : v[u0 + u], h2f(xraw[u]), acc);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < SET; ++u)
+                        if (j + u0 + u < j1) accumulate_piece<BITS, CPL>(v[u0 + u], h2f(xraw[u]), acc);
+                }
+            }
+            j += UNROLL;
+        } while (j < j1);
+    }
+    for (int j = kAllRequests ? j1 : j0; j < j1; j += UNROLL * SUB) {
         piece_t v[UNROLL];
         float xs[UNROLL];
         int row[UNROLL];
@@ -288,9 +431,16 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
     }
 }
 
-// Host: dynamic LDS of a kernel that selects for itself.
-inline unsigned selection_lds_bytes(int select_chunks, int k) {
-    return select_chunks > 0 ? (unsigned)(((size_t)k * 6 + 15) / 16 * 16) : 0u;
+template <int BITS, int SELECT_NCH>
+__device__ __forceinline__ void fetch_block(const CallArgs& a, int bid) {
+    __shared__ FetchLds<BITS, SELECT_NCH> lds;
+    if constexpr (kAsksEarly<BITS, SELECT_NCH>) {
+        if (a.early > 0) {
+            fetch_block<BITS, SELECT_NCH, true>(a, bid, lds);
+            return;
+        }
+    }
+    fetch_block<BITS, SELECT_NCH, false>(a, bid, lds);
 }
 
 }  // namespace decdec

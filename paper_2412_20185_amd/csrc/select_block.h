@@ -22,7 +22,9 @@
 //     2. every wavefront lists its chunks with a maximum >= L, in order, in its
 //        own part of an LDS list and takes them back one or two per lane (left out
 //        when every thread has one chunk), so that no barrier and no sum over
-//        wavefronts stands in front of the next step;
+//        wavefronts stands in front of the next step.  Fewer than k chunks have a
+//        maximum in a bin above; nearly always all of these maxima are selected,
+//        and a caller may act on them while the rest is found out (`ask`);
 //     3. a 256-bin LDS histogram of key - L over their keys gives T, the k-th
 //        largest key itself, and how many keys equal to T are needed; only when
 //        T >= L + 255 (large |x| crowded into few chunks) it is formed twice more,
@@ -43,6 +45,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -67,6 +70,7 @@ struct SelectShared {
     __attribute__((aligned(16))) unsigned hist2[256];
     __attribute__((aligned(16))) unsigned wtot[16];  // per wave: (keys > T) | (keys == T) << 16
     int overflow;                                     // 1: a wavefront's list is too short
+    uint16_t asked[THREADS / 64][8];                  // for the caller's `ask`
 };
 
 template <int CTRL, int ROW_MASK, bool BOUND_CTRL>
@@ -177,11 +181,12 @@ __device__ __forceinline__ unsigned totals_before(const unsigned* wtot, int wave
     return before;
 }
 
-// Writes the marked keys of one chunk: all of `gt`, of `eq` those with fewer than `need` equal keys in front.
+// Writes the marked keys of one chunk: all of `gt`, of `eq` those with fewer than `need` equal keys in front.  `tag`: 0, or a
+// key's position in the chunk (low three bits) and what its index gets from bit 16 on.
 template <bool MANY = false>
 __device__ __forceinline__ void write_marked(const uint4& c, int channel0, unsigned gt, unsigned eq, unsigned pos_gt,
                                              unsigned seen_eq, unsigned need, unsigned k, int32_t* idx_out,
-                                             uint16_t* xsel_out) {
+                                             uint16_t* xsel_out, unsigned tag = 0) {
     unsigned m = gt | eq;
     while (m) {
         const int e = __builtin_ctz(m);
@@ -190,7 +195,7 @@ __device__ __forceinline__ void write_marked(const uint4& c, int channel0, unsig
         const unsigned pos = pos_gt + min(seen_eq, need);
         // pos < k always holds for a taken key; the bound keeps a logic error from writing outside
         if ((is_gt || seen_eq < need) && pos < k) {
-            idx_out[pos] = channel0 + e;
+            idx_out[pos] = (channel0 + e) | ((unsigned)e == (tag & 7u) ? (int)(tag >> 3 << 16) : 0);
             if (xsel_out) xsel_out[pos] = raw_of<MANY>(c, e);
         }
         pos_gt += is_gt;
@@ -217,14 +222,21 @@ __device__ __forceinline__ void mark_chunk(const uint4& c, unsigned T, unsigned&
     eq = mark_above(c, T - 1) & ~gt;
 }
 
-// Requires 1 <= k <= nchunks and sh.hist1, sh.hist2, sh.overflow cleared (with a barrier behind).  False, in all threads, when
-// the chunks do not give the selection: nothing has been written to the outputs then.
+// A lane's chunks once those that cannot matter are gone.
 template <int THREADS, int NCH>
-__device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared<THREADS, NCH>& sh,
-                                                 int32_t* idx_out, uint16_t* xsel_out) {
-    constexpr int WAVES = THREADS / 64;
+struct Listed {
+    static constexpr int kPer = NCH == 1 ? 1 : kListedPerWave<THREADS, NCH> / 64;
+    uint4 keys[kPer];
+    int chunk[kPer];
+    unsigned count = 0;  // chunks of this wavefront
+    unsigned L = 0;      // the bound; 0: the chunks do not give one
+};
+
+// Steps 1 and 2.  Requires 1 <= k <= nchunks and sh.hist1, sh.overflow cleared (with a barrier behind).
+template <int THREADS, int NCH>
+__device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared<THREADS, NCH>& sh,
+                                            Listed<THREADS, NCH>& out) {
     constexpr int LIST = kListedPerWave<THREADS, NCH>;
-    constexpr int PER = NCH == 1 ? 1 : LIST / 64;  // listed chunks per lane at most
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c0 = wave * 64 * NCH + lane;
@@ -239,59 +251,67 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
     unsigned bin, need;
     wave_find_bin<4>(sh.hist1, (unsigned)k, bin, need, lane);
     const unsigned L = bin << 7;
-    if (L == 0) return false;
-
-    uint4 mine[PER];
-    int chunk[PER];
-    unsigned listed = 64;  // chunks of this wavefront
+    out.L = L;
+    if (L == 0) return;
     if constexpr (NCH == 1) {
-        mine[0] = ch[0];
-        chunk[0] = c0;
+        out.keys[0] = ch[0];
+        out.chunk[0] = c0;
+        out.count = 64;
     } else {
         uint4* list = sh.list + wave * LIST;
         uint16_t* list_chunk = sh.list_chunk + wave * LIST;
-        listed = 0;
+        unsigned count = 0;
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             const unsigned long long b = __ballot(cm[j] >= L);
-            const unsigned at = listed + lanes_before(b);
+            const unsigned at = count + lanes_before(b);
             if (cm[j] >= L && at < (unsigned)LIST) {
                 list[at] = ch[j];
                 list_chunk[at] = (uint16_t)(c0 + 64 * j);
             }
-            listed += (unsigned)__builtin_popcountll(b);
+            count += (unsigned)__builtin_popcountll(b);
         }
-        if (NCH * 64 > LIST && listed > (unsigned)LIST) {
+        if (NCH * 64 > LIST && count > (unsigned)LIST) {
             if (lane == 0) sh.overflow = 1;
-            listed = LIST;
+            count = LIST;
         }
         wave_writes_seen();
 #pragma unroll
-        for (int p = 0; p < PER; ++p) {
+        for (int p = 0; p < Listed<THREADS, NCH>::kPer; ++p) {
             const unsigned i = 64 * p + lane;
-            mine[p] = make_uint4(0, 0, 0, 0);  // keys below L: never taken
-            chunk[p] = 0;
-            if (i < listed) {
-                mine[p] = list[i];
-                chunk[p] = list_chunk[i];
+            out.keys[p] = make_uint4(0, 0, 0, 0);  // keys below L: never taken
+            out.chunk[p] = 0;
+            if (i < count) {
+                out.keys[p] = list[i];
+                out.chunk[p] = list_chunk[i];
             }
         }
+        out.count = count;
     }
+}
 
-    unsigned T = L;
+// Steps 3 and 4.  Requires L != 0 and sh.hist2 cleared.  False, in all threads, when a list was too short: nothing has been
+// written to the outputs then.
+template <int THREADS, int NCH>
+__device__ __forceinline__ bool select_listed(const Listed<THREADS, NCH>& l, int k, SelectShared<THREADS, NCH>& sh, int32_t* idx_out,
+                                              uint16_t* xsel_out, unsigned tag) {
+    constexpr int PER = Listed<THREADS, NCH>::kPer;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned T = l.L, bin, need;
     int shift = 0;  // bins of 2^shift keys from T on; the last one takes everything above
     while (true) {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
-            if (64u * p >= listed) break;  // wave-uniform
-            unsigned m = mark_above(mine[p], T - 1);
+            if (64u * p >= l.count) break;  // wave-uniform
+            unsigned m = mark_above(l.keys[p], T - 1);
             while (m) {
-                atomicAdd(&sh.hist2[min((key_of(mine[p], __builtin_ctz(m)) - T) >> shift, 255u)], 1u);
+                atomicAdd(&sh.hist2[min((key_of(l.keys[p], __builtin_ctz(m)) - T) >> shift, 255u)], 1u);
                 m &= m - 1;
             }
         }
         __syncthreads();
-        if (NCH * 64 > LIST && __builtin_amdgcn_readfirstlane(sh.overflow)) return false;
+        if (NCH * 64 > kListedPerWave<THREADS, NCH> && __builtin_amdgcn_readfirstlane(sh.overflow)) return false;
         wave_find_bin<4>(sh.hist2, (unsigned)k, bin, need, lane);  // need: keys equal to T to take (>= 1) in the end
         T += bin << shift;
         if (shift == 0 && bin < 255) break;
@@ -305,8 +325,8 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
         gt[p] = eq[p] = at[p] = 0;
-        if (64u * p >= listed) break;
-        mark_chunk(mine[p], T, gt[p], eq[p]);
+        if (64u * p >= l.count) break;
+        mark_chunk(l.keys[p], T, gt[p], eq[p]);
         const unsigned cnt = (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
         const unsigned incl = wave_incl_scan(cnt) + total;
         at[p] = incl - cnt;
@@ -314,12 +334,12 @@ __device__ __forceinline__ bool select_by_chunks(const uint4 (&ch)[NCH], int nch
     }
     if (lane == 63) sh.wtot[wave] = total;
     __syncthreads();
-    const unsigned before = totals_before<WAVES>(sh.wtot, wave);  // no carry between the halves: at most 16384 marked keys
+    const unsigned before = totals_before<THREADS / 64>(sh.wtot, wave);  // no carry between the halves: at most 16384 marked keys
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-        if (64u * p >= listed) break;
-        write_marked(mine[p], chunk[p] * 8, gt[p], eq[p], (before + at[p]) & 0xFFFFu, (before + at[p]) >> 16, need, (unsigned)k,
-                     idx_out, xsel_out);
+        if (64u * p >= l.count) break;
+        write_marked(l.keys[p], l.chunk[p] * 8, gt[p], eq[p], (before + at[p]) & 0xFFFFu, (before + at[p]) >> 16, need, (unsigned)k,
+                     idx_out, xsel_out, p == 0 ? tag : 0u);
     }
     return true;
 }
@@ -404,13 +424,22 @@ __device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, int K,
     for (int j = 0; j < NCH; ++j) ch[j] = c0 + 64 * j < nchunks ? x128[c0 + 64 * j] : make_uint4(0, 0, 0, 0);
 }
 
+// The caller does not act on a part of the selection.
+struct AskNothing {
+    __device__ __forceinline__ unsigned operator()(const uint4&, int, unsigned, unsigned) const { return 0; }
+};
+
 // All THREADS threads of the workgroup call this, with their keys (load_keys) and 1 <= k <= K.  idx_out / xsel_out may
 // point to global memory or LDS; xsel_out may be null.  Ends with the outputs
 // written but not yet synchronised (the caller adds the barrier it needs).  RADIX: the caller knows that
 // select_tries_chunks(K / 8, k) is false.
-template <int THREADS, int NCH, bool RADIX = false>
+//
+// ask(a chunk's keys, the chunk, its maximum, edge): called once by every lane, on every path, with its first listed chunk (maximum
+// 0: none).  Fewer than k chunks have a maximum >= edge.  Returns the lane's tag (write_marked), which only a selection by
+// chunks writes.
+template <int THREADS, int NCH, bool RADIX = false, typename Ask = AskNothing>
 __device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, int k, SelectShared<THREADS, NCH>& sh,
-                                                  int32_t* idx_out, uint16_t* xsel_out) {
+                                                  int32_t* idx_out, uint16_t* xsel_out, const Ask& ask = Ask()) {
     static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
     const int tid = threadIdx.x, nchunks = K / 8;
     const auto clear = [&] {
@@ -419,8 +448,20 @@ __device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K,
         __syncthreads();
     };
     clear();
-    if (!RADIX && select_tries_chunks(nchunks, k)) {
-        if (select_by_chunks<THREADS, NCH>(ch, nchunks, k, sh, idx_out, xsel_out)) return;
+    if constexpr (!std::is_same_v<Ask, AskNothing>) {  // on every path, see `ask`
+        const bool chunks = select_tries_chunks(nchunks, k);
+        Listed<THREADS, NCH> l;
+        if (chunks) list_chunks(ch, nchunks, k, sh, l);
+        const unsigned tag = ask(l.keys[0], l.chunk[0], l.L != 0 ? chunk_max(l.keys[0]) : 0u, l.L + 128);
+        if (l.L != 0 && select_listed(l, k, sh, idx_out, xsel_out, tag)) return;
+        if (chunks) {
+            __syncthreads();
+            clear();
+        }
+    } else if (!RADIX && select_tries_chunks(nchunks, k)) {
+        Listed<THREADS, NCH> l;
+        list_chunks(ch, nchunks, k, sh, l);
+        if (l.L != 0 && select_listed(l, k, sh, idx_out, xsel_out, 0)) return;
         __syncthreads();
         clear();
     }

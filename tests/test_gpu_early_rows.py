@@ -1,0 +1,82 @@
+"""Rows that are requested before the selection is complete: selections of which all, some and none of the requested rows are
+part, ties at the cut, shares of several workgroups, against the oracle and bit for bit against rows requested after it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+import paper_2412_20185_amd as dd
+from helpers import Problem, assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def activations(K, k):
+    """(name, x)"""
+    g = np.random.default_rng(K + k)
+    yield "outliers", workloads.x_gauss_outliers(71, 0, 0, 0, K)
+    # the k largest crowd in k / 4 chunks of 8, so that many chunks whose maximum is among the k largest maxima hold no
+    # selected channel
+    x = g.uniform(1.0, 3.9, K).astype(np.float16)
+    for c in g.choice(K // 8, max(1, k // 4), replace=False):
+        x[8 * c:8 * c + 4] = g.uniform(4, 60, 4).astype(np.float16)
+    yield "crowded", x
+    # all in one wavefront's run of channels, and in the last one
+    for name, at in (("first", 0), ("last", K - 4 * k)):
+        x = (g.standard_normal(K) * 0.05).astype(np.float16)
+        x[at:at + 4 * k] += (g.uniform(1, 40, 4 * k) * (g.random(4 * k) < 0.4)).astype(np.float16)
+        yield name, x
+    # few distinct magnitudes: ties at the cut, also among the requested
+    x = g.choice([0.5, 1.0, 2.0, 8.0], K, p=[0.9, 0.06, 0.03, 0.01]).astype(np.float16) * g.choice([-1, 1], K).astype(np.float16)
+    yield "ties", x
+    yield "zero", np.zeros(K, np.float16)
+    yield "equal", np.full(K, -1.5, np.float16)
+
+
+@pytest.mark.parametrize("rfmt,K,N,k", [("fp16", 4096, 1600, 81), ("int8", 4096, 2112, 60), ("int4", 4096, 4160, 61),
+                                        ("int4", 8320, 2048, 100), ("int8", 16384, 1536, 200), ("fp16", 2048, 4096, 85),
+                                        ("int4", 1024, 28672, 5)])
+def test_early_rows(rfmt, K, N, k):
+    g = np.random.default_rng(N)
+    W = workloads.weights(71, 0, 0, K, N) if K * N < 1 << 23 else (g.standard_normal((K, N), dtype=np.float32) * 0.02)
+    p = Problem(W, 4, rfmt=rfmt, alphas=oracle.quantize.DEFAULT_ALPHAS[::35])
+    ws = dd.Workspace(K, N, k)
+    try:
+        for name, x in activations(K, k):
+            y_ref, sc = p.reference(x, k)
+            ws.set_separate_select(True)
+            y_a, idx_a, _ = p.run(x, k, ws)
+            ws.set_separate_select(False)
+            for mode in (dd.MODE_FUSED, dd.MODE_SERIAL):
+                ws.set_mode(mode)
+                y, idx, xs = p.run(x, k, ws)
+                assert np.array_equal(xs.view(np.uint16), x[sc].view(np.uint16)), name
+                if name != "zero":
+                    assert_parity(y, y_ref, idx, sc, what=f"{name} mode {mode}")
+                else:
+                    assert np.array_equal(idx, sc) and not y.any()
+                if mode == dd.MODE_FUSED:
+                    assert np.array_equal(y.view(np.uint16), y_a.view(np.uint16)), name
+            ws.set_mode(dd.MODE_FUSED)
+    finally:
+        ws.close()
+
+
+def test_infinite_activations():
+    """An infinite and a NaN activation are selected first; the columns hold what the products give, as without early rows."""
+    K, N, k = 4096, 4096, 60
+    p = Problem(workloads.weights(72, 0, 0, K, N), 4)
+    x = workloads.x_gauss_outliers(72, 0, 0, 0, K)
+    x[[7, 2000]] = [np.inf, -np.inf]
+    x[3100] = np.nan
+    ws = dd.Workspace(K, N, k)
+    try:
+        ws.set_separate_select(True)
+        y_a, idx_a, _ = p.run(x, k, ws)
+        ws.set_separate_select(False)
+        y_b, idx_b, _ = p.run(x, k, ws)
+        assert np.array_equal(idx_a, idx_b) and {7, 2000, 3100} <= set(idx_b.tolist())
+        assert np.array_equal(y_a.view(np.uint16), y_b.view(np.uint16))
+    finally:
+        ws.close()
