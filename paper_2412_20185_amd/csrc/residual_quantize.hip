@@ -21,6 +21,8 @@
 // is one round-to-nearest-even done with integer arithmetic.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 #include "layout.h"
 
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(kSlots * COLS) void residual_scale_bounds_kernel(co
     __shared__ unsigned s_max[COLS];
     __shared__ uint16_t s_bits[COLS][kAlphas + 1];  // fp16 scale of every candidate; one more that equals none
     __shared__ unsigned char s_left[COLS][kAlphas + 1];  // candidates that are left
-    __shared__ int s_count[COLS], s_rounds;
+    __shared__ int s_count[COLS], s_most;
     // after the bounds the histogram's place holds the errors of the candidates that are left
     double* s_err = reinterpret_cast<double*>(hist);         // [COLS][kAlphas]
     double* s_part = s_err + COLS * kAlphas;                 // [COLS wavefronts][PER_PASS][COLS]
@@ -314,7 +316,7 @@ __global__ __launch_bounds__(kSlots * COLS) void residual_scale_bounds_kernel(co
 
     for (int i = tid; i < COLS * kStride; i += kSlots * COLS) hist[i] = 0;
     if (tid < COLS) s_max[tid] = 0;
-    if (tid == 0) s_rounds = 0;
+    if (tid == 0) s_most = 0;
     __syncthreads();
     unsigned mx = 0;  // as bits, which puts infinity and NaN above every number
     each_row([&](float v) { mx = max(mx, __builtin_bit_cast(unsigned, v)); });
@@ -421,12 +423,12 @@ __global__ __launch_bounds__(kSlots * COLS) void residual_scale_bounds_kernel(co
         if (lane == 0) {
             if (count <= 1) scales_out[n] = __builtin_bit_cast(_Float16, count == 1 ? s_bits[wave][s_left[wave][0]] : (uint16_t)0x3C00);
             s_count[wave] = count <= 1 ? 0 : count;
-            atomicMax(&s_rounds, count <= 1 ? 0 : (count + PER_PASS - 1) / PER_PASS);
+            if (count > 1) atomicMax(&s_most, count);
         }
     }
     __syncthreads();
 
-    const int rounds = s_rounds, mine = s_count[col];
+    const int rounds = (s_most + PER_PASS - 1) / PER_PASS, mine = s_count[col];
     for (int r = 0; r < rounds; ++r) {
         double S[PER_PASS], inv[PER_PASS], err[PER_PASS];
 #pragma unroll
@@ -436,12 +438,19 @@ __global__ __launch_bounds__(kSlots * COLS) void residual_scale_bounds_kernel(co
             inv[a] = 1.0 / S[a];
             err[a] = 0.0;
         }
-        if (r * PER_PASS < mine) {
+        // For all columns of the workgroup as many as the one with the most has left, which is two as a rule: four each, 4096 x
+        // 4096 took 63 us for 4 bits and 74 for 2 instead of 59 and 48.
+        const auto sum_errors = [&](auto count) {
             each_row([&](float f) {
                 const double v = (double)f;
 #pragma unroll
-                for (int a = 0; a < PER_PASS; ++a) err[a] = add_error(v, S[a], inv[a], qmax, err[a]);
+                for (int a = 0; a < decltype(count)::value; ++a) err[a] = add_error(v, S[a], inv[a], qmax, err[a]);
             });
+        };
+        if (s_most - r * PER_PASS <= 2) {
+            sum_errors(std::integral_constant<int, 2>());
+        } else {
+            sum_errors(std::integral_constant<int, PER_PASS>());
         }
 #pragma unroll
         for (int a = 0; a < PER_PASS; ++a) {
