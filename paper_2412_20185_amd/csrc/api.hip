@@ -655,7 +655,9 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     const GemvPlan gp = gemv_plan(kind, tiles, sh.K / kGroup, c.gemv_gpw, c.gemv_wpb, fused, !residuals_in_hbm);
     const int gslices = gp.slices;
     FetchPlan plan{0, 0, 0, 0};
-    if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm);
+    // 0: the selection is there, or a kernel of its own makes it
+    const int select_chunks = k > 0 && !have_idx && !c.separate_select ? fetch_select_chunks(sh.K, k) : 0;
+    if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm, select_chunks > 0);
     const int cslices = plan.slices;
 
     CallArgs a{};
@@ -689,6 +691,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     a.k = k;
     a.cslices = cslices;
     a.row_waves = plan.row_waves;
+    a.early = plan.early;
     a.rows_per = k > 0 ? (k + cslices * plan.row_waves - 1) / (cslices * plan.row_waves) : 0;
     a.cdiv = reciprocal_of(cslices);
     a.nfetch = plan.segments * plan.slices;
@@ -709,7 +712,6 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
             // The kernels that follow only read a selection that is given; the const is dropped for the shared struct.
             a.idx = const_cast<int32_t*>(idx_in);
             a.xsel = static_cast<uint16_t*>(const_cast<void*>(xsel_in));
-            int select_chunks = 0;
             const bool two_streams = c.mode == DECDEC_MODE_TWO_STREAMS;
             hipStream_t comp = two_streams ? c.side : stream;  // where steps 1-3 run
             if (two_streams) {
@@ -721,8 +723,6 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
             if (!have_idx) {
                 a.idx = c.idx;
                 a.xsel = static_cast<uint16_t*>(c.xsel);
-                select_chunks = c.separate_select ? 0 : fetch_select_chunks(sh.K, k);
-                a.early = select_chunks > 0 ? plan.early : 0;
                 if (select_chunks == 0) {
                     DD_HIP(launch_select_topk(x, sh.K, k, c.idx, c.xsel, comp, tm[1]));
                     if (pmask) *pmask |= 2;

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(kBlockThreads) void fetch_kernel(const CallArgs a) 
 
 }  // namespace
 
-FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool in_hbm) {
+FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool in_hbm, bool selects) {
     FetchPlan p;
     p.segments = 0;
     for (int m = 0; m < sh.n; ++m) p.segments += (sh.N[m] + kFetchSegmentCols - 1) / kFetchSegmentCols;
@@ -55,10 +55,12 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     p.early = 0;
     if (row_split <= 0 && !in_hbm && rfmt != 2 && bytes > 64 * 1024 && per_segment <= 4 * kWavesPerBlock && one_each <= kLinkBytes &&
         select_tries_chunks(sh.K / 8, k)) {
-        p.early = std::min((kLinkBytes + one_each - 1) / one_each, 2048 / segment_bytes);
+        if (selects) p.early = std::min((kLinkBytes + one_each - 1) / one_each, 2048 / segment_bytes);
         // All wavefronts take rows then, while they are not too many for the link: 4096 x 28672, 60 4-bit rows 21.5 us with three
-        // of each workgroup, 20.8 with eight; 5120 x 13824 13.9 and 12.7; 8192 x 57344, two and eight 47.9 and 54.
-        if (p.segments * kWavesPerBlock <= 448) per_segment = std::min(std::max(per_segment, kWavesPerBlock), k);
+        // of each workgroup, 20.8 with eight; 5120 x 13824 13.9 and 12.7; 8192 x 57344, two and eight 47.9 and 54.  With a
+        // supplied selection 4-bit rows gain too (21.1 and 20.5), 8-bit rows do not (5120 x 13824 19.1 and 20.4).
+        if ((selects || rfmt == 1) && p.segments * kWavesPerBlock <= 448)
+            per_segment = std::min(std::max(per_segment, kWavesPerBlock), k);
     }
     p.slices = (per_segment + kWavesPerBlock - 1) / kWavesPerBlock;
     p.row_waves = (per_segment + p.slices - 1) / p.slices;

@@ -162,7 +162,8 @@ struct FetchPlan {
 };
 // row_split: requested workgroups per segment (0 = automatic); in_hbm: the residual rows are in device
 // memory, not behind the host link.
-FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool in_hbm);
+// selects: the kernel makes the selection itself.
+FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool in_hbm, bool selects);
 // select_chunks (from fetch_select_chunks) > 0: the kernel runs the exact top-k on x itself and writes
 // the selection to a.idx / a.xsel; 0: they hold the selection already (x is not read).
 int fetch_select_chunks(int K, int k);
