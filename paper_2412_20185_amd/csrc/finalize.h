@@ -48,14 +48,39 @@ __device__ __forceinline__ long long to_fixed(float v) {
 // Fixed-point sum -> the fp16 result (one rounding to fp32, exact scaling, one rounding to fp16).
 __device__ __forceinline__ _Float16 from_fixed(long long s) { return (_Float16)((float)s * kFixedInvScale); }
 
+// The producer that knows the others' sum writes the result and leaves zero for the next call.
+__device__ __forceinline__ void finish(unsigned long long* word, _Float16* y, unsigned long long sum) {
+    *y = from_fixed((long long)sum >> kArrivalBits);
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// What the other producers have added so far.
+__device__ __forceinline__ unsigned long long arrived_so_far(const unsigned long long* word) {
+    return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ unsigned long long term_of(float v) {
+    return ((unsigned long long)to_fixed(v) << kArrivalBits) + 1ull;
+}
+__device__ __forceinline__ bool others_arrived(unsigned long long word, int producers) {
+    return (int)(word & ((1ull << kArrivalBits) - 1)) + 1 == producers;
+}
+
 // One thread per column: add part sum v into the column's accumulator.  Called once by every one of the `producers`
 // of that column; the last one writes *y.
 __device__ __forceinline__ void arrive(unsigned long long* word, _Float16* y, int producers, float v) {
-    const unsigned long long term = ((unsigned long long)to_fixed(v) << kArrivalBits) + 1ull;
+    const unsigned long long term = term_of(v);
     const unsigned long long old = __hip_atomic_fetch_add(word, term, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((int)(old & ((1ull << kArrivalBits) - 1)) + 1 == producers) {
-        *y = from_fixed((long long)(old + term) >> kArrivalBits);
-        __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next call
+    if (others_arrived(old, producers)) finish(word, y, old + term);
+}
+
+// The same, with what the word has shown earlier in this call: who has seen all others arrive is the last one and need not add.
+__device__ __forceinline__ void arrive_after_look(unsigned long long* word, _Float16* y, int producers, float v,
+                                                  unsigned long long seen) {
+    if (others_arrived(seen, producers)) {
+        finish(word, y, seen + term_of(v));
+    } else {
+        arrive(word, y, producers, v);
     }
 }
 
