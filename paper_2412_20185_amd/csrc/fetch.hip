@@ -45,8 +45,10 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     // up to 1.2 (4096 channels) to 2 (14336) before it is over: not with few bytes to fetch, nor where so many workgroups share
     // a segment's rows that a good part is asked for by the wrong one, nor with so many segments that one row per wavefront
     // is more than the link takes in that time.  us without and with, fp16 / 8-bit / 4-bit rows: 4096 x 4096, k = 60 14.9 -> 13.9 /
-    // 10.5 -> 9.2 / 8.1 -> 7.1; 14336 x 4096, k = 210 38.2 -> 36.9 / 22.4 -> 21.4 / 15.4 -> 14.7; but 4096 x 1024, k = 20 6.2 -> 6.2
-    // / 6.1 -> 6.6 / 5.9 -> 6.3; 4096 x 28672, k = 81 87.2 -> 88.7 (fp16).  A requested split is kept as it is, without.
+    // 10.5 -> 9.2 / 8.1 -> 7.1; 14336 x 4096, k = 210 38.2 -> 36.9 / 22.4 -> 21.4 / 15.4 -> 14.7; but 4096 x 28672, k = 81
+    // 87.2 -> 88.7 (fp16).  Between 54 and 64 KiB, 90 sizes (1024, 4096 and 14336 channels by 512 to 4096 columns, all three
+    // formats), the time is 6 % less to 5 % more with it (1024 x 1024, 32 fp16 rows 6.58 -> 6.83, 4096 x 4096, 8 of them
+    // 6.63 -> 6.22); at 24 KiB 2 % less to 9 % more.  A requested split is kept as it is, without.
     constexpr int row_bits[] = {16, 4, 2, 8};
     const int segment_bytes = kFetchSegmentCols / 8 * row_bits[rfmt];
     const size_t bytes = (size_t)p.segments * segment_bytes * k;
@@ -56,11 +58,16 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     if (row_split <= 0 && !in_hbm && rfmt != 2 && bytes > 64 * 1024 && per_segment <= 4 * kWavesPerBlock && one_each <= kLinkBytes &&
         select_tries_chunks(sh.K / 8, k)) {
         if (selects) p.early = std::min((kLinkBytes + one_each - 1) / one_each, 2048 / segment_bytes);
-        // All wavefronts take rows then, while they are not too many for the link: 4096 x 28672, 60 4-bit rows 21.5 us with three
-        // of each workgroup, 20.8 with eight; 5120 x 13824 13.9 and 12.7; 8192 x 57344, two and eight 47.9 and 54.  With a
-        // supplied selection 4-bit rows gain too (21.1 and 20.5), 8-bit rows do not (5120 x 13824 19.1 and 20.4).
-        if ((selects || rfmt == 1) && p.segments * kWavesPerBlock <= 448)
-            per_segment = std::min(std::max(per_segment, kWavesPerBlock), k);
+        // All wavefronts take rows then, where that is no slower with a supplied selection either: who selects must not show in
+        // how the rows are split, because y has the bits of that split.  us with three to seven wavefronts of each workgroup ->
+        // with eight: 60 4-bit rows, selecting 5120 x 13824 13.9 -> 12.7, 4096 x 28672 21.5 -> 20.8, supplied 4096 x 12288 12.8 ->
+        // 11.7, 4096 x 28672 21.1 -> 20.5; beyond 28672 columns, 20 to 90 rows, 4 % more to 8 % less.  8-bit rows above 32
+        // segments, if eight wavefronts have more than a batch (8) each, selecting / supplied: 4096 x 20480, k = 100 42.8 -> 42.0 /
+        // 42.3 -> 40.8; but k = 60 27.8 -> 27.1 / 25.9 -> 27.1, and up to 32 segments 4096 x 12288, k = 60 19.3 -> 18.3 / 17.3 ->
+        // 18.7, 8192 x 12288, k = 330 78.2 -> 80.2 / 78.0 -> 77.4.  fp16 rows stay as they are: 14336 x 16384, k = 33 26.3 ->
+        // 28.8 / 25.2 -> 26.7.
+        const bool all = rfmt == 1 || (rfmt == 3 && p.segments > 32 && k > 8 * kWavesPerBlock);
+        if (all && p.segments * kWavesPerBlock <= 448) per_segment = std::min(std::max(per_segment, kWavesPerBlock), k);
     }
     p.slices = (per_segment + kWavesPerBlock - 1) / kWavesPerBlock;
     p.row_waves = (per_segment + p.slices - 1) / p.slices;

@@ -2,6 +2,8 @@
 HIP path through the C ABI binding, and compare with the oracle."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -11,6 +13,27 @@ import paper_2412_20185_amd as dd
 RBITS = {"int2": 2, "int4": 4, "int8": 8}
 RFMT = {"fp16": dd.R_FP16, "int4": dd.R_INT4_SYM_COL, "int2": dd.R_INT2_SYM_COL, "int8": dd.R_INT8_SYM_COL}
 TOL_Y = 2e-3          # max relative error of y against the fp64 oracle (floor 1 % of rms on the denominator)
+
+
+class MultiShape(C.Structure):
+    _fields_ = [("n", C.c_int), ("K", C.c_int), ("N", C.c_int * 4), ("col0", C.c_int * 5)]
+
+
+class FetchPlan(C.Structure):
+    """How the residual rows are shared out: workgroups and wavefronts of each for a segment of 512 columns, and how many rows a
+    wavefront may ask for before the selection is complete."""
+    _fields_ = [(n, C.c_int) for n in ("segments", "slices", "row_waves", "early")]
+
+
+def fetch_plan(rfmt: int, K: int, Ns, k: int, row_split: int = 0, in_hbm: bool = False, selects: bool = True) -> FetchPlan:
+    """The library's own plan (host code, no GPU needed)."""
+    f = dd.lib()["_ZN6decdec10fetch_planEiRKNS_10MultiShapeEiibb"]
+    f.argtypes = [C.c_int, C.POINTER(MultiShape)] + [C.c_int] * 2 + [C.c_bool] * 2
+    f.restype = FetchPlan
+    sh = MultiShape(n=len(Ns), K=K)
+    for m, N in enumerate(Ns):
+        sh.N[m], sh.col0[m + 1] = N, sh.col0[m] + N
+    return f(rfmt, C.byref(sh), k, row_split, in_hbm, selects)
 
 
 class Problem:

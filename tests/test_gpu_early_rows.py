@@ -8,6 +8,7 @@ import oracle
 import workloads
 import paper_2412_20185_amd as dd
 from helpers import Problem, assert_parity
+from paper_2412_20185_amd.layer import StoredLinear
 
 pytestmark = pytest.mark.gpu
 
@@ -78,5 +79,28 @@ def test_infinite_activations():
         y_b, idx_b, _ = p.run(x, k, ws)
         assert np.array_equal(idx_a, idx_b) and {7, 2000, 3100} <= set(idx_b.tolist())
         assert np.array_equal(y_a.view(np.uint16), y_b.view(np.uint16))
+    finally:
+        ws.close()
+
+
+@pytest.mark.parametrize("rbits,K,N,k", [(16, 2048, 9728, 85), (16, 4096, 13824, 81), (16, 4096, 16384, 60), (8, 4096, 9728, 60),
+                                         (8, 4096, 20992, 64), (8, 4096, 20992, 65), (8, 2048, 28672, 85), (4, 4096, 10240, 60),
+                                         (4, 2048, 28672, 80)])
+def test_same_bits_whoever_selects(rbits, K, N, k):
+    """17 to 56 segments, where a workgroup has three to seven wavefronts for the rows, or all eight."""
+    lin = StoredLinear.random(K, N, 3, dd.W_UNIFORM_G128, rbits, seed=3)
+    ws = dd.Workspace(K, N, k)
+    y = [torch.full((N,), float("nan"), dtype=torch.float16, device="cuda") for _ in range(3)]
+    try:
+        for seed in range(4):
+            x = torch.from_numpy(workloads.x_gauss_outliers(73, seed, 0, 0, K)).cuda()
+            lin.gemv(x, k, y[0], ws)
+            ws.set_separate_select(True)
+            lin.gemv(x, k, y[1], ws)
+            ws.set_separate_select(False)
+            idx, xsel = (torch.from_numpy(a).cuda() for a in ws.read_selection(k))
+            dd.decdec_gemv_idx(lin.desc, x, lin.Wq, lin.scales, lin.zeros, lin.R, lin.R_scales, k, idx, xsel, y[2], ws)
+            for other in y[1:]:
+                assert torch.equal(y[0].view(torch.int16), other.view(torch.int16)), seed
     finally:
         ws.close()

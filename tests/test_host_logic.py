@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import paper_2412_20185_amd as dd
+from helpers import fetch_plan
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -247,3 +248,25 @@ def test_scale_search_whose_grid_fits():
         False, True, True, False, False, True]
     # 64 threads a column
     assert by_bounds(4, 384, (1 << 26) - 64) and not by_bounds(4, 384, 1 << 26) and not by_bounds(4, 384, (1 << 31) - 64)
+
+
+def test_row_split_does_not_depend_on_who_selects():
+    """The bits of y are those of the split of the rows: a call that selects for itself and one that is given the selection
+    split them alike, and only the former asks for rows early."""
+    rng = np.random.default_rng(4)
+    widths = [[64], [4096], [9728], [16384], [20992], [28672], [57344], [4096, 1024, 1024], [8192, 1024, 1024], [14336, 14336]]
+    widths += [(64 * np.exp(rng.uniform(0, np.log(1000), n)).astype(int)).tolist() for n in (1, 1, 1, 1, 2, 3, 4) for _ in range(6)]
+    early = set()
+    for Ns in widths:
+        for K in (128, 1024, 4096, 8192, 14336, 16384, 16512, 28672):
+            for k in sorted({1, 8, 60, 64, 65, 81, 170, 171, 290, 576, 577, K} & set(range(1, K + 1))):
+                for rfmt in range(4):
+                    for split, in_hbm in ((0, False), (0, True), (5, False), (128, False)):
+                        a = fetch_plan(rfmt, K, Ns, k, split, in_hbm, True)
+                        b = fetch_plan(rfmt, K, Ns, k, split, in_hbm, False)
+                        what = (rfmt, K, Ns, k, split, in_hbm)
+                        assert (a.segments, a.slices, a.row_waves) == (b.segments, b.slices, b.row_waves), what
+                        assert a.segments == sum((N + 511) // 512 for N in Ns) and 1 <= a.slices <= 16 and 1 <= a.row_waves <= 8, what
+                        assert b.early == 0 and (a.early == 0 or (split == 0 and not in_hbm)), what
+                        early.add((rfmt, a.early > 0))
+    assert early == {(r, e) for r in range(4) for e in (False, True)} - {(dd.R_INT2_SYM_COL, True)}
