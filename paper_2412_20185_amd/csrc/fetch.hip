@@ -54,9 +54,14 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     const size_t bytes = (size_t)p.segments * segment_bytes * k;
     const int one_each = p.segments * kWavesPerBlock * segment_bytes;  // a row per wavefront
     constexpr int kLinkBytes = 256 * 1024;
+    // Above 16384 channels the kernels have no such code (kAsksEarly), and eight wavefronts of each workgroup delay the base GEMV:
+    // us with three to seven and with eight, 60 4-bit rows, 17408 x 28672 (4-bit weights) 43.5 and 46.3, 28672 x 22016 42.1 and
+    // 44.3; 200 rows of 28672 x 16384 39.6 and 39.3.
+    constexpr int kEarlyMaxK = 4 * 8 * kBlockThreads;
+    static_assert(kAsksEarly<16, 4> && !kAsksEarly<16, 8>, "four chunks of eight keys per thread");
     p.early = 0;
-    if (row_split <= 0 && !in_hbm && rfmt != 2 && bytes > 64 * 1024 && per_segment <= 4 * kWavesPerBlock && one_each <= kLinkBytes &&
-        select_tries_chunks(sh.K / 8, k)) {
+    if (sh.K <= kEarlyMaxK && row_split <= 0 && !in_hbm && rfmt != 2 && bytes > 64 * 1024 && per_segment <= 4 * kWavesPerBlock &&
+        one_each <= kLinkBytes && select_tries_chunks(sh.K / 8, k)) {
         if (selects) p.early = std::min((kLinkBytes + one_each - 1) / one_each, 2048 / segment_bytes);
         // All wavefronts take rows then, where that is no slower with a supplied selection either: who selects must not show in
         // how the rows are split, because y has the bits of that split.  us with three to seven wavefronts of each workgroup ->

@@ -268,5 +268,7 @@ def test_row_split_does_not_depend_on_who_selects():
                         assert (a.segments, a.slices, a.row_waves) == (b.segments, b.slices, b.row_waves), what
                         assert a.segments == sum((N + 511) // 512 for N in Ns) and 1 <= a.slices <= 16 and 1 <= a.row_waves <= 8, what
                         assert b.early == 0 and (a.early == 0 or (split == 0 and not in_hbm)), what
+                        if K > 16384:  # no code for early rows, and as many wavefronts as without
+                            assert a.early == 0 and (split or in_hbm or a.segments < 17 or a.row_waves == min(k, -(-128 // a.segments))), what
                         early.add((rfmt, a.early > 0))
     assert early == {(r, e) for r in range(4) for e in (False, True)} - {(dd.R_INT2_SYM_COL, True)}
