@@ -87,15 +87,19 @@ int fetch_select_chunks(int K, int k) {
     return K <= per_chunk_round ? 1 : K <= 2 * per_chunk_round ? 2 : K <= 4 * per_chunk_round ? 4 : 8;
 }
 
+template <int BITS, int NCH>
+static hipError_t launch_fetch_kernel(const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
+    return launch_kernel(tm, fetch_kernel<BITS, NCH>, dim3((unsigned)(a.segments * a.cslices)), dim3(kBlockThreads),
+                         fetch_lds_bytes<BITS>(a, NCH), stream, a);
+}
+
 template <int NCH>
 static hipError_t launch_fetch_nch(int rfmt, const CallArgs& a, hipStream_t stream, const KernelTimer* tm) {
-    const unsigned lds = fetch_lds_bytes(a, NCH);
-    const dim3 grid((unsigned)(a.segments * a.cslices)), block(kBlockThreads);
     switch (rfmt) {
-        case 0: return launch_kernel(tm, fetch_kernel<16, NCH>, grid, block, lds, stream, a);
-        case 1: return launch_kernel(tm, fetch_kernel<4, NCH>, grid, block, lds, stream, a);
-        case 2: return launch_kernel(tm, fetch_kernel<2, NCH>, grid, block, lds, stream, a);
-        default: return launch_kernel(tm, fetch_kernel<8, NCH>, grid, block, lds, stream, a);
+        case 0: return launch_fetch_kernel<16, NCH>(a, stream, tm);
+        case 1: return launch_fetch_kernel<4, NCH>(a, stream, tm);
+        case 2: return launch_fetch_kernel<2, NCH>(a, stream, tm);
+        default: return launch_fetch_kernel<8, NCH>(a, stream, tm);
     }
 }
 

@@ -146,6 +146,14 @@ constexpr int kLanesPerEarlyRow = kFetchSegmentCols * BITS / 128;  // 16 bytes e
 template <int BITS>
 constexpr int kEarlyRows = 2 * 64 / kLanesPerEarlyRow<BITS>;  // per wavefront
 static_assert(kEarlyRows<4> <= 8, "SelectShared::asked");
+// Rows that a wavefront has LDS for: both 16-byte pieces of its lanes, or the first ones where that is enough, as it is in wide
+// matrices.  Their base GEMV outlasts few rows, and a workgroup starts earlier where the LDS holds one more than the wavefronts
+// that fit, because those of another that have ended leave its LDS behind: 20 4-bit rows, 4-bit weights, 8192 x 16384 13.1 us
+// with 31 KiB a workgroup, 13.5 with 32 (33 as allocated) or 39; 14336 x 16384 20.9 and 21.1.
+template <int BITS>
+__host__ __device__ constexpr int early_slots(int early) {
+    return early <= kEarlyRows<BITS> / 2 ? kEarlyRows<BITS> / 2 : kEarlyRows<BITS>;
+}
 
 // The selection and the sum over the wavefronts follow one another and share their LDS.
 template <int BITS, int SELECT_NCH>
@@ -159,10 +167,11 @@ union FetchLds {
 __host__ __device__ inline unsigned selection_lds_bytes(int select_chunks, int k) {
     return select_chunks > 0 ? (unsigned)(((size_t)k * 6 + 15) / 16 * 16) : 0u;
 }
-constexpr unsigned kEarlyLdsBytes = kWavesPerBlock * 2 * 64 * 16;
 // Host: of a kernel that selects for itself.
+template <int BITS>
 inline unsigned fetch_lds_bytes(const CallArgs& a, int select_chunks) {
-    return selection_lds_bytes(select_chunks, a.k) + (a.early > 0 ? kEarlyLdsBytes : 0u);
+    const unsigned early = a.early > 0 ? kWavesPerBlock * early_slots<BITS>(a.early) * (kFetchSegmentCols * BITS / 8) : 0u;
+    return selection_lds_bytes(select_chunks, a.k) + early;
 }
 
 // One workgroup = one column segment of 512 columns x the rows of row slice rs.  A lane reads 8 columns of a
@@ -249,7 +258,7 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid, FetchLds
             if (wanted && rank < n) {
                 const int e = __builtin_ctz(mark_above(chunk_keys, top - 1));
                 asked[rank] = (uint16_t)(chunk * 8 + e);
-                tag = (unsigned)e | (unsigned)(wave * kEarlyRows<BITS> + rank + 1) << 3;
+                tag = (unsigned)e | (unsigned)(wave * early_slots<BITS>(a.early) + rank + 1) << 3;
             }
             wave_writes_seen();
             const unsigned pieces = (unsigned)N * BITS / 128;
@@ -333,9 +342,12 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid, FetchLds
             if constexpr (EARLY) {
                 if (asked) {
                     asked = false;
-                    uint4* to = early_lds + wave * 128 + lane;
+                    const bool both = early_slots<BITS>(a.early) == kEarlyRows<BITS>;
+                    uint4* to = early_lds + (both ? wave * 128 : wave * 64) + lane;
                     to[0] = early0;
-                    to[64] = early1;
+                    // on every path, if need be to a place that nobody reads: with a condition 14336 x 4096 takes 0.15 us more
+                    to = both ? to + 64 : reinterpret_cast<uint4*>(red) + lane;
+                    to[0] = early1;
                     __syncthreads();
                 }
             }

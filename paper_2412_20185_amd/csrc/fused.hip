@@ -47,7 +47,8 @@ void compensated_gemv_kernel(const CallArgs a) {
 template <int KIND, int RBITS, int DEPTH>
 hipError_t launch_nch(const CallArgs& a, int nch, bool over_link, hipStream_t stream, const KernelTimer* tm) {
     const dim3 grid((unsigned)(a.nfetch + a.tiles * (kTileCols / kOneGridCols) * a.gslices)), block(kBlockThreads);
-    const unsigned lds = std::max(one_grid_lds(KIND, RBITS, nch, a.k, (long)a.tiles * a.gslices, over_link), fetch_lds_bytes(a, nch));
+    const unsigned lds = std::max(one_grid_lds(KIND, RBITS, nch, a.k, (long)a.tiles * a.gslices, over_link),
+                                  fetch_lds_bytes<RBITS>(a, nch));
     switch (nch) {
         case 0: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 0, DEPTH>, grid, block, lds, stream, a);
         case 1: return launch_kernel(tm, compensated_gemv_kernel<KIND, RBITS, 1, DEPTH>, grid, block, lds, stream, a);

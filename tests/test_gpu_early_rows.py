@@ -7,7 +7,7 @@ import torch
 import oracle
 import workloads
 import paper_2412_20185_amd as dd
-from helpers import Problem, assert_parity
+from helpers import RFMT, Problem, assert_parity, fetch_plan
 from paper_2412_20185_amd.layer import StoredLinear
 
 pytestmark = pytest.mark.gpu
@@ -36,9 +36,13 @@ def activations(K, k):
 
 
 @pytest.mark.parametrize("rfmt,K,N,k", [("fp16", 4096, 1600, 81), ("int8", 4096, 2112, 60), ("int4", 4096, 4160, 61),
-                                        ("int4", 8320, 2048, 100), ("int8", 16384, 1536, 200), ("fp16", 2048, 4096, 85),
-                                        ("int4", 1024, 28672, 5)])
+                                        ("int4", 8320, 2048, 100), ("int8", 16384, 2112, 200), ("fp16", 2048, 4096, 85),
+                                        ("int4", 1024, 28672, 5),
+                                        # two and four chunks of keys per thread; fp16 rows of eight segments are finished by a look
+                                        ("fp16", 6144, 3648, 90), ("int8", 6144, 4160, 90), ("int4", 6144, 2048, 90),
+                                        ("fp16", 8320, 3648, 100), ("int8", 8320, 4160, 100)])
 def test_early_rows(rfmt, K, N, k):
+    assert fetch_plan(RFMT[rfmt], K, [N], k).early > 0
     g = np.random.default_rng(N)
     W = workloads.weights(71, 0, 0, K, N) if K * N < 1 << 23 else (g.standard_normal((K, N), dtype=np.float32) * 0.02)
     p = Problem(W, 4, rfmt=rfmt, alphas=oracle.quantize.DEFAULT_ALPHAS[::35])
@@ -67,6 +71,7 @@ def test_early_rows(rfmt, K, N, k):
 def test_infinite_activations():
     """An infinite and a NaN activation are selected first; the columns hold what the products give, as without early rows."""
     K, N, k = 4096, 4096, 60
+    assert fetch_plan(dd.R_FP16, K, [N], k).early > 0
     p = Problem(workloads.weights(72, 0, 0, K, N), 4)
     x = workloads.x_gauss_outliers(72, 0, 0, 0, K)
     x[[7, 2000]] = [np.inf, -np.inf]
