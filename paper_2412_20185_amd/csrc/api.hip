@@ -654,7 +654,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     const bool fused = k > 0 && c.mode == DECDEC_MODE_FUSED;
     const GemvPlan gp = gemv_plan(kind, tiles, sh.K / kGroup, c.gemv_gpw, c.gemv_wpb, fused, !residuals_in_hbm);
     const int gslices = gp.slices;
-    FetchPlan plan{0, 0, 0, 0};
+    FetchPlan plan{};
     // 0: the selection is there, or a kernel of its own makes it
     const int select_chunks = k > 0 && !have_idx && !c.separate_select ? fetch_select_chunks(sh.K, k) : 0;
     if (k > 0) plan = fetch_plan(d0->rfmt, sh, k, c.fetch_split, residuals_in_hbm, select_chunks > 0);
@@ -692,6 +692,7 @@ int gemv_common(int32_t count, const decdec_linear* lin, const void* x, int32_t 
     a.cslices = cslices;
     a.row_waves = plan.row_waves;
     a.early = plan.early;
+    a.look = plan.look;
     a.rows_per = k > 0 ? (k + cslices * plan.row_waves - 1) / (cslices * plan.row_waves) : 0;
     a.cdiv = reciprocal_of(cslices);
     a.nfetch = plan.segments * plan.slices;

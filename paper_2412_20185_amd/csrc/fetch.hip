@@ -76,6 +76,16 @@ FetchPlan fetch_plan(int rfmt, const MultiShape& sh, int k, int row_split, bool 
     }
     p.slices = (per_segment + kWavesPerBlock - 1) / kWavesPerBlock;
     p.row_waves = (per_segment + p.slices - 1) / p.slices;
+    // With the rows of a segment in one workgroup, a look at the accumulators behind the requests of a batch: who sees the base
+    // GEMV's part sums there writes y without the trip of an atomic.  It is a trip to memory itself, which the rows behind it wait
+    // for, and a long one while the base GEMV adds its sums: only with fp16 rows (fewer bits 1 to 6 % slower) that take more than
+    // 16 us of the link, or a base GEMV of 8 Mi weights at most.  us without and with: 4096 x 6144, k = 96 25.7 and 25.4, 14336 x
+    // 6144, k = 122 32.5 and 31.9, 8192 x 8192, k = 61 23.4 and 22.8, 2048 x 4096, k = 32 9.4 and 9.2; but 14336 x 6144, k = 24
+    // 10.7 and 11.6, 8192 x 4096, k = 65 15.1 and 15.5, 14336 x 8192, k = 20 11.6 and 14.1; above 16 segments 8192 x 16384, k =
+    // 163 100.4 and 101.3.
+    constexpr size_t kLookBytes = 920000;
+    const bool rows_last = bytes > kLookBytes || (size_t)sh.K * sh.col0[sh.n] <= (size_t)1 << 23;
+    p.look = p.early > 0 && rfmt == 0 && p.slices == 1 && p.segments <= 16 && rows_last;
     return p;
 }
 

@@ -297,12 +297,10 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid, FetchLds
     const int j1 = wave < row_waves ? min(j0 + rows_per, k) : j0;
 
 
-    // Behind the requests of a batch a look at the column's accumulator: a workgroup that has a segment's rows to itself and sees
-    // the base GEMV's part sums there writes y without the trip of an atomic.  us, without and with: 4096 x 4096, 81 fp16 rows
-    // 17.4 and 16.1; 4096 x 6144 22.4 and 21.9; 8192 x 4096, 160 rows 28.9 and 28.1.  Where several workgroups share the
-    // rows it only costs (4096 x 2048, 81 rows 11.3 and 11.4), as it does with rows of fewer bits (14336 x 4096, 210 4-bit rows
-    // 14.7 and 14.9) and in GPU memory (4096 x 4096, 81 rows 5.4 and 5.6).
-    const bool looks = EARLY && BITS == 16 && slices == 1 && acc_words != nullptr;
+    // Behind the requests of a batch a look at the column's accumulator (fetch_plan says when): a workgroup that sees the base
+    // GEMV's part sums there writes y without the trip of an atomic.  Decided at run time: compiled without it, the loop takes 1 to
+    // 7 % longer with 61 to 122 rows of 4096 x 4096.
+    const bool looks = EARLY && BITS == 16 && a.look != 0 && acc_words != nullptr;
     unsigned long long seen = 0;
 
     float acc[CPL];

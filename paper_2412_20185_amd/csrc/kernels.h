@@ -90,6 +90,7 @@ struct CallArgs {
     int rows_per;             // rows of each of these wavefronts, rounded up
     unsigned cdiv;            // reciprocal_of(cslices)
     int early;                // rows a wavefront may ask for before the selection is complete
+    int look;                 // 1: a workgroup looks at the accumulators before it adds to them
     int nfetch;               // workgroups of the residual part of the one-grid kernel
     int32_t* idx;             // the selection: written by the kernel that selects, read by the others
     uint16_t* xsel;
@@ -156,9 +157,10 @@ hipError_t launch_select_bucket(const void* x, int K, int k_chunk, float b0, flo
 // fetch.hip --------------------------------------------------------------
 // How the residual kernel is laid out: `segments` column segments (one 16-byte piece per lane and row; all
 // matrices of the call together) x `slices` workgroups per segment; `row_waves` wavefronts of each workgroup
-// share its rows; `early`: rows that a wavefront may ask for before the selection is complete.
+// share its rows; `early`: rows that a wavefront may ask for before the selection is complete; `look`: whether a workgroup that
+// has asked for rows early looks at the accumulators before it adds to them.
 struct FetchPlan {
-    int segments, slices, row_waves, early;
+    int segments, slices, row_waves, early, look;
 };
 // row_split: requested workgroups per segment (0 = automatic); in_hbm: the residual rows are in device
 // memory, not behind the host link.

@@ -21,8 +21,8 @@ class MultiShape(C.Structure):
 
 class FetchPlan(C.Structure):
     """How the residual rows are shared out: workgroups and wavefronts of each for a segment of 512 columns, and how many rows a
-    wavefront may ask for before the selection is complete."""
-    _fields_ = [(n, C.c_int) for n in ("segments", "slices", "row_waves", "early")]
+    wavefront may ask for before the selection is complete, and whether the workgroup looks at the accumulators first."""
+    _fields_ = [(n, C.c_int) for n in ("segments", "slices", "row_waves", "early", "look")]
 
 
 def fetch_plan(rfmt: int, K: int, Ns, k: int, row_split: int = 0, in_hbm: bool = False, selects: bool = True) -> FetchPlan:

@@ -38,9 +38,9 @@ def activations(K, k):
 @pytest.mark.parametrize("rfmt,K,N,k", [("fp16", 4096, 1600, 81), ("int8", 4096, 2112, 60), ("int4", 4096, 4160, 61),
                                         ("int4", 8320, 2048, 100), ("int8", 16384, 2112, 200), ("fp16", 2048, 4096, 85),
                                         ("int4", 1024, 28672, 5),
-                                        # two and four chunks of keys per thread; fp16 rows of eight segments are finished by a look
-                                        ("fp16", 6144, 3648, 90), ("int8", 6144, 4160, 90), ("int4", 6144, 2048, 90),
-                                        ("fp16", 8320, 3648, 100), ("int8", 8320, 4160, 100)])
+                                        # two and four chunks of keys per thread; fp16 rows whose sums are added after a look
+                                        ("fp16", 4096, 5696, 90), ("fp16", 4224, 5184, 90), ("fp16", 6144, 3648, 90), ("int8", 6144, 4160, 90), ("int4", 6144, 2048, 90),
+                                        ("fp16", 8320, 3648, 140), ("int8", 8320, 4160, 100)])
 def test_early_rows(rfmt, K, N, k):
     assert fetch_plan(RFMT[rfmt], K, [N], k).early > 0
     g = np.random.default_rng(N)

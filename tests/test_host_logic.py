@@ -272,3 +272,12 @@ def test_row_split_does_not_depend_on_who_selects():
                             assert a.early == 0 and (split or in_hbm or a.segments < 17 or a.row_waves == min(k, -(-128 // a.segments))), what
                         early.add((rfmt, a.early > 0))
     assert early == {(r, e) for r in range(4) for e in (False, True)} - {(dd.R_INT2_SYM_COL, True)}
+
+
+def test_look_at_the_accumulators_only_behind_long_rows():
+    """The look waits for memory that the base GEMV is adding to: not where the rows are there before its sums are."""
+    plan = lambda K, N, k, rfmt=dd.R_FP16, **kw: fetch_plan(rfmt, K, [N], k, **kw)
+    assert [plan(K, N, k).look for K, N, k in ((14336, 16384, 20), (14336, 8192, 20), (8192, 8192, 12), (14336, 6144, 24))] == [0] * 4
+    assert [plan(K, N, k).look for K, N, k in ((4096, 6144, 81), (8192, 8192, 61), (14336, 4096, 286), (2048, 4096, 20))] == [1] * 4
+    assert [plan(8192, 8192, 61, **kw).look for kw in (dict(selects=False), dict(in_hbm=True), dict(row_split=8))] == [0] * 3
+    assert plan(8192, 8192, 200, dd.R_INT8_SYM_COL).look == 0 and plan(8192, 3584, 300).look == 0  # several workgroups a segment
