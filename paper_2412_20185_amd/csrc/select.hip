@@ -18,8 +18,9 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const uint16_t* __
                                                              uint16_t* __restrict__ xsel_out) {
     __shared__ SelectShared<THREADS, NCH> sh;
     uint4 ch[NCH];
-    load_keys(x, K, ch);
-    block_select_topk<THREADS, NCH, RADIX>(ch, K, k, sh, idx_out, xsel_out);
+    const bool even = even_runs<NCH>(K / 8, k);
+    load_keys<THREADS>(x, K, even, ch);
+    block_select_topk<THREADS, NCH, RADIX>(ch, K, even, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace

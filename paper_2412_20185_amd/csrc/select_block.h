@@ -2,38 +2,41 @@
 // Top-K of Section 5.2; a tie at the cut goes to the lower index).  Used by the
 // stand-alone selection kernel and by kernels that select for themselves.
 //
-// x is read once and stays in registers: wavefront w owns the 64*NCH consecutive
-// 8-key chunks starting at w*64*NCH; lane l holds chunk w*64*NCH + j*64 + l for
-// j = 0..NCH-1 (one coalesced 128-bit load per j), so inside a wavefront the
-// channel order is (j, lane, position in the chunk) and wavefronts follow one
-// another.  The order of |x| is the order of the 15-bit key (fp16 bits, sign
-// cleared).  Output is in ascending index order.
+// x is read once and stays in registers, in chunks of 8 keys: a wavefront owns a
+// run of consecutive chunks (ChunkRun), of which lane l holds chunk l, l + 64, ...
+// (one coalesced 128-bit load each), so inside a wavefront the channel order is
+// (j, lane, position in the chunk) and wavefronts follow one another.  The order
+// of |x| is the order of the 15-bit key (fp16 bits, sign cleared).  Output is in
+// ascending index order.
 //
 // What bounds the selection is the instruction issue of the one compute unit it
 // runs on, so few instructions may touch every key.  Two forms:
 //
-//   chunks (select_by_chunks), when k is at most a third of the number of chunks
-//   and at most 576 (beyond, the bound is too low to exclude much): k chunks
-//   hold a key at least as large as the k-th largest chunk maximum, so that is a
-//   lower bound of the k-th largest key.
+//   chunks (list_chunks, select_listed), when k is at most a third of the number
+//   of chunks and at most 576 (beyond, the bound is too low to exclude much): k
+//   chunks hold a key at least as large as the k-th largest chunk maximum, so that
+//   is a lower bound of the k-th largest key.
 //     1. chunk maxima by packed 16-bit maxima; a 256-bin LDS histogram of their
 //        high 8 bits gives the bin that holds the k-th largest; its lower edge L
 //        is the bound;
 //     2. every wavefront lists its chunks with a maximum >= L, in order, in its
-//        own part of an LDS list and takes them back one or two per lane (left out
-//        when every thread has one chunk), so that no barrier and no sum over
-//        wavefronts stands in front of the next step.  Fewer than k chunks have a
-//        maximum in a bin above; nearly always all of these maxima are selected,
-//        and a caller may act on them while the rest is found out (`ask`);
+//        own part of an LDS list and takes them back one to three per lane (left
+//        out when every thread has one chunk), so that no barrier and no sum over
+//        wavefronts stands in front of the next step.  A wavefront with more of
+//        them than its list holds then puts the others there and reads them when
+//        they are needed.  Fewer than k chunks have a maximum in a bin above;
+//        nearly always all of these maxima are selected, and a caller may act on
+//        them while the rest is found out (`ask`);
 //     3. a 256-bin LDS histogram of key - L over their keys gives T, the k-th
 //        largest key itself, and how many keys equal to T are needed; only when
 //        T >= L + 255 (large |x| crowded into few chunks) it is formed twice more,
 //        over 128-key bins and inside the bin that holds T;
 //     4. masks of the keys > T and == T and one prefix sum place every selected
 //        element.
-//   radix (select_by_radix), for larger k, or when more than kListedPerWave chunks
-//   of a wavefront reach L (many equal keys): LDS histograms of all keys over their
-//   high 8 and low 7 bits, then masks and prefix sums over every key.
+//   radix (select_by_radix), for larger k, or when the bound is zero (fewer than k
+//   chunks with a key of 2^-17 or more) or a wavefront has more than two lists of
+//   chunks (384 of up to 512): LDS histograms of all keys over their high 8 and
+//   low 7 bits, then masks and prefix sums over every key.
 // Every phase is a chain of dependent instructions of a few wavefronts, about 2 ns each, and of LDS trips (with all of its
 // instructions in the cache it takes the same time): finding a bin and marking keys take as few as they can.
 // Stand-alone kernel in graph replays, radix for every key -> chunks, us: K = 1024, k = 32: 3.4 -> 2.7; 4096, 60:
@@ -54,7 +57,8 @@ namespace decdec {
 constexpr int kSelectMaxChunks = 8;  // 8-key chunks per thread at most
 
 constexpr int kMaxByChunks = 576;    // the bin of L alone can make the list 1.77 times as long as k (|x| normal, k 1 % of K)
-// Chunks of a wavefront with a key that may be selected.  Of 1020 such chunks in all, each of eight wavefronts has 128 +- 10.
+// Chunks with a key that may be selected in a wavefront's list.  Of 1020 such chunks in all, each of eight wavefronts has 128 +- 10
+// where the channels' magnitudes are alike; where they fall along the channels the first wavefronts have more.
 template <int THREADS, int NCH>
 constexpr int kListedPerWave = THREADS <= 512 && NCH == 8 ? 192 : 128;
 
@@ -69,7 +73,7 @@ struct SelectShared {
     __attribute__((aligned(16))) unsigned hist1[256];
     __attribute__((aligned(16))) unsigned hist2[256];
     __attribute__((aligned(16))) unsigned wtot[16];  // per wave: (keys > T) | (keys == T) << 16
-    int overflow;                                     // 1: a wavefront's list is too short
+    int overflow;                                     // 1: a wavefront's list, filled twice, is too short
     uint16_t asked[THREADS / 64][8];                  // for the caller's `ask`
 };
 
@@ -222,30 +226,75 @@ __device__ __forceinline__ void mark_chunk(const uint4& c, unsigned T, unsigned&
     eq = mark_above(c, T - 1) & ~gt;
 }
 
-// A lane's chunks once those that cannot matter are gone.
+// The chunks of a thread: chunk(j) for those j that has(j) is true for.  The runs of the wavefronts are 64 * NCH chunks, with which
+// the fewest have any (each issues the steps 3 and 4, however few chunks it lists), or all alike.  us, full runs and even ones:
+// K = 22016, k = 220 4.3 and 4.5; 16512, 516, where five wavefronts would list 190 chunks each, 5.6 and 5.4.
+template <int THREADS, int NCH>
+struct ChunkRun {
+    int first, left;  // chunk(0); chunks of the wavefront's run from it on
+    __device__ __forceinline__ ChunkRun(int nchunks, bool even) {
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+        const int each = even ? (nchunks + THREADS / 64 - 1) / (THREADS / 64) : 64 * NCH;
+        first = wave * each + lane;
+        left = min(each, nchunks - wave * each) - lane;
+    }
+    __device__ __forceinline__ bool has(int j) const { return 64 * j < left; }
+    __device__ __forceinline__ int chunk(int j) const { return first + 64 * j; }
+};
+// Even runs where full ones would make the lists long (the bin of L makes them up to 1.77 times k).  Residual kernels with up to
+// four chunks per thread always have full ones: the choice in front of their first load takes 14336 x 4096 1 % longer.
+template <int NCH>
+__device__ __forceinline__ bool even_runs(int nchunks, int k) {
+    return NCH > 1 && k > 40 * ((nchunks + 64 * NCH - 1) / (64 * NCH));
+}
+
+// A lane's chunks once those that cannot matter are gone: entries lane, lane + 64, ... of the wavefront's list.
 template <int THREADS, int NCH>
 struct Listed {
-    static constexpr int kPer = NCH == 1 ? 1 : kListedPerWave<THREADS, NCH> / 64;
+    static constexpr int kList = NCH == 1 ? 64 : kListedPerWave<THREADS, NCH>;
+    static constexpr int kPer = kList / 64;
+    static constexpr bool kMayBeMore = NCH * 64 > kList;  // more than the list holds: the others then take their place in LDS,
+    static constexpr bool kMayOverflow = NCH * 64 > 2 * kList;  // and not even that is enough: sh.overflow
     uint4 keys[kPer];
     int chunk[kPer];
-    unsigned count = 0;  // chunks of this wavefront
-    unsigned L = 0;      // the bound; 0: the chunks do not give one
+    int count = 0;   // chunks of this wavefront
+    unsigned L = 0;  // the bound; 0: the chunks do not give one
+
+    // f(keys, chunk) in all lanes for 64 at a time of those that are more (keys of 0 in lanes that have none).  Few wavefronts
+    // have any, and they have a trip to LDS for them at every step; kept in registers they would cost every kernel 10 to 20.
+    template <typename F>
+    __device__ __forceinline__ void each_more(const SelectShared<THREADS, NCH>& sh, const F& f) const {
+        if constexpr (kMayBeMore) {
+            if (__builtin_expect(count > kList, 0)) {
+                const int lane = threadIdx.x & 63, at = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * kList;
+#pragma unroll 1
+                for (int i = 0; i < count - kList; i += 64) {
+                    const bool have = i + lane < count - kList;
+                    const int e = at + min(i + lane, count - kList - 1);
+                    uint4 c = sh.list[e];
+                    if (!have) c = make_uint4(0, 0, 0, 0);
+                    f(c, (int)sh.list_chunk[e]);
+                }
+            }
+        }
+    }
 };
 
-// Steps 1 and 2.  Requires 1 <= k <= nchunks and sh.hist1, sh.overflow cleared (with a barrier behind).
+// Steps 1 and 2.  Requires 1 <= k <= nchunks and sh.hist1 cleared (with a barrier behind).
 template <int THREADS, int NCH>
-__device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared<THREADS, NCH>& sh,
+__device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], int nchunks, bool even, int k, SelectShared<THREADS, NCH>& sh,
                                             Listed<THREADS, NCH>& out) {
-    constexpr int LIST = kListedPerWave<THREADS, NCH>;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c0 = wave * 64 * NCH + lane;
+    typedef Listed<THREADS, NCH> L_t;
+    constexpr int LIST = L_t::kList;
+    const ChunkRun<THREADS, NCH> run(nchunks, even);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 
     unsigned cm[NCH];  // absent chunks: 0
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
         cm[j] = chunk_max(ch[j]);
-        if (c0 + 64 * j < nchunks) atomicAdd(&sh.hist1[cm[j] >> 7], 1u);
+        if (run.has(j)) atomicAdd(&sh.hist1[cm[j] >> 7], 1u);
     }
     __syncthreads();
     unsigned bin, need;
@@ -255,63 +304,79 @@ __device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], int nchunks,
     if (L == 0) return;
     if constexpr (NCH == 1) {
         out.keys[0] = ch[0];
-        out.chunk[0] = c0;
+        out.chunk[0] = run.chunk(0);
         out.count = 64;
     } else {
         uint4* list = sh.list + wave * LIST;
         uint16_t* list_chunk = sh.list_chunk + wave * LIST;
-        unsigned count = 0;
+        // entries from `from` on to the list; returns how many there are in all
+        const auto fill = [&](int from, const auto& top) {
+            int count = 0;
 #pragma unroll
-        for (int j = 0; j < NCH; ++j) {
-            const unsigned long long b = __ballot(cm[j] >= L);
-            const unsigned at = count + lanes_before(b);
-            if (cm[j] >= L && at < (unsigned)LIST) {
-                list[at] = ch[j];
-                list_chunk[at] = (uint16_t)(c0 + 64 * j);
+            for (int j = 0; j < NCH; ++j) {
+                const bool wanted = top(j) >= L;
+                const unsigned long long b = __ballot(wanted);
+                const int at = count + (int)lanes_before(b) - from;
+                if (wanted && (!L_t::kMayBeMore || (unsigned)at < (unsigned)LIST)) {
+                    list[at] = ch[j];
+                    list_chunk[at] = (uint16_t)run.chunk(j);
+                }
+                count += (int)__builtin_popcountll(b);
             }
-            count += (unsigned)__builtin_popcountll(b);
-        }
-        if (NCH * 64 > LIST && count > (unsigned)LIST) {
-            if (lane == 0) sh.overflow = 1;
-            count = LIST;
-        }
-        wave_writes_seen();
+            wave_writes_seen();
+            return count;
+        };
+        out.count = fill(0, [&](int j) { return cm[j]; });
 #pragma unroll
-        for (int p = 0; p < Listed<THREADS, NCH>::kPer; ++p) {
-            const unsigned i = 64 * p + lane;
+        for (int p = 0; p < L_t::kPer; ++p) {
+            const int i = 64 * p + lane;
             out.keys[p] = make_uint4(0, 0, 0, 0);  // keys below L: never taken
             out.chunk[p] = 0;
-            if (i < count) {
+            if (i < out.count) {
                 out.keys[p] = list[i];
                 out.chunk[p] = list_chunk[i];
             }
         }
-        out.count = count;
+        if constexpr (L_t::kMayBeMore) {
+            if (__builtin_expect(out.count > LIST, 0)) {
+                wave_writes_seen();  // it has been read
+                (void)fill(LIST, [&](int j) { return chunk_max(ch[j]); });
+                if (L_t::kMayOverflow && out.count > 2 * LIST) {
+                    if (lane == 0) sh.overflow = 1;
+                    out.count = 2 * LIST;
+                }
+            }
+        }
     }
 }
 
 // Steps 3 and 4.  Requires L != 0 and sh.hist2 cleared.  False, in all threads, when a list was too short: nothing has been
 // written to the outputs then.
 template <int THREADS, int NCH>
-__device__ __forceinline__ bool select_listed(const Listed<THREADS, NCH>& l, int k, SelectShared<THREADS, NCH>& sh, int32_t* idx_out,
-                                              uint16_t* xsel_out, unsigned tag) {
-    constexpr int PER = Listed<THREADS, NCH>::kPer;
+__device__ __forceinline__ bool select_listed(const Listed<THREADS, NCH>& l, int k, SelectShared<THREADS, NCH>& sh,
+                                              int32_t* idx_out, uint16_t* xsel_out, unsigned tag) {
+    typedef Listed<THREADS, NCH> L_t;
+    constexpr int PER = L_t::kPer;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     unsigned T = l.L, bin, need;
     int shift = 0;  // bins of 2^shift keys from T on; the last one takes everything above
+    const auto count_keys = [&](const uint4& c) {
+        unsigned m = mark_above(c, T - 1);
+        while (m) {
+            atomicAdd(&sh.hist2[min((key_of(c, __builtin_ctz(m)) - T) >> shift, 255u)], 1u);
+            m &= m - 1;
+        }
+    };
     while (true) {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
-            if (64u * p >= l.count) break;  // wave-uniform
-            unsigned m = mark_above(l.keys[p], T - 1);
-            while (m) {
-                atomicAdd(&sh.hist2[min((key_of(l.keys[p], __builtin_ctz(m)) - T) >> shift, 255u)], 1u);
-                m &= m - 1;
-            }
+            if (64 * p >= l.count) break;  // wave-uniform
+            count_keys(l.keys[p]);
         }
+        l.each_more(sh, [&](const uint4& c, int) { count_keys(c); });
         __syncthreads();
-        if (NCH * 64 > kListedPerWave<THREADS, NCH> && __builtin_amdgcn_readfirstlane(sh.overflow)) return false;
+        if (L_t::kMayOverflow && __builtin_amdgcn_readfirstlane(sh.overflow)) return false;
         wave_find_bin<4>(sh.hist2, (unsigned)k, bin, need, lane);  // need: keys equal to T to take (>= 1) in the end
         T += bin << shift;
         if (shift == 0 && bin < 255) break;
@@ -322,39 +387,51 @@ __device__ __forceinline__ bool select_listed(const Listed<THREADS, NCH>& l, int
     }
 
     unsigned gt[PER], eq[PER], at[PER], total = 0;  // at: marked keys of this wavefront in front of the chunk's
+    const auto mark_and_count = [&](const uint4& c, unsigned& g, unsigned& e, unsigned& a) {
+        mark_chunk(c, T, g, e);
+        const unsigned cnt = (unsigned)__builtin_popcount(g) | ((unsigned)__builtin_popcount(e) << 16);
+        const unsigned incl = wave_incl_scan(cnt) + total;
+        a = incl - cnt;
+        total = PER == 1 ? incl : (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
+    };
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
         gt[p] = eq[p] = at[p] = 0;
-        if (64u * p >= l.count) break;
-        mark_chunk(l.keys[p], T, gt[p], eq[p]);
-        const unsigned cnt = (unsigned)__builtin_popcount(gt[p]) | ((unsigned)__builtin_popcount(eq[p]) << 16);
-        const unsigned incl = wave_incl_scan(cnt) + total;
-        at[p] = incl - cnt;
-        total = PER == 1 ? incl : (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
+        if (64 * p >= l.count) break;
+        mark_and_count(l.keys[p], gt[p], eq[p], at[p]);
     }
+    const unsigned listed = total;
+    unsigned g, e, a;
+    l.each_more(sh, [&](const uint4& c, int) { mark_and_count(c, g, e, a); });
     if (lane == 63) sh.wtot[wave] = total;
     __syncthreads();
-    const unsigned before = totals_before<THREADS / 64>(sh.wtot, wave);  // no carry between the halves: at most 16384 marked keys
+    // fewer than k keys > T, and at most 65535 equal ones in front of any key: no carry between the halves
+    const unsigned before = totals_before<THREADS / 64>(sh.wtot, wave);
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-        if (64u * p >= l.count) break;
+        if (64 * p >= l.count) break;
         write_marked(l.keys[p], l.chunk[p] * 8, gt[p], eq[p], (before + at[p]) & 0xFFFFu, (before + at[p]) >> 16, need, (unsigned)k,
                      idx_out, xsel_out, p == 0 ? tag : 0u);
     }
+    total = listed;
+    l.each_more(sh, [&](const uint4& c, int chunk) {
+        mark_and_count(c, g, e, a);
+        write_marked(c, chunk * 8, g, e, (before + a) & 0xFFFFu, (before + a) >> 16, need, (unsigned)k, idx_out, xsel_out);
+    });
     return true;
 }
 
 // Any 1 <= k <= K.  Requires sh.hist1, sh.hist2 cleared (with a barrier behind).  MANY: many keys per chunk are marked.
 template <int THREADS, int NCH, bool MANY = false>
-__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, int k, SelectShared<THREADS, NCH>& sh,
-                                                int32_t* idx_out, uint16_t* xsel_out) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c0 = wave * 64 * NCH + lane;  // this thread's chunk of round j is c0 + 64*j
+__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, bool even, int k,
+                                                SelectShared<THREADS, NCH>& sh, int32_t* idx_out, uint16_t* xsel_out) {
+    const ChunkRun<THREADS, NCH> run(nchunks, even);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
     // pass 1: high 8 bits of the key
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-        if (c0 + 64 * j < nchunks) {
+        if (run.has(j)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) atomicAdd(&sh.hist1[key_of(ch[j], e) >> 7], 1u);
         }
@@ -366,7 +443,7 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
     // pass 2: low 7 bits of the keys inside bin b1
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-        if (c0 + 64 * j < nchunks) {
+        if (run.has(j)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const unsigned key = key_of(ch[j], e);
@@ -386,7 +463,7 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
         gtm[j] = eqm[j] = 0;
-        if (c0 + 64 * j < nchunks) {
+        if (run.has(j)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const unsigned key = key_of(ch[j], e);
@@ -410,18 +487,17 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
     }
 #pragma unroll
     for (int j = 0; j < NCH; ++j)
-        write_marked<MANY>(ch[j], (c0 + 64 * j) * 8, gtm[j], eqm[j], base_gt + (excl[j] & 0xFFFFu), base_eq + (excl[j] >> 16), need,
+        write_marked<MANY>(ch[j], run.chunk(j) * 8, gtm[j], eqm[j], base_gt + (excl[j] & 0xFFFFu), base_eq + (excl[j] >> 16), need,
                      (unsigned)k, idx_out, xsel_out);
 }
 
-// The keys of a thread: chunk j * 64 + lane of its wavefront's run.  Requires K a multiple of 8, K <= 8 * THREADS * NCH and
-// x 16-byte aligned.
-template <int NCH>
-__device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, int K, uint4 (&ch)[NCH]) {
-    const int tid = threadIdx.x, c0 = (tid >> 6) * 64 * NCH + (tid & 63), nchunks = K / 8;
+// The keys of a thread (ChunkRun).  Requires K a multiple of 8, K <= 8 * THREADS * NCH and x 16-byte aligned.
+template <int THREADS, int NCH>
+__device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, int K, bool even, uint4 (&ch)[NCH]) {
+    const ChunkRun<THREADS, NCH> run(K / 8, even);
     const uint4* x128 = reinterpret_cast<const uint4*>(x);
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) ch[j] = c0 + 64 * j < nchunks ? x128[c0 + 64 * j] : make_uint4(0, 0, 0, 0);
+    for (int j = 0; j < NCH; ++j) ch[j] = run.has(j) ? x128[run.chunk(j)] : make_uint4(0, 0, 0, 0);
 }
 
 // The caller does not act on a part of the selection.
@@ -429,8 +505,8 @@ struct AskNothing {
     __device__ __forceinline__ unsigned operator()(const uint4&, int, unsigned, unsigned) const { return 0; }
 };
 
-// All THREADS threads of the workgroup call this, with their keys (load_keys) and 1 <= k <= K.  idx_out / xsel_out may
-// point to global memory or LDS; xsel_out may be null.  Ends with the outputs
+// All THREADS threads of the workgroup call this, with their keys (load_keys, the same `even`) and 1 <= k <= K.  idx_out / xsel_out
+// may point to global memory or LDS; xsel_out may be null.  Ends with the outputs
 // written but not yet synchronised (the caller adds the barrier it needs).  RADIX: the caller knows that
 // select_tries_chunks(K / 8, k) is false.
 //
@@ -438,20 +514,20 @@ struct AskNothing {
 // 0: none).  Fewer than k chunks have a maximum >= edge.  Returns the lane's tag (write_marked), which only a selection by
 // chunks writes.
 template <int THREADS, int NCH, bool RADIX = false, typename Ask = AskNothing>
-__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, int k, SelectShared<THREADS, NCH>& sh,
+__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, bool even, int k, SelectShared<THREADS, NCH>& sh,
                                                   int32_t* idx_out, uint16_t* xsel_out, const Ask& ask = Ask()) {
     static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
     const int tid = threadIdx.x, nchunks = K / 8;
     const auto clear = [&] {
         for (int i = tid; i < 256; i += THREADS) sh.hist1[i] = sh.hist2[i] = 0;
-        if (NCH * 64 > kListedPerWave<THREADS, NCH> && tid == 0) sh.overflow = 0;
+        if (Listed<THREADS, NCH>::kMayOverflow && tid == 0) sh.overflow = 0;
         __syncthreads();
     };
     clear();
     if constexpr (!std::is_same_v<Ask, AskNothing>) {  // on every path, see `ask`
         const bool chunks = select_tries_chunks(nchunks, k);
         Listed<THREADS, NCH> l;
-        if (chunks) list_chunks(ch, nchunks, k, sh, l);
+        if (chunks) list_chunks(ch, nchunks, even, k, sh, l);
         const unsigned tag = ask(l.keys[0], l.chunk[0], l.L != 0 ? chunk_max(l.keys[0]) : 0u, l.L + 128);
         if (l.L != 0 && select_listed(l, k, sh, idx_out, xsel_out, tag)) return;
         if (chunks) {
@@ -460,12 +536,12 @@ __device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K,
         }
     } else if (!RADIX && select_tries_chunks(nchunks, k)) {
         Listed<THREADS, NCH> l;
-        list_chunks(ch, nchunks, k, sh, l);
+        list_chunks(ch, nchunks, even, k, sh, l);
         if (l.L != 0 && select_listed(l, k, sh, idx_out, xsel_out, 0)) return;
         __syncthreads();
         clear();
     }
-    select_by_radix<THREADS, NCH, RADIX>(ch, nchunks, k, sh, idx_out, xsel_out);
+    select_by_radix<THREADS, NCH, RADIX>(ch, nchunks, even, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace decdec
