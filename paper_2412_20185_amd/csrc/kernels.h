@@ -21,7 +21,6 @@ constexpr int kCus = 256;               // compute units of the card
 constexpr int kFetchSegmentCols = 512;  // output columns of one column segment = threads of a fetch workgroup
 constexpr int kMaxGemvSlices = 16;   // part sums per column the base GEMV may contribute (K-slices)
 constexpr int kMaxFetchSlices = 16;  // part sums per column the residual kernel may contribute (row slices)
-constexpr int kSelectThreads = 1024;
 constexpr int kSelectMaxK = 65536;
 
 // Optional pair of events that receive the begin and end timestamps of one

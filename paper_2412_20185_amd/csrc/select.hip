@@ -18,7 +18,7 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const uint16_t* __
                                                              uint16_t* __restrict__ xsel_out) {
     __shared__ SelectShared<THREADS, NCH> sh;
     uint4 ch[NCH];
-    const bool even = even_runs<NCH>(K / 8, k);
+    const bool even = !RADIX && even_runs<NCH>(K / 8, k);
     load_keys<THREADS>(x, K, even, ch);
     block_select_topk<THREADS, NCH, RADIX>(ch, K, even, k, sh, idx_out, xsel_out);
 }
@@ -33,15 +33,14 @@ hipError_t launch_select_topk(const void* x, int K, int k, int32_t* idx_out, voi
     // one chunk of 8 channels per thread as long as that gives enough threads: no list of chunks is needed then
     if (K <= 2048) return launch_kernel(tm, select_topk_kernel<256, 1>, one, dim3(256), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 4096) return launch_kernel(tm, select_topk_kernel<512, 1>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
-    // Above, by chunks with eight wavefronts (select_block.h); a k too large for the chunk form has 1024 threads, and above 8192
-    // channels a kernel without that form, with its marked keys' words chosen by comparisons.  us, the kernel with both forms
-    // -> without: K = 14336, k = 1433: 7.24 -> 7.14; 28672, 2867: 11.53 -> 11.40; 32768, 3276: 12.14 -> 11.98.  Up to 8192 the
-    // two take the same, or this one 0.02 more.
+    // Above, by chunks with eight wavefronts (select_block.h); a k too large for the chunk form has 1024 threads and kernels without
+    // that form, with the marked keys' words chosen by comparisons.  us, the kernel with both forms -> without: K = 14336, k =
+    // 1433: 7.24 -> 7.14; 28672, 2867: 11.53 -> 11.40; 32768, 3276: 12.14 -> 11.98.
     const bool radix = !select_tries_chunks(K / 8, k);
     if (!radix && K <= 8192) return launch_kernel(tm, select_topk_kernel<512, 2>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
     if (!radix && K <= 16384) return launch_kernel(tm, select_topk_kernel<512, 4>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
     if (!radix && K <= 32768) return launch_kernel(tm, select_topk_kernel<512, 8>, one, dim3(512), 0, stream, xp, K, k, idx_out, xs);
-    if (K <= 8192) return launch_kernel(tm, select_topk_kernel<1024, 1>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
+    if (K <= 8192) return launch_kernel(tm, select_topk_kernel<1024, 1, true>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 16384) return launch_kernel(tm, select_topk_kernel<1024, 2, true>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
     if (K <= 32768) return launch_kernel(tm, select_topk_kernel<1024, 4, true>, one, dim3(1024), 0, stream, xp, K, k, idx_out, xs);
     return launch_kernel(tm, radix ? select_topk_kernel<1024, 8, true> : select_topk_kernel<1024, 8>, one, dim3(1024), 0, stream,
