@@ -343,7 +343,7 @@ __device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], int nchunks,
                 (void)fill(LIST, [&](int j) { return chunk_max(ch[j]); });
                 if (L_t::kMayOverflow && out.count > 2 * LIST) {
                     if (lane == 0) sh.overflow = 1;
-                    out.count = 2 * LIST;
+                    out.count = 0;  // all go to the radix form: many equal keys are not counted here too
                 }
             }
         }
