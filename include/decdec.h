@@ -133,9 +133,13 @@ int decdec_ws_read_selection(const decdec_ws* ws, int32_t k, int32_t* idx_host, 
  * in the residual kernel, 1 .. 128 (the counterpart of n_tb in Section 4.4:
  * how many requests are in flight on the host link, at the price of compute
  * units the base GEMV cannot use); they are grouped into workgroups of 8, each
- * of which adds its rows' sum once per column.  0 restores the built-in choice (about
- * 128 wavefronts in the whole kernel, which saturate the link; more than about
- * 500 lower its rate).  Affects later calls on this workspace. */
+ * of which adds its rows' sum once per column.  0 restores the built-in choice: about
+ * 128 wavefronts in the whole kernel, which saturate the link (more than about 500
+ * lower its rate); with 4- and 8-bit rows over the link all eight of every
+ * workgroup, up to 448, where that is no slower.  Only with the built-in choice does
+ * a call that selects for itself request rows before its selection is complete.  How
+ * the rows are split, and with it the bits of y, does not depend on where the
+ * selection is made.  Affects later calls on this workspace. */
 int decdec_ws_set_fetch_split(decdec_ws* ws, int32_t row_split);
 
 /* How one compensated GEMV (k > 0) is laid out on the GPU.  Every mode adds the
@@ -157,7 +161,7 @@ int decdec_ws_set_mode(decdec_ws* ws, int32_t mode);
  * on = 0 (default): inside the residual kernel, every workgroup selecting for
  * itself (K <= 32768 and k <= 4096; larger problems use the selection kernel).
  * on = 1: always as a kernel of its own before the residual kernel.  The
- * selection is the same either way. */
+ * selection and y are the same either way, bit for bit. */
 int decdec_ws_set_separate_select(decdec_ws* ws, int32_t on);
 
 /* How the part sums of the base GEMV (one per K-slice) and of the residual
@@ -168,7 +172,8 @@ int decdec_ws_set_separate_select(decdec_ws* ws, int32_t on);
  *     converts its fp32 part sum of a column to a multiple of 2^-30 and adds it
  *     to the column's 64-bit accumulator with one atomic, which also counts the
  *     producers; the one that arrives last rounds the sum to fp16, writes y and
- *     clears the accumulator.  No further launch.
+ *     clears the accumulator (one that has read it and seen all others there does so
+ *     without adding).  No further launch.
  *   on = 0: the producers write fp32 partial rows and a small kernel of its own
  *     on the caller's stream, after both, converts and adds them the same way
  *     (same bits).  The first such call allocates the partial rows

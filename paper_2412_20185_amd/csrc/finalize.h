@@ -14,9 +14,10 @@
 //
 // The producer whose atomic returns arrivals == producers - 1 holds the whole
 // sum (returned value + own term), rounds it once to fp16, writes y and stores
-// zero to the word for the next call.  One memory round trip per producer, no
-// partial rows, no fences (each column is a location of its own), nobody
-// waits, and no extra launch.
+// zero to the word for the next call.  A producer that has read the word earlier
+// in the call and saw all others there does the same without adding
+// (arrive_after_look).  One memory round trip per producer, no partial rows, no
+// fences (each column is a location of its own), nobody waits, and no extra launch.
 //
 // Range and resolution: a part sum is clamped to +-2^21 before conversion
 // (far outside fp16's +-65504, so a clamped term can only make y infinite, or
