@@ -59,7 +59,7 @@ struct Selection {
 
 // `ask`: select_block.h.  What it adds to an index is above bit 15 (K <= 32768 here).
 template <int SELECT_NCH, typename Ask>
-__device__ __forceinline__ Selection obtain_selection(const uint4* keys, int K, bool even, int k, int32_t* idx_g, uint16_t* xsel_g,
+__device__ __forceinline__ Selection obtain_selection(const uint4* keys, int K, int k, int32_t* idx_g, uint16_t* xsel_g,
                                                       SelectShared<kBlockThreads, SELECT_NCH>& sh, int bid, const Ask& ask) {
     if constexpr (SELECT_NCH > 0) {
         extern __shared__ uint4 s_sel_raw[];
@@ -68,7 +68,7 @@ __device__ __forceinline__ Selection obtain_selection(const uint4* keys, int K, 
         uint4 ch[SELECT_NCH];
 #pragma unroll
         for (int j = 0; j < SELECT_NCH; ++j) ch[j] = keys[j];
-        block_select_topk<kBlockThreads, SELECT_NCH>(ch, K, even, k, sh, idx_l, xs_l, ask);
+        block_select_topk<kBlockThreads, SELECT_NCH>(ch, FullRuns<kBlockThreads, SELECT_NCH>(K / 8), K, k, sh, idx_l, xs_l, ask);
         __syncthreads();
         if (bid == 0) {
             for (int i = threadIdx.x; i < k; i += kBlockThreads) {
@@ -206,9 +206,7 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid, FetchLds
     const int k = a.k, K = a.G * kGroup;
     // the keys are asked for before anything else: the selection is the first link of this workgroup's chain of waits
     uint4 keys[SELECT_NCH > 0 ? SELECT_NCH : 1];
-    bool even = false;
-    if constexpr (SELECT_NCH == 8) even = even_runs<SELECT_NCH>(K / 8, k);
-    if constexpr (SELECT_NCH > 0) load_keys<kBlockThreads>(a.x, K, even, keys);
+    if constexpr (SELECT_NCH > 0) load_keys(a.x, FullRuns<kBlockThreads, SELECT_NCH>(K / 8), keys);
     const int row_waves = a.row_waves, slices = a.cslices;
     const int seg = divide_by(bid, a.cdiv);
     const int rs = bid - seg * slices;
@@ -277,9 +275,9 @@ __device__ __forceinline__ void fetch_block(const CallArgs& a, int bid, FetchLds
     };
     const Selection sel = [&] {
         if constexpr (EARLY) {
-            return obtain_selection<SELECT_NCH>(keys, K, even, k, a.idx, a.xsel, lds.sh, bid, ask);
+            return obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid, ask);
         } else {
-            return obtain_selection<SELECT_NCH>(keys, K, even, k, a.idx, a.xsel, lds.sh, bid, AskNothing());
+            return obtain_selection<SELECT_NCH>(keys, K, k, a.idx, a.xsel, lds.sh, bid, AskNothing());
         }
     }();
     if constexpr (BITS != 16 && !kScaleFirst) {

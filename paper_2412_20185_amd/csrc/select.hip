@@ -18,9 +18,15 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const uint16_t* __
                                                              uint16_t* __restrict__ xsel_out) {
     __shared__ SelectShared<THREADS, NCH> sh;
     uint4 ch[NCH];
-    const bool even = !RADIX && even_runs<NCH>(K / 8, k);
-    load_keys<THREADS>(x, K, even, ch);
-    block_select_topk<THREADS, NCH, RADIX>(ch, K, even, k, sh, idx_out, xsel_out);
+    const auto select = [&](const auto& run) {
+        load_keys(x, run, ch);
+        block_select_topk<THREADS, NCH, RADIX>(ch, run, K, k, sh, idx_out, xsel_out);
+    };
+    if constexpr (RADIX || NCH == 1) {
+        select(FullRuns<THREADS, NCH>(K / 8));
+    } else {
+        select(ChosenRuns<THREADS, NCH>(K / 8, k));
+    }
 }
 
 }  // namespace

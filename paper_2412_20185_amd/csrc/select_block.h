@@ -3,7 +3,7 @@
 // stand-alone selection kernel and by kernels that select for themselves.
 //
 // x is read once and stays in registers, in chunks of 8 keys: a wavefront owns a
-// run of consecutive chunks (ChunkRun), of which lane l holds chunk l, l + 64, ...
+// run of consecutive chunks, of which lane l holds chunk l, l + 64, ...
 // (one coalesced 128-bit load each), so inside a wavefront the channel order is
 // (j, lane, position in the chunk) and wavefronts follow one another.  The order
 // of |x| is the order of the 15-bit key (fp16 bits, sign cleared).  Output is in
@@ -227,13 +227,31 @@ __device__ __forceinline__ void mark_chunk(const uint4& c, unsigned T, unsigned&
 }
 
 // The chunks of a thread: chunk(j) for those j that has(j) is true for.  The runs of the wavefronts are 64 * NCH chunks, with which
-// the fewest have any (each issues the steps 3 and 4, however few chunks it lists), or all alike.  us, full runs and even ones:
-// K = 22016, k = 220 4.3 and 4.5; 16512, 516, where five wavefronts would list 190 chunks each, 5.6 and 5.4.
+// the fewest have any (each issues the steps 3 and 4, however few chunks it lists) ...
+// (Eight chunks per thread compare them with nchunks: against what is left of the run 22016 x 2048 takes 0.6 us longer.  With
+// four the lane masks that the former keeps are more than the residual kernels have scalar registers for.)
 template <int THREADS, int NCH>
-struct ChunkRun {
-    int first, left;  // chunk(0); chunks of the wavefront's run from it on
-    __device__ __forceinline__ ChunkRun(int nchunks, bool even) {
+struct FullRuns {
+    static constexpr bool kOfAll = NCH == 8 || THREADS > 512;
+    int first, left;  // left: all chunks, or those of the run from `first` on
+    __device__ __forceinline__ explicit FullRuns(int nchunks) {
+        const int wave = kOfAll ? (int)threadIdx.x >> 6 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int lane = threadIdx.x & 63;
+        first = wave * 64 * NCH + lane;
+        left = kOfAll ? nchunks : min(64 * NCH, nchunks - wave * 64 * NCH) - lane;
+    }
+    __device__ __forceinline__ bool has(int j) const { return (kOfAll ? first : 0) + 64 * j < left; }
+    __device__ __forceinline__ int chunk(int j) const { return first + 64 * j; }
+};
+// ... or, for a k with which full ones would make the lists long (the bin of L makes them up to 1.77 times k), all alike.  us, full
+// runs and even ones: K = 22016, k = 220 4.3 and 4.5; 16512, 516, where five wavefronts would list 190 chunks each, 5.6 and 5.4.
+// Not in residual kernels: what the choice costs in front of their first load is 1 % of 14336 x 4096, 6 % of 22016 x 2048.
+template <int THREADS, int NCH>
+struct ChosenRuns {
+    int first, left;  // left: chunks of the run from `first` on
+    __device__ __forceinline__ ChosenRuns(int nchunks, int k) {
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+        const bool even = k > 40 * ((nchunks + 64 * NCH - 1) / (64 * NCH));
         const int each = even ? (nchunks + THREADS / 64 - 1) / (THREADS / 64) : 64 * NCH;
         first = wave * each + lane;
         left = min(each, nchunks - wave * each) - lane;
@@ -241,12 +259,6 @@ struct ChunkRun {
     __device__ __forceinline__ bool has(int j) const { return 64 * j < left; }
     __device__ __forceinline__ int chunk(int j) const { return first + 64 * j; }
 };
-// Even runs where full ones would make the lists long (the bin of L makes them up to 1.77 times k).  Residual kernels with up to
-// four chunks per thread always have full ones: the choice in front of their first load takes 14336 x 4096 1 % longer.
-template <int NCH>
-__device__ __forceinline__ bool even_runs(int nchunks, int k) {
-    return NCH > 1 && k > 40 * ((nchunks + 64 * NCH - 1) / (64 * NCH));
-}
 
 // A lane's chunks once those that cannot matter are gone: entries lane, lane + 64, ... of the wavefront's list.
 template <int THREADS, int NCH>
@@ -281,12 +293,11 @@ struct Listed {
 };
 
 // Steps 1 and 2.  Requires 1 <= k <= nchunks and sh.hist1 cleared (with a barrier behind).
-template <int THREADS, int NCH>
-__device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], int nchunks, bool even, int k, SelectShared<THREADS, NCH>& sh,
+template <int THREADS, int NCH, typename Runs>
+__device__ __forceinline__ void list_chunks(const uint4 (&ch)[NCH], const Runs& run, int k, SelectShared<THREADS, NCH>& sh,
                                             Listed<THREADS, NCH>& out) {
     typedef Listed<THREADS, NCH> L_t;
     constexpr int LIST = L_t::kList;
-    const ChunkRun<THREADS, NCH> run(nchunks, even);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 
@@ -422,10 +433,9 @@ __device__ __forceinline__ bool select_listed(const Listed<THREADS, NCH>& l, int
 }
 
 // Any 1 <= k <= K.  Requires sh.hist1, sh.hist2 cleared (with a barrier behind).  MANY: many keys per chunk are marked.
-template <int THREADS, int NCH, bool MANY = false>
-__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchunks, bool even, int k,
-                                                SelectShared<THREADS, NCH>& sh, int32_t* idx_out, uint16_t* xsel_out) {
-    const ChunkRun<THREADS, NCH> run(nchunks, even);
+template <int THREADS, int NCH, bool MANY = false, typename Runs>
+__device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], const Runs& run, int k, SelectShared<THREADS, NCH>& sh,
+                                                int32_t* idx_out, uint16_t* xsel_out) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
     // pass 1: high 8 bits of the key
@@ -491,10 +501,9 @@ __device__ __forceinline__ void select_by_radix(const uint4 (&ch)[NCH], int nchu
                      (unsigned)k, idx_out, xsel_out);
 }
 
-// The keys of a thread (ChunkRun).  Requires K a multiple of 8, K <= 8 * THREADS * NCH and x 16-byte aligned.
-template <int THREADS, int NCH>
-__device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, int K, bool even, uint4 (&ch)[NCH]) {
-    const ChunkRun<THREADS, NCH> run(K / 8, even);
+// The keys of a thread.  Requires K a multiple of 8, K <= 8 * THREADS * NCH and x 16-byte aligned.
+template <int NCH, typename Runs>
+__device__ __forceinline__ void load_keys(const uint16_t* __restrict__ x, const Runs& run, uint4 (&ch)[NCH]) {
     const uint4* x128 = reinterpret_cast<const uint4*>(x);
 #pragma unroll
     for (int j = 0; j < NCH; ++j) ch[j] = run.has(j) ? x128[run.chunk(j)] : make_uint4(0, 0, 0, 0);
@@ -505,7 +514,7 @@ struct AskNothing {
     __device__ __forceinline__ unsigned operator()(const uint4&, int, unsigned, unsigned) const { return 0; }
 };
 
-// All THREADS threads of the workgroup call this, with their keys (load_keys, the same `even`) and 1 <= k <= K.  idx_out / xsel_out
+// All THREADS threads of the workgroup call this, with their keys (load_keys) and their runs, and 1 <= k <= K.  idx_out / xsel_out
 // may point to global memory or LDS; xsel_out may be null.  Ends with the outputs
 // written but not yet synchronised (the caller adds the barrier it needs).  RADIX: the caller knows that
 // select_tries_chunks(K / 8, k) is false.
@@ -513,8 +522,8 @@ struct AskNothing {
 // ask(a chunk's keys, the chunk, its maximum, edge): called once by every lane, on every path, with its first listed chunk (maximum
 // 0: none).  Fewer than k chunks have a maximum >= edge.  Returns the lane's tag (write_marked), which only a selection by
 // chunks writes.
-template <int THREADS, int NCH, bool RADIX = false, typename Ask = AskNothing>
-__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K, bool even, int k, SelectShared<THREADS, NCH>& sh,
+template <int THREADS, int NCH, bool RADIX = false, typename Runs, typename Ask = AskNothing>
+__device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], const Runs& run, int K, int k, SelectShared<THREADS, NCH>& sh,
                                                   int32_t* idx_out, uint16_t* xsel_out, const Ask& ask = Ask()) {
     static_assert(THREADS % 256 == 0 && THREADS / 64 <= 16 && NCH <= kSelectMaxChunks, "select shape");
     const int tid = threadIdx.x, nchunks = K / 8;
@@ -527,7 +536,7 @@ __device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K,
     if constexpr (!std::is_same_v<Ask, AskNothing>) {  // on every path, see `ask`
         const bool chunks = select_tries_chunks(nchunks, k);
         Listed<THREADS, NCH> l;
-        if (chunks) list_chunks(ch, nchunks, even, k, sh, l);
+        if (chunks) list_chunks(ch, run, k, sh, l);
         const unsigned tag = ask(l.keys[0], l.chunk[0], l.L != 0 ? chunk_max(l.keys[0]) : 0u, l.L + 128);
         if (l.L != 0 && select_listed(l, k, sh, idx_out, xsel_out, tag)) return;
         if (chunks) {
@@ -536,12 +545,12 @@ __device__ __forceinline__ void block_select_topk(const uint4 (&ch)[NCH], int K,
         }
     } else if (!RADIX && select_tries_chunks(nchunks, k)) {
         Listed<THREADS, NCH> l;
-        list_chunks(ch, nchunks, even, k, sh, l);
+        list_chunks(ch, run, k, sh, l);
         if (l.L != 0 && select_listed(l, k, sh, idx_out, xsel_out, 0)) return;
         __syncthreads();
         clear();
     }
-    select_by_radix<THREADS, NCH, RADIX>(ch, nchunks, even, k, sh, idx_out, xsel_out);
+    select_by_radix<THREADS, NCH, RADIX>(ch, run, k, sh, idx_out, xsel_out);
 }
 
 }  // namespace decdec
