@@ -228,11 +228,12 @@ __device__ __forceinline__ void mark_chunk(const uint4& c, unsigned T, unsigned&
 
 // The chunks of a thread: chunk(j) for those j that has(j) is true for.  The runs of the wavefronts are 64 * NCH chunks, with which
 // the fewest have any (each issues the steps 3 and 4, however few chunks it lists) ...
-// (Eight chunks per thread compare them with nchunks: against what is left of the run 22016 x 2048 takes 0.6 us longer.  With
-// four the lane masks that the former keeps are more than the residual kernels have scalar registers for.)
+// (With two and four chunks per thread they are compared with what is left of the run: the lane masks that are kept when they are
+// compared with nchunks are more than the residual kernels have scalar registers for.  With eight that takes 22016 x 2048 0.6 us
+// longer.)
 template <int THREADS, int NCH>
 struct FullRuns {
-    static constexpr bool kOfAll = NCH == 8 || THREADS > 512;
+    static constexpr bool kOfAll = NCH == 1 || NCH == 8 || THREADS > 512;
     int first, left;  // left: all chunks, or those of the run from `first` on
     __device__ __forceinline__ explicit FullRuns(int nchunks) {
         const int wave = kOfAll ? (int)threadIdx.x >> 6 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
