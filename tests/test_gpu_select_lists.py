@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("K,run,held", [(8192, 128, 128), (16384, 256, 128), (28672, 512, 192), (32768, 512, 192), (40960, 512, 128),
-                                        (16512, 258, 192)])  # the last with runs that are all alike from k = 201 on
+                                        (16512, 258, 192)])  # the last: runs of the stand-alone kernel from k = 201 on
 def test_list_of_one_wavefront(K, run, held):
     """run: chunks of a wavefront; held: entries of its list."""
     g = np.random.default_rng(K)
